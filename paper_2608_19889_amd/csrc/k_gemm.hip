@@ -103,136 +103,241 @@ AXON_DEV int swz(int r, int c) {
   else return c ^ ((r >> 2) & 3);
 }
 
-// ============================================================================
-// Prefill GEMM: 128 (W rows) x 128 (tokens) x 64 (k) tiles, 4 wavefronts in a
-// 2 x 2 arrangement, each owning a 64 x 64 sub-tile = 2 x 2 blocks of
-// v_mfma_f32_32x32x16_bf16.  Tiles are staged through LDS, double-buffered;
-// a row of 64 k values is 8 chunks of 16 bytes, stored swizzled (swz)
-// so that the 16-byte fragment reads of 16 consecutive rows hit distinct banks.
-// ============================================================================
-namespace pf {
-constexpr int BN = 128, BM = 128, BK = 64, CH = BK / 8;
+// Store one finished 32 x 32 accumulator block: rows nb .. nb+31 (nb < N),
+// token t (t < M; output row t), v[i] = C[nb + (i/4)*8 + (lane/32)*4 + i%4][t].
+// part: offset of this workgroup's split-K partial in ep.out_f32 (0: unsplit).
+template <int EPI>
+AXON_DEV void store_block(const EpiArgs& ep, int nb, int t, RopeTok tok, const f32x16& v, int lane, int N,
+                          int64_t part) {
+  if constexpr (EPI == EPI_ROPE) {
+    rope_block(ep, nb, t, tok, v, lane);
+  } else if constexpr (EPI == EPI_SILU) {
+    // rows nb..nb+15 are gate rows, nb+16..nb+31 the matching up rows
+    // (features (nb / 32) * 16 .. +15: inside one 32-feature slice)
+    const int64_t f0 = (nb / 32) * 16;
+    bf16* out = (bf16*)ep.out_t + (ep.opair ? xp_off(t, f0, ep.ldo) : (int64_t)t * ep.ldo + f0);
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+      const int f = g * 8 + (lane >> 5) * 4;
+      bf16x4 o;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) o[j] = (bf16)(silu_f(v[g * 4 + j]) * v[8 + g * 4 + j]);
+      *(bf16x4*)(out + f) = o;
+    }
+  } else if constexpr (EPI == EPI_GELU) {
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const int n = nb + g * 8 + (lane >> 5) * 4;  // N % 32 == 0: all 4 rows exist
+      const bf16x4 bb = *(const bf16x4*)(ep.bias + n);
+      bf16x4 o;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) o[j] = (bf16)gelu_tanh_f(v[g * 4 + j] + (float)bb[j]);
+      *(bf16x4*)((bf16*)ep.out_t + (int64_t)t * ep.ldo + n) = o;
+    }
+  } else {
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const int n = nb + g * 8 + (lane >> 5) * 4;
+      if (n >= N) continue;
+      float* p = ep.out_f32 + part + (int64_t)t * ep.ldo + n;
+      f32x4 o = {v[g * 4 + 0], v[g * 4 + 1], v[g * 4 + 2], v[g * 4 + 3]};
+      if (ep.bias) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) o[j] += (float)ep.bias[min(n + j, N - 1)];
+      }
+      store_cols<EPI == EPI_RESID>(p, o, N - n);
+    }
+  }
 }
 
-template <int EPI>
-__global__ void __launch_bounds__(256) gemm_bf16_kernel(const bf16* __restrict__ W, const bf16* __restrict__ X,
-                                                        int N, int M, int K, EpiArgs ep) {
-  using namespace pf;
-  __shared__ bf16x8 lds[2][2][BN * CH];  // [buffer][0 = W, 1 = X][row * 8 + swizzled chunk]
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wr = wave >> 1, wc = wave & 1;
-  const int n0 = blockIdx.x * BN, m0 = blockIdx.y * BM;
+// Workgroup -> tile: each XCD (workgroup id mod 8) receives a contiguous range
+// of tiles, walked in groups of 8 token tiles so that neighbouring tiles
+// share operand panels in that XCD's L2.
+AXON_DEV void tile_order(int bid, int gx, int gy, int& pn, int& pm) {
+  const int G = gx * gy;
+  int logical = bid;
+  const int full = G / 8 * 8;
+  if (bid < full) logical = (bid % 8) * (full / 8) + bid / 8;
+  constexpr int GROUP = 8;
+  const int per_group = GROUP * gx;
+  const int gid = logical / per_group;
+  const int first_m = gid * GROUP;
+  const int gsize = min(gy - first_m, GROUP);
+  pm = first_m + (logical % per_group) % gsize;
+  pn = (logical % per_group) / gsize;
+}
 
-  // global -> register staging: 4 chunks of W and 4 of X per thread
-  bf16x8 ra[4], rb[4];
-  const bf16x8 zero8 = {};
-  auto gload = [&](int k0) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int idx = tid + i * 256, row = idx >> 3, ch = idx & 7;
-      const int n = n0 + row, m = m0 + row;
-      ra[i] = n < N ? *(const bf16x8*)(W + wt_chunk(n, (k0 >> 3) + ch, K)) : zero8;
-      rb[i] = m < M ? *(const bf16x8*)(X + (ep.xpair ? xp_off(m, k0 + ch * 8, K) : (int64_t)m * K + k0 + ch * 8))
-                    : zero8;
-    }
-  };
-  auto sstore = [&](int buf) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int idx = tid + i * 256, row = idx >> 3, ch = idx & 7;
-      lds[buf][0][row * CH + swz<8>(row, ch)] = ra[i];
-      lds[buf][1][row * CH + swz<8>(row, ch)] = rb[i];
-    }
-  };
-
-  f32x16 acc[2][2];
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b) acc[a][b] = f32x16{};
-  RopeTok tok[2] = {};
-
-  const int nk = K / BK;
-  gload(0);
-  if constexpr (EPI == EPI_ROPE) {  // behind the first tile's loads
-#pragma unroll
-    for (int b = 0; b < 2; ++b) tok[b] = rope_token(ep, min(m0 + wc * 64 + b * 32 + (lane & 31), M - 1));
+// wait until at most n * PER of this wavefront's loads are in flight, n in
+// [0, MAXN] (an immediate each; the steady state passes a constant)
+template <int PER, int MAXN>
+AXON_DEV void wait_loads(int n) {
+  static_assert(PER * MAXN <= 63, "vmcnt range");
+  if constexpr (MAXN == 0) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  } else {
+    if (n >= MAXN) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(MAXN * PER) : "memory");
+    else wait_loads<PER, MAXN - 1>(n);
   }
-  sstore(0);
-  __syncthreads();
-  for (int kt = 0; kt < nk; ++kt) {
-    const int buf = kt & 1;
-    if (kt + 1 < nk) gload((kt + 1) * BK);
+}
+
+// ============================================================================
+// Prefill GEMM of few tiles (short prompts, decode batches above 64, narrow
+// outputs): WN x WM wavefronts, each owning AN x AM blocks of
+// v_mfma_f32_32x32x16_bf16, over a ring of S stages of KU k-units of 32.
+// What bounds these shapes is how many operand bytes a CU keeps in flight, so
+// operands go straight to LDS (global_load_lds_dwordx4) S stages ahead,
+// with one barrier per stage.  A W panel is copied tile by tile (a 16 x 32
+// fragment tile is 1 KB in memory and in LDS: its lanes' reads are contiguous
+// per 16 lanes, no swizzle); token rows are 64 bytes per unit, swizzled by the
+// lane's source chunk (swz<4>); the next k-tile's fragments are read from LDS
+// under this one's MFMAs.  Each output is one ascending chain of MFMAs
+// over k, as in the 256 x 256 kernel: the same bits from every tile shape.
+// gridDim.y = ksplit > 1 (float32 partials): workgroup row y takes k-share y.
+// ============================================================================
+template <int WN, int WM, int AN, int AM, int KU, int S>
+struct RingShape {
+  static constexpr int NW = WN * WM, BN = 32 * WN * AN, BM = 32 * WM * AM;
+  static constexpr int WL = KU * BN / 16, XL = KU * BM / 16;  // 1 KB loads of a stage
+  static constexpr int LPT = (WL + XL) / NW;                  // per wavefront
+  static constexpr int STAGE = (WL + XL) * 64;                // 16-byte chunks
+  static constexpr int LDS_BYTES = S * STAGE * 16;
+  static_assert(WL % NW == 0 && XL % NW == 0, "a load instruction is W or X for every wavefront");
+};
+
+template <int EPI, bool XP, int WN, int WM, int AN, int AM, int KU, int S>
+__global__ void __launch_bounds__(64 * WN * WM) gemm_ring_kernel(const bf16* __restrict__ W,
+                                                                 const bf16* __restrict__ X, int N, int M, int K,
+                                                                 EpiArgs ep) {
+  using R = RingShape<WN, WM, AN, AM, KU, S>;
+  extern __shared__ bf16x8 lds2[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wn = wave / WM, wm = wave % WM;
+  int pn, pm;
+  tile_order(blockIdx.x, (N + R::BN - 1) / R::BN, (M + R::BM - 1) / R::BM, pn, pm);
+  const int n0 = pn * R::BN, m0 = pm * R::BM;
+  const int nu = K / 32 / (int)gridDim.y;  // k-units of this workgroup (KU divides it)
+  const int nk = nu / KU, ub = (int)blockIdx.y * nu;
+
+  // this wavefront's loads of a stage, j < LPT: load q = j * NW + wave, W tile
+  // (unit q / (BN/16), row block q % (BN/16)), then X tiles of 16 token rows;
+  // row blocks and rows past the edge read the last one (never stored)
+  const bf16* src[R::LPT];
 #pragma unroll
-    for (int ks = 0; ks < BK / 16; ++ks) {
-      const int ch = ks * 2 + (lane >> 5);
-      bf16x8 fa[2], fb[2];
+  for (int j = 0; j < R::LPT; ++j) {
+    if (j < R::WL / R::NW) {
+      const int q = j * R::NW + wave, u = q / (R::BN / 16), blk = q % (R::BN / 16);
+      const int nb = min(n0 / 16 + blk, (N - 1) / 16);
+      src[j] = W + ((int64_t)nb * (K / 32) + ub + u) * 512 + lane * 8;
+    } else {
+      const int q = (j - R::WL / R::NW) * R::NW + wave, u = q / (R::BM / 16), blk = q % (R::BM / 16);
+      const int row = blk * 16 + (lane >> 2), c = swz<4>(row, lane & 3);
+      const int64_t m = min(m0 + row, M - 1);
+      const int64_t k = (int64_t)(ub + u) * 32 + c * 8;
+      src[j] = X + (XP ? xp_off(m, k, K) : m * K + k);
+    }
+  }
+  auto issue = [&](int kt) {
+    bf16x8* base = lds2 + (kt % S) * R::STAGE;
 #pragma unroll
-      for (int r = 0; r < 2; ++r) {
-        const int ra_row = wr * 64 + r * 32 + (lane & 31);
-        const int rb_row = wc * 64 + r * 32 + (lane & 31);
-        fa[r] = lds[buf][0][ra_row * CH + swz<8>(ra_row, ch)];
-        fb[r] = lds[buf][1][rb_row * CH + swz<8>(rb_row, ch)];
+    for (int j = 0; j < R::LPT; ++j) {
+      const bool w = j < R::WL / R::NW;
+      const bf16* p = src[j] + (int64_t)kt * (KU * (w ? 512 : XP ? 64 : 32));
+      __builtin_amdgcn_global_load_lds((const void*)p,
+                                       (__attribute__((address_space(3))) void*)(base + (j * R::NW + wave) * 64), 16, 0,
+                                       0);
+    }
+  };
+
+  f32x16 acc[AN][AM];
+#pragma unroll
+  for (int a = 0; a < AN; ++a)
+#pragma unroll
+    for (int b = 0; b < AM; ++b) acc[a][b] = f32x16{};
+  RopeTok tok[AM] = {};
+#pragma unroll
+  for (int st = 0; st < S; ++st)
+    if (st < nk) issue(st);
+  if constexpr (EPI == EPI_ROPE) {  // behind the first stages' loads
+#pragma unroll
+    for (int b = 0; b < AM; ++b) tok[b] = rope_token(ep, min(m0 + (wm * AM + b) * 32 + (lane & 31), M - 1));
+  }
+
+  struct Frags {
+    bf16x8 a[KU * 2][AN], b[KU * 2][AM];
+  };
+  auto read_frags = [&](int kt, Frags& f) {
+    const bf16x8* la = lds2 + (kt % S) * R::STAGE;
+    const bf16x8* lb = la + R::WL * 64;
+#pragma unroll
+    for (int u = 0; u < KU; ++u)
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+        const int ch = ks * 2 + (lane >> 5);
+#pragma unroll
+        for (int a = 0; a < AN; ++a) {
+          const int blk = u * (R::BN / 16) + (wn * AN + a) * 2 + ((lane >> 4) & 1);
+          f.a[u * 2 + ks][a] = la[blk * 64 + (lane & 15) + 16 * ch];
+        }
+#pragma unroll
+        for (int b = 0; b < AM; ++b) {
+          const int r = (wm * AM + b) * 32 + (lane & 31);
+          f.b[u * 2 + ks][b] = lb[u * (R::BM * 4) + r * 4 + swz<4>(r, ch)];
+        }
       }
-#pragma unroll
-      for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-          acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[a], fb[b], acc[a][b], 0, 0, 0);
+  };
+  auto barrier = [] {
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // k-tile kt, its fragments in ``cur``: stage kt + 1 has landed (``after``
+  // later stages of this wavefront's loads stay in flight) and, after the
+  // barrier, every wavefront's share of it is visible and every wavefront
+  // holds its fragments of stage kt, whose buffer takes the loads of k-tile
+  // kt + S; the next fragments are read under this k-tile's MFMAs
+  auto ktile = [&](int kt, const Frags& cur, Frags& nxt, bool more, bool do_issue, int after) {
+    __builtin_amdgcn_sched_barrier(0);
+    // lgkmcnt(0) as the builtin: the compiler then knows that ``cur`` has
+    // arrived and does not wait for the next fragments in front of the MFMAs
+    __builtin_amdgcn_s_waitcnt(0xC07F);
+    if (more) {
+      wait_loads<R::LPT, S - 2>(after);
+      barrier();
+      read_frags(kt + 1, nxt);
+      if (do_issue) issue(kt + S);
+      __builtin_amdgcn_sched_barrier(0);
     }
-    if (kt + 1 < nk) sstore(buf ^ 1);
-    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < KU * 2; ++q)
+#pragma unroll
+      for (int a = 0; a < AN; ++a)
+#pragma unroll
+        for (int b = 0; b < AM; ++b)
+          acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur.a[q][a], cur.b[q][b], acc[a][b], 0, 0, 0);
+  };
+  Frags f0, f1;
+  wait_loads<R::LPT, S - 1>(min(S - 1, nk - 1));
+  barrier();
+  read_frags(0, f0);
+  int kt = 0;
+  for (; kt + 1 + S < nk; kt += 2) {  // steady state: constant arguments
+    ktile(kt, f0, f1, true, true, S - 2);
+    ktile(kt + 1, f1, f0, true, true, S - 2);
+  }
+  for (; kt < nk; kt += 2) {
+    ktile(kt, f0, f1, kt + 1 < nk, kt + S < nk, min(S - 2, nk - 2 - kt));
+    if (kt + 1 < nk) ktile(kt + 1, f1, f0, kt + 2 < nk, kt + 1 + S < nk, min(S - 2, nk - 3 - kt));
   }
 
-  // epilogue: acc[a][b][i] = C[n][t] with
-  //   n = n0 + wr*64 + a*32 + (i/4)*8 + (lane/32)*4 + i%4,  t = m0 + wc*64 + b*32 + lane%32
 #pragma unroll
-  for (int b = 0; b < 2; ++b) {
-    const int t = m0 + wc * 64 + b * 32 + (lane & 31);
+  for (int b = 0; b < AM; ++b) {
+    const int t = m0 + (wm * AM + b) * 32 + (lane & 31);
     if (t >= M) continue;
 #pragma unroll
-    for (int a = 0; a < 2; ++a) {
-      const int nb = n0 + wr * 64 + a * 32;  // 32-aligned row block
-      if (nb >= N) continue;
-      if constexpr (EPI == EPI_ROPE) {
-        rope_block(ep, nb, t, tok[b], acc[a][b], lane);
-      } else if constexpr (EPI == EPI_SILU) {
-        // rows nb..nb+15 are gate rows, nb+16..nb+31 the matching up rows
-        // (features (nb / 32) * 16 .. +15: inside one 32-feature slice)
-        const int64_t f0 = (nb / 32) * 16;
-        bf16* out = (bf16*)ep.out_t + (ep.opair ? xp_off(t, f0, ep.ldo) : (int64_t)t * ep.ldo + f0);
-#pragma unroll
-        for (int g = 0; g < 2; ++g) {
-          const int f = g * 8 + (lane >> 5) * 4;
-          bf16x4 v;
-#pragma unroll
-          for (int j = 0; j < 4; ++j) v[j] = (bf16)(silu_f(acc[a][b][g * 4 + j]) * acc[a][b][8 + g * 4 + j]);
-          *(bf16x4*)(out + f) = v;
-        }
-      } else if constexpr (EPI == EPI_GELU) {
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const int n = nb + g * 8 + (lane >> 5) * 4;  // N % 32 == 0: all 4 rows exist
-          const bf16x4 bb = *(const bf16x4*)(ep.bias + n);
-          bf16x4 v;
-#pragma unroll
-          for (int j = 0; j < 4; ++j) v[j] = (bf16)gelu_tanh_f(acc[a][b][g * 4 + j] + (float)bb[j]);
-          *(bf16x4*)((bf16*)ep.out_t + (int64_t)t * ep.ldo + n) = v;
-        }
-      } else {
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const int n = nb + g * 8 + (lane >> 5) * 4;
-          if (n >= N) continue;
-          float* p = ep.out_f32 + (int64_t)t * ep.ldo + n;
-          f32x4 v = {acc[a][b][g * 4 + 0], acc[a][b][g * 4 + 1], acc[a][b][g * 4 + 2], acc[a][b][g * 4 + 3]};
-          if (ep.bias) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) v[j] += (float)ep.bias[min(n + j, N - 1)];
-          }
-          store_cols<EPI == EPI_RESID>(p, v, N - n);
-        }
-      }
+    for (int a = 0; a < AN; ++a) {
+      const int nb = n0 + (wn * AN + a) * 32;
+      if (nb < N) store_block<EPI>(ep, nb, t, tok[b], acc[a][b], lane, N, (int64_t)blockIdx.y * ep.part_stride);
     }
   }
 }
@@ -265,20 +370,6 @@ constexpr int STAGE = 2 * PANEL;      // W panel + X panel
 constexpr int LPT = PANEL / 512;      // load instructions per operand per wave per k-tile
 constexpr int ROWSTEP = 512 / CH;     // panel rows between a lane's consecutive chunks
 constexpr int LDS_BYTES = STAGES * STAGE * 16;
-}
-
-AXON_DEV void tile_order(int bid, int gx, int gy, int& pn, int& pm) {
-  const int G = gx * gy;
-  int logical = bid;
-  const int full = G / 8 * 8;
-  if (bid < full) logical = (bid % 8) * (full / 8) + bid / 8;
-  constexpr int GROUP = 8;
-  const int per_group = GROUP * gx;
-  const int gid = logical / per_group;
-  const int first_m = gid * GROUP;
-  const int gsize = min(gy - first_m, GROUP);
-  pm = first_m + (logical % per_group) % gsize;
-  pn = (logical % per_group) / gsize;
 }
 
 // Wait until at most ``after`` k-tiles' loads of this wavefront are in flight
@@ -490,43 +581,7 @@ __global__ void __launch_bounds__(512, 1) gemm_bf16_256_kernel(const bf16* __res
 #pragma unroll
     for (int a = 0; a < 4; ++a) {
       const int nb = n0 + grp * 128 + a * 32;
-      if (nb >= N) continue;
-      if constexpr (EPI == EPI_ROPE) {
-        rope_block(ep, nb, t, tok[b], acc[a][b], lane);
-      } else if constexpr (EPI == EPI_SILU) {
-        bf16* out = (bf16*)ep.out_t + (int64_t)t * ep.ldo + (nb / 32) * 16;
-#pragma unroll
-        for (int g = 0; g < 2; ++g) {
-          const int f = g * 8 + (lane >> 5) * 4;
-          bf16x4 v;
-#pragma unroll
-          for (int j = 0; j < 4; ++j) v[j] = (bf16)(silu_f(acc[a][b][g * 4 + j]) * acc[a][b][8 + g * 4 + j]);
-          *(bf16x4*)(out + f) = v;
-        }
-      } else if constexpr (EPI == EPI_GELU) {
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const int n = nb + g * 8 + (lane >> 5) * 4;  // N % 32 == 0: all 4 rows exist
-          const bf16x4 bb = *(const bf16x4*)(ep.bias + n);
-          bf16x4 v;
-#pragma unroll
-          for (int j = 0; j < 4; ++j) v[j] = (bf16)gelu_tanh_f(acc[a][b][g * 4 + j] + (float)bb[j]);
-          *(bf16x4*)((bf16*)ep.out_t + (int64_t)t * ep.ldo + n) = v;
-        }
-      } else {
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const int n = nb + g * 8 + (lane >> 5) * 4;
-          if (n >= N) continue;
-          float* p = ep.out_f32 + (int64_t)blockIdx.y * ep.part_stride + (int64_t)t * ep.ldo + n;
-          f32x4 v = {acc[a][b][g * 4 + 0], acc[a][b][g * 4 + 1], acc[a][b][g * 4 + 2], acc[a][b][g * 4 + 3]};
-          if (ep.bias) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) v[j] += (float)ep.bias[min(n + j, N - 1)];
-          }
-          store_cols<EPI == EPI_RESID>(p, v, N - n);
-        }
-      }
+      if (nb < N) store_block<EPI>(ep, nb, t, tok[b], acc[a][b], lane, N, (int64_t)blockIdx.y * ep.part_stride);
     }
   }
 }
@@ -543,18 +598,6 @@ static auto kern_256() {
   return kern;
 }
 
-template <int EPI, bool XP = false>
-static void launch_256(const bf16* W, const bf16* X, int N, int M, int K, const EpiArgs& ep, hipStream_t s) {
-  if constexpr (!XP) {
-    if (ep.xpair) {
-      if constexpr (EPI != EPI_GELU) launch_256<EPI, true>(W, X, N, M, K, ep, s);  // GELU: GPT-2, row-major only
-      return;
-    }
-  }
-  const int tiles = ((N + pf2::BN - 1) / pf2::BN) * ((M + pf2::BM - 1) / pf2::BM);
-  klaunch(kern_256<EPI, false, XP>(), dim3(tiles), dim3(512), pf2::LDS_BYTES, s, W, X, N, M, K, ep);
-}
-
 template <int EPI>
 static void launch_grouped(const bf16* W, const bf16* X, int N, int K, int max_rows, const EpiArgs& ep,
                            hipStream_t s) {
@@ -564,6 +607,71 @@ static void launch_grouped(const bf16* W, const bf16* X, int N, int K, int max_r
   klaunch(kern_256<EPI, true, false>(), dim3((unsigned)tiles), dim3(512), pf2::LDS_BYTES, s, W, X, N, 0, K, ep);
 }
 
+// one ring kernel instance, its LDS size raised at first use
+template <int EPI, bool XP, int WN, int WM, int AN, int AM, int KU, int S>
+static void launch_ring_shape(const bf16* W, const bf16* X, int N, int M, int K, int ksplit, const EpiArgs& ep,
+                              hipStream_t s) {
+  using R = RingShape<WN, WM, AN, AM, KU, S>;
+  static bool attr = false;
+  auto kern = gemm_ring_kernel<EPI, XP, WN, WM, AN, AM, KU, S>;
+  if (!attr) {
+    (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, R::LDS_BYTES);
+    attr = true;
+  }
+  const int tiles = ((N + R::BN - 1) / R::BN) * ((M + R::BM - 1) / R::BM);
+  klaunch(kern, dim3(tiles, ksplit), dim3(64 * R::NW), R::LDS_BYTES, s, W, X, N, M, K, ep);
+}
+
+// Tile shapes of the projection GEMM and what one 32-deep k-unit of a tile
+// costs a CU (ns, from timing every shape on weights streamed from HBM, K
+// 2048 to 18944, 24 to 2048 tokens).  A CU's time is the sum of its tiles'
+// whether one or two workgroups share it, so the launch takes the shape of
+// the smallest rounds x cost, rounds = tiles over 256 CUs rounded up: large
+// tiles do more per operand byte, small ones leave fewer CUs idle.  Every
+// shape gives the same bits.  us at 3584 x 3584 (N x K): 93 tokens 128x128
+// tiles 33, 64x64 16, 32x64 14; 700 tokens 128x128 35, 64x64 40, 256x256 79;
+// 1500 tokens 256x128 52, 128x128 60, 256x256 81.  The 128x128 kernel before
+// this one, staged through registers one k-tile ahead, took 74-80 for all.
+enum Tile : int { T256x256, T256x128, T128x128, T128x64, T64x64, T32x64, T32x32, TILES };
+struct TileCost {
+  int bn, bm, ku, ns;
+};
+static constexpr TileCost TILE_COST[TILES] = {{256, 256, 1, 660}, {256, 128, 1, 420}, {128, 128, 1, 265},
+                                              {128, 64, 1, 190},  {64, 64, 2, 120},   {32, 64, 2, 80},
+                                              {32, 32, 2, 71}};
+static Tile pick_tile(int N, int M, int K, int ksplit) {
+  const int units = K / 32 / ksplit;
+  Tile best = T256x256;
+  int64_t least = INT64_MAX;
+  for (int i = 0; i < TILES; ++i) {
+    const TileCost& t = TILE_COST[i];
+    if (units % t.ku) continue;  // a stage is ku whole k-units
+    const int64_t tiles = (int64_t)((N + t.bn - 1) / t.bn) * ((M + t.bm - 1) / t.bm) * ksplit;
+    const int64_t cost = (tiles + 255) / 256 * t.ns;
+    if (cost < least) {
+      least = cost;
+      best = (Tile)i;
+    }
+  }
+  return best;
+}
+
+template <int EPI, bool XP>
+static void launch_tiles(const bf16* W, const bf16* X, int N, int M, int K, int ksplit, const EpiArgs& ep,
+                         hipStream_t s) {
+  switch (pick_tile(N, M, K, ksplit)) {
+    case T256x128: launch_ring_shape<EPI, XP, 4, 2, 2, 2, 1, 4>(W, X, N, M, K, ksplit, ep, s); return;
+    case T128x128: launch_ring_shape<EPI, XP, 2, 2, 2, 2, 1, 4>(W, X, N, M, K, ksplit, ep, s); return;
+    case T128x64: launch_ring_shape<EPI, XP, 2, 2, 2, 1, 1, 6>(W, X, N, M, K, ksplit, ep, s); return;
+    case T64x64: launch_ring_shape<EPI, XP, 2, 2, 1, 1, 2, 5>(W, X, N, M, K, ksplit, ep, s); return;
+    case T32x64: launch_ring_shape<EPI, XP, 1, 2, 1, 1, 2, 5>(W, X, N, M, K, ksplit, ep, s); return;
+    case T32x32: launch_ring_shape<EPI, XP, 1, 1, 1, 1, 2, 8>(W, X, N, M, K, ksplit, ep, s); return;
+    default: break;
+  }
+  const int tiles = ((N + pf2::BN - 1) / pf2::BN) * ((M + pf2::BM - 1) / pf2::BM);
+  klaunch(kern_256<EPI, false, XP>(), dim3(tiles, ksplit), dim3(512), pf2::LDS_BYTES, s, W, X, N, M, K, ep);
+}
+
 void launch_gemm_bf16_split(const bf16* W, const bf16* X, int N, int M, int K, int ksplit, float* part,
                             int64_t part_stride, hipStream_t s, bool xpair) {
   if (M <= 0) return;
@@ -571,10 +679,8 @@ void launch_gemm_bf16_split(const bf16* W, const bf16* X, int N, int M, int K, i
   ep.out_f32 = part;
   ep.ldo = N;
   ep.part_stride = part_stride;
-  const int tiles = ((N + pf2::BN - 1) / pf2::BN) * ((M + pf2::BM - 1) / pf2::BM);
-  const dim3 grid(tiles, ksplit);
-  if (xpair) klaunch(kern_256<EPI_F32, false, true>(), grid, dim3(512), pf2::LDS_BYTES, s, W, X, N, M, K, ep);
-  else klaunch(kern_256<EPI_F32, false, false>(), grid, dim3(512), pf2::LDS_BYTES, s, W, X, N, M, K, ep);
+  if (xpair) launch_tiles<EPI_F32, true>(W, X, N, M, K, ksplit, ep, s);
+  else launch_tiles<EPI_F32, false>(W, X, N, M, K, ksplit, ep, s);
 }
 
 int gemm_ksplit(int N, int M, int K) {
@@ -597,27 +703,20 @@ void launch_gemm_bf16_grouped(const bf16* W, const bf16* X, int N, int K, int ma
 void launch_gemm_bf16(const bf16* W, const bf16* X, int N, int M, int K, int epi, const EpiArgs& ep,
                       hipStream_t s) {
   if (M <= 0) return;
-  // 256 x 256 tiles unless that leaves most CUs idle (fewer than 160 tiles)
-  const int64_t tiles256 = (int64_t)((N + 255) / 256) * ((M + 255) / 256);
-  if (M >= 256 && N >= 256 && tiles256 >= 160) {
-    switch (epi) {
-      case EPI_F32: launch_256<EPI_F32>(W, X, N, M, K, ep, s); return;
-      case EPI_RESID: launch_256<EPI_RESID>(W, X, N, M, K, ep, s); return;
-      case EPI_SILU: launch_256<EPI_SILU>(W, X, N, M, K, ep, s); return;
-      case EPI_ROPE: launch_256<EPI_ROPE>(W, X, N, M, K, ep, s); return;
-      case EPI_GELU: launch_256<EPI_GELU>(W, X, N, M, K, ep, s); return;
-      default: break;
-    }
-  }
-  dim3 grid((N + pf::BN - 1) / pf::BN, (M + pf::BM - 1) / pf::BM);
+#define AXON_TILES(E)                                                  \
+  case E:                                                              \
+    if (ep.xpair) launch_tiles<E, true>(W, X, N, M, K, 1, ep, s);      \
+    else launch_tiles<E, false>(W, X, N, M, K, 1, ep, s);              \
+    return;
   switch (epi) {
-    case EPI_F32: klaunch(gemm_bf16_kernel<EPI_F32>, grid, dim3(256), 0, s, W, X, N, M, K, ep); break;
-    case EPI_RESID: klaunch(gemm_bf16_kernel<EPI_RESID>, grid, dim3(256), 0, s, W, X, N, M, K, ep); break;
-    case EPI_SILU: klaunch(gemm_bf16_kernel<EPI_SILU>, grid, dim3(256), 0, s, W, X, N, M, K, ep); break;
-    case EPI_ROPE: klaunch(gemm_bf16_kernel<EPI_ROPE>, grid, dim3(256), 0, s, W, X, N, M, K, ep); break;
-    case EPI_GELU: klaunch(gemm_bf16_kernel<EPI_GELU>, grid, dim3(256), 0, s, W, X, N, M, K, ep); break;
-    default: break;
+    AXON_TILES(EPI_F32)
+    AXON_TILES(EPI_RESID)
+    AXON_TILES(EPI_SILU)
+    AXON_TILES(EPI_ROPE)
+    case EPI_GELU: launch_tiles<EPI_GELU, false>(W, X, N, M, K, 1, ep, s); return;  // GPT-2: row-major only
+    default: return;
   }
+#undef AXON_TILES
 }
 
 // ============================================================================

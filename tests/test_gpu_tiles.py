@@ -1,0 +1,52 @@
+"""The projection GEMM's tile shapes on the GPU.  The launch picks a tile by
+the output's size, so one prompt fed at growing lengths passes through all of
+them: every length must give the oracle's logits and, position by position, the
+bits of the longest prompt (each output is one ascending sum over k, whatever
+the tile)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from parity_util import check_bf16, gpu_model
+from synthetic import model_weights, prompts, small_shape
+
+pytestmark = pytest.mark.gpu
+
+# tile edges (32, 64, 128, 256 tokens), one past and one before them
+LENS = [1, 2, 31, 32, 33, 63, 65, 97, 128, 129, 255, 257, 390, 600]
+
+SHAPES = {
+    # K of an odd number of 32-deep units per K half (hidden and intermediate
+    # 34 and 66 units in two halves): stages of one unit only; odd vocabulary
+    "odd_units": ("1b", dict(layers=1, vocab=3001, hidden=1088, intermediate=2112)),
+    # even units, biases, head dimension 128, N with a remainder in every tile
+    "even_units_bias": ("7b", dict(layers=1, vocab=2016, hidden=1152, intermediate=1216)),
+    # an output wide enough for the 256-token tiles
+    "wide": ("1b", dict(layers=1, vocab=5000, hidden=512, intermediate=20480)),
+}
+
+
+@pytest.mark.parametrize("case", list(SHAPES))
+def test_every_tile_shape_gives_the_same_bits_and_the_oracles_logits(case):
+    base, ov = SHAPES[case]
+    shape = small_shape(base, **ov)
+    w = model_weights(shape, seed=41)
+    ids = prompts(1, max(LENS), shape["vocab_size"], seed=42)[0]
+    m = gpu_model(shape, w, max_batch=1, max_seq=max(LENS))
+    flat = ids.to("cuda")
+    full, _ = m.prefill(flat, [0, max(LENS)], all_logits=True)
+    full = full.cpu()
+    for n in LENS[:-1]:
+        lg, nxt = m.prefill(flat[:n].contiguous(), [0, n], all_logits=True)
+        lg = lg.cpu()
+        assert torch.equal(lg, full[:n]), f"{n} tokens: {(lg - full[:n]).abs().max():.3e} off the longest prompt"
+        assert int(nxt[0]) == int(lg[-1].argmax())
+    m.close()
+    n = 129
+    w64 = oracle.weights_f64(w)
+    exact = oracle.OracleDecoder(shape, w64).extend(0, ids[:n].numpy(), all_logits=True)
+    b16 = oracle.OracleDecoder(shape, w64, io_round="bf16").extend(0, ids[:n].numpy(), all_logits=True)
+    # the band around the bf16 storage error is the bar: at these widths that
+    # error alone (mean 2.8e-3) is past the absolute 2e-3
+    check_bf16(full[:n].double().numpy(), np.asarray(exact), np.asarray(b16), f"tiles {case}", absolute=False)
