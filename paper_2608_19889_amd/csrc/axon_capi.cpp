@@ -502,14 +502,20 @@ int prefill_split(axon_model* m, int N, int M, int K) {
   return 2;
 }
 
+// Split of a decode step's residual projection over more tokens than the
+// fused kernels take.
+int decode_split(axon_model* m, int N, int M, int K) {
+  const int64_t fit = m->gemm_part_floats / ((int64_t)M * N);
+  return gemm_ksplit_few(N, M, K, (int)std::min<int64_t>(fit, 8));
+}
+
 // x += X W^T, then h = RMSNorm(x) g for ``rows`` rows (the last row of each
-// sequence when cu_last is set): a split-K GEMM's partials are summed into x
-// by the normalization kernel itself.  xpair / hpair: X / h in the row-pair
+// sequence when cu_last is set): the partials of a GEMM split ks ways over K
+// are summed into x by the normalization kernel itself.  xpair / hpair: X / h in the row-pair
 // layout.
 void gemm_resid_norm(axon_model* m, const void* W, const bf16* X, int T, int K, const bf16* g, bf16* h, int rows,
-                     const int32_t* cu_last, hipStream_t s, bool by_shape = false, bool xpair = false,
-                     bool hpair = false) {
-  const int D = m->D(), ks = by_shape ? prefill_split(m, D, T, K) : split_for(m, D, T, K);
+                     const int32_t* cu_last, hipStream_t s, int ks, bool xpair = false, bool hpair = false) {
+  const int D = m->D();
   if (ks > 1) {
     m->timed(1, D, T, K, s, [&] {
       launch_gemm_bf16_split((const bf16*)W, X, D, T, K, ks, m->gemm_part, (int64_t)T * D, s, xpair);
@@ -708,8 +714,8 @@ void enqueue_prefill(axon_model* m, int B, int Ttok, const int32_t* d_tokens, co
     }
     const bool llama_bf16 = sizeof(T) == 2 && !gpt2;
     if (llama_bf16) {
-      gemm_resid_norm(m, w.wo, (const bf16*)m->o, Ttok, H * hd, (const bf16*)w.gpost, (bf16*)h, Ttok, nullptr, s, true,
-                      o_pair, xp);
+      gemm_resid_norm(m, w.wo, (const bf16*)m->o, Ttok, H * hd, (const bf16*)w.gpost, (bf16*)h, Ttok, nullptr, s,
+                      prefill_split(m, D, Ttok, H * hd), o_pair, xp);
     } else {
       gemm_many<T>(m, w.wo, m->o, D, Ttok, H * hd, EPI_RESID, m->x, nullptr, D, s, nullptr, w.bo);
       if (gpt2)
@@ -730,7 +736,8 @@ void enqueue_prefill(axon_model* m, int B, int Ttok, const int32_t* d_tokens, co
         gemm_many<T>(m, w.wgu, h, 2 * I, Ttok, D, EPI_SILU, nullptr, m->a, I, s, nullptr, nullptr, xp, xp);
         const bool to_last = last && !all_logits;  // hlast: row-major rows for the head projection
         gemm_resid_norm(m, w.wd, (const bf16*)m->a, Ttok, I, (const bf16*)gnext, (bf16*)(to_last ? m->hlast : h),
-                        to_last ? B : Ttok, to_last ? d_cu : nullptr, s, true, xp, xp && !to_last);
+                        to_last ? B : Ttok, to_last ? d_cu : nullptr, s, prefill_split(m, D, Ttok, I), xp,
+                        xp && !to_last);
         normed = true;
       } else {
         gemm_many<T>(m, w.wgu, h, 2 * I, Ttok, D, EPI_F32, m->gu_f32, nullptr, 2 * I, s);
@@ -753,7 +760,7 @@ void enqueue_prefill(axon_model* m, int B, int Ttok, const int32_t* d_tokens, co
   }
   if (all_logits) {
     gemm_many<T>(m, m->lm_head, h, V, Ttok, D, EPI_F32, d_logits, nullptr, V, s, nullptr, nullptr, xp);
-    launch_argmax_rows(d_logits, B, V, d_next, d_cu, s);
+    launch_argmax(d_logits, B, V, m->am_val, m->am_idx, d_next, nullptr, d_cu, s);
   } else if (sizeof(T) == 2 && B <= GEMV_MAX_M) {
     GemvArgs ha{};
     ha.W = (const bf16*)m->lm_head; ha.N = V; ha.K = D; ha.M = B; ha.X = (const bf16*)m->hlast;
@@ -765,7 +772,7 @@ void enqueue_prefill(axon_model* m, int B, int Ttok, const int32_t* d_tokens, co
     float* dst = d_logits ? d_logits : m->logits_int;
     if constexpr (sizeof(T) == 2) gemm_many<T>(m, m->lm_head, m->hlast, V, B, D, EPI_F32, dst, nullptr, V, s);
     else gemm_few_f32(m, m->lm_head, m->hlast, V, B, D, EPI_F32, dst, V, s);
-    launch_argmax(dst, B, V, d_next, nullptr, s);
+    launch_argmax(dst, B, V, m->am_val, m->am_idx, d_next, nullptr, nullptr, s);
   }
 }
 
@@ -795,26 +802,34 @@ void enqueue_decode_many(axon_model* m, int B, const int32_t* d_tokens, float* d
                         m->d_len, H, s);
     }
     launch_attn_decode<T>((const T*)m->q, kv, (T*)m->o, m->attn_part, m->attn_cnt, B, H, m->d_len, m->cfg.max_seq, s);
-    proj(w.wo, m->o, D, H * hd, EPI_RESID, m->x, nullptr, D);
-    launch_resid_rmsnorm<T>(m->x, nullptr, 0, 0, (const T*)w.gpost, h, B, D, eps, nullptr, s);
-    if (w.moe) {
-      enqueue_moe(m, w, (const bf16*)h, B, s);
-    } else {
-      if constexpr (sizeof(T) == 2) {
-        proj(w.wgu, h, 2 * I, D, EPI_SILU, nullptr, m->a, I);
-      } else {
-        proj(w.wgu, h, 2 * I, D, EPI_F32, m->gu_f32, nullptr, 2 * I);
-        launch_silu_reduce<T>(m->gu_f32, 1, 0, (T*)m->a, B, I, s);
-      }
-      proj(w.wd, m->a, D, I, EPI_RESID, m->x, nullptr, D);
-    }
     const bool last = l + 1 == m->cfg.n_layers;
     const T* gnext = (const T*)(last ? m->gfinal : m->layers[l + 1].gin);
-    launch_resid_rmsnorm<T>(m->x, nullptr, 0, 0, gnext, h, B, D, eps, nullptr, s);
+    // x += X W^T, then h = RMSNorm(x) gain
+    auto resid_norm = [&](const void* W, const void* X, int K, const T* gain) {
+      if constexpr (sizeof(T) == 2) {
+        gemm_resid_norm(m, W, (const bf16*)X, B, K, gain, h, B, nullptr, s, decode_split(m, D, B, K));
+      } else {
+        proj(W, X, D, K, EPI_RESID, m->x, nullptr, D);
+        launch_resid_rmsnorm<T>(m->x, nullptr, 0, 0, gain, h, B, D, eps, nullptr, s);
+      }
+    };
+    resid_norm(w.wo, m->o, H * hd, (const T*)w.gpost);
+    if (w.moe) {
+      enqueue_moe(m, w, (const bf16*)h, B, s);
+      launch_resid_rmsnorm<T>(m->x, nullptr, 0, 0, gnext, h, B, D, eps, nullptr, s);
+      continue;
+    }
+    if constexpr (sizeof(T) == 2) {
+      proj(w.wgu, h, 2 * I, D, EPI_SILU, nullptr, m->a, I);
+    } else {
+      proj(w.wgu, h, 2 * I, D, EPI_F32, m->gu_f32, nullptr, 2 * I);
+      launch_silu_reduce<T>(m->gu_f32, 1, 0, (T*)m->a, B, I, s);
+    }
+    resid_norm(w.wd, m->a, I, gnext);
   }
   float* dst = d_logits ? d_logits : m->logits_int;
   proj(m->lm_head, h, V, D, EPI_F32, dst, nullptr, V);
-  launch_argmax(dst, B, V, d_next, m->d_len, s);
+  launch_argmax(dst, B, V, m->am_val, m->am_idx, d_next, m->d_len, nullptr, s);
 }
 
 // Decode step, bf16: five fused weight-streaming projections per layer.
@@ -1055,7 +1070,7 @@ void enqueue_decode_gpt2(axon_model* m, int B, const int32_t* d_tokens, float* d
   } else {
     float* dst = d_logits ? d_logits : m->logits_int;
     gemm_many<bf16>(m, m->lm_head, h, V, B, D, EPI_F32, dst, nullptr, V, s);
-    launch_argmax(dst, B, V, d_next, m->d_len, s);
+    launch_argmax(dst, B, V, m->am_val, m->am_idx, d_next, m->d_len, nullptr, s);
   }
   if (plan) launch_set_step_lengths(d_cu, plan->d_slot, plan->d_base, m->d_len, B, s);
 }
@@ -1451,11 +1466,12 @@ extern "C" int axon_init_model(const axon_config* cfg, const axon_weight* weight
                           gemv_workspace_floats((int)D, Is, b, GV_RESID)});
       }
       if (wsf > 0) TRY(dev_alloc(m, (void**)&m->gemv_part, (size_t)wsf * 4));
-      // two K halves of the narrow prefill residual projections (hidden <= 2048)
-      if (!m->gpt2() && D <= 2048) {
-        m->gemm_part_floats = 2 * tmax * D;
-        TRY(dev_alloc(m, (void**)&m->gemm_part, (size_t)m->gemm_part_floats * 4));
-      }
+      // two K halves of the narrow prefill residual projections (hidden <=
+      // 2048); up to 8 splits of a decode step above 64 sequences, 64 MB at most
+      if (!m->gpt2() && D <= 2048) m->gemm_part_floats = 2 * tmax * D;
+      if (!m->gpt2() && c.max_batch > GEMV_MAX_M)
+        m->gemm_part_floats = std::max(m->gemm_part_floats, std::min<int64_t>(8 * c.max_batch * D, 16 << 20));
+      if (m->gemm_part_floats > 0) TRY(dev_alloc(m, (void**)&m->gemm_part, (size_t)m->gemm_part_floats * 4));
     }
     TRY(dev_alloc(m, (void**)&m->ss, (int64_t)std::max<int64_t>(D / 8, 1) * c.max_batch * 4));
     TRY(dev_alloc(m, &m->xg, (int64_t)std::max(c.max_batch, XT_ROWS) * D * esz));
@@ -1996,14 +2012,15 @@ void enqueue_train(axon_model* m, int B, int T, const int32_t* d_tokens, const i
     m->timed(3, H, B, T, s, [&] {
       launch_attn_prefill<bf16>(t.q, kv, t.o, T, B, d_cu, h_cu, H, s, nullptr, nullptr, nullptr, nullptr, t.lse);
     });
-    gemm_resid_norm(m, w.wo, t.o, T, Hhd, (const bf16*)w.gpost, t.h2, T, nullptr, s);
+    gemm_resid_norm(m, w.wo, t.o, T, Hhd, (const bf16*)w.gpost, t.h2, T, nullptr, s, split_for(m, D, T, Hhd));
     (void)hipMemcpyAsync(t.xmid, m->x, (size_t)T * D * 4, hipMemcpyDeviceToDevice, s);
     gemm_many<bf16>(m, w.wgu, t.h2, 2 * I, T, D, EPI_F32, t.gu, nullptr, 2 * I, s);
     launch_silu_reduce<bf16>(t.gu, 1, 0, t.a, T, I, s);
     if (l + 1 < L) {
-      gemm_resid_norm(m, w.wd, t.a, T, I, (const bf16*)m->layers[l + 1].gin, tb.L[l + 1].h1, T, nullptr, s);
+      gemm_resid_norm(m, w.wd, t.a, T, I, (const bf16*)m->layers[l + 1].gin, tb.L[l + 1].h1, T, nullptr, s,
+                      split_for(m, D, T, I));
     } else {
-      gemm_resid_norm(m, w.wd, t.a, T, I, (const bf16*)m->gfinal, tb.hf, T, nullptr, s);
+      gemm_resid_norm(m, w.wd, t.a, T, I, (const bf16*)m->gfinal, tb.hf, T, nullptr, s, split_for(m, D, T, I));
       (void)hipMemcpyAsync(tb.xfin, m->x, (size_t)T * D * 4, hipMemcpyDeviceToDevice, s);
     }
   }

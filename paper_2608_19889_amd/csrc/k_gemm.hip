@@ -639,7 +639,7 @@ struct TileCost {
 static constexpr TileCost TILE_COST[TILES] = {{256, 256, 1, 660}, {256, 128, 1, 420}, {128, 128, 1, 265},
                                               {128, 64, 1, 190},  {64, 64, 2, 120},   {32, 64, 2, 80},
                                               {32, 32, 2, 71}};
-static Tile pick_tile(int N, int M, int K, int ksplit) {
+static Tile pick_tile(int N, int M, int K, int ksplit, int64_t* ns = nullptr) {
   const int units = K / 32 / ksplit;
   Tile best = T256x256;
   int64_t least = INT64_MAX;
@@ -653,6 +653,7 @@ static Tile pick_tile(int N, int M, int K, int ksplit) {
       best = (Tile)i;
     }
   }
+  if (ns) *ns = least * units;
   return best;
 }
 
@@ -691,6 +692,25 @@ int gemm_ksplit(int N, int M, int K) {
   for (int ks : {2, 4})
     if (tiles * ks >= 200 && nk % ks == 0 && nk / ks >= 8) return ks;
   return nk % 2 == 0 && nk / 2 >= 8 ? 2 : 1;
+}
+
+int gemm_ksplit_few(int N, int M, int K, int max_split) {
+  const int units = K / 32;
+  int best = 1;
+  int64_t least = INT64_MAX;
+  for (int ks = 1; ks <= max_split; ks *= 2) {
+    if (units % ks || units / ks < 8) break;
+    int64_t ns = 0;
+    pick_tile(N, M, K, ks, &ns);
+    // partials written and read again, ~6 bytes per ns through the caches; a
+    // split saves the residual's read-modify-write in the GEMM
+    if (ks > 1) ns += (int64_t)ks * M * N * 8 / 6000;
+    if (ns < least) {
+      least = ns;
+      best = ks;
+    }
+  }
+  return best;
 }
 
 void launch_gemm_bf16_grouped(const bf16* W, const bf16* X, int N, int K, int max_rows, int epi, const EpiArgs& ep,

@@ -67,9 +67,14 @@ __global__ void __launch_bounds__(256) resid_rmsnorm_kernel(float* __restrict__ 
   for (int i = threadIdx.x * 4; i < D; i += blockDim.x * 4) {
     f32x4 v = load4(xr + i);
     if (nparts > 0) {
-      for (int s = 0; s < nparts; ++s) {
-        f32x4 p = load4(parts + s * part_stride + (int64_t)r * D + i);
-        v[0] += p[0]; v[1] += p[1]; v[2] += p[2]; v[3] += p[3];
+      // in order, 4 parts' loads in flight per round
+      for (int s0 = 0; s0 < nparts; s0 += 4) {
+        f32x4 p[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) p[q] = load4(parts + min(s0 + q, nparts - 1) * part_stride + (int64_t)r * D + i);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (s0 + q < nparts) v += p[q];
       }
       store4(xr + i, v);
     }
@@ -84,39 +89,45 @@ __global__ void __launch_bounds__(256) resid_rmsnorm_kernel(float* __restrict__ 
   }
 }
 
-// next[r] = argmax_v logits[r, v] (lowest index among equal maxima); when
-// ``len`` is set, len[r] += 1 (the decode step has appended one position).
-// The row read is cu_last[i+1]-1 when ``cu_last`` is set (last position of
-// sequence i in a packed all-positions logits matrix), else i.
-__global__ void __launch_bounds__(1024) argmax_kernel(const float* __restrict__ logits, int V,
-                                                      int32_t* __restrict__ next,
-                                                      int32_t* __restrict__ len,
-                                                      const int32_t* __restrict__ cu_last) {
-  __shared__ float sv[16];
-  __shared__ int si[16];
-  const int i_out = blockIdx.x;
+// Partial argmax of a logits row: workgroup (chunk, i) writes the largest of
+// row r's columns ARGMAX_COLS chunk .. and its lowest index (a row of -inf or
+// NaN: -inf and no index); launch_argmax_final merges the chunks.  r = i, or
+// cu_last[i+1]-1 when ``cu_last`` is set (last position of sequence i in a
+// packed all-positions logits matrix).  HBM bound: one workgroup per row, 160
+// rows of 128256 columns, kept too few loads in flight (63 us; chunks of 4096
+// columns with 16 independent loads per thread and the merge 18 us).
+constexpr int ARGMAX_COLS = 4096;
+__global__ void __launch_bounds__(256) argmax_part_kernel(const float* __restrict__ logits, int V,
+                                                          float* __restrict__ val, int32_t* __restrict__ idx,
+                                                          const int32_t* __restrict__ cu_last) {
+  __shared__ float sv[4];
+  __shared__ int si[4];
+  const int i_out = blockIdx.y;
   const int r = cu_last ? cu_last[i_out + 1] - 1 : i_out;
   const float* row = logits + (int64_t)r * V;
+  const int c0 = blockIdx.x * ARGMAX_COLS + threadIdx.x;
+  float v[ARGMAX_COLS / 256];
+#pragma unroll
+  for (int j = 0; j < ARGMAX_COLS / 256; ++j) v[j] = row[min(c0 + j * 256, V - 1)];  // past the row: its last column
   float best = -INFINITY;
   int bi = 0x7fffffff;
-  for (int i = threadIdx.x; i < V; i += blockDim.x) {
-    float v = row[i];
-    if (v > best) { best = v; bi = i; }  // ascending scan: first maximum per thread
-  }
+#pragma unroll
+  for (int j = 0; j < ARGMAX_COLS / 256; ++j)
+    if (v[j] > best) { best = v[j]; bi = min(c0 + j * 256, V - 1); }  // ascending scan: first maximum per thread
 #pragma unroll
   for (int m = 32; m >= 1; m >>= 1) {
-    float ov = __shfl_xor(best, m, 64);
-    int oi = __shfl_xor(bi, m, 64);
+    const float ov = __shfl_xor(best, m, 64);
+    const int oi = __shfl_xor(bi, m, 64);
     if (ov > best || (ov == best && oi < bi)) { best = ov; bi = oi; }
   }
   const int w = threadIdx.x >> 6;
   if ((threadIdx.x & 63) == 0) { sv[w] = best; si[w] = bi; }
   __syncthreads();
   if (threadIdx.x == 0) {
-    for (int k = 1; k < (int)(blockDim.x >> 6); ++k)
+    for (int k = 1; k < 4; ++k)
       if (sv[k] > best || (sv[k] == best && si[k] < bi)) { best = sv[k]; bi = si[k]; }
-    next[i_out] = bi == 0x7fffffff ? 0 : bi;
-    if (len) len[i_out] += 1;
+    val[(int64_t)i_out * gridDim.x + blockIdx.x] = best;
+    idx[(int64_t)i_out * gridDim.x + blockIdx.x] = bi;
   }
 }
 
@@ -147,14 +158,12 @@ void launch_resid_rmsnorm(float* x, const float* parts, int nparts, int64_t part
   resid_rmsnorm_kernel<T><<<rows, 256, 0, s>>>(x, parts, nparts, part_stride, g, h, D, eps, cu_last, h_pair ? 1 : 0);
 }
 
-void launch_argmax(const float* logits, int rows, int V, int32_t* next, int32_t* len, hipStream_t s) {
+void launch_argmax(const float* logits, int rows, int V, float* am_val, int32_t* am_idx, int32_t* next, int32_t* len,
+                   const int32_t* cu_last, hipStream_t s) {
   if (rows <= 0) return;
-  argmax_kernel<<<rows, 1024, 0, s>>>(logits, V, next, len, nullptr);
-}
-
-void launch_argmax_rows(const float* logits, int nseq, int V, int32_t* next, const int32_t* cu, hipStream_t s) {
-  if (nseq <= 0) return;
-  argmax_kernel<<<nseq, 1024, 0, s>>>(logits, V, next, nullptr, cu);
+  const int chunks = (V + ARGMAX_COLS - 1) / ARGMAX_COLS;
+  argmax_part_kernel<<<dim3(chunks, rows), 256, 0, s>>>(logits, V, am_val, am_idx, cu_last);
+  launch_argmax_final(am_val, am_idx, chunks, rows, next, len, s);
 }
 
 void launch_set_lengths(const int32_t* cu, int32_t* len, int n, hipStream_t s) {

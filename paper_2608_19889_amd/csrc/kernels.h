@@ -149,9 +149,11 @@ void launch_embed_rmsnorm(const int32_t* tok, const T* emb, const T* g, float* x
 template <typename T>
 void launch_resid_rmsnorm(float* x, const float* parts, int nparts, int64_t part_stride, const T* g, T* h,
                           int rows, int D, float eps, const int32_t* cu_last, hipStream_t s, bool h_pair = false);
-void launch_argmax(const float* logits, int rows, int V, int32_t* next, int32_t* len, hipStream_t s);
-// argmax of row cu[i+1]-1 for each sequence i
-void launch_argmax_rows(const float* logits, int nseq, int V, int32_t* next, const int32_t* cu, hipStream_t s);
+// next[i] = argmax of logits row i, or (cu_last) of row cu_last[i+1]-1, the lowest
+// index on ties; len[i] += 1 when set; am_val / am_idx: scratch of rows x
+// ceil(V / 4096)
+void launch_argmax(const float* logits, int rows, int V, float* am_val, int32_t* am_idx, int32_t* next, int32_t* len,
+                   const int32_t* cu_last, hipStream_t s);
 void launch_set_lengths(const int32_t* cu, int32_t* len, int n, hipStream_t s);
 // len[ent_slot[e]] = ent_base[e] + cu[e+1] - cu[e] for the n entries of a step
 void launch_set_step_lengths(const int32_t* cu, const int32_t* ent_slot, const int32_t* ent_base, int32_t* len,
@@ -175,6 +177,10 @@ void launch_gemm_bf16_grouped(const bf16* W, const bf16* X, int N, int K, int ma
 void launch_gemm_bf16_split(const bf16* W, const bf16* X, int N, int M, int K, int ksplit, float* part,
                             int64_t part_stride, hipStream_t s, bool xpair = false);
 int gemm_ksplit(int N, int M, int K);
+// the split of a few-token residual projection (decode batches above 64) whose
+// partials the next normalization sums: the least of GEMM time and partials'
+// traffic, at most max_split
+int gemm_ksplit_few(int N, int M, int K, int max_split);
 // out[i] (accumulate ? += : =) sum of parts[s * stride + i] over s in order (n % 4 == 0)
 void launch_sum_parts(float* out, const float* parts, int nparts, int64_t stride, int64_t n, int accumulate,
                       hipStream_t s);

@@ -8,7 +8,7 @@ import pytest
 import torch
 
 import oracle
-from parity_util import check_bf16, gpu_model
+from parity_util import check_bf16, gpu_model, run_teacher_forced
 from synthetic import model_weights, prompts, small_shape
 
 pytestmark = pytest.mark.gpu
@@ -50,3 +50,31 @@ def test_every_tile_shape_gives_the_same_bits_and_the_oracles_logits(case):
     # the band around the bf16 storage error is the bar: at these widths that
     # error alone (mean 2.8e-3) is past the absolute 2e-3
     check_bf16(full[:n].double().numpy(), np.asarray(exact), np.asarray(b16), f"tiles {case}", absolute=False)
+
+
+# decode batches above 64: the residual projections' K splits (the partials are
+# summed by the next normalization) and the argmax over several column chunks;
+# widths, K of even and odd unit counts, an odd vocabulary past two chunks
+WIDE = {
+    "split_deep": (66, dict(layers=2, vocab=9001, hidden=512, intermediate=8192)),
+    "odd_units": (129, dict(layers=2, vocab=4097, hidden=576, intermediate=1088)),
+}
+
+
+@pytest.mark.parametrize("case", list(WIDE))
+def test_decode_above_64_sequences(case):
+    B, ov = WIDE[case]
+    shape = small_shape("1b", **ov)
+    w = model_weights(shape, seed=43)
+    V = shape["vocab_size"]
+    ids = prompts(B, 6, V, seed=44).numpy()
+    seqs = [ids[b, :1 + b % 4] for b in range(B)]
+    forced = ids[:, 4:6]
+    w64 = oracle.weights_f64(w)
+    exact = oracle.teacher_forced(oracle.OracleDecoder(shape, w64), seqs, forced)
+    b16 = oracle.teacher_forced(oracle.OracleDecoder(shape, w64, io_round="bf16"), seqs, forced)
+    m = gpu_model(shape, w, max_batch=B, max_seq=8)
+    got, toks = run_teacher_forced(m, seqs, forced)
+    m.close()
+    check_bf16(got, exact, b16, f"decode above 64 {case}", absolute=False)
+    np.testing.assert_array_equal(toks.T, got.argmax(-1))
