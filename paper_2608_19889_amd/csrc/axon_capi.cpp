@@ -247,15 +247,15 @@ struct TrainLayer {
 };
 struct TrainBufs {
   bool ready = false;
-  int Tc = 0, Tp = 0, Vp = 0;
+  int Tc = 0, Vp = 0;
   int SP = 0;       // positions per sequence in the attention backward's packed copies
   int64_t W = 0;    // max_batch * SP
   bf16 *kr, *vr, *kt, *qt, *dot;
   std::vector<TrainLayer> L;
   float *xfin, *logits, *rowloss, *valid, *lserow, *scal, *dx, *dtmp, *dgrow, *dqf, *dkf, *dvf, *dsum, *dqkvf,
-      *colpart, *gtmp, *dkh, *dvh;
+      *colpart, *dkh, *dvh;
   float* statp;     // attention backward: log2-sum-exp and D in packed per-head rows [2][H][W]
-  bf16 *hf, *dlog, *dxb, *dgu, *dob, *dqkv, *tra, *trs, *trb, *headT;
+  bf16 *hf, *dlog, *dxb, *dgu, *dob, *dqkv, *headT;
 };
 
 // Per-step work buffers of the bf16 decode step: the model's own (allocated
@@ -1877,9 +1877,8 @@ int train_setup(axon_model* m, hipStream_t s) {
   const int64_t D = c.hidden, H = c.n_heads, KV = c.n_kv_heads, hd = c.head_dim, I = c.intermediate, V = c.vocab;
   const int64_t nq = (H + 2 * KV) * hd, Hhd = H * hd;
   tb.Tc = m->rows;
-  tb.Tp = (tb.Tc + 31) / 32 * 32;
   tb.Vp = (int)((V + 31) / 32 * 32);
-  const int64_t T = tb.Tc, Tp = tb.Tp, Vp = tb.Vp;
+  const int64_t T = tb.Tc, Vp = tb.Vp;
   auto tiled = [](int64_t rows, int64_t cols) { return (rows + 15) / 16 * 16 * cols; };
   auto fa = [&](float** p, int64_t n) { return dev_alloc(m, (void**)p, (size_t)n * 4); };
   auto ba = [&](bf16** p, int64_t n) { return dev_alloc(m, (void**)p, (size_t)n * 2); };
@@ -1900,7 +1899,6 @@ int train_setup(axon_model* m, hipStream_t s) {
     if (!r) r = ba(&l.wguT, tiled(D, 2 * I));
     if (!r) r = ba(&l.wdT, tiled(I, D));
   }
-  const int64_t maxN = std::max({Vp, 2 * I, nq, D}), maxK = std::max({D, I, Hhd});
   if (!r) r = fa(&tb.xfin, T * D);
   if (!r) r = fa(&tb.logits, T * Vp);
   if (!r) r = fa(&tb.rowloss, T);
@@ -1918,16 +1916,12 @@ int train_setup(axon_model* m, hipStream_t s) {
   if (!r) r = fa(&tb.dsum, T * H);
   if (!r) r = fa(&tb.dqkvf, T * nq);
   if (!r) r = fa(&tb.colpart, (int64_t)colsum_chunks((int)T) * std::max(nq, D));
-  if (!r) r = fa(&tb.gtmp, std::max(nq, 2 * I) * D);
   if (!r) r = ba(&tb.hf, T * D);
   if (!r) r = ba(&tb.dlog, T * Vp);
   if (!r) r = ba(&tb.dxb, T * D);
   if (!r) r = ba(&tb.dgu, T * 2 * I);
   if (!r) r = ba(&tb.dob, T * Hhd);
   if (!r) r = ba(&tb.dqkv, T * nq);
-  if (!r) r = ba(&tb.tra, maxN * Tp);
-  if (!r) r = ba(&tb.trs, maxK * Tp);
-  if (!r) r = ba(&tb.trb, tiled(maxK, Tp));
   if (!r) r = ba(&tb.headT, tiled(D, Vp));
   // split-K partials of the narrow training GEMMs: up to 4 splits of an
   // output as large as T x max(D, I) or one weight's gradient
@@ -1994,7 +1988,7 @@ void enqueue_train(axon_model* m, int B, int T, const int32_t* d_tokens, const i
   const axon_config& c = m->cfg;
   TrainBufs& tb = m->train;
   const int D = c.hidden, H = c.n_heads, KV = c.n_kv_heads, hd = c.head_dim, I = c.intermediate, V = c.vocab;
-  const int nq = (H + 2 * KV) * hd, Hhd = H * hd, Tp = tb.Tp, Vp = tb.Vp, L = c.n_layers;
+  const int nq = (H + 2 * KV) * hd, Hhd = H * hd, Vp = tb.Vp, L = c.n_layers;
   const float eps = c.rms_eps;
   auto G = [&](const std::string& n) { return g[gi.at(n)]; };
   // ---- forward, keeping activations
@@ -2032,16 +2026,17 @@ void enqueue_train(axon_model* m, int B, int T, const int32_t* d_tokens, const i
   auto dX = [&](const bf16* WT, const bf16* dY, int N, int K, float* out) {
     gemm_f32_out(m, WT, dY, K, T, N, out, false, s);
   };
-  // dW = dY^T X: [N][K] float from dY [T][N] (rows ldy apart) and X [T][K]
-  auto dW = [&](const bf16* dY, int ldy, int N, const bf16* X, int K, float* out) {
-    launch_transpose_pad(dY, ldy, T, N, tb.tra, Tp, s);
-    launch_transpose_pad(X, K, T, K, tb.trs, Tp, s);
-    launch_tile_weight(tb.trs, tb.trb, K, Tp, s);
-    gemm_f32_out(m, tb.trb, tb.tra, K, N, Tp, out, false, s);
+  // dW = dY^T X, [N][K] float (or its rows' own tensors), from dY [T][N] (rows
+  // ldy apart) and X [T][K]
+  auto dW = [&](const bf16* dY, int ldy, int N, const bf16* X, int K, int mode, float* o0, float* o1 = nullptr,
+                float* o2 = nullptr) {
+    m->timed(1, K, N, T, s, [&] {
+      launch_wgrad(mode, dY, ldy, N, X, K, T, false, o0, o1, o2, hd, H, KV, m->gemm_part, m->gemm_part_floats, s);
+    });
   };
   const bool tied = c.tie_embeddings;
   float* g_embed = G("model.embed_tokens.weight");
-  dW(tb.dlog, Vp, V, tb.hf, D, tied ? g_embed : G("lm_head.weight"));
+  dW(tb.dlog, Vp, V, tb.hf, D, WGRAD_ROWS, tied ? g_embed : G("lm_head.weight"));
   dX(tb.headT, tb.dlog, Vp, D, tb.dtmp);
   launch_rmsnorm_bwd(tb.xfin, (const bf16*)m->gfinal, tb.dtmp, D, T, D, eps, tb.dx, 0, tb.dgrow, s);
   launch_colsum(tb.dgrow, D, T, D, tb.colpart, G("model.norm.weight"), s);
@@ -2052,18 +2047,16 @@ void enqueue_train(axon_model* m, int B, int T, const int32_t* d_tokens, const i
     const std::string p = "model.layers." + std::to_string(l) + ".";
     // MLP
     launch_to_bf16(tb.dx, tb.dxb, (int64_t)T * D, s);
-    dW(tb.dxb, D, D, t.a, I, G(p + "mlp.down_proj.weight"));
+    dW(tb.dxb, D, D, t.a, I, WGRAD_ROWS, G(p + "mlp.down_proj.weight"));
     dX(t.wdT, tb.dxb, D, I, tb.dtmp);
     launch_swiglu_bwd(t.gu, tb.dtmp, tb.dgu, T, I, s);
-    dW(tb.dgu, 2 * I, 2 * I, t.h2, D, tb.gtmp);
-    launch_scatter_rows(tb.gtmp, 2 * I, D, 1, hd, H, KV, G(p + "mlp.gate_proj.weight"), G(p + "mlp.up_proj.weight"),
-                        nullptr, s);
+    dW(tb.dgu, 2 * I, 2 * I, t.h2, D, WGRAD_GU, G(p + "mlp.gate_proj.weight"), G(p + "mlp.up_proj.weight"));
     dX(t.wguT, tb.dgu, 2 * I, D, tb.dtmp);
     launch_rmsnorm_bwd(t.xmid, (const bf16*)w.gpost, tb.dtmp, D, T, D, eps, tb.dx, 1, tb.dgrow, s);
     launch_colsum(tb.dgrow, D, T, D, tb.colpart, G(p + "post_attention_layernorm.weight"), s);
     // attention
     launch_to_bf16(tb.dx, tb.dxb, (int64_t)T * D, s);
-    dW(tb.dxb, D, D, t.o, Hhd, G(p + "self_attn.o_proj.weight"));
+    dW(tb.dxb, D, D, t.o, Hhd, WGRAD_ROWS, G(p + "self_attn.o_proj.weight"));
     dX(t.woT, tb.dxb, D, Hhd, tb.dtmp);
     launch_to_bf16(tb.dtmp, tb.dob, (int64_t)T * Hhd, s);
     m->timed(5, H, B, T, s, [&] {
@@ -2074,9 +2067,8 @@ void enqueue_train(axon_model* m, int B, int T, const int32_t* d_tokens, const i
     });
     launch_rope_bwd(tb.dqf, tb.dkf, tb.dvf, m->rope_cos, m->rope_sin, d_cu, B, T, H, KV, hd, tb.dqkv,
                     c.qkv_bias ? tb.dqkvf : nullptr, s);
-    dW(tb.dqkv, nq, nq, t.h1, D, tb.gtmp);
-    launch_scatter_rows(tb.gtmp, nq, D, 0, hd, H, KV, G(p + "self_attn.q_proj.weight"),
-                        G(p + "self_attn.k_proj.weight"), G(p + "self_attn.v_proj.weight"), s);
+    dW(tb.dqkv, nq, nq, t.h1, D, WGRAD_QKV, G(p + "self_attn.q_proj.weight"), G(p + "self_attn.k_proj.weight"),
+       G(p + "self_attn.v_proj.weight"));
     if (c.qkv_bias) {
       launch_colsum(tb.dqkvf, nq, T, Hhd, tb.colpart, G(p + "self_attn.q_proj.bias"), s);
       launch_colsum(tb.dqkvf + Hhd, nq, T, KV * hd, tb.colpart, G(p + "self_attn.k_proj.bias"), s);

@@ -586,6 +586,240 @@ __global__ void __launch_bounds__(512, 1) gemm_bf16_256_kernel(const bf16* __res
   }
 }
 
+// ============================================================================
+// Weight-gradient GEMM: out[r][c] = sum_t Y[t][r] X[t][c] over T token rows
+// (dW = dY^T X), both operands token-major as the backward pass leaves them.
+// The schedule, tile and ring of the 256 x 256 kernel; a k-tile is 32 token
+// rows of 256 columns of either operand (X the MFMA A operand, Y the B
+// operand), and the transposition the fragments need is done by the LDS read
+// itself: ds_read_tr16_b64, where 16 lanes read 4 token rows of 16 columns
+// (lane i: row i / 4, columns 4 (i % 4) ..) and lane i receives column i's 4
+// values.  A wavefront's read touches 8 token rows of 64 bytes; rows 512 bytes
+// apart would share 16 banks, so a row's 64-byte segments are permuted by the
+// row (segment ^ row % 4, by the chunk a lane loads).  Token rows past T read
+// row T - 1; their Y values are zeroed in the last k-tile.
+// The transposed copies it replaces (both operands through LDS tiles, X also
+// fragment-tiled) took 2.4 ms of the 21.1 ms 1B-shaped 4-layer training step.
+// XP: Y and X in the row-pair layout (xp_off).
+// ============================================================================
+struct TnArgs {
+  const bf16* Y;  // [T][ldy], output row r = column r
+  const bf16* X;  // [T][ldx], output column c = column c
+  int R, C, T, ldy, ldx;
+  float* out;     // WGRAD_ROWS: [R][C]; split K: partials [split][R][C]
+  // WGRAD_QKV / WGRAD_GU: the rows' own tensors (q, k, v / gate, up)
+  float *out1, *out2;
+  int hd, H, KVh;
+};
+// Row r of the gradient's destination.  WGRAD_QKV: heads q, k, v, a head's
+// rows in groups of 8 = 4 first halves and their rotation partners; WGRAD_GU:
+// 16 gate rows, then the 16 matching up rows.
+template <int MODE>
+AXON_DEV float* wgrad_row(const TnArgs& a, int r) {
+  if constexpr (MODE == WGRAD_QKV) {
+    const int hh = r / a.hd, rr = r % a.hd, g = rr / 8, j = rr % 8;
+    const int64_t row = (int64_t)hh * a.hd + (j < 4 ? 4 * g + j : a.hd / 2 + 4 * g + j - 4);
+    if (hh < a.H) return a.out + row * a.C;
+    if (hh < a.H + a.KVh) return a.out1 + (row - (int64_t)a.H * a.hd) * a.C;
+    return a.out2 + (row - (int64_t)(a.H + a.KVh) * a.hd) * a.C;
+  } else if constexpr (MODE == WGRAD_GU) {
+    const int64_t row = r / 32 * 16 + r % 16;
+    return (r % 32 < 16 ? a.out : a.out1) + row * a.C;
+  } else {
+    return a.out + (int64_t)r * a.C;
+  }
+}
+
+template <int MODE, bool XP>
+__global__ void __launch_bounds__(512, 1) gemm_tn_256_kernel(TnArgs g) {
+  using namespace pf2;
+  extern __shared__ bf16x8 lds2[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int grp = wave >> 2, wc = wave & 3;
+  int pn, pm;
+  tile_order(blockIdx.x, (g.C + BN - 1) / BN, (g.R + BM - 1) / BM, pn, pm);
+  const int n0 = pn * BN, m0 = pm * BM;
+
+  // split K (gridDim.y): k-tiles kb .. kb + nk - 1 of ceil(T / 32)
+  const int nkt = (g.T + BK - 1) / BK, per = (nkt + gridDim.y - 1) / gridDim.y;
+  const int kb = min((int)blockIdx.y * per, nkt), nk = min(nkt - kb, per);
+
+  // load i of a wavefront: token rows 4 wave + 2 i, + 1 of the k-tile, 32 chunks
+  // of 8 columns each; columns past the operand read its last 8 (never stored)
+  const int lrow = wave * 4 + (lane >> 5), pch = lane & 31;
+  auto src = [&](const bf16* p, int ld, int t, int c) -> const bf16* {
+    t = min(t, g.T - 1);
+    c = min(c, ld - 8);
+    return p + (XP ? xp_off(t, c, ld) : (int64_t)t * ld + c);
+  };
+  auto issue = [&](int stage, int kt) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int row = lrow + i * 2, c = (pch ^ ((row & 3) << 2)) * 8;
+      bf16x8* base = lds2 + stage * STAGE + (wave * 2 + i) * 64;
+      __builtin_amdgcn_global_load_lds((const void*)src(g.X, g.ldx, kt * BK + row, n0 + c),
+                                       (__attribute__((address_space(3))) void*)base, 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((const void*)src(g.Y, g.ldy, kt * BK + row, m0 + c),
+                                       (__attribute__((address_space(3))) void*)(base + PANEL), 16, 0, 0);
+    }
+  };
+
+  f32x16 acc[4][2];
+#pragma unroll
+  for (int a = 0; a < 4; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b) acc[a][b] = f32x16{};
+#pragma unroll
+  for (int st = 0; st < STAGES - 1; ++st)
+    if (st < nk) issue(st, kb + st);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (grp == 1) phase_barrier();  // group 1 runs one phase behind group 0
+
+  // element offset of this lane's first read of column block cb (32 columns):
+  // token row 8 (lane / 32) + (lane % 16) / 4, columns cb * 32 + 16 ((lane / 16)
+  // % 2) + 4 (lane % 4) ..
+  auto frag_at = [&](int cb) {
+    const int row = (lane >> 5) * 8 + ((lane >> 2) & 3);
+    const int ch = (cb * 4 + ((lane >> 4) & 1) * 2 + ((lane >> 1) & 1)) ^ (((lane >> 2) & 3) << 2);
+    return row * 256 + ch * 8 + (lane & 1) * 4;
+  };
+  int offa[4], offb[2];
+#pragma unroll
+  for (int a = 0; a < 4; ++a) offa[a] = frag_at(grp * 4 + a);
+#pragma unroll
+  for (int b = 0; b < 2; ++b) offb[b] = frag_at(wc * 2 + b);
+  // 8 token rows (ks * 16 + 8 (lane / 32) ..) of this lane's column
+  auto read8 = [&](const bf16* p, int off, int ks) {
+    typedef __attribute__((address_space(3))) bf16x4 lds4;
+    const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds4*)(p + off + ks * 16 * 256));
+    const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds4*)(p + off + (ks * 16 + 4) * 256));
+    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+  };
+
+  bf16x8 fa[2][4], fb[2][2];
+  auto ktile = [&](int kt, bool do_issue, int after, bool last) {
+    const bf16* la = (const bf16*)(lds2 + (kt % STAGES) * STAGE);
+    const bf16* lb = la + PANEL * 8;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+#pragma unroll
+      for (int a = 0; a < 4; ++a) fa[ks][a] = read8(la, offa[a], ks);
+#pragma unroll
+      for (int b = 0; b < 2; ++b) fb[ks][b] = read8(lb, offb[b], ks);
+    }
+    const int kn = kt + STAGES - 1;
+    if (do_issue) issue(kn % STAGES, kb + kn);
+    if (grp == 1) wait_tiles(after);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    if (last && (kb + kt + 1) * BK > g.T) {  // token rows past T contribute nothing
+      const int t0 = (kb + kt) * BK + (lane >> 5) * 8;
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+          for (int j = 0; j < 8; ++j)
+            if (t0 + ks * 16 + j >= g.T) fb[ks][b][j] = (bf16)0.f;
+    }
+    phase_barrier();
+    __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+          acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ks][a], fb[ks][b], acc[a][b], 0, 0, 0);
+    __builtin_amdgcn_s_setprio(0);
+    if (grp == 0) wait_tiles(after);
+    phase_barrier();
+  };
+  int kt = 0;
+  for (; kt + STAGES - 1 < nk; ++kt) ktile(kt, true, STAGES - 2, false);
+#pragma unroll
+  for (int j = 0; j < STAGES - 1; ++j)
+    if (kt < nk) {
+      ktile(kt, false, min(STAGES - 2, nk - 2 - kt), kt == nk - 1);
+      ++kt;
+    }
+  if (grp == 0) phase_barrier();  // same barrier count in both groups
+
+#pragma unroll
+  for (int b = 0; b < 2; ++b) {
+    const int r = m0 + wc * 64 + b * 32 + (lane & 31);
+    if (r >= g.R) continue;
+    float* row = gridDim.y > 1 ? g.out + ((int64_t)blockIdx.y * g.R + r) * g.C : wgrad_row<MODE>(g, r);
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int c = n0 + grp * 128 + a * 32 + q * 8 + (lane >> 5) * 4;  // C % 32 == 0
+        if (c < g.C)
+          *(f32x4*)(row + c) = f32x4{acc[a][b][q * 4], acc[a][b][q * 4 + 1], acc[a][b][q * 4 + 2], acc[a][b][q * 4 + 3]};
+      }
+  }
+}
+
+// the split partials summed in order into the gradient's rows
+template <int MODE>
+__global__ void __launch_bounds__(256) wgrad_sum_kernel(TnArgs g, const float* __restrict__ parts, int nparts) {
+  const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
+  if (i >= (int64_t)g.R * g.C) return;
+  const int r = (int)(i / g.C), c = (int)(i % g.C);
+  f32x4 v = {};
+  for (int s0 = 0; s0 < nparts; s0 += 4) {
+    f32x4 p[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) p[q] = *(const f32x4*)(parts + min(s0 + q, nparts - 1) * ((int64_t)g.R * g.C) + i);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (s0 + q < nparts) v += p[q];
+  }
+  *(f32x4*)(wgrad_row<MODE>(g, r) + c) = v;
+}
+
+template <int MODE, bool XP>
+static void launch_tn(TnArgs g, float* part, int64_t part_floats, hipStream_t s) {
+  static bool attr = false;
+  auto kern = gemm_tn_256_kernel<MODE, XP>;
+  if (!attr) {
+    (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, pf2::LDS_BYTES);
+    attr = true;
+  }
+  const int tiles = ((g.R + 255) / 256) * ((g.C + 255) / 256), nkt = (g.T + 31) / 32;
+  // few tiles: split the tokens towards 256 workgroups, at least 16 k-tiles each
+  int ks = 1;
+  while (ks < 8 && tiles * ks * 2 <= 256 && nkt / (ks * 2) >= 16 && (int64_t)ks * 2 * g.R * g.C <= part_floats) ks *= 2;
+  if (ks == 1) {
+    klaunch(kern, dim3(tiles, 1), dim3(512), pf2::LDS_BYTES, s, g);
+    return;
+  }
+  TnArgs p = g;
+  p.out = part;
+  klaunch(kern, dim3(tiles, ks), dim3(512), pf2::LDS_BYTES, s, p);
+  const int64_t n4 = (int64_t)g.R * g.C / 4;
+  wgrad_sum_kernel<MODE><<<(unsigned)((n4 + 255) / 256), 256, 0, s>>>(g, part, ks);
+}
+
+void launch_wgrad(int mode, const bf16* Y, int ldy, int R, const bf16* X, int C, int T, bool xpair, float* out,
+                  float* out1, float* out2, int hd, int H, int KVh, float* part, int64_t part_floats, hipStream_t s) {
+  if (T <= 0 || R <= 0 || C <= 0) return;
+  const TnArgs g{Y, X, R, C, T, ldy, C, out, out1, out2, hd, H, KVh};
+#define AXON_TN(M)                                            \
+  case M:                                                     \
+    if (xpair) launch_tn<M, true>(g, part, part_floats, s);   \
+    else launch_tn<M, false>(g, part, part_floats, s);        \
+    return;
+  switch (mode) {
+    AXON_TN(WGRAD_ROWS)
+    AXON_TN(WGRAD_QKV)
+    AXON_TN(WGRAD_GU)
+  }
+#undef AXON_TN
+}
+
 // the 256 x 256 kernel instance, its LDS size raised at first use
 template <int EPI, bool GROUPED, bool XP>
 static auto kern_256() {

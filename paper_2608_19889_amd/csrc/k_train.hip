@@ -604,29 +604,6 @@ __global__ void __launch_bounds__(256) rope_bwd_kernel(const float* __restrict__
   }
 }
 
-// Rows of a projection gradient [R][D] in the kernel layout, back to the
-// weight map's tensors: mode 0 (fused QKV, heads q then k then v, grouped rows)
-// into dst0 / dst1 / dst2 = q / k / v; mode 1 (gate/up interleaved in blocks
-// of 16) into dst0 / dst1 = gate / up.  4 columns per thread.
-__global__ void __launch_bounds__(256) scatter_rows_kernel(const float* __restrict__ src, int D, int mode, int hd,
-                                                           int H, int KVh, float* __restrict__ dst0,
-                                                           float* __restrict__ dst1, float* __restrict__ dst2) {
-  const int r = blockIdx.x;
-  const int c = (blockIdx.y * 256 + threadIdx.x) * 4;
-  if (c >= D) return;
-  float* dst;
-  if (mode == 0) {
-    const int hh = r / hd, rr = r % hd, g = rr / 8, j = rr % 8;
-    const int L = hh * hd + (j < 4 ? 4 * g + j : hd / 2 + 4 * g + j - 4);
-    dst = hh < H ? dst0 + (int64_t)L * D
-                 : (hh < H + KVh ? dst1 + (int64_t)(L - H * hd) * D : dst2 + (int64_t)(L - (H + KVh) * hd) * D);
-  } else {
-    const int b = r / 32, j = r % 32;
-    dst = j < 16 ? dst0 + (int64_t)(b * 16 + j) * D : dst1 + (int64_t)(b * 16 + j - 16) * D;
-  }
-  *(f32x4*)(dst + c) = *(const f32x4*)(src + (int64_t)r * D + c);
-}
-
 // dE[tok[t]] += dx[t] (tokens repeat, hence atomic additions)
 __global__ void __launch_bounds__(256) embed_bwd_kernel(const int32_t* __restrict__ tok, const float* __restrict__ dx,
                                                         int D, int V, float* __restrict__ dE) {
@@ -642,11 +619,6 @@ void launch_ce_loss(const float* logits, int ldl, int V, const int32_t* targets,
   ce_rows_kernel<<<T, 256, 0, s>>>(logits, ldl, V, targets, rowloss, valid, lse);
   ce_reduce_kernel<<<1, 256, 0, s>>>(rowloss, valid, T, loss, scal);
   ce_grad_kernel<<<dim3((ldl / 4 + 255) / 256, T), 256, 0, s>>>(logits, ldl, V, targets, valid, lse, scal, dlog);
-}
-
-void launch_transpose_pad(const bf16* src, int ld, int T, int C, bf16* dst, int Tp, hipStream_t s) {
-  if (C <= 0 || Tp <= 0) return;
-  transpose_tile_kernel<<<dim3((Tp + 63) / 64, (C + 63) / 64), 256, 0, s>>>(src, ld, T, Tp, C, dst, Tp, nullptr, 0, 0);
 }
 
 void launch_untile_transpose(const bf16* W, int64_t N, int K, bf16* dst, int64_t Np, hipStream_t s) {
@@ -730,11 +702,6 @@ void launch_rope_bwd(const float* dq, const float* dk, const float* dv, const fl
   if (n > 0)
     rope_bwd_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(dq, dk, dv, cos_t, sin_t, cu, nseq, T, H, KVh, hd,
                                                                 dqkv, dqkv_f);
-}
-
-void launch_scatter_rows(const float* src, int R, int D, int mode, int hd, int H, int KVh, float* dst0, float* dst1,
-                         float* dst2, hipStream_t s) {
-  if (R > 0) scatter_rows_kernel<<<dim3(R, (D / 4 + 255) / 256), 256, 0, s>>>(src, D, mode, hd, H, KVh, dst0, dst1, dst2);
 }
 
 void launch_embed_bwd(const int32_t* tok, const float* dx, int T, int D, int V, float* dE, hipStream_t s) {

@@ -99,8 +99,6 @@ void launch_transpose_rows(const bf16* src, bf16* dst, int K, int N, const int32
 // its gradient (zero padding); rowloss / valid / lse [T] and scal [1] scratch
 void launch_ce_loss(const float* logits, int ldl, int V, const int32_t* targets, int T, float* rowloss, float* valid,
                     float* lse, float* loss, float* scal, bf16* dlog, hipStream_t s);
-// dst [C][Tp] = src [T][C]^T (rows ld apart), zero columns T .. Tp-1 (Tp % 8 == 0)
-void launch_transpose_pad(const bf16* src, int ld, int T, int C, bf16* dst, int Tp, hipStream_t s);
 // dst [K][Np] (row-major) = W^T for the fragment-tiled W [N][K]
 void launch_untile_transpose(const bf16* W, int64_t N, int K, bf16* dst, int64_t Np, hipStream_t s);
 void launch_to_bf16(const float* src, bf16* dst, int64_t n, hipStream_t s);  // n % 4 == 0
@@ -131,10 +129,6 @@ bool launch_attn_bwd(const bf16* q, KVView kv, const bf16* o, const bf16* dob, c
 void launch_rope_bwd(const float* dq, const float* dk, const float* dv, const float* cos_t, const float* sin_t,
                      const int32_t* cu, int nseq, int T, int H, int KVh, int hd, bf16* dqkv, float* dqkv_f,
                      hipStream_t s);
-// projection gradient rows back to the weight map's tensors (mode 0: QKV into
-// q / k / v; mode 1: gate/up into gate / up)
-void launch_scatter_rows(const float* src, int R, int D, int mode, int hd, int H, int KVh, float* dst0, float* dst1,
-                         float* dst2, hipStream_t s);
 void launch_embed_bwd(const int32_t* tok, const float* dx, int T, int D, int V, float* dE, hipStream_t s);
 
 // ---- weight layout (k_layout.hip): fragment-tiled copy of row-major bf16
@@ -181,6 +175,15 @@ int gemm_ksplit(int N, int M, int K);
 // partials the next normalization sums: the least of GEMM time and partials'
 // traffic, at most max_split
 int gemm_ksplit_few(int N, int M, int K, int max_split);
+// Weight gradient dW = Y^T X over T token rows: out[r][c] = sum_t Y[t][r] X[t][c],
+// Y [T][ldy] (R <= ldy columns used, ldy % 8 == 0), X [T][C] (C % 32 == 0), both
+// row-major or (xpair) both in the row-pair layout.  The rows go to out [R][C], or
+// back from the kernel row orders to the weight map's tensors: WGRAD_QKV out / out1
+// / out2 = q / k / v, WGRAD_GU out / out1 = gate / up.  part: part_floats floats of
+// scratch for a split over the tokens.
+enum WgradMode : int { WGRAD_ROWS = 0, WGRAD_QKV = 1, WGRAD_GU = 2 };
+void launch_wgrad(int mode, const bf16* Y, int ldy, int R, const bf16* X, int C, int T, bool xpair, float* out,
+                  float* out1, float* out2, int hd, int H, int KVh, float* part, int64_t part_floats, hipStream_t s);
 // out[i] (accumulate ? += : =) sum of parts[s * stride + i] over s in order (n % 4 == 0)
 void launch_sum_parts(float* out, const float* parts, int nparts, int64_t stride, int64_t n, int accumulate,
                       hipStream_t s);
