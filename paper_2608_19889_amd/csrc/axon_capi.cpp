@@ -254,6 +254,7 @@ struct TrainBufs {
   std::vector<TrainLayer> L;
   float *xfin, *logits, *rowloss, *valid, *lserow, *scal, *dx, *dtmp, *dgrow, *dqf, *dkf, *dvf, *dsum, *dqkvf,
       *colpart, *dkh, *dvh;
+  float2* lsep;     // log-sum-exp partials of the logits rows (EPI_LSE)
   float* statp;     // attention backward: log2-sum-exp and D in packed per-head rows [2][H][W]
   bf16 *hf, *dlog, *dxb, *dgu, *dob, *dqkv, *headT;
 };
@@ -1901,6 +1902,7 @@ int train_setup(axon_model* m, hipStream_t s) {
   }
   if (!r) r = fa(&tb.xfin, T * D);
   if (!r) r = fa(&tb.logits, T * Vp);
+  if (!r) r = fa((float**)&tb.lsep, T * ((V + LSE_COLS - 1) / LSE_COLS) * 2);
   if (!r) r = fa(&tb.rowloss, T);
   if (!r) r = fa(&tb.valid, T);
   if (!r) r = fa(&tb.lserow, T);
@@ -2018,9 +2020,11 @@ void enqueue_train(axon_model* m, int B, int T, const int32_t* d_tokens, const i
       (void)hipMemcpyAsync(tb.xfin, m->x, (size_t)T * D * 4, hipMemcpyDeviceToDevice, s);
     }
   }
-  gemm_many<bf16>(m, m->lm_head, tb.hf, V, T, D, EPI_F32, tb.logits, nullptr, Vp, s);
+  EpiArgs le{};
+  le.lse_part = tb.lsep;
+  gemm_many<bf16>(m, m->lm_head, tb.hf, V, T, D, EPI_LSE, tb.logits, nullptr, Vp, s, &le);
   // ---- loss and its gradient at the logits
-  launch_ce_loss(tb.logits, Vp, V, d_targets, T, tb.rowloss, tb.valid, tb.lserow, d_loss, tb.scal, tb.dlog, s);
+  launch_ce_loss(tb.logits, Vp, V, tb.lsep, d_targets, T, tb.rowloss, tb.valid, tb.lserow, d_loss, tb.scal, tb.dlog, s);
   // ---- backward
   // dX = dY W: [T][K] float from dY [T][N] and the tiled W^T [K][N]
   auto dX = [&](const bf16* WT, const bf16* dY, int N, int K, float* out) {

@@ -150,6 +150,32 @@ AXON_DEV void store_block(const EpiArgs& ep, int nb, int t, RopeTok tok, const f
   }
 }
 
+// EPI_LSE: the log-sum-exp partial of 64 columns nb .. nb+63 of token t (two
+// accumulator blocks; the two lanes of a token hold 16 rows of each).  Costs
+// the epilogue 64 exponentials per token; a pass over the logits for the same
+// statistics read them twice (1.19 ms for 4096 x 128256 floats).
+AXON_DEV void store_lse(const EpiArgs& ep, int nb, int t, const f32x16& v0, const f32x16& v1, int lane, int N) {
+  const int half = (lane >> 5) * 4;
+  float m = -INFINITY;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int n = nb + (i >> 2) * 8 + half + (i & 3);
+    if (n < N) m = fmaxf(m, v0[i]);
+    if (n + 32 < N) m = fmaxf(m, v1[i]);
+  }
+  m = fmaxf(m, lane_xor32(m));
+  const float ref = m == -INFINITY ? 0.f : m;  // 64 columns of -inf: sum 0
+  float s = 0.f;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int n = nb + (i >> 2) * 8 + half + (i & 3);
+    if (n < N) s += __expf(v0[i] - ref);
+    if (n + 32 < N) s += __expf(v1[i] - ref);
+  }
+  s += lane_xor32(s);
+  if (lane < 32) ep.lse_part[(int64_t)t * ((N + LSE_COLS - 1) / LSE_COLS) + nb / LSE_COLS] = float2{m, s};
+}
+
 // Workgroup -> tile: each XCD (workgroup id mod 8) receives a contiguous range
 // of tiles, walked in groups of 8 token tiles so that neighbouring tiles
 // share operand panels in that XCD's L2.
@@ -334,6 +360,13 @@ __global__ void __launch_bounds__(64 * WN * WM) gemm_ring_kernel(const bf16* __r
   for (int b = 0; b < AM; ++b) {
     const int t = m0 + (wm * AM + b) * 32 + (lane & 31);
     if (t >= M) continue;
+    if constexpr (EPI == EPI_LSE) {
+#pragma unroll
+      for (int a = 0; a + 1 < AN; a += 2) {
+        const int nb = n0 + (wn * AN + a) * 32;
+        if (nb < N) store_lse(ep, nb, t, acc[a][b], acc[a + 1][b], lane, N);
+      }
+    }
 #pragma unroll
     for (int a = 0; a < AN; ++a) {
       const int nb = n0 + (wn * AN + a) * 32;
@@ -578,6 +611,13 @@ __global__ void __launch_bounds__(512, 1) gemm_bf16_256_kernel(const bf16* __res
     const int tl = m0 + wc * 64 + b * 32 + (lane & 31);
     if (tl >= M) continue;
     const int t = rowbase + tl;
+    if constexpr (EPI == EPI_LSE) {
+#pragma unroll
+      for (int a = 0; a < 4; a += 2) {
+        const int nb = n0 + grp * 128 + a * 32;
+        if (nb < N) store_lse(ep, nb, t, acc[a][b], acc[a + 1][b], lane, N);
+      }
+    }
 #pragma unroll
     for (int a = 0; a < 4; ++a) {
       const int nb = n0 + grp * 128 + a * 32;
@@ -873,12 +913,13 @@ struct TileCost {
 static constexpr TileCost TILE_COST[TILES] = {{256, 256, 1, 660}, {256, 128, 1, 420}, {128, 128, 1, 265},
                                               {128, 64, 1, 190},  {64, 64, 2, 120},   {32, 64, 2, 80},
                                               {32, 32, 2, 71}};
-static Tile pick_tile(int N, int M, int K, int ksplit, int64_t* ns = nullptr) {
+static Tile pick_tile(int N, int M, int K, int ksplit, int64_t* ns = nullptr, bool two_blocks = false) {
   const int units = K / 32 / ksplit;
   Tile best = T256x256;
   int64_t least = INT64_MAX;
   for (int i = 0; i < TILES; ++i) {
     const TileCost& t = TILE_COST[i];
+    if (two_blocks && i >= T64x64) break;  // EPI_LSE: a wavefront owns pairs of 32-row blocks
     if (units % t.ku) continue;  // a stage is ku whole k-units
     const int64_t tiles = (int64_t)((N + t.bn - 1) / t.bn) * ((M + t.bm - 1) / t.bm) * ksplit;
     const int64_t cost = (tiles + 255) / 256 * t.ns;
@@ -894,6 +935,14 @@ static Tile pick_tile(int N, int M, int K, int ksplit, int64_t* ns = nullptr) {
 template <int EPI, bool XP>
 static void launch_tiles(const bf16* W, const bf16* X, int N, int M, int K, int ksplit, const EpiArgs& ep,
                          hipStream_t s) {
+  if constexpr (EPI == EPI_LSE) {
+    switch (pick_tile(N, M, K, ksplit, nullptr, true)) {
+      case T256x128: launch_ring_shape<EPI, XP, 4, 2, 2, 2, 1, 4>(W, X, N, M, K, ksplit, ep, s); return;
+      case T128x128: launch_ring_shape<EPI, XP, 2, 2, 2, 2, 1, 4>(W, X, N, M, K, ksplit, ep, s); return;
+      case T128x64: launch_ring_shape<EPI, XP, 2, 2, 2, 1, 1, 6>(W, X, N, M, K, ksplit, ep, s); return;
+      default: break;
+    }
+  } else
   switch (pick_tile(N, M, K, ksplit)) {
     case T256x128: launch_ring_shape<EPI, XP, 4, 2, 2, 2, 1, 4>(W, X, N, M, K, ksplit, ep, s); return;
     case T128x128: launch_ring_shape<EPI, XP, 2, 2, 2, 2, 1, 4>(W, X, N, M, K, ksplit, ep, s); return;
@@ -967,6 +1016,7 @@ void launch_gemm_bf16(const bf16* W, const bf16* X, int N, int M, int K, int epi
     AXON_TILES(EPI_RESID)
     AXON_TILES(EPI_SILU)
     AXON_TILES(EPI_ROPE)
+    AXON_TILES(EPI_LSE)
     case EPI_GELU: launch_tiles<EPI_GELU, false>(W, X, N, M, K, 1, ep, s); return;  // GPT-2: row-major only
     default: return;
   }

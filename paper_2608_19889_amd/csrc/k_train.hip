@@ -41,27 +41,28 @@ AXON_DEV float block_max(float v, float* red) {
 
 // ---------------------------------------------------------------- the loss
 
-// Row t of logits [T][ldl]: lse = log sum_v exp(logit_v) over v < V; a target
-// in [0, V) counts (rowloss = lse - logit_target, valid = 1), any other value
-// does not (0, 0).
+// Row t: lse = log sum_v exp(logit_v) over v < V, merged from the np (largest,
+// sum) partials of its 64-column pieces; a target in [0, V) counts (rowloss =
+// lse - logit_target, valid = 1), any other value does not (0, 0).
 __global__ void __launch_bounds__(256) ce_rows_kernel(const float* __restrict__ logits, int ldl, int V,
+                                                      const float2* __restrict__ part, int np,
                                                       const int32_t* __restrict__ targets,
                                                       float* __restrict__ rowloss, float* __restrict__ valid,
                                                       float* __restrict__ lse_out) {
   __shared__ float red[16];
   const int t = blockIdx.x;
-  const float* row = logits + (int64_t)t * ldl;
+  const float2* row = part + (int64_t)t * np;
   float mx = -INFINITY;
-  for (int v = threadIdx.x; v < V; v += 256) mx = fmaxf(mx, row[v]);
+  for (int i = threadIdx.x; i < np; i += 256) mx = fmaxf(mx, row[i].x);
   mx = block_max(mx, red);
   float sum = 0.f;
-  for (int v = threadIdx.x; v < V; v += 256) sum += __expf(row[v] - mx);
+  for (int i = threadIdx.x; i < np; i += 256) sum += row[i].y * __expf(row[i].x - mx);
   sum = block_sum(sum, red);
   if (threadIdx.x == 0) {
     const float lse = mx + __logf(sum);
     const int tg = targets[t];
     const bool ok = tg >= 0 && tg < V;
-    rowloss[t] = ok ? lse - row[tg] : 0.f;
+    rowloss[t] = ok ? lse - logits[(int64_t)t * ldl + tg] : 0.f;
     valid[t] = ok ? 1.f : 0.f;
     lse_out[t] = lse;
   }
@@ -87,27 +88,31 @@ __global__ void __launch_bounds__(256) ce_reduce_kernel(const float* __restrict_
 }
 
 // dlogits[t][v] = (softmax_v - [v == target]) / N for counted rows, else 0;
-// columns V .. ldl-1 are zero.  4 columns per thread (ldl % 4 == 0).
+// columns V .. ldl-1 are zero.  8 columns per thread (ldl % 8 == 0), every load
+// unconditional 16 bytes (the padding columns hold whatever the buffer held and
+// are not used).
 __global__ void __launch_bounds__(256) ce_grad_kernel(const float* __restrict__ logits, int ldl, int V,
                                                       const int32_t* __restrict__ targets,
                                                       const float* __restrict__ valid,
                                                       const float* __restrict__ lse, const float* __restrict__ scal,
                                                       bf16* __restrict__ dlog) {
   const int t = blockIdx.y;
-  const int v0 = (blockIdx.x * 256 + threadIdx.x) * 4;
+  const int v0 = (blockIdx.x * 256 + threadIdx.x) * 8;
   if (v0 >= ldl) return;
+  const float* row = logits + (int64_t)t * ldl + v0;
+  const f32x4 lo = *(const f32x4*)row, hi = *(const f32x4*)(row + 4);
   const bool ok = valid[t] > 0.f;
   const float l = lse[t], inv = scal[0];
   const int tg = targets[t];
-  bf16x4 o;
+  bf16x8 o;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
+  for (int j = 0; j < 8; ++j) {
     const int v = v0 + j;
-    float g = 0.f;
-    if (ok && v < V) g = (__expf(logits[(int64_t)t * ldl + v] - l) - (v == tg ? 1.f : 0.f)) * inv;
-    o[j] = (bf16)g;
+    const float x = j < 4 ? lo[j & 3] : hi[j & 3];
+    const float g = (__expf(x - l) - (v == tg ? 1.f : 0.f)) * inv;
+    o[j] = (bf16)(ok && v < V ? g : 0.f);
   }
-  *(bf16x4*)(dlog + (int64_t)t * ldl + v0) = o;
+  *(bf16x8*)(dlog + (int64_t)t * ldl + v0) = o;
 }
 
 // ---------------------------------------------------------------- layouts
@@ -614,11 +619,12 @@ __global__ void __launch_bounds__(256) embed_bwd_kernel(const int32_t* __restric
 
 // ---------------------------------------------------------------- launchers
 
-void launch_ce_loss(const float* logits, int ldl, int V, const int32_t* targets, int T, float* rowloss, float* valid,
-                    float* lse, float* loss, float* scal, bf16* dlog, hipStream_t s) {
-  ce_rows_kernel<<<T, 256, 0, s>>>(logits, ldl, V, targets, rowloss, valid, lse);
+void launch_ce_loss(const float* logits, int ldl, int V, const float2* lse_part, const int32_t* targets, int T,
+                    float* rowloss, float* valid, float* lse, float* loss, float* scal, bf16* dlog, hipStream_t s) {
+  ce_rows_kernel<<<T, 256, 0, s>>>(logits, ldl, V, lse_part, (V + LSE_COLS - 1) / LSE_COLS, targets, rowloss, valid,
+                                   lse);
   ce_reduce_kernel<<<1, 256, 0, s>>>(rowloss, valid, T, loss, scal);
-  ce_grad_kernel<<<dim3((ldl / 4 + 255) / 256, T), 256, 0, s>>>(logits, ldl, V, targets, valid, lse, scal, dlog);
+  ce_grad_kernel<<<dim3((ldl / 8 + 255) / 256, T), 256, 0, s>>>(logits, ldl, V, targets, valid, lse, scal, dlog);
 }
 
 void launch_untile_transpose(const bf16* W, int64_t N, int K, bf16* dst, int64_t Np, hipStream_t s) {

@@ -34,10 +34,11 @@ enum Epi : int {
   EPI_RESID = 1,  // out_f32[t * ldo + n] += acc   (residual stream, float)
   EPI_SILU = 2,   // W rows interleaved in blocks of 16 gate rows then 16 up rows;
                   // out_t[t * ldo + f] = silu(gate_f) * up_f
-  EPI_PART = 3,   // (reserved)
   EPI_ROPE = 4,   // bf16 fused QKV projection (rows in the rotation-pair order of
                   // the decode projections): bias + rotary embedding, then q ->
                   // q_out, k -> K pages, v -> transposed V pages
+  EPI_LSE = 3,    // EPI_F32 (no bias) and, per token and 64 columns, their largest
+                  // value and the sum of exp(value - largest) (lse_part)
   EPI_GELU = 5    // out_t[t * ldo + n] = gelu_tanh(acc + bias[n])  (GPT-2 MLP, bf16)
 };
 // EPI_F32 / EPI_RESID add EpiArgs::bias[n] to acc when it is set.
@@ -75,7 +76,10 @@ struct EpiArgs {
   // out_t of the SiLU epilogue; 0: row-major
   int xpair;
   int opair;
+  // EPI_LSE: [T][ceil(N / 64)] (largest, sum) of columns 64 i .. 64 i + 63
+  float2* lse_part;
 };
+constexpr int LSE_COLS = 64;
 
 // ---- GPT-2 rows (k_layernorm.hip).  Token t is at position len[t] (decode)
 // or, with len null, ent_base[e] + t - cu[e] of its entry e (0-based when
@@ -94,11 +98,12 @@ void launch_layernorm(const float* x, const bf16* g, const bf16* beta, bf16* h, 
 void launch_transpose_rows(const bf16* src, bf16* dst, int K, int N, const int32_t* perm, hipStream_t s);
 
 // ---- backward pass (k_train.hip)
-// loss over logits [T][ldl] (V real columns, ldl % 4 == 0) and targets
-// (counted when in [0, V)): loss[0] = mean cross-entropy, dlog [T][ldl] bf16 =
-// its gradient (zero padding); rowloss / valid / lse [T] and scal [1] scratch
-void launch_ce_loss(const float* logits, int ldl, int V, const int32_t* targets, int T, float* rowloss, float* valid,
-                    float* lse, float* loss, float* scal, bf16* dlog, hipStream_t s);
+// loss over logits [T][ldl] (V real columns, ldl % 8 == 0) and targets
+// (counted when in [0, V)), from the logits and their projection's EPI_LSE
+// partials: loss[0] = mean cross-entropy, dlog [T][ldl] bf16 = its gradient
+// (zero padding); rowloss / valid / lse [T] and scal [1] scratch
+void launch_ce_loss(const float* logits, int ldl, int V, const float2* lse_part, const int32_t* targets, int T,
+                    float* rowloss, float* valid, float* lse, float* loss, float* scal, bf16* dlog, hipStream_t s);
 // dst [K][Np] (row-major) = W^T for the fragment-tiled W [N][K]
 void launch_untile_transpose(const bf16* W, int64_t N, int K, bf16* dst, int64_t Np, hipStream_t s);
 void launch_to_bf16(const float* src, bf16* dst, int64_t n, hipStream_t s);  // n % 4 == 0
@@ -187,7 +192,7 @@ void launch_wgrad(int mode, const bf16* Y, int ldy, int R, const bf16* X, int C,
 // out[i] (accumulate ? += : =) sum of parts[s * stride + i] over s in order (n % 4 == 0)
 void launch_sum_parts(float* out, const float* parts, int nparts, int64_t stride, int64_t n, int accumulate,
                       hipStream_t s);
-// float32 check-mode GEMM (any M): EPI_F32 / EPI_RESID / EPI_PART(split 0 only).
+// float32 check-mode GEMM (any M): EPI_F32 / EPI_RESID.
 void launch_gemm_f32(const float* W, const float* X, int N, int M, int K, int epi, const EpiArgs& ep,
                      hipStream_t s);
 // a[t][f] = silu(sum_s gate) * sum_s up over split-K partials of the
