@@ -742,7 +742,7 @@ void enqueue_prefill(axon_model* m, int B, int Ttok, const int32_t* d_tokens, co
         normed = true;
       } else {
         gemm_many<T>(m, w.wgu, h, 2 * I, Ttok, D, EPI_F32, m->gu_f32, nullptr, 2 * I, s);
-        launch_silu_reduce<T>(m->gu_f32, 1, 0, (T*)m->a, Ttok, I, s);
+        launch_silu_f32(m->gu_f32, (float*)m->a, Ttok, I, s);
         gemm_many<T>(m, w.wd, m->a, D, Ttok, I, EPI_RESID, m->x, nullptr, D, s);
       }
     }
@@ -824,7 +824,7 @@ void enqueue_decode_many(axon_model* m, int B, const int32_t* d_tokens, float* d
       proj(w.wgu, h, 2 * I, D, EPI_SILU, nullptr, m->a, I);
     } else {
       proj(w.wgu, h, 2 * I, D, EPI_F32, m->gu_f32, nullptr, 2 * I);
-      launch_silu_reduce<T>(m->gu_f32, 1, 0, (T*)m->a, B, I, s);
+      launch_silu_f32(m->gu_f32, (float*)m->a, B, I, s);
     }
     resid_norm(w.wd, m->a, I, gnext);
   }
@@ -1908,7 +1908,7 @@ int train_setup(axon_model* m, hipStream_t s) {
   if (!r) r = fa(&tb.lserow, T);
   if (!r) r = fa(&tb.scal, 4);
   if (!r) r = fa(&tb.dx, T * D);
-  if (!r) r = fa(&tb.dtmp, T * std::max({D, I, Hhd}));
+  if (!r) r = fa(&tb.dtmp, T * std::max(D, Hhd));
   if (!r) r = fa(&tb.dgrow, T * D);
   if (!r) r = fa(&tb.dqf, T * Hhd);
   if (!r) r = fa(&tb.dkf, T * KV * hd);
@@ -2010,8 +2010,7 @@ void enqueue_train(axon_model* m, int B, int T, const int32_t* d_tokens, const i
     });
     gemm_resid_norm(m, w.wo, t.o, T, Hhd, (const bf16*)w.gpost, t.h2, T, nullptr, s, split_for(m, D, T, Hhd));
     (void)hipMemcpyAsync(t.xmid, m->x, (size_t)T * D * 4, hipMemcpyDeviceToDevice, s);
-    gemm_many<bf16>(m, w.wgu, t.h2, 2 * I, T, D, EPI_F32, t.gu, nullptr, 2 * I, s);
-    launch_silu_reduce<bf16>(t.gu, 1, 0, t.a, T, I, s);
+    gemm_many<bf16>(m, w.wgu, t.h2, 2 * I, T, D, EPI_GU, t.gu, t.a, 2 * I, s);
     if (l + 1 < L) {
       gemm_resid_norm(m, w.wd, t.a, T, I, (const bf16*)m->layers[l + 1].gin, tb.L[l + 1].h1, T, nullptr, s,
                       split_for(m, D, T, I));
@@ -2052,8 +2051,9 @@ void enqueue_train(axon_model* m, int B, int T, const int32_t* d_tokens, const i
     // MLP
     launch_to_bf16(tb.dx, tb.dxb, (int64_t)T * D, s);
     dW(tb.dxb, D, D, t.a, I, WGRAD_ROWS, G(p + "mlp.down_proj.weight"));
-    dX(t.wdT, tb.dxb, D, I, tb.dtmp);
-    launch_swiglu_bwd(t.gu, tb.dtmp, tb.dgu, T, I, s);
+    EpiArgs de{};  // the gated activation's gradient stays in the epilogue
+    de.gu = t.gu;
+    gemm_many<bf16>(m, t.wdT, tb.dxb, I, T, D, EPI_DGU, nullptr, tb.dgu, I, s, &de);
     dW(tb.dgu, 2 * I, 2 * I, t.h2, D, WGRAD_GU, G(p + "mlp.gate_proj.weight"), G(p + "mlp.up_proj.weight"));
     dX(t.wguT, tb.dgu, 2 * I, D, tb.dtmp);
     launch_rmsnorm_bwd(t.xmid, (const bf16*)w.gpost, tb.dtmp, D, T, D, eps, tb.dx, 1, tb.dgrow, s);

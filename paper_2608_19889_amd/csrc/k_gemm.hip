@@ -111,11 +111,18 @@ AXON_DEV void store_block(const EpiArgs& ep, int nb, int t, RopeTok tok, const f
                           int64_t part) {
   if constexpr (EPI == EPI_ROPE) {
     rope_block(ep, nb, t, tok, v, lane);
-  } else if constexpr (EPI == EPI_SILU) {
+  } else if constexpr (EPI == EPI_SILU || EPI == EPI_GU) {
     // rows nb..nb+15 are gate rows, nb+16..nb+31 the matching up rows
     // (features (nb / 32) * 16 .. +15: inside one 32-feature slice)
     const int64_t f0 = (nb / 32) * 16;
-    bf16* out = (bf16*)ep.out_t + (ep.opair ? xp_off(t, f0, ep.ldo) : (int64_t)t * ep.ldo + f0);
+    const int lda = EPI == EPI_GU ? ep.ldo / 2 : ep.ldo;
+    if constexpr (EPI == EPI_GU) {
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        *(f32x4*)(ep.out_f32 + (int64_t)t * ep.ldo + nb + g * 8 + (lane >> 5) * 4) =
+            f32x4{v[g * 4], v[g * 4 + 1], v[g * 4 + 2], v[g * 4 + 3]};
+    }
+    bf16* out = (bf16*)ep.out_t + (ep.opair ? xp_off(t, f0, lda) : (int64_t)t * lda + f0);
 #pragma unroll
     for (int g = 0; g < 2; ++g) {
       const int f = g * 8 + (lane >> 5) * 4;
@@ -123,6 +130,32 @@ AXON_DEV void store_block(const EpiArgs& ep, int nb, int t, RopeTok tok, const f
 #pragma unroll
       for (int j = 0; j < 4; ++j) o[j] = (bf16)(silu_f(v[g * 4 + j]) * v[8 + g * 4 + j]);
       *(bf16x4*)(out + f) = o;
+    }
+  } else if constexpr (EPI == EPI_DGU) {
+    // a = silu(g) u: dg = da u s (1 + g (1 - s)), du = da g s, s = sigmoid(g).
+    // Feature nb + 16 j + i sits at columns 2 nb + 32 j + i (gate), + 16 (up);
+    // both slices of 32 columns are loaded before the first store
+    const int half = (lane >> 5) * 4;
+    const float* gr = ep.gu + (int64_t)t * 2 * ep.ldo + 2 * nb + half;
+    f32x4 gv[4], uv[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      gv[q] = *(const f32x4*)(gr + (q >> 1) * 32 + (q & 1) * 8);
+      uv[q] = *(const f32x4*)(gr + (q >> 1) * 32 + (q & 1) * 8 + 16);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int64_t c0 = 2 * (int64_t)nb + (q >> 1) * 32;
+      bf16* out = (bf16*)ep.out_t + (ep.opair ? xp_off(t, c0, 2 * ep.ldo) : (int64_t)t * 2 * ep.ldo + c0) + (q & 1) * 8 + half;
+      bf16x4 dg, du;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float gg = gv[q][j], d = v[q * 4 + j], sg = 1.f / (1.f + __expf(-gg));
+        dg[j] = (bf16)(d * uv[q][j] * sg * (1.f + gg * (1.f - sg)));
+        du[j] = (bf16)(d * gg * sg);
+      }
+      *(bf16x4*)out = dg;
+      *(bf16x4*)(out + 16) = du;
     }
   } else if constexpr (EPI == EPI_GELU) {
 #pragma unroll
@@ -1017,6 +1050,8 @@ void launch_gemm_bf16(const bf16* W, const bf16* X, int N, int M, int K, int epi
     AXON_TILES(EPI_SILU)
     AXON_TILES(EPI_ROPE)
     AXON_TILES(EPI_LSE)
+    AXON_TILES(EPI_GU)
+    AXON_TILES(EPI_DGU)
     case EPI_GELU: launch_tiles<EPI_GELU, false>(W, X, N, M, K, 1, ep, s); return;  // GPT-2: row-major only
     default: return;
   }
@@ -1250,29 +1285,18 @@ void launch_sum_parts(float* out, const float* parts, int nparts, int64_t stride
   const int64_t n4 = n / 4;
   if (n4 > 0) sum_parts_kernel<<<(unsigned)((n4 + 255) / 256), 256, 0, s>>>(out, parts, nparts, stride, n4, accumulate);
 }
-template <typename T>
-__global__ void silu_reduce_kernel(const float* __restrict__ parts, int nparts, int64_t part_stride,
-                                   T* __restrict__ a, int M, int I) {
+__global__ void __launch_bounds__(256) silu_f32_kernel(const float* __restrict__ gu, float* __restrict__ a, int M,
+                                                       int I) {
   const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= (int64_t)M * I) return;
   const int t = (int)(idx / I), f = (int)(idx % I);
-  const int rg = (f / 16) * 32 + (f % 16);  // gate row in the interleaved layout; up row = rg + 16
-  const float* p = parts + (int64_t)t * 2 * I;
-  float g = 0.f, u = 0.f;
-  for (int s = 0; s < nparts; ++s) {
-    g += p[s * part_stride + rg];
-    u += p[s * part_stride + rg + 16];
-  }
-  a[idx] = from_f32<T>(silu_f(g) * u);
+  const float* p = gu + (int64_t)t * 2 * I + (f / 16) * 32 + f % 16;  // gate; up 16 later
+  a[idx] = silu_f(p[0]) * p[16];
 }
 
-template <typename T>
-void launch_silu_reduce(const float* parts, int nparts, int64_t part_stride, T* a, int M, int I, hipStream_t s) {
+void launch_silu_f32(const float* gu, float* a, int M, int I, hipStream_t s) {
   const int64_t n = (int64_t)M * I;
-  if (n <= 0) return;
-  silu_reduce_kernel<T><<<(unsigned)((n + 255) / 256), 256, 0, s>>>(parts, nparts, part_stride, a, M, I);
+  if (n > 0) silu_f32_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(gu, a, M, I);
 }
-template void launch_silu_reduce<float>(const float*, int, int64_t, float*, int, int, hipStream_t);
-template void launch_silu_reduce<bf16>(const float*, int, int64_t, bf16*, int, int, hipStream_t);
 
 }  // namespace axon

@@ -221,21 +221,6 @@ __global__ void __launch_bounds__(256) rmsnorm_bwd_kernel(const float* __restric
   }
 }
 
-// gate/up pre-activations gu [T][2I] in the interleaved row order (16 gate
-// rows, then the 16 matching up rows); da [T][I]: dgu = (da u silu'(g),
-// da silu(g)) in the same order, silu'(g) = s (1 + g (1 - s)), s = sigmoid(g)
-__global__ void __launch_bounds__(256) swiglu_bwd_kernel(const float* __restrict__ gu, const float* __restrict__ da,
-                                                         bf16* __restrict__ dgu, int T, int I) {
-  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (idx >= (int64_t)T * I) return;
-  const int t = (int)(idx / I), f = (int)(idx % I);
-  const int64_t rg = (int64_t)t * 2 * I + (f / 16) * 32 + (f % 16);
-  const float g = gu[rg], u = gu[rg + 16], d = da[idx];
-  const float s = 1.f / (1.f + __expf(-g));
-  dgu[rg] = (bf16)(d * u * s * (1.f + g * (1.f - s)));
-  dgu[rg + 16] = (bf16)(d * g * s);
-}
-
 // column sums of src [T][C] (rows ld apart) in two deterministic passes:
 // part[chunk][c] over rows chunk*rpc .., then dst[c] = sum over chunks
 __global__ void __launch_bounds__(256) colsum_part_kernel(const float* __restrict__ src, int64_t ld, int T, int C,
@@ -640,11 +625,6 @@ void launch_to_bf16(const float* src, bf16* dst, int64_t n, hipStream_t s) {
 void launch_rmsnorm_bwd(const float* x, const bf16* g, const float* dy, int ldy, int T, int D, float eps, float* dx,
                         int accumulate, float* dgrow, hipStream_t s) {
   if (T > 0) rmsnorm_bwd_kernel<<<T, 256, 0, s>>>(x, g, dy, ldy, D, eps, dx, accumulate, dgrow);
-}
-
-void launch_swiglu_bwd(const float* gu, const float* da, bf16* dgu, int T, int I, hipStream_t s) {
-  const int64_t n = (int64_t)T * I;
-  if (n > 0) swiglu_bwd_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(gu, da, dgu, T, I);
 }
 
 int colsum_chunks(int T) { return std::max(1, std::min(256, (T + 63) / 64)); }

@@ -39,6 +39,11 @@ enum Epi : int {
                   // q_out, k -> K pages, v -> transposed V pages
   EPI_LSE = 3,    // EPI_F32 (no bias) and, per token and 64 columns, their largest
                   // value and the sum of exp(value - largest) (lse_part)
+  EPI_GU = 6,     // the interleaved gate/up pre-activations kept (out_f32, rows of
+                  // ldo) beside EPI_SILU's out_t (rows of ldo / 2)
+  EPI_DGU = 7,    // acc = gradient of gated feature n; its gate/up pre-activations
+                  // gu [T][2 ldo] give the gradients of both, bf16, interleaved
+                  // like gu: out_t [T][2 ldo]
   EPI_GELU = 5    // out_t[t * ldo + n] = gelu_tanh(acc + bias[n])  (GPT-2 MLP, bf16)
 };
 // EPI_F32 / EPI_RESID add EpiArgs::bias[n] to acc when it is set.
@@ -72,8 +77,9 @@ struct EpiArgs {
   const int32_t* g_xrow;
   int64_t g_wstride;
   int g_E;
+  const float* gu;  // EPI_DGU
   // row-pair layout (xp_off) of the token operand X, and of the bf16 output
-  // out_t of the SiLU epilogue; 0: row-major
+  // out_t of EPI_SILU / EPI_GU / EPI_DGU; 0: row-major
   int xpair;
   int opair;
   // EPI_LSE: [T][ceil(N / 64)] (largest, sum) of columns 64 i .. 64 i + 63
@@ -110,7 +116,6 @@ void launch_to_bf16(const float* src, bf16* dst, int64_t n, hipStream_t s);  // 
 // RMSNorm backward: dx (accumulate ? += : =) and per-row gain terms dgrow [T][D]
 void launch_rmsnorm_bwd(const float* x, const bf16* g, const float* dy, int ldy, int T, int D, float eps, float* dx,
                         int accumulate, float* dgrow, hipStream_t s);
-void launch_swiglu_bwd(const float* gu, const float* da, bf16* dgu, int T, int I, hipStream_t s);
 // dst[c] = sum_t src[t][c], deterministic; part holds colsum_chunks(T) * C floats
 int colsum_chunks(int T);
 void launch_colsum(const float* src, int64_t ld, int T, int C, float* part, float* dst, hipStream_t s);
@@ -195,11 +200,8 @@ void launch_sum_parts(float* out, const float* parts, int nparts, int64_t stride
 // float32 check-mode GEMM (any M): EPI_F32 / EPI_RESID.
 void launch_gemm_f32(const float* W, const float* X, int N, int M, int K, int epi, const EpiArgs& ep,
                      hipStream_t s);
-// a[t][f] = silu(sum_s gate) * sum_s up over split-K partials of the
-// interleaved gate/up projection ([nparts][M][2I] floats).
-template <typename T>
-void launch_silu_reduce(const float* parts, int nparts, int64_t part_stride, T* a, int M, int I,
-                        hipStream_t s);
+// a[t][f] = silu(gate) * up of the interleaved gate/up projection [M][2I]
+void launch_silu_f32(const float* gu, float* a, int M, int I, hipStream_t s);
 // ---- fused decode projections (k_gemv.hip)
 enum GvEpi : int { GV_HEAD = 0, GV_RESID = 1, GV_SILU = 2, GV_ROPE = 3, GV_PART = 4 /* internal: split-K partials */,
                    GV_F32 = 5 /* grouped experts: float rows out_f32[row][n] */,
