@@ -252,8 +252,8 @@ struct TrainBufs {
   int64_t W = 0;    // max_batch * SP
   bf16 *kr, *vr, *kt, *qt, *dot;
   std::vector<TrainLayer> L;
-  float *xfin, *logits, *rowloss, *valid, *lserow, *scal, *dx, *dtmp, *dgrow, *dqf, *dkf, *dvf, *dsum, *dqkvf,
-      *colpart, *dkh, *dvh;
+  float *xfin, *logits, *rowloss, *valid, *lserow, *scal, *dx, *dtmp, *dgrow = nullptr, *dqf, *dsum, *colpart,
+      *dkh, *dvh;
   float2* lsep;     // log-sum-exp partials of the logits rows (EPI_LSE)
   float* statp;     // attention backward: log2-sum-exp and D in packed per-head rows [2][H][W]
   bf16 *hf, *dlog, *dxb, *dgu, *dob, *dqkv, *headT;
@@ -477,19 +477,23 @@ int split_for(axon_model* m, int N, int M, int K) {
   return ks > 1 && (int64_t)ks * M * N <= m->gemm_part_floats ? ks : 1;
 }
 
-// out (accumulate ? += : =) X W^T (float32 [M][N], rows N apart), split over
-// K when the output has few 256-tiles (partials summed in order)
-void gemm_f32_out(axon_model* m, const void* W, const void* X, int N, int M, int K, float* out, bool accumulate,
-                  hipStream_t s) {
+// X W^T in float32 [M][N], split over K when the output has few 256-tiles:
+// returns the partials (``out``, one, when unsplit; else m->gemm_part, good
+// until the next split GEMM) for the consumer to sum in order.
+struct Parts {
+  const float* p;
+  int n;
+};
+Parts gemm_f32_parts(axon_model* m, const void* W, const void* X, int N, int M, int K, float* out, hipStream_t s) {
   const int ks = split_for(m, N, M, K);
-  if (ks > 1) {
-    m->timed(1, N, M, K, s, [&] {
-      launch_gemm_bf16_split((const bf16*)W, (const bf16*)X, N, M, K, ks, m->gemm_part, (int64_t)M * N, s);
-    });
-    launch_sum_parts(out, m->gemm_part, ks, (int64_t)M * N, (int64_t)M * N, accumulate ? 1 : 0, s);
-  } else {
-    gemm_many<bf16>(m, W, X, N, M, K, accumulate ? EPI_RESID : EPI_F32, out, nullptr, N, s);
+  if (ks == 1) {
+    gemm_many<bf16>(m, W, X, N, M, K, EPI_F32, out, nullptr, N, s, nullptr, nullptr, true);
+    return {out, 1};
   }
+  m->timed(1, N, M, K, s, [&] {
+    launch_gemm_bf16_split((const bf16*)W, (const bf16*)X, N, M, K, ks, m->gemm_part, (int64_t)M * N, s, true);
+  });
+  return {m->gemm_part, ks};
 }
 
 // Split of an inference prefill's residual projection (O, dense down): by
@@ -512,20 +516,25 @@ int decode_split(axon_model* m, int N, int M, int K) {
 
 // x += X W^T, then h = RMSNorm(x) g for ``rows`` rows (the last row of each
 // sequence when cu_last is set): the partials of a GEMM split ks ways over K
-// are summed into x by the normalization kernel itself.  xpair / hpair: X / h in the row-pair
-// layout.
+// are summed into x by the normalization kernel itself.  xpair / hpair: X / h in
+// the row-pair layout; x_in / x_out: the residual rows before and after (m->x).
 void gemm_resid_norm(axon_model* m, const void* W, const bf16* X, int T, int K, const bf16* g, bf16* h, int rows,
-                     const int32_t* cu_last, hipStream_t s, int ks, bool xpair = false, bool hpair = false) {
+                     const int32_t* cu_last, hipStream_t s, int ks, bool xpair = false, bool hpair = false,
+                     float* x_in = nullptr, float* x_out = nullptr) {
   const int D = m->D();
+  float* xi = x_in ? x_in : m->x;
+  float* xo = x_out ? x_out : m->x;
   if (ks > 1) {
     m->timed(1, D, T, K, s, [&] {
       launch_gemm_bf16_split((const bf16*)W, X, D, T, K, ks, m->gemm_part, (int64_t)T * D, s, xpair);
     });
-    launch_resid_rmsnorm<bf16>(m->x, m->gemm_part, ks, (int64_t)T * D, g, h, rows, D, m->cfg.rms_eps, cu_last, s,
-                               hpair);
+    launch_resid_rmsnorm<bf16>(xi, m->gemm_part, ks, (int64_t)T * D, g, h, rows, D, m->cfg.rms_eps, cu_last, s, hpair,
+                               xo);
   } else {
-    gemm_many<bf16>(m, W, X, D, T, K, EPI_RESID, m->x, nullptr, D, s, nullptr, nullptr, xpair);
-    launch_resid_rmsnorm<bf16>(m->x, nullptr, 0, 0, g, h, rows, D, m->cfg.rms_eps, cu_last, s, hpair);
+    EpiArgs re{};
+    re.resid = xi;
+    gemm_many<bf16>(m, W, X, D, T, K, EPI_RESID, xo, nullptr, D, s, &re, nullptr, xpair);
+    launch_resid_rmsnorm<bf16>(xo, nullptr, 0, 0, g, h, rows, D, m->cfg.rms_eps, cu_last, s, hpair);
   }
 }
 
@@ -1879,7 +1888,7 @@ int train_setup(axon_model* m, hipStream_t s) {
   const int64_t nq = (H + 2 * KV) * hd, Hhd = H * hd;
   tb.Tc = m->rows;
   tb.Vp = (int)((V + 31) / 32 * 32);
-  const int64_t T = tb.Tc, Vp = tb.Vp;
+  const int64_t T = tb.Tc, Vp = tb.Vp, T2 = (T + 1) & ~(int64_t)1;  // T2: rows of the row-pair layout
   auto tiled = [](int64_t rows, int64_t cols) { return (rows + 15) / 16 * 16 * cols; };
   auto fa = [&](float** p, int64_t n) { return dev_alloc(m, (void**)p, (size_t)n * 4); };
   auto ba = [&](bf16** p, int64_t n) { return dev_alloc(m, (void**)p, (size_t)n * 2); };
@@ -1890,11 +1899,11 @@ int train_setup(axon_model* m, hipStream_t s) {
     if (!r) r = fa(&l.xmid, T * D);
     if (!r) r = fa(&l.lse, T * H);
     if (!r) r = fa(&l.gu, T * 2 * I);
-    if (!r) r = ba(&l.h1, T * D);
-    if (!r) r = ba(&l.h2, T * D);
+    if (!r) r = ba(&l.h1, T2 * D);
+    if (!r) r = ba(&l.h2, T2 * D);
     if (!r) r = ba(&l.q, T * Hhd);
-    if (!r) r = ba(&l.o, T * Hhd);
-    if (!r) r = ba(&l.a, T * I);
+    if (!r) r = ba(&l.o, T2 * Hhd);
+    if (!r) r = ba(&l.a, T2 * I);
     if (!r) r = ba(&l.wqkvT, tiled(D, nq));
     if (!r) r = ba(&l.woT, tiled(Hhd, D));
     if (!r) r = ba(&l.wguT, tiled(D, 2 * I));
@@ -1909,21 +1918,18 @@ int train_setup(axon_model* m, hipStream_t s) {
   if (!r) r = fa(&tb.scal, 4);
   if (!r) r = fa(&tb.dx, T * D);
   if (!r) r = fa(&tb.dtmp, T * std::max(D, Hhd));
-  if (!r) r = fa(&tb.dgrow, T * D);
+  if (!r && D > NORM_BWD_COLS) r = fa(&tb.dgrow, T * D);
   if (!r) r = fa(&tb.dqf, T * Hhd);
-  if (!r) r = fa(&tb.dkf, T * KV * hd);
-  if (!r) r = fa(&tb.dvf, T * KV * hd);
   if (!r) r = fa(&tb.dkh, T * Hhd);
   if (!r) r = fa(&tb.dvh, T * Hhd);
   if (!r) r = fa(&tb.dsum, T * H);
-  if (!r) r = fa(&tb.dqkvf, T * nq);
-  if (!r) r = fa(&tb.colpart, (int64_t)colsum_chunks((int)T) * std::max(nq, D));
-  if (!r) r = ba(&tb.hf, T * D);
-  if (!r) r = ba(&tb.dlog, T * Vp);
-  if (!r) r = ba(&tb.dxb, T * D);
-  if (!r) r = ba(&tb.dgu, T * 2 * I);
+  if (!r) r = fa(&tb.colpart, ROW_PARTS * std::max(nq, D));
+  if (!r) r = ba(&tb.hf, T2 * D);
+  if (!r) r = ba(&tb.dlog, T2 * Vp);
+  if (!r) r = ba(&tb.dxb, T2 * D);
+  if (!r) r = ba(&tb.dgu, T2 * 2 * I);
   if (!r) r = ba(&tb.dob, T * Hhd);
-  if (!r) r = ba(&tb.dqkv, T * nq);
+  if (!r) r = ba(&tb.dqkv, T2 * nq);
   if (!r) r = ba(&tb.headT, tiled(D, Vp));
   // split-K partials of the narrow training GEMMs: up to 4 splits of an
   // output as large as T x max(D, I) or one weight's gradient
@@ -1995,92 +2001,82 @@ void enqueue_train(axon_model* m, int B, int T, const int32_t* d_tokens, const i
   auto G = [&](const std::string& n) { return g[gi.at(n)]; };
   // ---- forward, keeping activations
   launch_set_lengths(d_cu, m->d_len, B, s);
-  launch_embed_rmsnorm<bf16>(d_tokens, (const bf16*)m->embed, (const bf16*)m->layers[0].gin, m->x, tb.L[0].h1, T, D,
-                             V, eps, s);
+  // every GEMM's token operand (h1, o, h2, a, hf and the gradients) lies in the
+  // row-pair layout
+  launch_embed_rmsnorm<bf16>(d_tokens, (const bf16*)m->embed, (const bf16*)m->layers[0].gin, tb.L[0].xin, tb.L[0].h1,
+                             T, D, V, eps, s, true);
   for (int l = 0; l < L; ++l) {
     const LayerW& w = m->layers[l];
     TrainLayer& t = tb.L[l];
     KVView kv = m->kv(l, false);
-    (void)hipMemcpyAsync(t.xin, m->x, (size_t)T * D * 4, hipMemcpyDeviceToDevice, s);
     EpiArgs re = rope_epi(m, w, kv, d_cu, B, nullptr);
     re.q_out = t.q;
-    gemm_many<bf16>(m, w.wqkv, t.h1, nq, T, D, EPI_ROPE, nullptr, nullptr, nq, s, &re);
+    gemm_many<bf16>(m, w.wqkv, t.h1, nq, T, D, EPI_ROPE, nullptr, nullptr, nq, s, &re, nullptr, true);
     m->timed(3, H, B, T, s, [&] {
-      launch_attn_prefill<bf16>(t.q, kv, t.o, T, B, d_cu, h_cu, H, s, nullptr, nullptr, nullptr, nullptr, t.lse);
+      launch_attn_prefill<bf16>(t.q, kv, t.o, T, B, d_cu, h_cu, H, s, nullptr, nullptr, nullptr, nullptr, t.lse, true);
     });
-    gemm_resid_norm(m, w.wo, t.o, T, Hhd, (const bf16*)w.gpost, t.h2, T, nullptr, s, split_for(m, D, T, Hhd));
-    (void)hipMemcpyAsync(t.xmid, m->x, (size_t)T * D * 4, hipMemcpyDeviceToDevice, s);
-    gemm_many<bf16>(m, w.wgu, t.h2, 2 * I, T, D, EPI_GU, t.gu, t.a, 2 * I, s);
-    if (l + 1 < L) {
-      gemm_resid_norm(m, w.wd, t.a, T, I, (const bf16*)m->layers[l + 1].gin, tb.L[l + 1].h1, T, nullptr, s,
-                      split_for(m, D, T, I));
-    } else {
-      gemm_resid_norm(m, w.wd, t.a, T, I, (const bf16*)m->gfinal, tb.hf, T, nullptr, s, split_for(m, D, T, I));
-      (void)hipMemcpyAsync(tb.xfin, m->x, (size_t)T * D * 4, hipMemcpyDeviceToDevice, s);
-    }
+    gemm_resid_norm(m, w.wo, t.o, T, Hhd, (const bf16*)w.gpost, t.h2, T, nullptr, s, split_for(m, D, T, Hhd), true,
+                    true, t.xin, t.xmid);
+    gemm_many<bf16>(m, w.wgu, t.h2, 2 * I, T, D, EPI_GU, t.gu, t.a, 2 * I, s, nullptr, nullptr, true, true);
+    const bool last = l + 1 == L;
+    gemm_resid_norm(m, w.wd, t.a, T, I, (const bf16*)(last ? m->gfinal : m->layers[l + 1].gin),
+                    last ? tb.hf : tb.L[l + 1].h1, T, nullptr, s, split_for(m, D, T, I), true, true, t.xmid,
+                    last ? tb.xfin : tb.L[l + 1].xin);
   }
   EpiArgs le{};
   le.lse_part = tb.lsep;
-  gemm_many<bf16>(m, m->lm_head, tb.hf, V, T, D, EPI_LSE, tb.logits, nullptr, Vp, s, &le);
+  gemm_many<bf16>(m, m->lm_head, tb.hf, V, T, D, EPI_LSE, tb.logits, nullptr, Vp, s, &le, nullptr, true);
   // ---- loss and its gradient at the logits
   launch_ce_loss(tb.logits, Vp, V, tb.lsep, d_targets, T, tb.rowloss, tb.valid, tb.lserow, d_loss, tb.scal, tb.dlog, s);
   // ---- backward
-  // dX = dY W: [T][K] float from dY [T][N] and the tiled W^T [K][N]
-  auto dX = [&](const bf16* WT, const bf16* dY, int N, int K, float* out) {
-    gemm_f32_out(m, WT, dY, K, T, N, out, false, s);
-  };
   // dW = dY^T X, [N][K] float (or its rows' own tensors), from dY [T][N] (rows
   // ldy apart) and X [T][K]
   auto dW = [&](const bf16* dY, int ldy, int N, const bf16* X, int K, int mode, float* o0, float* o1 = nullptr,
                 float* o2 = nullptr) {
     m->timed(1, K, N, T, s, [&] {
-      launch_wgrad(mode, dY, ldy, N, X, K, T, false, o0, o1, o2, hd, H, KV, m->gemm_part, m->gemm_part_floats, s);
+      launch_wgrad(mode, dY, ldy, N, X, K, T, true, o0, o1, o2, hd, H, KV, m->gemm_part, m->gemm_part_floats, s);
     });
+  };
+  // dX = dY W ([T][K] from dY [T][N] and the tiled W^T [K][N]) through a
+  // normalization: the gradients of its input (tb.dx, += after the first) and gain
+  auto dX_norm = [&](const bf16* WT, const bf16* dY, int N, const float* x, const void* gain, float* g_gain,
+                     int accumulate) {
+    const Parts dy = gemm_f32_parts(m, WT, dY, D, T, N, tb.dtmp, s);
+    launch_norm_bwd(x, (const bf16*)gain, dy.p, dy.n, (int64_t)T * D, T, D, eps, tb.dx, accumulate, tb.dxb, g_gain,
+                    tb.colpart, tb.dgrow, s);
   };
   const bool tied = c.tie_embeddings;
   float* g_embed = G("model.embed_tokens.weight");
   dW(tb.dlog, Vp, V, tb.hf, D, WGRAD_ROWS, tied ? g_embed : G("lm_head.weight"));
-  dX(tb.headT, tb.dlog, Vp, D, tb.dtmp);
-  launch_rmsnorm_bwd(tb.xfin, (const bf16*)m->gfinal, tb.dtmp, D, T, D, eps, tb.dx, 0, tb.dgrow, s);
-  launch_colsum(tb.dgrow, D, T, D, tb.colpart, G("model.norm.weight"), s);
+  dX_norm(tb.headT, tb.dlog, Vp, tb.xfin, m->gfinal, G("model.norm.weight"), 0);
   for (int l = L - 1; l >= 0; --l) {
     const LayerW& w = m->layers[l];
     TrainLayer& t = tb.L[l];
     KVView kv = m->kv(l, false);
     const std::string p = "model.layers." + std::to_string(l) + ".";
     // MLP
-    launch_to_bf16(tb.dx, tb.dxb, (int64_t)T * D, s);
     dW(tb.dxb, D, D, t.a, I, WGRAD_ROWS, G(p + "mlp.down_proj.weight"));
     EpiArgs de{};  // the gated activation's gradient stays in the epilogue
     de.gu = t.gu;
-    gemm_many<bf16>(m, t.wdT, tb.dxb, I, T, D, EPI_DGU, nullptr, tb.dgu, I, s, &de);
+    gemm_many<bf16>(m, t.wdT, tb.dxb, I, T, D, EPI_DGU, nullptr, tb.dgu, I, s, &de, nullptr, true, true);
     dW(tb.dgu, 2 * I, 2 * I, t.h2, D, WGRAD_GU, G(p + "mlp.gate_proj.weight"), G(p + "mlp.up_proj.weight"));
-    dX(t.wguT, tb.dgu, 2 * I, D, tb.dtmp);
-    launch_rmsnorm_bwd(t.xmid, (const bf16*)w.gpost, tb.dtmp, D, T, D, eps, tb.dx, 1, tb.dgrow, s);
-    launch_colsum(tb.dgrow, D, T, D, tb.colpart, G(p + "post_attention_layernorm.weight"), s);
+    dX_norm(t.wguT, tb.dgu, 2 * I, t.xmid, w.gpost, G(p + "post_attention_layernorm.weight"), 1);
     // attention
-    launch_to_bf16(tb.dx, tb.dxb, (int64_t)T * D, s);
     dW(tb.dxb, D, D, t.o, Hhd, WGRAD_ROWS, G(p + "self_attn.o_proj.weight"));
-    dX(t.woT, tb.dxb, D, Hhd, tb.dtmp);
-    launch_to_bf16(tb.dtmp, tb.dob, (int64_t)T * Hhd, s);
+    const Parts dof = gemm_f32_parts(m, t.woT, tb.dxb, Hhd, T, D, tb.dtmp, s);
     m->timed(5, H, B, T, s, [&] {
-      if (!launch_attn_bwd(t.q, kv, t.o, tb.dob, t.lse, tb.dsum, tb.statp, d_cu, h_cu, B, T, H, tb.SP, tb.W, tb.kr, tb.vr, tb.kt,
-                      tb.qt, tb.dot, tb.dqf, tb.dkh, tb.dvh, tb.dkf, tb.dvf, s) &&
+      if (!launch_attn_bwd(t.q, kv, t.o, dof.p, dof.n, (int64_t)T * Hhd, tb.dob, t.lse, tb.dsum, tb.statp, d_cu, h_cu,
+                           B, T, H, tb.SP, tb.W, tb.kr, tb.vr, tb.kt, tb.qt, tb.dot, tb.dqf, tb.dkh, tb.dvh, s) &&
           m->enqueue_err.empty())
         m->enqueue_err = "attention backward: packed layout does not fit the shape";
     });
-    launch_rope_bwd(tb.dqf, tb.dkf, tb.dvf, m->rope_cos, m->rope_sin, d_cu, B, T, H, KV, hd, tb.dqkv,
-                    c.qkv_bias ? tb.dqkvf : nullptr, s);
+    launch_rope_bwd(tb.dqf, tb.dkh, tb.dvh, m->rope_cos, m->rope_sin, d_cu, B, T, H, KV, hd, tb.dqkv, tb.colpart,
+                    c.qkv_bias ? G(p + "self_attn.q_proj.bias") : nullptr,
+                    c.qkv_bias ? G(p + "self_attn.k_proj.bias") : nullptr,
+                    c.qkv_bias ? G(p + "self_attn.v_proj.bias") : nullptr, s);
     dW(tb.dqkv, nq, nq, t.h1, D, WGRAD_QKV, G(p + "self_attn.q_proj.weight"), G(p + "self_attn.k_proj.weight"),
        G(p + "self_attn.v_proj.weight"));
-    if (c.qkv_bias) {
-      launch_colsum(tb.dqkvf, nq, T, Hhd, tb.colpart, G(p + "self_attn.q_proj.bias"), s);
-      launch_colsum(tb.dqkvf + Hhd, nq, T, KV * hd, tb.colpart, G(p + "self_attn.k_proj.bias"), s);
-      launch_colsum(tb.dqkvf + Hhd + KV * hd, nq, T, KV * hd, tb.colpart, G(p + "self_attn.v_proj.bias"), s);
-    }
-    dX(t.wqkvT, tb.dqkv, nq, D, tb.dtmp);
-    launch_rmsnorm_bwd(t.xin, (const bf16*)w.gin, tb.dtmp, D, T, D, eps, tb.dx, 1, tb.dgrow, s);
-    launch_colsum(tb.dgrow, D, T, D, tb.colpart, G(p + "input_layernorm.weight"), s);
+    dX_norm(t.wqkvT, tb.dqkv, nq, t.xin, w.gin, G(p + "input_layernorm.weight"), 1);
   }
   if (!tied) (void)hipMemsetAsync(g_embed, 0, (size_t)V * D * 4, s);
   launch_embed_bwd(d_tokens, tb.dx, T, D, V, g_embed, s);

@@ -13,15 +13,15 @@ namespace axon {
 
 AXON_DEV float silu_f(float z) { return z / (1.f + __expf(-z)); }
 
-// Store (or add, for the residual stream) four consecutive output columns of
-// which ``left`` are inside the matrix.
+// Store (for the residual stream, added to r) four consecutive output columns
+// of which ``left`` are inside the matrix.
 template <bool ADD>
-AXON_DEV void store_cols(float* p, f32x4 v, int left) {
+AXON_DEV void store_cols(float* p, const float* r, f32x4 v, int left) {
   if (left >= 4) {
-    if constexpr (ADD) v += *(const f32x4*)p;
+    if constexpr (ADD) v += *(const f32x4*)r;
     *(f32x4*)p = v;
   } else {
-    for (int j = 0; j < left; ++j) p[j] = ADD ? p[j] + v[j] : v[j];
+    for (int j = 0; j < left; ++j) p[j] = ADD ? r[j] + v[j] : v[j];
   }
 }
 
@@ -178,7 +178,8 @@ AXON_DEV void store_block(const EpiArgs& ep, int nb, int t, RopeTok tok, const f
 #pragma unroll
         for (int j = 0; j < 4; ++j) o[j] += (float)ep.bias[min(n + j, N - 1)];
       }
-      store_cols<EPI == EPI_RESID>(p, o, N - n);
+      const float* r = EPI == EPI_RESID && ep.resid ? ep.resid + (int64_t)t * ep.ldo + n : p;
+      store_cols<EPI == EPI_RESID>(p, r, o, N - n);
     }
   }
 }
@@ -721,20 +722,30 @@ __global__ void __launch_bounds__(512, 1) gemm_tn_256_kernel(TnArgs g) {
   // load i of a wavefront: token rows 4 wave + 2 i, + 1 of the k-tile, 32 chunks
   // of 8 columns each; columns past the operand read its last 8 (never stored)
   const int lrow = wave * 4 + (lane >> 5), pch = lane & 31;
-  auto src = [&](const bf16* p, int ld, int t, int c) -> const bf16* {
-    t = min(t, g.T - 1);
+  auto at = [&](int ld, int t, int c) -> int64_t {
     c = min(c, ld - 8);
-    return p + (XP ? xp_off(t, c, ld) : (int64_t)t * ld + c);
+    return XP ? xp_off(t, c, ld) : (int64_t)t * ld + c;
   };
+  // a k-tile's 32 token rows are 32 ld elements in either layout: addresses are
+  // a fixed offset plus that, except in a k-tile that passes T
+  const int c0 = (pch ^ ((lrow & 3) << 2)) * 8, c1 = (pch ^ (((lrow + 2) & 3) << 2)) * 8;
+  const bf16* xs[2] = {g.X + at(g.ldx, lrow, n0 + c0), g.X + at(g.ldx, lrow + 2, n0 + c1)};
+  const bf16* ys[2] = {g.Y + at(g.ldy, lrow, m0 + c0), g.Y + at(g.ldy, lrow + 2, m0 + c1)};
   auto issue = [&](int stage, int kt) {
+    const bool tail = (kt + 1) * BK > g.T;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      const int row = lrow + i * 2, c = (pch ^ ((row & 3) << 2)) * 8;
+      const bf16* px = xs[i] + (int64_t)kt * BK * g.ldx;
+      const bf16* py = ys[i] + (int64_t)kt * BK * g.ldy;
+      if (tail) {
+        const int t = min(kt * BK + lrow + i * 2, g.T - 1), c = i ? c1 : c0;
+        px = g.X + at(g.ldx, t, n0 + c);
+        py = g.Y + at(g.ldy, t, m0 + c);
+      }
       bf16x8* base = lds2 + stage * STAGE + (wave * 2 + i) * 64;
-      __builtin_amdgcn_global_load_lds((const void*)src(g.X, g.ldx, kt * BK + row, n0 + c),
-                                       (__attribute__((address_space(3))) void*)base, 16, 0, 0);
-      __builtin_amdgcn_global_load_lds((const void*)src(g.Y, g.ldy, kt * BK + row, m0 + c),
-                                       (__attribute__((address_space(3))) void*)(base + PANEL), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((const void*)px, (__attribute__((address_space(3))) void*)base, 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((const void*)py, (__attribute__((address_space(3))) void*)(base + PANEL), 16, 0,
+                                       0);
     }
   };
 
@@ -1267,24 +1278,6 @@ void launch_gemm_f32(const float* W, const float* X, int N, int M, int K, int ep
   else klaunch(gemm_f32_kernel<EPI_F32>, grid, dim3(256), 0, s, W, X, N, M, K, ep);
 }
 
-// ============================================================================
-// split-K reductions
-// ============================================================================
-// out[i] (accumulate ? += : =) sum over s of parts[s * stride + i], in order
-__global__ void __launch_bounds__(256) sum_parts_kernel(float* __restrict__ out, const float* __restrict__ parts,
-                                                        int nparts, int64_t stride, int64_t n4, int accumulate) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n4) return;
-  f32x4 v = accumulate ? *(const f32x4*)(out + i * 4) : f32x4{};
-  for (int p = 0; p < nparts; ++p) v += *(const f32x4*)(parts + p * stride + i * 4);
-  *(f32x4*)(out + i * 4) = v;
-}
-
-void launch_sum_parts(float* out, const float* parts, int nparts, int64_t stride, int64_t n, int accumulate,
-                      hipStream_t s) {
-  const int64_t n4 = n / 4;
-  if (n4 > 0) sum_parts_kernel<<<(unsigned)((n4 + 255) / 256), 256, 0, s>>>(out, parts, nparts, stride, n4, accumulate);
-}
 __global__ void __launch_bounds__(256) silu_f32_kernel(const float* __restrict__ gu, float* __restrict__ a, int M,
                                                        int I) {
   const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;

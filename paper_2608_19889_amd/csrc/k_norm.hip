@@ -53,7 +53,7 @@ __global__ void __launch_bounds__(256) embed_rmsnorm_kernel(const int32_t* __res
 // r = i, or r = cu[i+1]-1 (last position of sequence i) when ``cu_last`` is set;
 // h rows in the row-pair layout when h_pair is set (both kernels).
 template <typename T>
-__global__ void __launch_bounds__(256) resid_rmsnorm_kernel(float* __restrict__ x,
+__global__ void __launch_bounds__(256) resid_rmsnorm_kernel(const float* x, float* x_out,
                                                             const float* __restrict__ parts,
                                                             int nparts, int64_t part_stride,
                                                             const T* __restrict__ g, T* __restrict__ h,
@@ -62,7 +62,8 @@ __global__ void __launch_bounds__(256) resid_rmsnorm_kernel(float* __restrict__ 
   __shared__ float red[16];
   const int i_out = blockIdx.x;
   const int r = cu_last ? cu_last[i_out + 1] - 1 : i_out;
-  float* xr = x + (int64_t)r * D;
+  const float* xr = x + (int64_t)r * D;
+  float* xo = x_out + (int64_t)r * D;
   float ss = 0.f;
   for (int i = threadIdx.x * 4; i < D; i += blockDim.x * 4) {
     f32x4 v = load4(xr + i);
@@ -76,14 +77,14 @@ __global__ void __launch_bounds__(256) resid_rmsnorm_kernel(float* __restrict__ 
         for (int q = 0; q < 4; ++q)
           if (s0 + q < nparts) v += p[q];
       }
-      store4(xr + i, v);
+      store4(xo + i, v);
     }
     ss += v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
   }
   ss = block_sum(ss, red);
   const float inv = rsqrtf(ss / (float)D + eps);
   for (int i = threadIdx.x * 4; i < D; i += blockDim.x * 4) {
-    f32x4 v = load4(xr + i), gv = load4(g + i);
+    f32x4 v = load4(xo + i), gv = load4(g + i);
     store4(h + (h_pair ? xp_off(i_out, i, D) : (int64_t)i_out * D + i),
            f32x4{v[0] * inv * gv[0], v[1] * inv * gv[1], v[2] * inv * gv[2], v[3] * inv * gv[3]});
   }
@@ -153,9 +154,11 @@ void launch_embed_rmsnorm(const int32_t* tok, const T* emb, const T* g, float* x
 
 template <typename T>
 void launch_resid_rmsnorm(float* x, const float* parts, int nparts, int64_t part_stride, const T* g, T* h,
-                          int rows, int D, float eps, const int32_t* cu_last, hipStream_t s, bool h_pair) {
+                          int rows, int D, float eps, const int32_t* cu_last, hipStream_t s, bool h_pair,
+                          float* x_out) {
   if (rows <= 0) return;
-  resid_rmsnorm_kernel<T><<<rows, 256, 0, s>>>(x, parts, nparts, part_stride, g, h, D, eps, cu_last, h_pair ? 1 : 0);
+  resid_rmsnorm_kernel<T><<<rows, 256, 0, s>>>(x, nparts > 0 && x_out ? x_out : x, parts, nparts, part_stride, g, h, D,
+                                               eps, cu_last, h_pair ? 1 : 0);
 }
 
 void launch_argmax(const float* logits, int rows, int V, float* am_val, int32_t* am_idx, int32_t* next, int32_t* len,
@@ -182,8 +185,8 @@ template void launch_embed_rmsnorm<float>(const int32_t*, const float*, const fl
 template void launch_embed_rmsnorm<bf16>(const int32_t*, const bf16*, const bf16*, float*, bf16*, int, int, int,
                                          float, hipStream_t, bool);
 template void launch_resid_rmsnorm<float>(float*, const float*, int, int64_t, const float*, float*, int, int,
-                                          float, const int32_t*, hipStream_t, bool);
+                                          float, const int32_t*, hipStream_t, bool, float*);
 template void launch_resid_rmsnorm<bf16>(float*, const float*, int, int64_t, const bf16*, bf16*, int, int,
-                                         float, const int32_t*, hipStream_t, bool);
+                                         float, const int32_t*, hipStream_t, bool, float*);
 
 }  // namespace axon

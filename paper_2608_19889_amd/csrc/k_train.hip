@@ -2,13 +2,11 @@
 // reverse of each forward step that is not a projection, and the layout
 // helpers that let the projection gradients run on the prefill GEMM.
 //
-// Every projection Y = X W^T (X [T][K], W [N][K]) has two gradients, both run
-// by gemm_bf16 (out[r][c] = sum_k A[r][k] B[c][k], B fragment-tiled):
-//   dX = dY W       : A = dY [T][N],   B = W^T tiled [K][N]  (contraction N)
-//   dW = dY^T X     : A = dY^T [N][Tp], B = X^T tiled [K][Tp] (contraction Tp,
-//                     the token count padded to 32 with zero columns)
-// so the weights get a transposed tiled copy once, and the activations and
-// their gradients are transposed per use (transpose_pad_kernel).
+// Every projection Y = X W^T (X [T][K], W [N][K]) has two gradients: dX = dY W,
+// run by the prefill GEMM on W^T, and dW = dY^T X,
+// so the weights get a transposed tiled copy once; the weight gradients read the
+// token-major operands as they are (gemm_tn_256_kernel).  Every GEMM operand
+// lies in the row-pair layout (xp_off).
 //
 // Attention backward recomputes the probabilities from the forward pass's
 // per-(query, head) log2-sum-exp: P = 2^(s sc - lse) with sc = log2(e) /
@@ -88,17 +86,19 @@ __global__ void __launch_bounds__(256) ce_reduce_kernel(const float* __restrict_
 }
 
 // dlogits[t][v] = (softmax_v - [v == target]) / N for counted rows, else 0;
-// columns V .. ldl-1 are zero.  8 columns per thread (ldl % 8 == 0), every load
-// unconditional 16 bytes (the padding columns hold whatever the buffer held and
-// are not used).
-__global__ void __launch_bounds__(256) ce_grad_kernel(const float* __restrict__ logits, int ldl, int V,
+// columns V .. ldl-1 are zero; dlog in the row-pair layout.  8 columns per
+// thread (ldl % 32 == 0), every load unconditional 16 bytes (the padding columns
+// hold whatever the buffer held and are not used); 8 lanes fill one 128-byte line of
+// a row pair.
+__global__ void __launch_bounds__(256) ce_grad_kernel(const float* __restrict__ logits, int ldl, int V, int T,
                                                       const int32_t* __restrict__ targets,
                                                       const float* __restrict__ valid,
                                                       const float* __restrict__ lse, const float* __restrict__ scal,
                                                       bf16* __restrict__ dlog) {
-  const int t = blockIdx.y;
-  const int v0 = (blockIdx.x * 256 + threadIdx.x) * 8;
-  if (v0 >= ldl) return;
+  const int tid = threadIdx.x;
+  const int t = blockIdx.y * 2 + ((tid >> 2) & 1);
+  const int v0 = (blockIdx.x * 32 + (tid >> 3)) * 32 + (tid & 3) * 8;
+  if (t >= T || v0 >= ldl) return;
   const float* row = logits + (int64_t)t * ldl + v0;
   const f32x4 lo = *(const f32x4*)row, hi = *(const f32x4*)(row + 4);
   const bool ok = valid[t] > 0.f;
@@ -112,7 +112,7 @@ __global__ void __launch_bounds__(256) ce_grad_kernel(const float* __restrict__ 
     const float g = (__expf(x - l) - (v == tg ? 1.f : 0.f)) * inv;
     o[j] = (bf16)(ok && v < V ? g : 0.f);
   }
-  *(bf16x8*)(dlog + (int64_t)t * ldl + v0) = o;
+  *(bf16x8*)(dlog + xp_off(t, v0, ldl)) = o;
 }
 
 // ---------------------------------------------------------------- layouts
@@ -130,14 +130,12 @@ AXON_DEV int64_t frag_off(int64_t c, int64_t col, int64_t dld) {
   return ((((c >> 5) * (dld >> 5) + (col >> 5)) * 2 + kk) * 64 + hl * 32 + (c & 31)) * 8 + j;
 }
 
-// dst[c][col(t)] = src[t][c] through a 64 x 64 LDS tile, both sides
-// coalesced: rows t < T are read (rows T .. Tmax-1 give zeros), col(t) = t,
-// or with cu: e * SP + (t - cu[e]) for t's sequence e (t < T only).  C % 4
-// == 0, ld % 4 == 0.  frag: dst in the fragment order of frag_off.
-__global__ void __launch_bounds__(256) transpose_tile_kernel(const bf16* __restrict__ src, int64_t ld, int T, int Tmax,
-                                                             int C, bf16* __restrict__ dst, int64_t dld,
-                                                             const int32_t* __restrict__ cu, int nseq, int SP,
-                                                             bool frag = false) {
+// dst[frag_off(c, col(t))] = src[t][c] through a 64 x 64 LDS tile, both sides
+// coalesced: col(t) = e * SP + (t - cu[e]) for t's sequence e.  C % 4 == 0, ld %
+// 4 == 0.
+__global__ void __launch_bounds__(256) transpose_tile_kernel(const bf16* __restrict__ src, int64_t ld, int T, int C,
+                                                             bf16* __restrict__ dst, int64_t dld,
+                                                             const int32_t* __restrict__ cu, int nseq, int SP) {
   __shared__ bf16 tile[64][66];
   const int t0 = blockIdx.x * 64, c0 = blockIdx.y * 64;
   const int tid = threadIdx.x, ty = tid >> 4, tx = tid & 15;
@@ -157,13 +155,9 @@ __global__ void __launch_bounds__(256) transpose_tile_kernel(const bf16* __restr
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int t = t0 + tx * 4 + j;
-      if (t >= (cu ? T : Tmax)) continue;
-      int64_t col = t;
-      if (cu) {
-        const int e = seq_of_token(cu, nseq, t);
-        col = (int64_t)e * SP + (t - cu[e]);
-      }
-      dst[frag ? frag_off(c, col, dld) : (int64_t)c * dld + col] = tile[tx * 4 + j][ty + 16 * r];
+      if (t >= T) continue;
+      const int e = seq_of_token(cu, nseq, t);
+      dst[frag_off(c, (int64_t)e * SP + (t - cu[e]), dld)] = tile[tx * 4 + j][ty + 16 * r];
     }
   }
 }
@@ -182,92 +176,210 @@ __global__ void __launch_bounds__(256) untile_transpose_kernel(const bf16* __res
   for (int j = 0; j < 8; ++j) dst[(int64_t)(c * 8 + j) * Np + n] = v[j];
 }
 
-__global__ void __launch_bounds__(256) to_bf16_kernel(const float* __restrict__ src, bf16* __restrict__ dst,
-                                                      int64_t n4) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n4) return;
-  const f32x4 v = *(const f32x4*)(src + i * 4);
-  *(bf16x4*)(dst + i * 4) = bf16x4{(bf16)v[0], (bf16)v[1], (bf16)v[2], (bf16)v[3]};
-}
-
-// ---------------------------------------------------------------- norms, MLP
+// ---------------------------------------------------------------- norms
 
 // RMSNorm y = x r g, r = rsqrt(mean(x^2) + eps): dx (= or +=) r g dy - x r^3
-// mean(g dy x); dgrow = dy x r (summed over rows by the column sum)
-__global__ void __launch_bounds__(256) rmsnorm_bwd_kernel(const float* __restrict__ x, const bf16* __restrict__ g,
-                                                          const float* __restrict__ dy, int ldy, int D, float eps,
-                                                          float* __restrict__ dx, int accumulate,
-                                                          float* __restrict__ dgrow) {
+// mean(g dy x), the gain's gradient dy x r summed over rows, and dx in bf16 (the
+// next projections' operand, row-pair layout).  dy arrives as the np split-K
+// partials of the GEMM that made it (in order).  HBM bound.  A workgroup takes
+// ``rows`` rows, a thread the same columns (4 NV of them) of each, so the gain's
+// terms stay in registers until one partial row per workgroup is left for the
+// column sum; the next row's operands are loaded before this row's reduction (one
+// barrier per row, its slots alternating).  The separate kernels for dx, the
+// gain's terms through memory, their column sum, the partials' sum and the bf16
+// copy took 100 us on 4096 x 2048; this one and the column sum 37 us (182 MB: 4.9 TB/s).
+template <int NV>
+__global__ void __launch_bounds__(256) norm_bwd_kernel(const float* __restrict__ x, const bf16* __restrict__ g,
+                                                       const float* __restrict__ dy, int np, int64_t stride, int T,
+                                                       int D, float eps, float* __restrict__ dx, int accumulate,
+                                                       bf16* __restrict__ dxb, float* __restrict__ gpart, int rows) {
+  __shared__ float red[2][2][4];
+  const int tid = threadIdx.x, wave = tid >> 6;
+  const int t0 = blockIdx.x * rows, t1 = min(T, t0 + rows);
+  int col[NV];
+  bool own[NV];
+  f32x4 gv[NV], gsum[NV];
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    const int c = (v * 256 + tid) * 4;
+    own[v] = c < D;
+    col[v] = min(c, D - 4);  // columns past D: the last ones again, not counted
+    const bf16x4 b = *(const bf16x4*)(g + col[v]);
+    gv[v] = f32x4{(float)b[0], (float)b[1], (float)b[2], (float)b[3]};
+    gsum[v] = f32x4{};
+  }
+  f32x4 xn[NV], dn[NV], an[NV];
+  auto load = [&](int t) {
+    const int64_t base = (int64_t)t * D;
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      xn[v] = *(const f32x4*)(x + base + col[v]);
+      dn[v] = *(const f32x4*)(dy + base + col[v]);
+      an[v] = accumulate ? *(const f32x4*)(dx + base + col[v]) : f32x4{};
+    }
+    for (int p = 1; p < np; ++p)
+#pragma unroll
+      for (int v = 0; v < NV; ++v) dn[v] += *(const f32x4*)(dy + p * stride + base + col[v]);
+  };
+  load(t0);
+  for (int t = t0; t < t1; ++t) {
+    f32x4 xc[NV], dc[NV], ac[NV];
+    float ss = 0.f, sgd = 0.f;
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      xc[v] = xn[v];
+      dc[v] = dn[v];
+      ac[v] = an[v];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        ss += own[v] ? xc[v][j] * xc[v][j] : 0.f;
+        sgd += own[v] ? gv[v][j] * dc[v][j] * xc[v][j] : 0.f;
+      }
+    }
+    if (t + 1 < t1) load(t + 1);
+    ss = wave_sum(ss);
+    sgd = wave_sum(sgd);
+    const int par = (t - t0) & 1;
+    if ((tid & 63) == 0) {
+      red[par][0][wave] = ss;
+      red[par][1][wave] = sgd;
+    }
+    __syncthreads();
+    ss = (red[par][0][0] + red[par][0][1]) + (red[par][0][2] + red[par][0][3]);
+    sgd = (red[par][1][0] + red[par][1][1]) + (red[par][1][2] + red[par][1][3]);
+    const float r = rsqrtf(ss / (float)D + eps), c = r * r * r * sgd / (float)D;
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      const f32x4 o = ac[v] + (gv[v] * dc[v] * r - xc[v] * c);
+      gsum[v] += dc[v] * xc[v] * r;
+      if (own[v]) {
+        *(f32x4*)(dx + (int64_t)t * D + col[v]) = o;
+        *(bf16x4*)(dxb + xp_off(t, col[v], D)) = bf16x4{(bf16)o[0], (bf16)o[1], (bf16)o[2], (bf16)o[3]};
+      }
+    }
+  }
+#pragma unroll
+  for (int v = 0; v < NV; ++v)
+    if (own[v]) *(f32x4*)(gpart + (int64_t)blockIdx.x * D + col[v]) = gsum[v];
+}
+
+// The same for D past the register form (8192): dgrow [T][D] receives the
+// gain's terms, which colsum_part_kernel sums.
+__global__ void __launch_bounds__(256) norm_bwd_wide_kernel(const float* __restrict__ x, const bf16* __restrict__ g,
+                                                            const float* __restrict__ dy, int np, int64_t stride, int D,
+                                                            float eps, float* __restrict__ dx, int accumulate,
+                                                            bf16* __restrict__ dxb, float* __restrict__ dgrow) {
   __shared__ float red[16];
-  const int t = blockIdx.x;
-  const float* xr = x + (int64_t)t * D;
-  const float* dyr = dy + (int64_t)t * ldy;
+  const int64_t t = blockIdx.x, base = t * D;
+  auto grad = [&](int i) {
+    float d = dy[base + i];
+    for (int p = 1; p < np; ++p) d += dy[p * stride + base + i];
+    return d;
+  };
   float ss = 0.f, sgd = 0.f;
   for (int i = threadIdx.x; i < D; i += 256) {
-    const float xv = xr[i];
+    const float xv = x[base + i];
     ss += xv * xv;
-    sgd += (float)g[i] * dyr[i] * xv;
+    sgd += (float)g[i] * grad(i) * xv;
   }
   ss = block_sum(ss, red);
   sgd = block_sum(sgd, red);
-  const float r = rsqrtf(ss / (float)D + eps);
-  const float c = r * r * r * sgd / (float)D;
-  float* dxr = dx + (int64_t)t * D;
+  const float r = rsqrtf(ss / (float)D + eps), c = r * r * r * sgd / (float)D;
   for (int i = threadIdx.x; i < D; i += 256) {
-    const float xv = xr[i], d = dyr[i];
-    const float v = r * (float)g[i] * d - xv * c;
-    dxr[i] = accumulate ? dxr[i] + v : v;
-    dgrow[(int64_t)t * D + i] = d * xv * r;
+    const float xv = x[base + i], d = grad(i);
+    const float v = r * (float)g[i] * d - xv * c + (accumulate ? dx[base + i] : 0.f);
+    dx[base + i] = v;
+    dxb[xp_off(t, i, D)] = (bf16)v;
+    dgrow[base + i] = d * xv * r;
   }
 }
 
-// column sums of src [T][C] (rows ld apart) in two deterministic passes:
-// part[chunk][c] over rows chunk*rpc .., then dst[c] = sum over chunks
-__global__ void __launch_bounds__(256) colsum_part_kernel(const float* __restrict__ src, int64_t ld, int T, int C,
-                                                          int rpc, float* __restrict__ part) {
+// column sums of src [T][C] over rows chunk*rpc ..: part[chunk][c]
+__global__ void __launch_bounds__(256) colsum_part_kernel(const float* __restrict__ src, int T, int C, int rpc,
+                                                          float* __restrict__ part) {
   const int c = blockIdx.x * 256 + threadIdx.x;
   if (c >= C) return;
   const int t0 = blockIdx.y * rpc, t1 = min(T, t0 + rpc);
   float s = 0.f;
-  for (int t = t0; t < t1; ++t) s += src[(int64_t)t * ld + c];
+  for (int t = t0; t < t1; ++t) s += src[(int64_t)t * C + c];
   part[(int64_t)blockIdx.y * C + c] = s;
 }
-__global__ void __launch_bounds__(256) colsum_final_kernel(const float* __restrict__ part, int nchunks, int C,
-                                                           float* __restrict__ dst) {
-  const int c = blockIdx.x * 256 + threadIdx.x;
-  if (c >= C) return;
+
+// The column sum's second pass: column c of part [n][C], the partials in 16
+// interleaved groups of fixed order, then the groups in order.  Columns below
+// c1 go to d0, below c2 to d1, the rest to d2.
+__global__ void __launch_bounds__(1024) colsum_final_kernel(const float* __restrict__ part, int n, int C,
+                                                            float* __restrict__ d0, int c1, float* __restrict__ d1,
+                                                            int c2, float* __restrict__ d2) {
+  __shared__ float sums[16][64];
+  const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
+  const int c = blockIdx.x * 64 + lane;
   float s = 0.f;
-  for (int i = 0; i < nchunks; ++i) s += part[(int64_t)i * C + c];
-  dst[c] = s;
+  for (int i0 = grp; i0 < n; i0 += 16 * 8) {
+    float v[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = part[(int64_t)min(i0 + q * 16, n - 1) * C + min(c, C - 1)];
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+      if (i0 + q * 16 < n) s += v[q];
+  }
+  sums[grp][lane] = s;
+  __syncthreads();
+  if (grp > 0 || c >= C) return;
+  s = 0.f;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) s += sums[i][lane];
+  if (c < c1) d0[c] = s;
+  else if (c < c2) d1[c - c1] = s;
+  else d2[c - c2] = s;
 }
 
 // ---------------------------------------------------------------- attention
 
-// D[t][h] = sum_d dO[t][h][d] O[t][h][d]; D and the forward's log2-sum-exp
-// are also copied into the packed per-head rows lsep / dsump [H][W] (column
-// e*SP + position), where the 4 consecutive queries a lane of the dK / dV
-// kernel needs are one 16-byte load
-__global__ void __launch_bounds__(256) attn_bwd_d_kernel(const bf16* __restrict__ dob, const bf16* __restrict__ o,
-                                                         int TH, int hd, float* __restrict__ dsum,
-                                                         const float* __restrict__ lse, const int32_t* __restrict__ cu,
-                                                         int nseq, int H, int SP, int64_t W,
-                                                         float* __restrict__ lsep, float* __restrict__ dsump) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= TH) return;
-  const bf16* a = dob + (int64_t)i * hd;
-  const bf16* b = o + (int64_t)i * hd;
-  float s = 0.f;
-  for (int d = 0; d < hd; d += 8) {
-    const bf16x8 x = *(const bf16x8*)(a + d), y = *(const bf16x8*)(b + d);
-#pragma unroll
-    for (int j = 0; j < 8; ++j) s += (float)x[j] * (float)y[j];
+// dO in bf16 from the np split-K partials of its GEMM (in order), and D[t][h] =
+// sum_d dO[t][h][d] O[t][h][d] (dO rounded; O in the row-pair layout).  D and the
+// forward's log2-sum-exp are also copied into the packed per-head rows lsep /
+// dsump [H][W] (column e*SP + position), where the 4 consecutive queries a lane
+// of the dK / dV kernel needs are one 16-byte load.  A thread takes 8 dims.
+template <int HD>
+__global__ void __launch_bounds__(256) attn_bwd_do_kernel(const float* __restrict__ dof, int np, int64_t stride,
+                                                          const bf16* __restrict__ o, int T, int H,
+                                                          bf16* __restrict__ dob, float* __restrict__ dsum,
+                                                          const float* __restrict__ lse,
+                                                          const int32_t* __restrict__ cu, int nseq, int SP, int64_t W,
+                                                          float* __restrict__ lsep, float* __restrict__ dsump) {
+  constexpr int LPH = HD / 8;  // lanes of a head
+  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t th = min(idx / LPH, (int64_t)T * H - 1);  // past the end: the last head again, not stored
+  const int d0 = (int)(idx % LPH) * 8, t = (int)(th / H), h = (int)(th % H);
+  const float* src = dof + th * HD + d0;
+  f32x4 lo = *(const f32x4*)src, hi = *(const f32x4*)(src + 4);
+  for (int p = 1; p < np; ++p) {
+    lo += *(const f32x4*)(src + p * stride);
+    hi += *(const f32x4*)(src + p * stride + 4);
   }
-  dsum[i] = s;
-  const int t = i / H, h = i % H;
-  const int e = seq_of_token(cu, nseq, t);
-  const int64_t col = (int64_t)h * W + (int64_t)e * SP + (t - cu[e]);
-  lsep[col] = lse[i];
-  dsump[col] = s;
+  const bf16x8 ov = *(const bf16x8*)(o + xp_off(t, h * HD + d0, H * HD));
+  bf16x8 b;
+  float s = 0.f;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    b[j] = (bf16)(j < 4 ? lo[j & 3] : hi[j & 3]);
+    s += (float)b[j] * (float)ov[j];
+  }
+  // over the 8 or 16 lanes of the head (see wave_sum)
+  s += dpp_move<0xB1>(s);
+  s += dpp_move<0x4E>(s);
+  s += dpp_move<0x141>(s);
+  if constexpr (LPH == 16) s += dpp_move<0x140>(s);
+  if (idx / LPH >= (int64_t)T * H) return;
+  *(bf16x8*)(dob + th * HD + d0) = b;
+  if (d0 == 0) {
+    dsum[th] = s;
+    const int e = seq_of_token(cu, nseq, t);
+    const int64_t c = (int64_t)h * W + (int64_t)e * SP + (t - cu[e]);
+    lsep[c] = lse[th];
+    dsump[c] = s;
+  }
 }
 
 // ---- MFMA attention backward.  v_mfma_f32_32x32x16_bf16 with lane L, half
@@ -444,8 +556,7 @@ __global__ void __launch_bounds__(64) attn_bwd_dq_kernel(const bf16* __restrict_
 // over the query blocks from the key block on, S = Q K^T and dP = dO V^T (k =
 // head dim), then dV^T += dO^T P and dK^T += Q^T dS (k = the block's 32
 // queries).  Writes the head's share into dk / dv [T][H][hd] (the heads of a
-// group are summed by attn_bwd_group_sum_kernel; with one head per group they
-// are the result).
+// group are summed by rope_bwd_kernel).
 template <int HD>
 __global__ void __launch_bounds__(64) attn_bwd_dkv_kernel(const bf16* __restrict__ q, const bf16* __restrict__ dob,
                                                           const bf16* __restrict__ kr, const bf16* __restrict__ vr,
@@ -537,60 +648,56 @@ __global__ void __launch_bounds__(64) attn_bwd_dkv_kernel(const bf16* __restrict
     }
 }
 
-// dk[t][kvh] = sum over the group's heads (in order) of dkh[t][head], same for v
-__global__ void __launch_bounds__(256) attn_bwd_group_sum_kernel(const float* __restrict__ dkh,
-                                                                 const float* __restrict__ dvh, int64_t n, int group,
-                                                                 int hd, float* __restrict__ dk,
-                                                                 float* __restrict__ dv) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;  // over T * KV * hd
-  if (i >= n) return;
-  const int64_t row = i / hd, d = i % hd;  // row = t * KV + kvh
-  const int64_t base = row * group * hd + d;
-  float a = 0.f, b = 0.f;
-  for (int g = 0; g < group; ++g) {
-    a += dkh[base + (int64_t)g * hd];
-    b += dvh[base + (int64_t)g * hd];
-  }
-  dk[i] = a;
-  dv[i] = b;
-}
-
 // Gradients at the rotated q / k and at v back through RoPE (the transpose of
 // a rotation rotates by the opposite angle) into the fused QKV layout: dqkv
-// [T][nq] bf16 in the projection's row order (within a head, groups of 8 =
-// 4 first halves and their partners), dqkv_f [T][nq] float in the original
-// order (for the bias gradient; may be null).  One thread per (token, head,
-// pair i < hd/2).
-__global__ void __launch_bounds__(256) rope_bwd_kernel(const float* __restrict__ dq, const float* __restrict__ dk,
-                                                       const float* __restrict__ dv, const float* __restrict__ cos_t,
+// [T][nq] bf16 in the projection's row order (within a head, groups of 8 = 4
+// first halves and their partners), row-pair layout.  dkh / dvh hold a share per
+// query head; a kv head's are summed in head order.  A thread owns one 8-row
+// group (16-byte loads and stores) over ``rows`` tokens, so that with bpart the
+// bias gradient's column sums [workgroup][nq] (original row order) stay in
+// registers.  One thread per rotation pair, with the share sum and a float32 copy
+// of dqkv for the bias as passes of their own, took 46 us on 4096 x 3072; this
+// kernel 27 us (125 MB).
+__global__ void __launch_bounds__(128) rope_bwd_kernel(const float* __restrict__ dq, const float* __restrict__ dkh,
+                                                       const float* __restrict__ dvh, const float* __restrict__ cos_t,
                                                        const float* __restrict__ sin_t,
                                                        const int32_t* __restrict__ cu, int nseq, int T, int H,
                                                        int KVh, int hd, bf16* __restrict__ dqkv,
-                                                       float* __restrict__ dqkv_f) {
-  const int half = hd / 2, NH = H + 2 * KVh;
-  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (idx >= (int64_t)T * NH * half) return;
-  const int i = (int)(idx % half);
-  const int hh = (int)((idx / half) % NH);
-  const int t = (int)(idx / ((int64_t)half * NH));
-  const float* src = hh < H ? dq + ((int64_t)t * H + hh) * hd
-                            : (hh < H + KVh ? dk + ((int64_t)t * KVh + hh - H) * hd
-                                            : dv + ((int64_t)t * KVh + hh - H - KVh) * hd);
-  float y1 = src[i], y2 = src[i + half];
-  if (hh < H + KVh) {
-    const int pos = t - cu[seq_of_token(cu, nseq, t)];
-    const float c = cos_t[(int64_t)pos * half + i], s = sin_t[(int64_t)pos * half + i];
-    const float x1 = y1 * c + y2 * s, x2 = y2 * c - y1 * s;
-    y1 = x1;
-    y2 = x2;
+                                                       float* __restrict__ bpart, int rows) {
+  const int half = hd / 2, NH = H + 2 * KVh, nq = NH * hd, group = H / KVh;
+  const int item = blockIdx.x * 128 + threadIdx.x;
+  if (item >= nq / 8) return;
+  const int hh = item / (hd / 8), i0 = item % (hd / 8) * 4;  // rotation pairs i0 .. i0 + 3 of head hh
+  const int t0 = blockIdx.y * rows, t1 = min(T, t0 + rows);
+  const bool rot = hh < H + KVh;
+  const float* src = hh < H ? dq : hh < H + KVh ? dkh : dvh;
+  const int head = hh < H ? hh : (hh - H - (rot ? 0 : KVh)) * group, nsum = hh < H ? 1 : group;
+  int e = seq_of_token(cu, nseq, t0);
+  f32x4 s1 = {}, s2 = {};
+  for (int t = t0; t < t1; ++t) {
+    while (t >= cu[e + 1]) ++e;  // sequences are not empty
+    const float* p = src + ((int64_t)t * H + head) * hd + i0;
+    f32x4 y1 = *(const f32x4*)p, y2 = *(const f32x4*)(p + half);
+    for (int g = 1; g < nsum; ++g) {
+      y1 += *(const f32x4*)(p + g * hd);
+      y2 += *(const f32x4*)(p + g * hd + half);
+    }
+    if (rot) {
+      const int64_t at = (int64_t)(t - cu[e]) * half + i0;
+      const f32x4 c = *(const f32x4*)(cos_t + at), sn = *(const f32x4*)(sin_t + at);
+      const f32x4 x1 = y1 * c + y2 * sn;
+      y2 = y2 * c - y1 * sn;
+      y1 = x1;
+    }
+    *(bf16x8*)(dqkv + xp_off(t, (int64_t)item * 8, nq)) =
+        bf16x8{(bf16)y1[0], (bf16)y1[1], (bf16)y1[2], (bf16)y1[3], (bf16)y2[0], (bf16)y2[1], (bf16)y2[2], (bf16)y2[3]};
+    s1 += y1;
+    s2 += y2;
   }
-  const int64_t nq = (int64_t)NH * hd;
-  const int r1 = 8 * (i / 4) + (i % 4);  // row of element i in the grouped order; its partner is 4 later
-  dqkv[(int64_t)t * nq + hh * hd + r1] = (bf16)y1;
-  dqkv[(int64_t)t * nq + hh * hd + r1 + 4] = (bf16)y2;
-  if (dqkv_f) {
-    dqkv_f[(int64_t)t * nq + hh * hd + i] = y1;
-    dqkv_f[(int64_t)t * nq + hh * hd + i + half] = y2;
+  if (bpart) {
+    float* b = bpart + (int64_t)blockIdx.y * nq + hh * hd + i0;
+    *(f32x4*)b = s1;
+    *(f32x4*)(b + half) = s2;
   }
 }
 
@@ -609,7 +716,8 @@ void launch_ce_loss(const float* logits, int ldl, int V, const float2* lse_part,
   ce_rows_kernel<<<T, 256, 0, s>>>(logits, ldl, V, lse_part, (V + LSE_COLS - 1) / LSE_COLS, targets, rowloss, valid,
                                    lse);
   ce_reduce_kernel<<<1, 256, 0, s>>>(rowloss, valid, T, loss, scal);
-  ce_grad_kernel<<<dim3((ldl / 8 + 255) / 256, T), 256, 0, s>>>(logits, ldl, V, targets, valid, lse, scal, dlog);
+  ce_grad_kernel<<<dim3((ldl / 32 + 31) / 32, (T + 1) / 2), 256, 0, s>>>(logits, ldl, V, T, targets, valid, lse, scal,
+                                                                       dlog);
 }
 
 void launch_untile_transpose(const bf16* W, int64_t N, int K, bf16* dst, int64_t Np, hipStream_t s) {
@@ -617,23 +725,32 @@ void launch_untile_transpose(const bf16* W, int64_t N, int K, bf16* dst, int64_t
   if (n > 0) untile_transpose_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(W, N, K, dst, Np);
 }
 
-void launch_to_bf16(const float* src, bf16* dst, int64_t n, hipStream_t s) {
-  const int64_t n4 = n / 4;
-  if (n4 > 0) to_bf16_kernel<<<(unsigned)((n4 + 255) / 256), 256, 0, s>>>(src, dst, n4);
+// rows per workgroup of the row kernels that leave one partial per workgroup:
+// at most ROW_PARTS partials
+static int row_chunk(int T) { return (T + ROW_PARTS - 1) / ROW_PARTS; }
+
+static void colsum_final(const float* part, int n, int C, float* d0, int c1, float* d1, int c2, float* d2,
+                         hipStream_t s) {
+  colsum_final_kernel<<<(C + 63) / 64, 1024, 0, s>>>(part, n, C, d0, c1, d1, c2, d2);
 }
 
-void launch_rmsnorm_bwd(const float* x, const bf16* g, const float* dy, int ldy, int T, int D, float eps, float* dx,
-                        int accumulate, float* dgrow, hipStream_t s) {
-  if (T > 0) rmsnorm_bwd_kernel<<<T, 256, 0, s>>>(x, g, dy, ldy, D, eps, dx, accumulate, dgrow);
-}
-
-int colsum_chunks(int T) { return std::max(1, std::min(256, (T + 63) / 64)); }
-
-void launch_colsum(const float* src, int64_t ld, int T, int C, float* part, float* dst, hipStream_t s) {
-  if (T <= 0 || C <= 0) return;
-  const int nch = colsum_chunks(T), rpc = (T + nch - 1) / nch;
-  colsum_part_kernel<<<dim3((C + 255) / 256, nch), 256, 0, s>>>(src, ld, T, C, rpc, part);
-  colsum_final_kernel<<<(C + 255) / 256, 256, 0, s>>>(part, nch, C, dst);
+void launch_norm_bwd(const float* x, const bf16* g, const float* dy, int np, int64_t stride, int T, int D, float eps,
+                     float* dx, int accumulate, bf16* dxb, float* dg, float* part, float* dgrow, hipStream_t s) {
+  if (T <= 0) return;
+  const int rows = row_chunk(T), n = (T + rows - 1) / rows;
+  if (D > NORM_BWD_COLS) {
+    norm_bwd_wide_kernel<<<T, 256, 0, s>>>(x, g, dy, np, stride, D, eps, dx, accumulate, dxb, dgrow);
+    colsum_part_kernel<<<dim3((D + 255) / 256, n), 256, 0, s>>>(dgrow, T, D, rows, part);
+  } else {
+    auto go = [&](auto kern) {
+      kern<<<n, 256, 0, s>>>(x, g, dy, np, stride, T, D, eps, dx, accumulate, dxb, part, rows);
+    };
+    if (D <= 1024) go(norm_bwd_kernel<1>);
+    else if (D <= 2048) go(norm_bwd_kernel<2>);
+    else if (D <= 4096) go(norm_bwd_kernel<4>);
+    else go(norm_bwd_kernel<8>);
+  }
+  colsum_final(part, n, D, dg, D, nullptr, D, nullptr, s);
 }
 
 bool attn_bwd_layout_ok(int H, int KVh, int hd, int SP, int64_t W) {
@@ -643,51 +760,49 @@ bool attn_bwd_layout_ok(int H, int KVh, int hd, int SP, int64_t W) {
          ((int64_t)H * hd) % 32 == 0 && ((int64_t)KVh * hd) % 32 == 0;
 }
 
-bool launch_attn_bwd(const bf16* q, KVView kv, const bf16* o, const bf16* dob, const float* lse, float* dsum,
-                     float* statp, const int32_t* cu, const int32_t* h_cu, int nseq, int T, int H, int SP, int64_t W,
-                     bf16* kr, bf16* vr, bf16* kt, bf16* qt, bf16* dot, float* dq, float* dkh, float* dvh, float* dk,
-                     float* dv, hipStream_t s) {
+bool launch_attn_bwd(const bf16* q, KVView kv, const bf16* o, const float* dof, int np, int64_t stride, bf16* dob,
+                     const float* lse, float* dsum, float* statp, const int32_t* cu, const int32_t* h_cu, int nseq,
+                     int T, int H, int SP, int64_t W, bf16* kr, bf16* vr, bf16* kt, bf16* qt, bf16* dot, float* dq,
+                     float* dkh, float* dvh, hipStream_t s) {
   if (!attn_bwd_layout_ok(H, kv.kv_heads, kv.hd, SP, W)) return false;
   if (T <= 0) return true;
-  const int KVh = kv.kv_heads, hd = kv.hd, group = H / KVh;
+  const int KVh = kv.kv_heads, hd = kv.hd;
   float* lsep = statp;
   float* dsump = statp + (int64_t)H * W;
-  attn_bwd_d_kernel<<<(T * H + 255) / 256, 256, 0, s>>>(dob, o, T * H, hd, dsum, lse, cu, nseq, H, SP, W, lsep, dsump);
+  const unsigned nd = (unsigned)(((int64_t)T * H * hd / 8 + 255) / 256);
+  if (hd == 64)
+    attn_bwd_do_kernel<64><<<nd, 256, 0, s>>>(dof, np, stride, o, T, H, dob, dsum, lse, cu, nseq, SP, W, lsep, dsump);
+  else
+    attn_bwd_do_kernel<128><<<nd, 256, 0, s>>>(dof, np, stride, o, T, H, dob, dsum, lse, cu, nseq, SP, W, lsep, dsump);
   int blocks16 = 0;
   for (int e = 0; e < nseq; ++e) blocks16 += (h_cu[e + 1] - h_cu[e] + 15) / 16;
   if (hd == 64) attn_bwd_pack_kernel<64><<<dim3(blocks16, KVh), 256, 0, s>>>(kv, cu, nseq, SP, W, kr, vr, kt);
   else attn_bwd_pack_kernel<128><<<dim3(blocks16, KVh), 256, 0, s>>>(kv, cu, nseq, SP, W, kr, vr, kt);
-  transpose_tile_kernel<<<dim3((T + 63) / 64, (H * hd + 63) / 64), 256, 0, s>>>(q, (int64_t)H * hd, T, T, H * hd, qt,
-                                                                                 W, cu, nseq, SP, true);
-  transpose_tile_kernel<<<dim3((T + 63) / 64, (H * hd + 63) / 64), 256, 0, s>>>(dob, (int64_t)H * hd, T, T, H * hd,
-                                                                                 dot, W, cu, nseq, SP, true);
+  const dim3 tg((T + 63) / 64, (H * hd + 63) / 64);
+  transpose_tile_kernel<<<tg, 256, 0, s>>>(q, (int64_t)H * hd, T, H * hd, qt, W, cu, nseq, SP);
+  transpose_tile_kernel<<<tg, 256, 0, s>>>(dob, (int64_t)H * hd, T, H * hd, dot, W, cu, nseq, SP);
   int blocks = 0;
   for (int e = 0; e < nseq; ++e) blocks += (h_cu[e + 1] - h_cu[e] + 31) / 32;
-  float* dkt = group > 1 ? dkh : dk;  // per-head shares, summed below when a group has several heads
-  float* dvt = group > 1 ? dvh : dv;
   if (hd == 64) {
     attn_bwd_dq_kernel<64><<<dim3(blocks, H), 64, 0, s>>>(q, dob, kr, vr, kt, lse, dsum, cu, nseq, H, KVh, SP, W, dq);
     attn_bwd_dkv_kernel<64><<<dim3(blocks, H), 64, 0, s>>>(q, dob, kr, vr, qt, dot, lsep, dsump, cu, nseq, H, KVh, SP,
-                                                           W, dkt, dvt);
+                                                           W, dkh, dvh);
   } else {
     attn_bwd_dq_kernel<128><<<dim3(blocks, H), 64, 0, s>>>(q, dob, kr, vr, kt, lse, dsum, cu, nseq, H, KVh, SP, W, dq);
     attn_bwd_dkv_kernel<128><<<dim3(blocks, H), 64, 0, s>>>(q, dob, kr, vr, qt, dot, lsep, dsump, cu, nseq, H, KVh, SP,
-                                                            W, dkt, dvt);
-  }
-  if (group > 1) {
-    const int64_t n = (int64_t)T * KVh * hd;
-    attn_bwd_group_sum_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(dkh, dvh, n, group, hd, dk, dv);
+                                                            W, dkh, dvh);
   }
   return true;
 }
 
-void launch_rope_bwd(const float* dq, const float* dk, const float* dv, const float* cos_t, const float* sin_t,
-                     const int32_t* cu, int nseq, int T, int H, int KVh, int hd, bf16* dqkv, float* dqkv_f,
-                     hipStream_t s) {
-  const int64_t n = (int64_t)T * (H + 2 * KVh) * (hd / 2);
-  if (n > 0)
-    rope_bwd_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(dq, dk, dv, cos_t, sin_t, cu, nseq, T, H, KVh, hd,
-                                                                dqkv, dqkv_f);
+void launch_rope_bwd(const float* dq, const float* dkh, const float* dvh, const float* cos_t, const float* sin_t,
+                     const int32_t* cu, int nseq, int T, int H, int KVh, int hd, bf16* dqkv, float* bpart, float* dbq,
+                     float* dbk, float* dbv, hipStream_t s) {
+  if (T <= 0) return;
+  const int nq = (H + 2 * KVh) * hd, rows = row_chunk(T), n = (T + rows - 1) / rows;
+  rope_bwd_kernel<<<dim3((nq / 8 + 127) / 128, n), 128, 0, s>>>(dq, dkh, dvh, cos_t, sin_t, cu, nseq, T, H, KVh, hd,
+                                                               dqkv, dbq ? bpart : nullptr, rows);
+  if (dbq) colsum_final(bpart, n, nq, dbq, H * hd, dbk, (H + KVh) * hd, dbv, s);
 }
 
 void launch_embed_bwd(const int32_t* tok, const float* dx, int T, int D, int V, float* dE, hipStream_t s) {

@@ -31,7 +31,8 @@ void klaunch(Kern kern, dim3 grid, dim3 block, uint32_t shmem, hipStream_t s, Ar
 // Epilogues of the projection GEMMs (out[t][n] = sum_k X[t][k] * W[n][k]).
 enum Epi : int {
   EPI_F32 = 0,    // out_f32[t * ldo + n] = acc
-  EPI_RESID = 1,  // out_f32[t * ldo + n] += acc   (residual stream, float)
+  EPI_RESID = 1,  // out_f32[t * ldo + n] = resid[t * ldo + n] + acc  (residual
+                  // stream, float; resid null: out_f32)
   EPI_SILU = 2,   // W rows interleaved in blocks of 16 gate rows then 16 up rows;
                   // out_t[t * ldo + f] = silu(gate_f) * up_f
   EPI_ROPE = 4,   // bf16 fused QKV projection (rows in the rotation-pair order of
@@ -52,6 +53,7 @@ struct EpiArgs {
   float* out_f32;
   void* out_t;
   int ldo;
+  const float* resid;
   int64_t part_stride;
   // EPI_ROPE.  Token t is at position t - cu[seq] of sequence seq (prefill,
   // len == nullptr) or at position len[t] of slot t (decode).
@@ -104,41 +106,42 @@ void launch_layernorm(const float* x, const bf16* g, const bf16* beta, bf16* h, 
 void launch_transpose_rows(const bf16* src, bf16* dst, int K, int N, const int32_t* perm, hipStream_t s);
 
 // ---- backward pass (k_train.hip)
-// loss over logits [T][ldl] (V real columns, ldl % 8 == 0) and targets
+// loss over logits [T][ldl] (V real columns, ldl % 32 == 0) and targets
 // (counted when in [0, V)), from the logits and their projection's EPI_LSE
 // partials: loss[0] = mean cross-entropy, dlog [T][ldl] bf16 = its gradient
-// (zero padding); rowloss / valid / lse [T] and scal [1] scratch
+// (zero padding, row-pair layout); rowloss / valid / lse [T] and scal [1] scratch
 void launch_ce_loss(const float* logits, int ldl, int V, const float2* lse_part, const int32_t* targets, int T,
                     float* rowloss, float* valid, float* lse, float* loss, float* scal, bf16* dlog, hipStream_t s);
 // dst [K][Np] (row-major) = W^T for the fragment-tiled W [N][K]
 void launch_untile_transpose(const bf16* W, int64_t N, int K, bf16* dst, int64_t Np, hipStream_t s);
-void launch_to_bf16(const float* src, bf16* dst, int64_t n, hipStream_t s);  // n % 4 == 0
-// RMSNorm backward: dx (accumulate ? += : =) and per-row gain terms dgrow [T][D]
-void launch_rmsnorm_bwd(const float* x, const bf16* g, const float* dy, int ldy, int T, int D, float eps, float* dx,
-                        int accumulate, float* dgrow, hipStream_t s);
-// dst[c] = sum_t src[t][c], deterministic; part holds colsum_chunks(T) * C floats
-int colsum_chunks(int T);
-void launch_colsum(const float* src, int64_t ld, int T, int C, float* part, float* dst, hipStream_t s);
+// The row kernels below that reduce over tokens leave at most ROW_PARTS partial
+// rows.  RMSNorm backward: dx (accumulate ? += : =), its bf16 copy dxb (row-pair
+// layout) and the gain's gradient dg [D], from dy as np partials [T][D] ``stride``
+// apart; part: ROW_PARTS x D floats; dgrow: [T][D] scratch, needed for D >
+// NORM_BWD_COLS only.  D % 32 == 0.
+constexpr int ROW_PARTS = 512, NORM_BWD_COLS = 8192;
+void launch_norm_bwd(const float* x, const bf16* g, const float* dy, int np, int64_t stride, int T, int D, float eps,
+                     float* dx, int accumulate, bf16* dxb, float* dg, float* part, float* dgrow, hipStream_t s);
 // attention backward over nseq fresh sequences in slots 0.. (contiguous cache):
-// dq [T][H][hd], dk / dv [T][KV][hd] (float), from q / o / dO [T][H][hd] bf16,
-// the forward's log2-sum-exp lse [T][H]; dsum [T][H] scratch.  Packed copies
-// (scratch, finite at allocation): kr / vr [nseq*SP][KV][hd], kt [KV*hd][W],
-// qt / dot [H*hd][W], W >= nseq*SP, SP >= the longest sequence rounded up to
-// 32, plus 32
-// dkh / dvh [T][H][hd] scratch (the per-head shares of dk / dv)
+// dq [T][H][hd] and each query head's share of dk / dv, dkh / dvh [T][H][hd]
+// (float), from q [T][H][hd] and o (row-pair layout) bf16, the gradient of o as
+// np float partials ``stride`` apart (dob [T][H][hd] receives it in bf16) and the
+// forward's log2-sum-exp lse [T][H]; dsum [T][H] scratch.  Packed copies (scratch,
+// finite at allocation): kr / vr [nseq*SP][KV][hd], kt [KV*hd][W], qt / dot
+// [H*hd][W], W >= nseq*SP, SP >= the longest sequence rounded up to 32, plus 32.
 // false (nothing launched) unless the packed fragment layouts fit the shape:
 // attn_bwd_layout_ok(H, kv heads, head_dim, SP, W)
 bool attn_bwd_layout_ok(int H, int KVh, int hd, int SP, int64_t W);
-bool launch_attn_bwd(const bf16* q, KVView kv, const bf16* o, const bf16* dob, const float* lse, float* dsum,
-                     float* statp /* [2][H][W] */, const int32_t* cu, const int32_t* h_cu, int nseq, int T, int H,
-                     int SP, int64_t W,
-                     bf16* kr, bf16* vr, bf16* kt, bf16* qt, bf16* dot, float* dq, float* dkh, float* dvh, float* dk,
-                     float* dv, hipStream_t s);
-// back through RoPE into the fused QKV row order (bf16) and the original order
-// (float, may be null)
-void launch_rope_bwd(const float* dq, const float* dk, const float* dv, const float* cos_t, const float* sin_t,
-                     const int32_t* cu, int nseq, int T, int H, int KVh, int hd, bf16* dqkv, float* dqkv_f,
-                     hipStream_t s);
+bool launch_attn_bwd(const bf16* q, KVView kv, const bf16* o, const float* dof, int np, int64_t stride, bf16* dob,
+                     const float* lse, float* dsum, float* statp /* [2][H][W] */, const int32_t* cu,
+                     const int32_t* h_cu, int nseq, int T, int H, int SP, int64_t W, bf16* kr, bf16* vr, bf16* kt,
+                     bf16* qt, bf16* dot, float* dq, float* dkh, float* dvh, hipStream_t s);
+// back through RoPE into the fused QKV row order (bf16, row-pair layout), the
+// heads' shares of dk / dv summed; with dbq the bias gradients dbq / dbk / dbv too
+// (bpart: ROW_PARTS x nq floats)
+void launch_rope_bwd(const float* dq, const float* dkh, const float* dvh, const float* cos_t, const float* sin_t,
+                     const int32_t* cu, int nseq, int T, int H, int KVh, int hd, bf16* dqkv, float* bpart, float* dbq,
+                     float* dbk, float* dbv, hipStream_t s);
 void launch_embed_bwd(const int32_t* tok, const float* dx, int T, int D, int V, float* dE, hipStream_t s);
 
 // ---- weight layout (k_layout.hip): fragment-tiled copy of row-major bf16
@@ -152,7 +155,8 @@ void launch_embed_rmsnorm(const int32_t* tok, const T* emb, const T* g, float* x
                           float eps, hipStream_t s, bool h_pair = false);
 template <typename T>
 void launch_resid_rmsnorm(float* x, const float* parts, int nparts, int64_t part_stride, const T* g, T* h,
-                          int rows, int D, float eps, const int32_t* cu_last, hipStream_t s, bool h_pair = false);
+                          int rows, int D, float eps, const int32_t* cu_last, hipStream_t s, bool h_pair = false,
+                          float* x_out = nullptr);  // nparts > 0: the new x goes to x_out (x when null)
 // next[i] = argmax of logits row i, or (cu_last) of row cu_last[i+1]-1, the lowest
 // index on ties; len[i] += 1 when set; am_val / am_idx: scratch of rows x
 // ceil(V / 4096)
@@ -194,9 +198,6 @@ int gemm_ksplit_few(int N, int M, int K, int max_split);
 enum WgradMode : int { WGRAD_ROWS = 0, WGRAD_QKV = 1, WGRAD_GU = 2 };
 void launch_wgrad(int mode, const bf16* Y, int ldy, int R, const bf16* X, int C, int T, bool xpair, float* out,
                   float* out1, float* out2, int hd, int H, int KVh, float* part, int64_t part_floats, hipStream_t s);
-// out[i] (accumulate ? += : =) sum of parts[s * stride + i] over s in order (n % 4 == 0)
-void launch_sum_parts(float* out, const float* parts, int nparts, int64_t stride, int64_t n, int accumulate,
-                      hipStream_t s);
 // float32 check-mode GEMM (any M): EPI_F32 / EPI_RESID.
 void launch_gemm_f32(const float* W, const float* X, int N, int M, int K, int epi, const EpiArgs& ep,
                      hipStream_t s);
