@@ -470,14 +470,15 @@ void gemm_many(axon_model* m, const void* W, const void* X, int N, int M, int K,
   });
 }
 
-// Split-K choice for a bf16 GEMM with a float32 result: the split
-// gemm_ksplit takes when its partials fit m->gemm_part, else 1.
+// Split-K choice of the training forward pass's residual projections: the split
+// gemm_ksplit takes when its partials fit m->gemm_part, else 1.  By the number
+// of 256-tiles alone, as ever, so that a loss stays the number it was.
 int split_for(axon_model* m, int N, int M, int K) {
   const int ks = gemm_ksplit(N, M, K);
   return ks > 1 && (int64_t)ks * M * N <= m->gemm_part_floats ? ks : 1;
 }
 
-// X W^T in float32 [M][N], split over K when the output has few 256-tiles:
+// X W^T in float32 [M][N] of the backward pass, split over K where that pays:
 // returns the partials (``out``, one, when unsplit; else m->gemm_part, good
 // until the next split GEMM) for the consumer to sum in order.
 struct Parts {
@@ -485,7 +486,12 @@ struct Parts {
   int n;
 };
 Parts gemm_f32_parts(axon_model* m, const void* W, const void* X, int N, int M, int K, float* out, hipStream_t s) {
-  const int ks = split_for(m, N, M, K);
+  // few tiles: as the forward pass; more, in a ragged number of rounds, by cost
+  // (the 7B-shaped step's gate/up input gradient: 182 tiles of K 37888 on 256
+  // CUs, 4 splits; the step 22.9 -> 22.1 ms)
+  int ks = split_for(m, N, M, K);
+  const int64_t fit = m->gemm_part_floats / ((int64_t)M * N);
+  if (ks == 1) ks = std::max(1, gemm_ksplit_cost(N, M, K, (int)std::min<int64_t>(fit, 4)));
   if (ks == 1) {
     gemm_many<bf16>(m, W, X, N, M, K, EPI_F32, out, nullptr, N, s, nullptr, nullptr, true);
     return {out, 1};
@@ -511,7 +517,7 @@ int prefill_split(axon_model* m, int N, int M, int K) {
 // fused kernels take.
 int decode_split(axon_model* m, int N, int M, int K) {
   const int64_t fit = m->gemm_part_floats / ((int64_t)M * N);
-  return gemm_ksplit_few(N, M, K, (int)std::min<int64_t>(fit, 8));
+  return gemm_ksplit_cost(N, M, K, (int)std::min<int64_t>(fit, 8));
 }
 
 // x += X W^T, then h = RMSNorm(x) g for ``rows`` rows (the last row of each

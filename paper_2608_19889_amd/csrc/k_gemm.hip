@@ -1021,7 +1021,7 @@ int gemm_ksplit(int N, int M, int K) {
   return nk % 2 == 0 && nk / 2 >= 8 ? 2 : 1;
 }
 
-int gemm_ksplit_few(int N, int M, int K, int max_split) {
+int gemm_ksplit_cost(int N, int M, int K, int max_split) {
   const int units = K / 32;
   int best = 1;
   int64_t least = INT64_MAX;
@@ -1029,9 +1029,9 @@ int gemm_ksplit_few(int N, int M, int K, int max_split) {
     if (units % ks || units / ks < 8) break;
     int64_t ns = 0;
     pick_tile(N, M, K, ks, &ns);
-    // partials written and read again, ~6 bytes per ns through the caches; a
-    // split saves the residual's read-modify-write in the GEMM
-    if (ks > 1) ns += (int64_t)ks * M * N * 8 / 6000;
+    // each further split writes and reads M x N floats more (~5000 bytes per
+    // ns): worth it on a long K or a small output, not on a short K
+    ns += (int64_t)(ks - 1) * M * N * 8 / 5000;
     if (ns < least) {
       least = ns;
       best = ks;

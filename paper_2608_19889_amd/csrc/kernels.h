@@ -185,10 +185,9 @@ void launch_gemm_bf16_grouped(const bf16* W, const bf16* X, int N, int K, int ma
 void launch_gemm_bf16_split(const bf16* W, const bf16* X, int N, int M, int K, int ksplit, float* part,
                             int64_t part_stride, hipStream_t s, bool xpair = false);
 int gemm_ksplit(int N, int M, int K);
-// the split of a few-token residual projection (decode batches above 64) whose
-// partials the next normalization sums: the least of GEMM time and partials'
-// traffic, at most max_split
-int gemm_ksplit_few(int N, int M, int K, int max_split);
+// the split of a GEMM whose partials the next kernel sums (decode batches above
+// 64, the backward pass): the least of its time and the partials' traffic
+int gemm_ksplit_cost(int N, int M, int K, int max_split);
 // Weight gradient dW = Y^T X over T token rows: out[r][c] = sum_t Y[t][r] X[t][c],
 // Y [T][ldy] (R <= ldy columns used, ldy % 8 == 0), X [T][C] (C % 32 == 0), both
 // row-major or (xpair) both in the row-pair layout.  The rows go to out [R][C], or
