@@ -248,14 +248,10 @@ struct TrainLayer {
 struct TrainBufs {
   bool ready = false;
   int Tc = 0, Vp = 0;
-  int SP = 0;       // positions per sequence in the attention backward's packed copies
-  int64_t W = 0;    // max_batch * SP
-  bf16 *kr, *vr, *kt, *qt, *dot;
   std::vector<TrainLayer> L;
   float *xfin, *logits, *rowloss, *valid, *lserow, *scal, *dx, *dtmp, *dgrow = nullptr, *dqf, *dsum, *colpart,
       *dkh, *dvh;
   float2* lsep;     // log-sum-exp partials of the logits rows (EPI_LSE)
-  float* statp;     // attention backward: log2-sum-exp and D in packed per-head rows [2][H][W]
   bf16 *hf, *dlog, *dxb, *dgu, *dob, *dqkv, *headT;
 };
 
@@ -1948,18 +1944,7 @@ int train_setup(axon_model* m, hipStream_t s) {
       m->gemm_part_floats = want;
     }
   }
-  tb.SP = (c.max_seq + 31) / 32 * 32 + 32;
-  tb.W = (int64_t)c.max_batch * tb.SP;
-  if (!r) r = fa(&tb.statp, 2 * H * tb.W);
-  if (!r) r = ba(&tb.kr, tb.W * KV * hd);
-  if (!r) r = ba(&tb.vr, tb.W * KV * hd);
-  if (!r) r = ba(&tb.kt, tb.W * KV * hd);
-  if (!r) r = ba(&tb.qt, tb.W * Hhd);
-  if (!r) r = ba(&tb.dot, tb.W * Hhd);
   if (r) return r;
-  // the packed copies' padding is read (masked) past each sequence's end: finite from the start
-  for (bf16* p : {tb.kr, tb.vr, tb.kt}) (void)hipMemsetAsync(p, 0, (size_t)tb.W * KV * hd * 2, s);
-  for (bf16* p : {tb.qt, tb.dot}) (void)hipMemsetAsync(p, 0, (size_t)tb.W * Hhd * 2, s);
   // W [N][K] (tiled) -> W^T [K][Np] tiled, through a row-major staging copy
   // whose columns N .. Np-1 are zero
   bf16* stage = nullptr;
@@ -2071,10 +2056,8 @@ void enqueue_train(axon_model* m, int B, int T, const int32_t* d_tokens, const i
     dW(tb.dxb, D, D, t.o, Hhd, WGRAD_ROWS, G(p + "self_attn.o_proj.weight"));
     const Parts dof = gemm_f32_parts(m, t.woT, tb.dxb, Hhd, T, D, tb.dtmp, s);
     m->timed(5, H, B, T, s, [&] {
-      if (!launch_attn_bwd(t.q, kv, t.o, dof.p, dof.n, (int64_t)T * Hhd, tb.dob, t.lse, tb.dsum, tb.statp, d_cu, h_cu,
-                           B, T, H, tb.SP, tb.W, tb.kr, tb.vr, tb.kt, tb.qt, tb.dot, tb.dqf, tb.dkh, tb.dvh, s) &&
-          m->enqueue_err.empty())
-        m->enqueue_err = "attention backward: packed layout does not fit the shape";
+      launch_attn_bwd(t.q, kv, t.o, dof.p, dof.n, (int64_t)T * Hhd, tb.dob, t.lse, tb.dsum, d_cu, h_cu, B, T, H, tb.dqf,
+                      tb.dkh, tb.dvh, s);
     });
     launch_rope_bwd(tb.dqf, tb.dkh, tb.dvh, m->rope_cos, m->rope_sin, d_cu, B, T, H, KV, hd, tb.dqkv, tb.colpart,
                     c.qkv_bias ? G(p + "self_attn.q_proj.bias") : nullptr,
@@ -2142,9 +2125,6 @@ extern "C" int axon_loss_and_grads(axon_model* m, int32_t batch, const int32_t* 
     if (!g[i]) return fail(AXON_E_MISSING, "missing gradient '" + expected[i].first + "'");
   hipStream_t s = (hipStream_t)stream;
   if (int r = train_setup(m, s)) return r;
-  if (!attn_bwd_layout_ok(m->H(), m->KVh(), m->hd(), m->train.SP, m->train.W))
-    return fail(AXON_E_INVALID, "attention backward: the packed layout needs H*hd, KV*hd, the packed width and the "
-                                "per-sequence stride to be multiples of 32 (hd 64 or 128)");
   enqueue_train(m, batch, (int)total, d_tokens, d_cu_seqlens, h_cu_seqlens, d_targets, d_loss, g, index, s);
   if (int r = check_launch("backward pass")) return r;
   if (int r = take_enqueue_err(m, "backward pass")) return r;

@@ -70,6 +70,45 @@ AXON_DEV float wave_max(float v) {
   return v;
 }
 
+// wait until at most n * PER of this wavefront's loads are in flight, n in
+// [0, MAXN] (an immediate each; a steady state passes a constant)
+template <int PER, int MAXN>
+AXON_DEV void wait_loads(int n) {
+  static_assert(PER * MAXN <= 63, "vmcnt range");
+  if constexpr (MAXN == 0) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  } else {
+    if (n >= MAXN) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(MAXN * PER) : "memory");
+    else wait_loads<PER, MAXN - 1>(n);
+  }
+}
+
+// a workgroup barrier the compiler schedules nothing across
+AXON_DEV void phase_barrier() {
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// Direct global -> LDS copy: lane L's 16 (4) bytes land at dst + 16 L (4 L)
+AXON_DEV void load_lds16(const bf16* src, bf16x8* dst) {
+  __builtin_amdgcn_global_load_lds((const void*)src, (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
+}
+AXON_DEV void load_lds4(const float* src, float* dst) {
+  __builtin_amdgcn_global_load_lds((const void*)src, (__attribute__((address_space(3))) void*)dst, 4, 0, 0);
+}
+
+// Transposing LDS reads (ds_read_tr16_b64): each group of 16 lanes reads 4 rows
+// of 16 bf16 columns, lane i of the group 4 consecutive columns 4 (i % 4) .. of
+// row i / 4 from its own address (8-byte aligned), and lane i receives column
+// i's 4 values in row order.  Two of them make an 8-value MFMA operand.
+AXON_DEV bf16x8 read_tr8(const bf16* lo_p, const bf16* hi_p) {
+  typedef __attribute__((address_space(3))) bf16x4 lds4;
+  const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds4*)lo_p);
+  const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds4*)hi_p);
+  return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+
 // Block-wide sum for blockDim.x a multiple of 64 (<= 1024); every thread gets the result.
 AXON_DEV float block_sum(float v, float* red /* >= 16 floats of shared memory */) {
   v = wave_sum(v);

@@ -227,19 +227,6 @@ AXON_DEV void tile_order(int bid, int gx, int gy, int& pn, int& pm) {
   pn = (logical % per_group) / gsize;
 }
 
-// wait until at most n * PER of this wavefront's loads are in flight, n in
-// [0, MAXN] (an immediate each; the steady state passes a constant)
-template <int PER, int MAXN>
-AXON_DEV void wait_loads(int n) {
-  static_assert(PER * MAXN <= 63, "vmcnt range");
-  if constexpr (MAXN == 0) {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  } else {
-    if (n >= MAXN) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(MAXN * PER) : "memory");
-    else wait_loads<PER, MAXN - 1>(n);
-  }
-}
-
 // ============================================================================
 // Prefill GEMM of few tiles (short prompts, decode batches above 64, narrow
 // outputs): WN x WM wavefronts, each owning AN x AM blocks of
@@ -346,11 +333,6 @@ __global__ void __launch_bounds__(64 * WN * WM) gemm_ring_kernel(const bf16* __r
         }
       }
   };
-  auto barrier = [] {
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_sched_barrier(0);
-  };
   // k-tile kt, its fragments in ``cur``: stage kt + 1 has landed (``after``
   // later stages of this wavefront's loads stay in flight) and, after the
   // barrier, every wavefront's share of it is visible and every wavefront
@@ -363,7 +345,7 @@ __global__ void __launch_bounds__(64 * WN * WM) gemm_ring_kernel(const bf16* __r
     __builtin_amdgcn_s_waitcnt(0xC07F);
     if (more) {
       wait_loads<R::LPT, S - 2>(after);
-      barrier();
+      phase_barrier();
       read_frags(kt + 1, nxt);
       if (do_issue) issue(kt + S);
       __builtin_amdgcn_sched_barrier(0);
@@ -378,7 +360,7 @@ __global__ void __launch_bounds__(64 * WN * WM) gemm_ring_kernel(const bf16* __r
   };
   Frags f0, f1;
   wait_loads<R::LPT, S - 1>(min(S - 1, nk - 1));
-  barrier();
+  phase_barrier();
   read_frags(0, f0);
   int kt = 0;
   for (; kt + 1 + S < nk; kt += 2) {  // steady state: constant arguments
@@ -447,13 +429,6 @@ AXON_DEV void wait_tiles(int after) {
   if (after >= 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * 2 * LPT) : "memory");
   else if (after == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * LPT) : "memory");
   else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-}
-
-// a workgroup barrier the compiler schedules nothing across
-AXON_DEV void phase_barrier() {
-  __builtin_amdgcn_sched_barrier(0);
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_sched_barrier(0);
 }
 
 // GROUPED: the mixture-of-experts form (EpiArgs::g_*): workgroup L takes n-tile
@@ -776,10 +751,7 @@ __global__ void __launch_bounds__(512, 1) gemm_tn_256_kernel(TnArgs g) {
   for (int b = 0; b < 2; ++b) offb[b] = frag_at(wc * 2 + b);
   // 8 token rows (ks * 16 + 8 (lane / 32) ..) of this lane's column
   auto read8 = [&](const bf16* p, int off, int ks) {
-    typedef __attribute__((address_space(3))) bf16x4 lds4;
-    const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds4*)(p + off + ks * 16 * 256));
-    const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds4*)(p + off + (ks * 16 + 4) * 256));
-    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    return read_tr8(p + off + ks * 16 * 256, p + off + (ks * 16 + 4) * 256);
   };
 
   bf16x8 fa[2][4], fb[2][2];

@@ -12,11 +12,10 @@
 // per-(query, head) log2-sum-exp: P = 2^(s sc - lse) with sc = log2(e) /
 // sqrt(hd); dP = dO V^T; dS = P (dP - D) with D = rowsum(dO O); dQ = dS K /
 // sqrt(hd); dK = dS^T Q / sqrt(hd); dV = P^T dO, all on the matrix cores.
-// One wavefront per 32-query block and head accumulates dQ over the keys; one
-// per 32-key block and query head accumulates that head's share of dK and dV
-// over the later queries, and the shares of a group's heads are summed in
-// order.  No atomics, so every gradient but the embedding's is
-// deterministic.
+// A wavefront accumulates dQ of 32 queries of a head over the keys, or one query
+// head's share of dK and dV of 32 keys over the later queries; the shares of a
+// group's heads are summed in order.  No atomics, so every gradient but the
+// embedding's is deterministic.
 #include <algorithm>
 
 #include "common.h"
@@ -116,51 +115,6 @@ __global__ void __launch_bounds__(256) ce_grad_kernel(const float* __restrict__ 
 }
 
 // ---------------------------------------------------------------- layouts
-
-// Element offset of (row c, column col) of a [C][dld] matrix stored in the
-// A-operand fragments of the attention backward's Q^T / dO^T / K^T products
-// (C and dld multiples of 32): fragment (c / 32, col / 32, kk) is 1 KB of 64
-// lanes x 8 values, lane hl * 32 + c % 32 holding the block's columns kk * 16 +
-// kap(hl, j), j = 0..7, kap(hl, j) = (j / 4) * 8 + 4 hl + j % 4 (the order of
-// the dS / P operand it multiplies), so a wavefront's fragment is one
-// contiguous read.
-AXON_DEV int64_t frag_off(int64_t c, int64_t col, int64_t dld) {
-  const int q = (int)(col & 31), kk = q >> 4, r16 = q & 15;
-  const int hl = (r16 >> 2) & 1, j = (r16 >> 3) * 4 + (r16 & 3);
-  return ((((c >> 5) * (dld >> 5) + (col >> 5)) * 2 + kk) * 64 + hl * 32 + (c & 31)) * 8 + j;
-}
-
-// dst[frag_off(c, col(t))] = src[t][c] through a 64 x 64 LDS tile, both sides
-// coalesced: col(t) = e * SP + (t - cu[e]) for t's sequence e.  C % 4 == 0, ld %
-// 4 == 0.
-__global__ void __launch_bounds__(256) transpose_tile_kernel(const bf16* __restrict__ src, int64_t ld, int T, int C,
-                                                             bf16* __restrict__ dst, int64_t dld,
-                                                             const int32_t* __restrict__ cu, int nseq, int SP) {
-  __shared__ bf16 tile[64][66];
-  const int t0 = blockIdx.x * 64, c0 = blockIdx.y * 64;
-  const int tid = threadIdx.x, ty = tid >> 4, tx = tid & 15;
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int t = t0 + ty + 16 * r, c = c0 + tx * 4;
-    bf16x4 v = {(bf16)0.f, (bf16)0.f, (bf16)0.f, (bf16)0.f};
-    if (t < T && c < C) v = *(const bf16x4*)(src + (int64_t)t * ld + c);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) tile[ty + 16 * r][tx * 4 + j] = v[j];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int c = c0 + ty + 16 * r;
-    if (c >= C) continue;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int t = t0 + tx * 4 + j;
-      if (t >= T) continue;
-      const int e = seq_of_token(cu, nseq, t);
-      dst[frag_off(c, (int64_t)e * SP + (t - cu[e]), dld)] = tile[tx * 4 + j][ty + 16 * r];
-    }
-  }
-}
 
 // dst[k][n] = W[n][k] from the fragment-tiled W [N][K]; dst rows are Np
 // apart (the caller zeroes columns N .. Np-1)
@@ -337,17 +291,12 @@ __global__ void __launch_bounds__(1024) colsum_final_kernel(const float* __restr
 // ---------------------------------------------------------------- attention
 
 // dO in bf16 from the np split-K partials of its GEMM (in order), and D[t][h] =
-// sum_d dO[t][h][d] O[t][h][d] (dO rounded; O in the row-pair layout).  D and the
-// forward's log2-sum-exp are also copied into the packed per-head rows lsep /
-// dsump [H][W] (column e*SP + position), where the 4 consecutive queries a lane
-// of the dK / dV kernel needs are one 16-byte load.  A thread takes 8 dims.
+// sum_d dO[t][h][d] O[t][h][d] (dO rounded; O in the row-pair layout).  A thread
+// takes 8 dims.
 template <int HD>
 __global__ void __launch_bounds__(256) attn_bwd_do_kernel(const float* __restrict__ dof, int np, int64_t stride,
                                                           const bf16* __restrict__ o, int T, int H,
-                                                          bf16* __restrict__ dob, float* __restrict__ dsum,
-                                                          const float* __restrict__ lse,
-                                                          const int32_t* __restrict__ cu, int nseq, int SP, int64_t W,
-                                                          float* __restrict__ lsep, float* __restrict__ dsump) {
+                                                          bf16* __restrict__ dob, float* __restrict__ dsum) {
   constexpr int LPH = HD / 8;  // lanes of a head
   const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int64_t th = min(idx / LPH, (int64_t)T * H - 1);  // past the end: the last head again, not stored
@@ -373,13 +322,7 @@ __global__ void __launch_bounds__(256) attn_bwd_do_kernel(const float* __restric
   if constexpr (LPH == 16) s += dpp_move<0x140>(s);
   if (idx / LPH >= (int64_t)T * H) return;
   *(bf16x8*)(dob + th * HD + d0) = b;
-  if (d0 == 0) {
-    dsum[th] = s;
-    const int e = seq_of_token(cu, nseq, t);
-    const int64_t c = (int64_t)h * W + (int64_t)e * SP + (t - cu[e]);
-    lsep[c] = lse[th];
-    dsump[c] = s;
-  }
+  if (d0 == 0) dsum[th] = s;
 }
 
 // ---- MFMA attention backward.  v_mfma_f32_32x32x16_bf16 with lane L, half
@@ -388,113 +331,79 @@ __global__ void __launch_bounds__(256) attn_bwd_do_kernel(const float* __restric
 // 4 hl + i%4, column c.  The accumulator of a 32 x 32 block therefore holds,
 // per lane, 16 rows of one column: taken 8 at a time (k-steps kk = 0, 1) it
 // is directly a B operand whose k slot (hl, j) stands for row kk*16 +
-// kap(hl, j), kap(hl, j) = (j/4)*8 + 4 hl + j%4, and the A operand of that
-// product reads its rows in the same order: two runs of 4 consecutive
-// positions, which the transposed copies (positions contiguous) serve as two
-// 8-byte reads.
+// (j/4)*8 + 4 hl + j%4, and the A operand of that product reads its rows in
+// the same order: two runs of 4 consecutive positions, each one transposing LDS
+// read (read_tr8).
 //
-// Packed copies, per sequence e at columns / rows e*SP + position (SP = the
-// longest sequence rounded up to 32, plus 32 positions of finite padding, so
-// a block's reads past its sequence end stay inside the sequence's range;
-// W = the packed width), every one stored in MFMA fragment order so that a
-// wavefront's operand fragment is one contiguous 1 KB read:
-//   kr, vr  K and V rows (row_frag_off: fragment = 32 positions x 16 dims)
-//   qt, dot, kt  Q^T, dO^T [H*hd][W], K^T [KV*hd][W] (frag_off)
+// Both kernels share a sequence's tiles among the 4 wavefronts of a workgroup
+// (32 queries or keys each, 128 together) through a ring of LDS stages filled by
+// direct copies: dQ streams 32-key tiles of the cache's K and V^T blocks, dK / dV
+// 32-query tiles of Q and dO rows with their statistics.  Rows, columns and both
+// transposes come from the one tile.  One wavefront per block reading packed,
+// transposed copies from L2 waited for each block's loads in turn (1B shape, 8 x
+// 512 tokens: dQ 130 us, dK / dV 136, the copies 71; now 67 and
+// 88).
 
-// Element offset of dimension d of packed row col of kv head g in kr / vr:
-// fragment (g, col / 32, d / 16) holds lane (d % 16) / 8 * 32 + col % 32,
-// values d % 8 (the A / B operand lane order of a 32-row x 16-k fragment)
-AXON_DEV int64_t row_frag_off(int64_t g, int64_t col, int d, int hd, int64_t W) {
-  return (((g * (W >> 5) + (col >> 5)) * (hd >> 4) + (d >> 4)) * 64 + ((d & 15) >> 3) * 32 + (col & 31)) * 8 + (d & 7);
-}
-
-// the layer's K / V rows from the cache into kr / vr (row e*SP + position)
-// and K^T into kt.  Workgroup = 16 positions p0 .. p0+15 of one sequence
-// (p0 % 16 == 0, blockIdx.x counts the sequences' 16-position blocks in
-// order) x one kv head: the cache's K block (positions x 8-dim chunks) and
-// V^T block (dims x 16 positions) are staged in LDS, then every output leaves
-// in 16-byte stores: 8 dims of one position (kr, vr) or 8 positions of one
-// dim (kt, in the kap order of its fragment).  Positions past the sequence
-// end are written as zeros, which is what the zero-filled padding holds.
-template <int HD>
-__global__ void __launch_bounds__(256) attn_bwd_pack_kernel(KVView kv, const int32_t* __restrict__ cu, int nseq,
-                                                            int SP, int64_t W, bf16* __restrict__ kr,
-                                                            bf16* __restrict__ vr, bf16* __restrict__ kt) {
-  __shared__ bf16 ks[16][HD + 8];  // K rows (padded: the kt gather reads a column)
-  __shared__ bf16 vs[HD][16 + 8];  // V^T rows
-  const int h = blockIdx.y, tid = threadIdx.x;
-  int e = 0, blk = blockIdx.x;
-  for (; e < nseq - 1; ++e) {
-    const int nb = (cu[e + 1] - cu[e] + 15) / 16;
-    if (blk < nb) break;
-    blk -= nb;
-  }
-  const int p0 = blk * 16, len = cu[e + 1] - cu[e];
-  const bf16 zero = (bf16)0.f;
-  // K: thread -> (position, 8-dim chunk); V^T: thread -> (dim, 8 positions)
-  for (int i = tid; i < 16 * (HD / 8); i += 256) {
-    const int pp = i / (HD / 8), d0 = (i % (HD / 8)) * 8, p = p0 + pp;
-    bf16x8 v = {zero, zero, zero, zero, zero, zero, zero, zero};
-    if (p < len) v = *(const bf16x8*)((const bf16*)kv.k + k_el(kv, e, h, p, d0));
-    *(bf16x8*)&ks[pp][d0] = v;
-  }
-  for (int i = tid; i < HD * 2; i += 256) {
-    const int d = i / 2, half = i % 2;
-    // the block's V^T row of dim d holds positions p0 .. p0+15 contiguously
-    const bf16x8 v = *(const bf16x8*)((const bf16*)kv.v + v_el(kv, e, h, min(p0, len - 1) & ~15, d) + half * 8);
-#pragma unroll
-    for (int j = 0; j < 8; ++j) vs[d][half * 8 + j] = p0 + half * 8 + j < len ? v[j] : zero;
-  }
-  __syncthreads();
-  const int64_t col0 = (int64_t)e * SP + p0;
-  for (int i = tid; i < 16 * (HD / 8); i += 256) {
-    const int pp = i / (HD / 8), d0 = (i % (HD / 8)) * 8;
-    bf16x8 vv;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) vv[j] = vs[d0 + j][pp];
-    *(bf16x8*)(kr + row_frag_off(h, col0 + pp, d0, HD, W)) = *(const bf16x8*)&ks[pp][d0];
-    *(bf16x8*)(vr + row_frag_off(h, col0 + pp, d0, HD, W)) = vv;
-  }
-  // kt: dim d, half hl of the 16 positions (kap(hl, j) = (j/4)*8 + 4 hl + j%4)
-  for (int i = tid; i < HD * 2; i += 256) {
-    const int d = i / 2, hl = i % 2;
-    bf16x8 v;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) v[j] = ks[(j / 4) * 8 + hl * 4 + j % 4][d];
-    *(bf16x8*)(kt + frag_off((int64_t)h * HD + d, col0 + hl * 4, W)) = v;
-  }
-}
-
-AXON_DEV int kap(int hl, int j) { return (j >> 2) * 8 + hl * 4 + (j & 3); }
-
-// the 32-position block blockIdx.x of the sequences in order: (sequence, first position)
-AXON_DEV void locate_block(const int32_t* __restrict__ cu, int nseq, int& e, int& p0) {
-  int blk = blockIdx.x;
+// the ``rows``-position block blk of the sequences in order: (sequence, first position)
+AXON_DEV void locate_block(const int32_t* __restrict__ cu, int nseq, int blk, int rows, int& e, int& p0) {
   for (e = 0; e < nseq - 1; ++e) {
-    const int nb = (cu[e + 1] - cu[e] + 31) / 32;
+    const int nb = (cu[e + 1] - cu[e] + rows - 1) / rows;
     if (blk < nb) break;
     blk -= nb;
   }
-  p0 = blk * 32;
+  p0 = blk * rows;
 }
 
-// dQ of 32 queries (one head): over the key blocks up to the last query,
-// S^T = K Q^T and dP^T = V dO^T (k = head dim), then dQ^T += K^T dS^T (k =
-// the block's 32 keys).  One wavefront per workgroup; no LDS.
-template <int HD>
-__global__ void __launch_bounds__(64) attn_bwd_dq_kernel(const bf16* __restrict__ q, const bf16* __restrict__ dob,
-                                                         const bf16* __restrict__ kr, const bf16* __restrict__ vr,
-                                                         const bf16* __restrict__ kt, const float* __restrict__ lse,
-                                                         const float* __restrict__ dsum,
-                                                         const int32_t* __restrict__ cu, int nseq, int H, int KVh,
-                                                         int SP, int64_t W, float* __restrict__ dq) {
+constexpr int BWD_ROWS = 128;  // queries (dQ) or keys (dK / dV) of a workgroup
+
+// dS as a bf16 pair hi + lo: a row of dS sums to zero, so dQ = dS K and dK =
+// dS^T Q cancel, and rounding dS to one bf16 would leave an error of 2^-9 of the
+// row's absolute sum times the keys' (queries') common part
+AXON_DEV void split_bf16(float v, bf16& hi, bf16& lo) {
+  hi = (bf16)v;
+  lo = (bf16)(v - (float)hi);
+}
+
+// dQ of 128 queries (one head): over the key tiles up to the last query, S^T =
+// K Q^T and dP^T = V dO^T (k = head dim), then dQ^T += K^T dS^T (k = the tile's 32
+// keys).  Workgroups of late queries (the most tiles) come first.
+template <int HD, int S>
+__global__ void __launch_bounds__(256) attn_bwd_dq_kernel(const bf16* __restrict__ q, const bf16* __restrict__ dob,
+                                                          KVView kv, const float* __restrict__ lse,
+                                                          const float* __restrict__ dsum,
+                                                          const int32_t* __restrict__ cu, int nseq, int H,
+                                                          float* __restrict__ dq) {
+  constexpr int KL = HD / 64, LPT = 2 * KL;  // copies per wavefront and tile: K, and with V
+  constexpr int PANEL = HD * 4, STAGE = 2 * PANEL;  // 16-byte chunks: 32 keys of K; K and V
+  __shared__ bf16x8 ring[S * STAGE];
   int e, q0;
-  locate_block(cu, nseq, e, q0);
-  const int h = blockIdx.y, kvh = h / (H / KVh);
-  const int tok0 = cu[e], S = cu[e + 1] - tok0;
-  const int lane = threadIdx.x, hl = lane >> 5, c = lane & 31;
-  const int myq = q0 + c;
-  const int64_t tq = tok0 + min(myq, S - 1);  // columns past the sequence read its last query (not stored)
+  locate_block(cu, nseq, gridDim.x - 1 - blockIdx.x, BWD_ROWS, e, q0);
+  const int h = blockIdx.y, KVh = kv.kv_heads, kvh = h / (H / KVh);
+  const int tok0 = cu[e], N = cu[e + 1] - tok0;
+  const int tid = threadIdx.x, lane = tid & 63, hl = lane >> 5, c = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int qw = q0 + wave * 32, myq = qw + c;
+  const bf16* ks = (const bf16*)kv.k + ((int64_t)e * KVh + kvh) * kv.ps * HD;
+  const bf16* vs = (const bf16*)kv.v + ((int64_t)e * KVh + kvh) * kv.ps * HD;
+  // keys past the sequence read its last key, V^T blocks past it its last block
+  auto issue = [&](int kt) {
+    bf16x8* base = ring + (kt % S) * STAGE;
+#pragma unroll
+    for (int j = 0; j < KL; ++j) {
+      const int i = j * 4 + wave, ch = i * 64 + lane, r = ch % (2 * HD);
+      const int key = min(kt * 32 + ch / (2 * HD) * 16 + r % 16, N - 1);
+      load_lds16(ks + (int64_t)(key >> 4) * 16 * HD + r / 16 * 128 + (key & 15) * 8, base + i * 64);
+      const int blk = min(kt * 2 + ch / (2 * HD), (N - 1) >> 4);
+      load_lds16(vs + (int64_t)blk * 16 * HD + r * 8, base + PANEL + i * 64);
+    }
+  };
+  const int nkt = (min(N, q0 + BWD_ROWS) + 31) / 32;  // tiles of the workgroup
+  const int mine = qw < N ? (min(N, qw + 32) + 31) / 32 : 0;
+#pragma unroll
+  for (int st = 0; st < S - 1; ++st)
+    if (st < nkt) issue(st);
+
+  const int64_t tq = tok0 + min(myq, N - 1);  // columns past the sequence read its last query (not stored)
   bf16x8 qf[HD / 16], df[HD / 16];
 #pragma unroll
   for (int s = 0; s < HD / 16; ++s) {
@@ -506,40 +415,49 @@ __global__ void __launch_bounds__(64) attn_bwd_dq_kernel(const bf16* __restrict_
   f32x16 acc[HD / 32];
 #pragma unroll
   for (int b = 0; b < HD / 32; ++b) acc[b] = f32x16{};
-  const int kend = min(S, q0 + 32);
-  for (int kb0 = 0; kb0 < kend; kb0 += 32) {
+  // lane offsets inside a tile (elements): K row c; V^T read, 16 keys (lane / 16)
+  // % 2 of dims 8 hl + (lane % 16) / 4; K^T read, keys 4 hl + (lane % 16) / 4 of
+  // dims 16 ((lane / 16) % 2) + 4 (lane % 4)
+  const int g16 = (lane >> 4) & 1, r4 = (lane >> 2) & 3, c4 = lane & 3;
+  const int krow = (c >> 4) * 16 * HD + hl * 128 + (c & 15) * 8;
+  const int vtr = g16 * 16 * HD + (hl * 8 + r4) * 16 + c4 * 4;
+  const int ktr = (g16 * 2 + (c4 >> 1)) * 128 + (hl * 4 + r4) * 8 + (c4 & 1) * 4;
+  for (int kt = 0; kt < nkt; ++kt) {
+    wait_loads<LPT, S - 2>(min(S - 2, nkt - 1 - kt));
+    phase_barrier();
+    if (kt + S - 1 < nkt) issue(kt + S - 1);
+    if (kt >= mine) continue;  // wave-uniform; the barriers are at the top
+    const bf16* K = (const bf16*)(ring + (kt % S) * STAGE);
+    const bf16* V = K + PANEL * 8;
     f32x16 st = {}, dpt = {};
-    const int64_t kfr = ((int64_t)kvh * (W >> 5) + (((int64_t)e * SP + kb0) >> 5)) * (HD / 16) * 512 + lane * 8;
 #pragma unroll
     for (int s = 0; s < HD / 16; ++s) {
-      st = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8*)(kr + kfr + s * 512), qf[s], st, 0, 0, 0);
-      dpt = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8*)(vr + kfr + s * 512), df[s], dpt, 0, 0, 0);
+      st = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8*)(K + krow + s * 256), qf[s], st, 0, 0, 0);
+      dpt = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_tr8(V + vtr + s * 256, V + vtr + s * 256 + 64), df[s], dpt, 0,
+                                                    0, 0);
     }
-    // dS as a bf16 pair hi + lo: a row of dS sums to zero, so dQ = dS K
-    // cancels, and rounding dS to one bf16 would leave an error of 2^-9 of
-    // the row's absolute sum times the keys' common part
     bf16x8 dsh[2], dsl[2];
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-      const int key = kb0 + (i >> 2) * 8 + hl * 4 + (i & 3);
-      const float p = (key <= myq && myq < S) ? exp2f(st[i] * sc - l2) : 0.f;
-      const float ds = p * (dpt[i] - Dq);
-      const bf16 hi = (bf16)ds;
+      const int key = kt * 32 + (i >> 2) * 8 + hl * 4 + (i & 3);
+      const float p = __builtin_amdgcn_exp2f(st[i] * sc - l2);
+      const float ds = key <= myq && myq < N ? p * (dpt[i] - Dq) : 0.f;
+      bf16 hi, lo;
+      split_bf16(ds, hi, lo);
       dsh[i >> 3][i & 7] = hi;
-      dsl[i >> 3][i & 7] = (bf16)(ds - (float)hi);
+      dsl[i >> 3][i & 7] = lo;
     }
 #pragma unroll
     for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
       for (int b = 0; b < HD / 32; ++b) {
-        const bf16x8 a =
-            *(const bf16x8*)(kt + frag_off((int64_t)kvh * HD + b * 32 + c, (int64_t)e * SP + kb0 + kk * 16, W) +
-                             hl * 256);
+        const bf16* p = K + kk * 16 * HD + b * 512 + ktr;
+        const bf16x8 a = read_tr8(p, p + 64);
         acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, dsh[kk], acc[b], 0, 0, 0);
         acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, dsl[kk], acc[b], 0, 0, 0);
       }
   }
-  if (myq >= S) return;
+  if (myq >= N) return;
   const float rs = 1.f / sqrtf((float)HD);
   float* out = dq + ((int64_t)(tok0 + myq) * H + h) * HD;
 #pragma unroll
@@ -552,34 +470,76 @@ __global__ void __launch_bounds__(64) attn_bwd_dq_kernel(const bf16* __restrict_
     }
 }
 
-// dK and dV of 32 keys from one query head h = blockIdx.y (kv head h / group):
-// over the query blocks from the key block on, S = Q K^T and dP = dO V^T (k =
-// head dim), then dV^T += dO^T P and dK^T += Q^T dS (k = the block's 32
+// dK and dV of 128 keys from one query head h = blockIdx.y (kv head h / group):
+// over the query tiles from the first key on, S = Q K^T and dP = dO V^T (k =
+// head dim), then dV^T += dO^T P and dK^T += Q^T dS (k = the tile's 32
 // queries).  Writes the head's share into dk / dv [T][H][hd] (the heads of a
 // group are summed by rope_bwd_kernel).
-template <int HD>
-__global__ void __launch_bounds__(64) attn_bwd_dkv_kernel(const bf16* __restrict__ q, const bf16* __restrict__ dob,
-                                                          const bf16* __restrict__ kr, const bf16* __restrict__ vr,
-                                                          const bf16* __restrict__ qt, const bf16* __restrict__ dot,
-                                                          const float* __restrict__ lsep,
-                                                          const float* __restrict__ dsump,
-                                                          const int32_t* __restrict__ cu, int nseq, int H, int KVh,
-                                                          int SP, int64_t W, float* __restrict__ dk,
-                                                          float* __restrict__ dv) {
-  int e, kb0;
-  locate_block(cu, nseq, e, kb0);
-  const int h = blockIdx.y, kvh = h / (H / KVh);
-  const int tok0 = cu[e], S = cu[e + 1] - tok0;
-  const int lane = threadIdx.x, hl = lane >> 5, c = lane & 31;
-  const int mykey = kb0 + c;
+template <int HD, int S>
+__global__ void __launch_bounds__(256) attn_bwd_dkv_kernel(const bf16* __restrict__ q, const bf16* __restrict__ dob,
+                                                           KVView kv, const float* __restrict__ lse,
+                                                           const float* __restrict__ dsum,
+                                                           const int32_t* __restrict__ cu, int nseq, int H,
+                                                           float* __restrict__ dk, float* __restrict__ dv) {
+  constexpr int RL = HD / 64, LPT = 2 * RL + 1;     // copies per wavefront and tile: Q rows; with dO and statistics
+  constexpr int CH = HD / 8;                        // 16-byte chunks of a row
+  constexpr int PANEL = 32 * CH, STAGE = 2 * PANEL;
+  __shared__ bf16x8 ring[S * STAGE];
+  __shared__ float stats[S][4][64];  // per wavefront (its own copy): 32 log2-sum-exp, 32 D
+  int e, k0;
+  locate_block(cu, nseq, blockIdx.x, BWD_ROWS, e, k0);
+  const int h = blockIdx.y, KVh = kv.kv_heads, kvh = h / (H / KVh);
+  const int tok0 = cu[e], N = cu[e + 1] - tok0;
+  const int tid = threadIdx.x, lane = tid & 63, hl = lane >> 5, c = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kw = k0 + wave * 32, mykey = kw + c;
+  const bf16* ks = (const bf16*)kv.k + ((int64_t)e * KVh + kvh) * kv.ps * HD;
+  const bf16* vs = (const bf16*)kv.v + ((int64_t)e * KVh + kvh) * kv.ps * HD;
+  const int g16 = (lane >> 4) & 1, r4 = (lane >> 2) & 3, c4 = lane & 3;
+
+  // this wavefront's keys as B operands: K rows from the cache, V rows through a
+  // transposing read of its V^T blocks (staged in the ring before its first use);
+  // keys past the sequence: its last key (block), not stored
   bf16x8 kf[HD / 16], vf[HD / 16];
-  // this lane's key mykey (padded rows past the sequence), fragments of 16 dims
-  const int64_t kfr = ((int64_t)kvh * (W >> 5) + (((int64_t)e * SP + kb0) >> 5)) * (HD / 16) * 512 + lane * 8;
+  {
+    static_assert(S * STAGE >= 4 * 4 * HD, "the ring holds every wavefront's V tile");
+    bf16x8* tile = ring + wave * 4 * HD;
 #pragma unroll
-  for (int s = 0; s < HD / 16; ++s) {
-    kf[s] = *(const bf16x8*)(kr + kfr + s * 512);
-    vf[s] = *(const bf16x8*)(vr + kfr + s * 512);
+    for (int j = 0; j < HD / 16; ++j) {
+      const int ch = j * 64 + lane, blk = min((kw >> 4) + ch / (2 * HD), (N - 1) >> 4);
+      load_lds16(vs + (int64_t)blk * 16 * HD + ch % (2 * HD) * 8, tile + j * 64);
+    }
+    const int key = min(mykey, N - 1);
+#pragma unroll
+    for (int s = 0; s < HD / 16; ++s)
+      kf[s] = *(const bf16x8*)(ks + (int64_t)(key >> 4) * 16 * HD + (s * 2 + hl) * 128 + (key & 15) * 8);
+    wait_loads<1, 0>(0);
+    const bf16* p = (const bf16*)tile + g16 * 16 * HD + (hl * 8 + r4) * 16 + c4 * 4;
+#pragma unroll
+    for (int s = 0; s < HD / 16; ++s) vf[s] = read_tr8(p + s * 256, p + s * 256 + 64);
+    __syncthreads();  // every V tile has been read: the ring is free
   }
+
+  // chunk c of tile row r sits at chunk c ^ key(r): 16 rows' reads of one chunk
+  // hit distinct banks
+  auto swzkey = [](int r) { return HD == 64 ? (r >> 1) & 7 : r & 15; };
+  const int qt0 = k0 / 32, nqt = (N + 31) / 32;
+  auto issue = [&](int qt) {  // rows past the sequence read its last query
+    bf16x8* base = ring + ((qt - qt0) % S) * STAGE;
+#pragma unroll
+    for (int j = 0; j < RL; ++j) {
+      const int i = j * 4 + wave, ch = i * 64 + lane, row = ch / CH, cc = ch % CH ^ swzkey(row);
+      const int64_t at = ((int64_t)(tok0 + min(qt * 32 + row, N - 1)) * H + h) * HD + cc * 8;
+      load_lds16(q + at, base + i * 64);
+      load_lds16(dob + at, base + PANEL + i * 64);
+    }
+    load_lds4((lane < 32 ? lse : dsum) + (int64_t)(tok0 + min(qt * 32 + c, N - 1)) * H + h,
+              &stats[(qt - qt0) % S][wave][0]);
+  };
+#pragma unroll
+  for (int st = 0; st < S - 1; ++st)
+    if (qt0 + st < nqt) issue(qt0 + st);
+
   const float sc = LOG2E / sqrtf((float)HD);
   f32x16 akk[HD / 32], avv[HD / 32];
 #pragma unroll
@@ -587,54 +547,58 @@ __global__ void __launch_bounds__(64) attn_bwd_dkv_kernel(const bf16* __restrict
     akk[b] = f32x16{};
     avv[b] = f32x16{};
   }
-  {
-    for (int qb0 = kb0; qb0 < S; qb0 += 32) {
-      const int64_t tq = tok0 + min(qb0 + c, S - 1);  // rows past the sequence read its last query
-      f32x16 sq = {}, dpq = {};
+  for (int qt = qt0; qt < nqt; ++qt) {
+    wait_loads<LPT, S - 2>(min(S - 2, nqt - 1 - qt));
+    phase_barrier();
+    if (qt + S - 1 < nqt) issue(qt + S - 1);
+    if (qt * 32 < kw || kw >= N) continue;  // wave-uniform; the barriers are at the top
+    const bf16* Q = (const bf16*)(ring + ((qt - qt0) % S) * STAGE);
+    const bf16* O = Q + PANEL * 8;
+    f32x16 sq = {}, dpq = {};
 #pragma unroll
-      for (int s = 0; s < HD / 16; ++s) {
-        sq = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8*)(q + (tq * H + h) * HD + s * 16 + hl * 8), kf[s],
-                                                     sq, 0, 0, 0);
-        dpq = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8*)(dob + (tq * H + h) * HD + s * 16 + hl * 8),
-                                                      vf[s], dpq, 0, 0, 0);
+    for (int s = 0; s < HD / 16; ++s) {
+      const int at = c * HD + ((s * 2 + hl) ^ swzkey(c)) * 8;
+      sq = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8*)(Q + at), kf[s], sq, 0, 0, 0);
+      dpq = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8*)(O + at), vf[s], dpq, 0, 0, 0);
+    }
+    const float* stt = &stats[(qt - qt0) % S][wave][0];
+    f32x4 lq[4], dq4[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      lq[g] = *(const f32x4*)(stt + g * 8 + hl * 4);
+      dq4[g] = *(const f32x4*)(stt + 32 + g * 8 + hl * 4);
+    }
+    // P in bf16, dS as a bf16 pair
+    bf16x8 pb[2], dsh[2], dsl[2];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int qi = qt * 32 + (i >> 2) * 8 + hl * 4 + (i & 3);
+      const bool ok = qi < N && mykey <= qi;
+      const float p = ok ? __builtin_amdgcn_exp2f(sq[i] * sc - lq[i >> 2][i & 3]) : 0.f;
+      pb[i >> 3][i & 7] = (bf16)p;
+      const float ds = ok ? p * (dpq[i] - dq4[i >> 2][i & 3]) : 0.f;
+      bf16 hi, lo;
+      split_bf16(ds, hi, lo);
+      dsh[i >> 3][i & 7] = hi;
+      dsl[i >> 3][i & 7] = lo;
+    }
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+      // rows of the transposing reads: queries kk * 16 + 4 hl + (lane % 16) / 4, + 8
+      const int r0 = kk * 16 + hl * 4 + r4, r1 = r0 + 8;
+#pragma unroll
+      for (int b = 0; b < HD / 32; ++b) {
+        const int ch = b * 4 + g16 * 2 + (c4 >> 1), sub = (c4 & 1) * 4;
+        const int a0 = r0 * HD + (ch ^ swzkey(r0)) * 8 + sub, a1 = r1 * HD + (ch ^ swzkey(r1)) * 8 + sub;
+        const bf16x8 ao = read_tr8(O + a0, O + a1);
+        const bf16x8 aq = read_tr8(Q + a0, Q + a1);
+        avv[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ao, pb[kk], avv[b], 0, 0, 0);
+        akk[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(aq, dsh[kk], akk[b], 0, 0, 0);
+        akk[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(aq, dsl[kk], akk[b], 0, 0, 0);
       }
-      // the statistics of queries qb0 + g*8 + hl*4 .. +3 (packed rows; past
-      // the sequence end they are whatever the padding holds, and unused)
-      const int64_t srow = (int64_t)h * W + (int64_t)e * SP + qb0 + hl * 4;
-      f32x4 lq[4], dq4[4];
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        lq[g] = *(const f32x4*)(lsep + srow + g * 8);
-        dq4[g] = *(const f32x4*)(dsump + srow + g * 8);
-      }
-      // P in bf16; dS as a bf16 pair hi + lo (dK = dS^T Q sums a row of dS,
-      // which sums to zero, against the queries: see the dQ kernel)
-      bf16x8 pb[2], dsh[2], dsl[2];
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int qi = qb0 + (i >> 2) * 8 + hl * 4 + (i & 3);
-        const bool ok = qi < S && mykey <= qi;
-        const float p = ok ? exp2f(sq[i] * sc - lq[i >> 2][i & 3]) : 0.f;
-        pb[i >> 3][i & 7] = (bf16)p;
-        const float ds = ok ? p * (dpq[i] - dq4[i >> 2][i & 3]) : 0.f;
-        const bf16 hi = (bf16)ds;
-        dsh[i >> 3][i & 7] = hi;
-        dsl[i >> 3][i & 7] = (bf16)(ds - (float)hi);
-      }
-#pragma unroll
-      for (int kk = 0; kk < 2; ++kk)
-#pragma unroll
-        for (int b = 0; b < HD / 32; ++b) {
-          const int64_t off = frag_off((int64_t)h * HD + b * 32 + c, (int64_t)e * SP + qb0 + kk * 16, W) + hl * 256;
-          const bf16x8 ao = *(const bf16x8*)(dot + off);
-          const bf16x8 aq = *(const bf16x8*)(qt + off);
-          avv[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ao, pb[kk], avv[b], 0, 0, 0);
-          akk[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(aq, dsh[kk], akk[b], 0, 0, 0);
-          akk[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(aq, dsl[kk], akk[b], 0, 0, 0);
-        }
     }
   }
-  if (mykey >= S) return;
+  if (mykey >= N) return;
   const float rs = 1.f / sqrtf((float)HD);
   const int64_t orow = ((int64_t)(tok0 + mykey) * H + h) * HD;
 #pragma unroll
@@ -753,46 +717,23 @@ void launch_norm_bwd(const float* x, const bf16* g, const float* dy, int np, int
   colsum_final(part, n, D, dg, D, nullptr, D, nullptr, s);
 }
 
-bool attn_bwd_layout_ok(int H, int KVh, int hd, int SP, int64_t W) {
-  // frag_off / row_frag_off cut rows, columns and packed positions into
-  // 32-wide fragments and head dimensions into 16-wide k-steps
-  return H > 0 && KVh > 0 && H % KVh == 0 && (hd == 64 || hd == 128) && SP > 0 && SP % 32 == 0 && W % 32 == 0 &&
-         ((int64_t)H * hd) % 32 == 0 && ((int64_t)KVh * hd) % 32 == 0;
-}
-
-bool launch_attn_bwd(const bf16* q, KVView kv, const bf16* o, const float* dof, int np, int64_t stride, bf16* dob,
-                     const float* lse, float* dsum, float* statp, const int32_t* cu, const int32_t* h_cu, int nseq,
-                     int T, int H, int SP, int64_t W, bf16* kr, bf16* vr, bf16* kt, bf16* qt, bf16* dot, float* dq,
-                     float* dkh, float* dvh, hipStream_t s) {
-  if (!attn_bwd_layout_ok(H, kv.kv_heads, kv.hd, SP, W)) return false;
-  if (T <= 0) return true;
-  const int KVh = kv.kv_heads, hd = kv.hd;
-  float* lsep = statp;
-  float* dsump = statp + (int64_t)H * W;
-  const unsigned nd = (unsigned)(((int64_t)T * H * hd / 8 + 255) / 256);
-  if (hd == 64)
-    attn_bwd_do_kernel<64><<<nd, 256, 0, s>>>(dof, np, stride, o, T, H, dob, dsum, lse, cu, nseq, SP, W, lsep, dsump);
-  else
-    attn_bwd_do_kernel<128><<<nd, 256, 0, s>>>(dof, np, stride, o, T, H, dob, dsum, lse, cu, nseq, SP, W, lsep, dsump);
-  int blocks16 = 0;
-  for (int e = 0; e < nseq; ++e) blocks16 += (h_cu[e + 1] - h_cu[e] + 15) / 16;
-  if (hd == 64) attn_bwd_pack_kernel<64><<<dim3(blocks16, KVh), 256, 0, s>>>(kv, cu, nseq, SP, W, kr, vr, kt);
-  else attn_bwd_pack_kernel<128><<<dim3(blocks16, KVh), 256, 0, s>>>(kv, cu, nseq, SP, W, kr, vr, kt);
-  const dim3 tg((T + 63) / 64, (H * hd + 63) / 64);
-  transpose_tile_kernel<<<tg, 256, 0, s>>>(q, (int64_t)H * hd, T, H * hd, qt, W, cu, nseq, SP);
-  transpose_tile_kernel<<<tg, 256, 0, s>>>(dob, (int64_t)H * hd, T, H * hd, dot, W, cu, nseq, SP);
+void launch_attn_bwd(const bf16* q, KVView kv, const bf16* o, const float* dof, int np, int64_t stride, bf16* dob,
+                     const float* lse, float* dsum, const int32_t* cu, const int32_t* h_cu, int nseq, int T, int H,
+                     float* dq, float* dkh, float* dvh, hipStream_t s) {
+  if (T <= 0) return;
   int blocks = 0;
-  for (int e = 0; e < nseq; ++e) blocks += (h_cu[e + 1] - h_cu[e] + 31) / 32;
-  if (hd == 64) {
-    attn_bwd_dq_kernel<64><<<dim3(blocks, H), 64, 0, s>>>(q, dob, kr, vr, kt, lse, dsum, cu, nseq, H, KVh, SP, W, dq);
-    attn_bwd_dkv_kernel<64><<<dim3(blocks, H), 64, 0, s>>>(q, dob, kr, vr, qt, dot, lsep, dsump, cu, nseq, H, KVh, SP,
-                                                           W, dkh, dvh);
+  for (int e = 0; e < nseq; ++e) blocks += (h_cu[e + 1] - h_cu[e] + BWD_ROWS - 1) / BWD_ROWS;
+  const dim3 grid(blocks, H);
+  const unsigned nd = (unsigned)(((int64_t)T * H * kv.hd / 8 + 255) / 256);
+  if (kv.hd == 64) {
+    attn_bwd_do_kernel<64><<<nd, 256, 0, s>>>(dof, np, stride, o, T, H, dob, dsum);
+    attn_bwd_dq_kernel<64, 4><<<grid, 256, 0, s>>>(q, dob, kv, lse, dsum, cu, nseq, H, dq);
+    attn_bwd_dkv_kernel<64, 4><<<grid, 256, 0, s>>>(q, dob, kv, lse, dsum, cu, nseq, H, dkh, dvh);
   } else {
-    attn_bwd_dq_kernel<128><<<dim3(blocks, H), 64, 0, s>>>(q, dob, kr, vr, kt, lse, dsum, cu, nseq, H, KVh, SP, W, dq);
-    attn_bwd_dkv_kernel<128><<<dim3(blocks, H), 64, 0, s>>>(q, dob, kr, vr, qt, dot, lsep, dsump, cu, nseq, H, KVh, SP,
-                                                            W, dkh, dvh);
+    attn_bwd_do_kernel<128><<<nd, 256, 0, s>>>(dof, np, stride, o, T, H, dob, dsum);
+    attn_bwd_dq_kernel<128, 3><<<grid, 256, 0, s>>>(q, dob, kv, lse, dsum, cu, nseq, H, dq);
+    attn_bwd_dkv_kernel<128, 3><<<grid, 256, 0, s>>>(q, dob, kv, lse, dsum, cu, nseq, H, dkh, dvh);
   }
-  return true;
 }
 
 void launch_rope_bwd(const float* dq, const float* dkh, const float* dvh, const float* cos_t, const float* sin_t,

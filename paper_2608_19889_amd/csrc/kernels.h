@@ -126,16 +126,10 @@ void launch_norm_bwd(const float* x, const bf16* g, const float* dy, int np, int
 // dq [T][H][hd] and each query head's share of dk / dv, dkh / dvh [T][H][hd]
 // (float), from q [T][H][hd] and o (row-pair layout) bf16, the gradient of o as
 // np float partials ``stride`` apart (dob [T][H][hd] receives it in bf16) and the
-// forward's log2-sum-exp lse [T][H]; dsum [T][H] scratch.  Packed copies (scratch,
-// finite at allocation): kr / vr [nseq*SP][KV][hd], kt [KV*hd][W], qt / dot
-// [H*hd][W], W >= nseq*SP, SP >= the longest sequence rounded up to 32, plus 32.
-// false (nothing launched) unless the packed fragment layouts fit the shape:
-// attn_bwd_layout_ok(H, kv heads, head_dim, SP, W)
-bool attn_bwd_layout_ok(int H, int KVh, int hd, int SP, int64_t W);
-bool launch_attn_bwd(const bf16* q, KVView kv, const bf16* o, const float* dof, int np, int64_t stride, bf16* dob,
-                     const float* lse, float* dsum, float* statp /* [2][H][W] */, const int32_t* cu,
-                     const int32_t* h_cu, int nseq, int T, int H, int SP, int64_t W, bf16* kr, bf16* vr, bf16* kt,
-                     bf16* qt, bf16* dot, float* dq, float* dkh, float* dvh, hipStream_t s);
+// forward's log2-sum-exp lse [T][H]; dsum [T][H] scratch.  head_dim 64 or 128.
+void launch_attn_bwd(const bf16* q, KVView kv, const bf16* o, const float* dof, int np, int64_t stride, bf16* dob,
+                     const float* lse, float* dsum, const int32_t* cu, const int32_t* h_cu, int nseq, int T, int H,
+                     float* dq, float* dkh, float* dvh, hipStream_t s);
 // back through RoPE into the fused QKV row order (bf16, row-pair layout), the
 // heads' shares of dk / dv summed; with dbq the bias gradients dbq / dbk / dbv too
 // (bpart: ROW_PARTS x nq floats)
