@@ -567,15 +567,23 @@ void gemv_step(axon_model* m, const GemvArgs& a, int epi, hipStream_t s) {
 void moe_routed(axon_model* m, const LayerW& w, const bf16* h, int T, hipStream_t s) {
   const axon_config& c = m->cfg;
   const int D = m->D(), E = c.n_experts, k = c.top_k, Ie = c.moe_intermediate, Ep = m->moe_ep();
+  const float* logits = m->moe_logits;
+  int nparts = 1;
   if (T <= GEMV_MAX_M) {
     GemvArgs ra{};
     ra.W = (const bf16*)w.wrouter; ra.N = Ep; ra.K = D; ra.M = T; ra.X = h;
     ra.out_f32 = m->moe_logits; ra.ldo = Ep; ra.part = m->gemv_part;
+    const int ks = gemv_shape(Ep, D, T, GV_F32).ksplit;
+    if (ks > 1) {  // the routing kernel sums the K splits' partials
+      ra.parts_only = 1;
+      logits = m->gemv_part;
+      nparts = ks;
+    }
     gemv_step(m, ra, GV_F32, s);
   } else {
     gemm_many<bf16>(m, w.wrouter, h, Ep, T, D, EPI_F32, m->moe_logits, nullptr, Ep, s);
   }
-  launch_moe_route(m->moe_logits, Ep, T, E, k, c.norm_topk_prob, m->moe_topi, m->moe_topw, s);
+  launch_moe_route(logits, nparts, (int64_t)T * Ep, Ep, T, E, k, c.norm_topk_prob, m->moe_topi, m->moe_topw, s);
   launch_moe_plan(m->moe_topi, T, E, k, m->moe_cnt, m->moe_off, m->moe_toff, m->moe_xrow, m->moe_inv, s);
   if (T <= GEMV_MAX_M) {
     GemvArgs ga{};

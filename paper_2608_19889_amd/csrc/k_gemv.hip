@@ -935,10 +935,12 @@ static bool gv_split(const GemvArgs& a, const GvShape& sh, hipStream_t s) {
   const TimingSlot t = g_timing_slot;
   g_timing_slot = TimingSlot{};
   if (t.start) {
-    hipExtLaunchKernelGGL(k1, g1, dim3(256), 0, s, t.start, nullptr, 0, a);
+    hipExtLaunchKernelGGL(k1, g1, dim3(256), 0, s, t.start, a.parts_only ? t.stop : nullptr, 0, a);
+    if (a.parts_only) return true;
     hipExtLaunchKernelGGL(k2, g2, dim3(256), 0, s, nullptr, t.stop, 0, a, sh.ksplit);
   } else {
     k1<<<g1, 256, 0, s>>>(a);
+    if (a.parts_only) return true;
     k2<<<g2, 256, 0, s>>>(a, sh.ksplit);
   }
   return true;
@@ -970,6 +972,7 @@ bool launch_gemv_fused(const GemvArgs& a, int epi, hipStream_t s) {
   // the tile order serves the unsplit one-block kernel only
   if ((a.x_tiled || a.out_tiled) && (a.M > XT_ROWS || sh.wide || sh.ksplit > 1 || epi == GV_F32)) return false;
   if (a.out_tiled && epi != GV_RESID && epi != GV_SILU) return false;
+  if (a.parts_only && (epi != GV_F32 || sh.ksplit <= 1)) return false;
   if (sh.ksplit > 1) {
     if (epi == GV_RESID) return !norm && gv_split_nb<GV_RESID, false>(a, sh, nb, s);
     if (epi == GV_ROPE) return norm ? gv_split_nb<GV_ROPE, true>(a, sh, nb, s) : gv_split_nb<GV_ROPE, false>(a, sh, nb, s);

@@ -21,61 +21,159 @@ namespace axon {
 
 constexpr int MOE_MAX_E = 256, MOE_MAX_K = 8;
 
-// one wavefront per token; lane l holds experts l, l + 64, l + 128, l + 192
-__global__ void __launch_bounds__(256) moe_route_kernel(const float* __restrict__ logits, int ldl, int T, int E,
-                                                        int k, int norm, int32_t* __restrict__ topi,
-                                                        float* __restrict__ topw) {
+// One wavefront per token; lane l holds experts l, l + 64, l + 128, l + 192.  The
+// logits are the sum of nparts partials [T][ldl] ``stride`` apart, in order (a
+// router projection split over K leaves them; 4 loads in flight per round).  A
+// round of the top k finds the largest remaining probability by register moves
+// (wave_max) and its lowest expert by ballots, expert block by block.
+__global__ void __launch_bounds__(256) moe_route_kernel(const float* __restrict__ logits, int nparts, int64_t stride,
+                                                        int ldl, int T, int E, int k, int norm,
+                                                        int32_t* __restrict__ topi, float* __restrict__ topw) {
+  constexpr int NJ = MOE_MAX_E / 64;
   const int lane = threadIdx.x & 63;
   const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (t >= T) return;  // whole wavefronts; no barrier follows
-  float p[MOE_MAX_E / 64];
+  float p[NJ];
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) p[j] = 0.f;
+  for (int s0 = 0; s0 < nparts; s0 += 4) {
+    float v[NJ][4];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+      if (64 * j < E)  // uniform
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          v[j][q] = logits[min(s0 + q, nparts - 1) * stride + (int64_t)t * ldl + min(lane + 64 * j, E - 1)];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+      if (64 * j < E)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (s0 + q < nparts) p[j] += v[j][q];
+  }
   float mx = -INFINITY;
 #pragma unroll
-  for (int j = 0; j < MOE_MAX_E / 64; ++j) {
-    const int e = lane + 64 * j;
-    p[j] = e < E ? logits[(int64_t)t * ldl + e] : -INFINITY;
+  for (int j = 0; j < NJ; ++j) {
+    if (lane + 64 * j >= E) p[j] = -INFINITY;
     mx = fmaxf(mx, p[j]);
   }
   mx = wave_max(mx);
   float sum = 0.f;
 #pragma unroll
-  for (int j = 0; j < MOE_MAX_E / 64; ++j) {
+  for (int j = 0; j < NJ; ++j) {
     p[j] = lane + 64 * j < E ? __expf(p[j] - mx) : 0.f;
     sum += p[j];
   }
   sum = wave_sum(sum);
   const float inv = 1.f / sum;
 #pragma unroll
-  for (int j = 0; j < MOE_MAX_E / 64; ++j) p[j] = lane + 64 * j < E ? p[j] * inv : -1.f;  // -1: never chosen
-  float wsel[MOE_MAX_K];
-  int isel[MOE_MAX_K];
-  float wsum = 0.f;
+  for (int j = 0; j < NJ; ++j) p[j] = lane + 64 * j < E ? p[j] * inv : -1.f;  // -1: never chosen
+  float wsel = 0.f, wsum = 0.f;  // lane c keeps choice c
+  int isel = 0;
   for (int c = 0; c < k; ++c) {
-    // the largest remaining probability, lowest expert index on ties
-    float bv = -2.f;
-    int bi = 0x7fffffff;
+    float bv = p[0];
 #pragma unroll
-    for (int j = 0; j < MOE_MAX_E / 64; ++j)
-      if (p[j] > bv) { bv = p[j]; bi = lane + 64 * j; }
+    for (int j = 1; j < NJ; ++j) bv = fmaxf(bv, p[j]);
+    bv = wave_max(bv);
+    int bi = -1;
 #pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) {
-      const float ov = __shfl_xor(bv, m, 64);
-      const int oi = __shfl_xor(bi, m, 64);
-      if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
+    for (int j = 0; j < NJ; ++j) {
+      const uint64_t hit = __ballot(p[j] == bv);
+      if (bi < 0 && hit) bi = 64 * j + __ffsll((unsigned long long)hit) - 1;
     }
-    wsel[c] = bv;
-    isel[c] = bi;
+    if (bi < 0) bi = 0x7fffffff;  // NaN logits: no expert compares equal
+    if (lane == c) {
+      wsel = bv;
+      isel = bi;
+    }
     wsum += bv;
 #pragma unroll
-    for (int j = 0; j < MOE_MAX_E / 64; ++j)
+    for (int j = 0; j < NJ; ++j)
       if (lane + 64 * j == bi) p[j] = -1.f;
   }
-  if (lane == 0) {
-    const float sc = norm ? 1.f / wsum : 1.f;
-    for (int c = 0; c < k; ++c) {
-      topi[(int64_t)t * k + c] = isel[c];
-      topw[(int64_t)t * k + c] = wsel[c] * sc;
+  if (lane < k) {
+    topi[(int64_t)t * k + lane] = isel;
+    topw[(int64_t)t * k + lane] = wsel * (norm ? 1.f / wsum : 1.f);
+  }
+}
+
+// The whole plan of at most MOE_SMALL choices (a decode step) in one workgroup:
+// counts, offsets and each choice's grouped row = off[expert] + earlier choices of
+// the same expert.  A wavefront finds the lanes of equal experts from the ballots
+// of their bits, so there is no loop over choices.  Three kernels of ~5 us each
+// were mostly launch and ramp (14 us on 32 x 6 choices; this one 4.5).
+constexpr int MOE_SMALL = 512;
+__global__ void __launch_bounds__(MOE_SMALL) moe_plan_small_kernel(const int32_t* __restrict__ topi, int n, int E, int k,
+                                                                   int32_t* __restrict__ off,
+                                                                   int32_t* __restrict__ toff,
+                                                                   int32_t* __restrict__ xrow,
+                                                                   int32_t* __restrict__ inv) {
+  constexpr int NW = MOE_SMALL / 64;
+  __shared__ int wcnt[NW][MOE_MAX_E], cnt[MOE_MAX_E], start[MOE_MAX_E + 1], tiles[MOE_MAX_E + 1];
+  const int i = threadIdx.x, lane = i & 63, wave = i >> 6;
+  for (int j = i; j < NW * MOE_MAX_E; j += MOE_SMALL) wcnt[j / MOE_MAX_E][j % MOE_MAX_E] = 0;
+  int e = i < n ? topi[i] : -1;
+  if (e < 0 || e >= E) e = -1;  // not a choice (or one of NaN logits): no row
+  __syncthreads();
+  uint64_t same = __ballot(e >= 0);
+#pragma unroll
+  for (int b = 0; b < 8; ++b) {
+    const uint64_t on = __ballot((e >> b) & 1);
+    same &= (e >> b) & 1 ? on : ~on;
+  }
+  const int before = __popcll(same & ((1ull << lane) - 1));
+  if (e >= 0 && before == 0) wcnt[wave][e] = __popcll(same);
+  __syncthreads();
+  int rank = before;
+  if (e >= 0)
+#pragma unroll
+    for (int w = 0; w < NW; ++w) rank += w < wave ? wcnt[w][e] : 0;
+  if (i < E) {
+    int c = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) c += wcnt[w][i];
+    cnt[i] = c;
+  }
+  __syncthreads();
+  if (i < 64) {  // exclusive scans over the experts, 4 per lane of the first wavefront
+    int r[4], tl[4], sr = 0, st = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int c = i * 4 + q < E ? cnt[i * 4 + q] : 0;
+      r[q] = sr;
+      tl[q] = st;
+      sr += c;
+      st += (c + 255) / 256;
     }
+    int ar = sr, at = st;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int xr = __shfl_up(ar, d, 64), xt = __shfl_up(at, d, 64);
+      if (i >= d) {
+        ar += xr;
+        at += xt;
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (i * 4 + q < E) {
+        start[i * 4 + q] = ar - sr + r[q];
+        tiles[i * 4 + q] = at - st + tl[q];
+      }
+    if (i == 63) {
+      start[E] = ar;
+      tiles[E] = at;
+    }
+  }
+  __syncthreads();
+  if (i <= E && i < MOE_SMALL) {
+    off[i] = start[i];
+    toff[i] = tiles[i];
+  }
+  if (e >= 0) {
+    const int row = start[e] + rank;
+    xrow[row] = i / k;
+    inv[i] = row;
   }
 }
 
@@ -192,15 +290,19 @@ void launch_moe_gather(const bf16* h, const int32_t* xrow, int rows, int D, bf16
   moe_gather_kernel<<<dim3((D / 8 + 255) / 256, rows), 256, 0, s>>>(h, xrow, D, out);
 }
 
-void launch_moe_route(const float* logits, int ldl, int T, int E, int k, int norm, int32_t* topi, float* topw,
-                      hipStream_t s) {
+void launch_moe_route(const float* logits, int nparts, int64_t stride, int ldl, int T, int E, int k, int norm,
+                      int32_t* topi, float* topw, hipStream_t s) {
   if (T <= 0) return;
-  moe_route_kernel<<<(T + 3) / 4, 256, 0, s>>>(logits, ldl, T, E, k, norm, topi, topw);
+  moe_route_kernel<<<(T + 3) / 4, 256, 0, s>>>(logits, nparts, stride, ldl, T, E, k, norm, topi, topw);
 }
 
 void launch_moe_plan(const int32_t* topi, int T, int E, int k, int32_t* cnt, int32_t* off, int32_t* toff,
                      int32_t* xrow, int32_t* inv, hipStream_t s) {
   const int n = T * k;
+  if (n <= MOE_SMALL) {
+    moe_plan_small_kernel<<<1, MOE_SMALL, 0, s>>>(topi, n, E, k, off, toff, xrow, inv);
+    return;
+  }
   moe_count_kernel<<<E, 256, 0, s>>>(topi, n, cnt);
   moe_scan_kernel<<<1, 64, 0, s>>>(cnt, E, off, toff);
   moe_scatter_kernel<<<E, 256, 0, s>>>(topi, n, k, off, xrow, inv);

@@ -341,8 +341,9 @@ __global__ void __launch_bounds__(256) attn_bwd_do_kernel(const float* __restric
 // 32-query tiles of Q and dO rows with their statistics.  Rows, columns and both
 // transposes come from the one tile.  One wavefront per block reading packed,
 // transposed copies from L2 waited for each block's loads in turn (1B shape, 8 x
-// 512 tokens: dQ 130 us, dK / dV 136, the copies 71; now 67 and
-// 88).
+// 512 tokens: dQ 130 us, dK / dV 136, the copies 71; now 50 and
+// 79, with launch bounds that keep the accumulators out of the second register
+// file half: 67 and 88 before).
 
 // the ``rows``-position block blk of the sequences in order: (sequence, first position)
 AXON_DEV void locate_block(const int32_t* __restrict__ cu, int nseq, int blk, int rows, int& e, int& p0) {
@@ -368,7 +369,7 @@ AXON_DEV void split_bf16(float v, bf16& hi, bf16& lo) {
 // K Q^T and dP^T = V dO^T (k = head dim), then dQ^T += K^T dS^T (k = the tile's 32
 // keys).  Workgroups of late queries (the most tiles) come first.
 template <int HD, int S>
-__global__ void __launch_bounds__(256) attn_bwd_dq_kernel(const bf16* __restrict__ q, const bf16* __restrict__ dob,
+__global__ void __launch_bounds__(256, HD == 64 ? 3 : 2) attn_bwd_dq_kernel(const bf16* __restrict__ q, const bf16* __restrict__ dob,
                                                           KVView kv, const float* __restrict__ lse,
                                                           const float* __restrict__ dsum,
                                                           const int32_t* __restrict__ cu, int nseq, int H,
@@ -476,7 +477,7 @@ __global__ void __launch_bounds__(256) attn_bwd_dq_kernel(const bf16* __restrict
 // queries).  Writes the head's share into dk / dv [T][H][hd] (the heads of a
 // group are summed by rope_bwd_kernel).
 template <int HD, int S>
-__global__ void __launch_bounds__(256) attn_bwd_dkv_kernel(const bf16* __restrict__ q, const bf16* __restrict__ dob,
+__global__ void __launch_bounds__(256, HD == 64 ? 2 : 1) attn_bwd_dkv_kernel(const bf16* __restrict__ q, const bf16* __restrict__ dob,
                                                            KVView kv, const float* __restrict__ lse,
                                                            const float* __restrict__ dsum,
                                                            const int32_t* __restrict__ cu, int nseq, int H,

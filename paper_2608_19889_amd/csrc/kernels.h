@@ -239,6 +239,9 @@ struct GemvArgs {
   const int32_t* g_off;
   const int32_t* g_xrow;
   int64_t g_wstride;
+  // GV_F32: leave the partials of a split K in ``part`` ([split][M][N]; their
+  // consumer sums them) instead of running the epilogue
+  int parts_only;
   // tile order (xt_off) of the token operands, up to 16 tokens, unsplit
   // fused projections only: x_tiled -- X is stored in it; out_tiled -- the
   // epilogue writes xg_out (GV_RESID) or out_t (GV_SILU) in it
@@ -357,10 +360,10 @@ void launch_attn_decode(const T* q, KVView kv, T* o, float* part, int32_t* cnt, 
 
 // ---- mixture of experts (k_moe.hip)
 // topi / topw [T][k]: the top_k experts of each token (E <= 256, k <= 8) from
-// float logits [T][ldl], and their softmax probabilities (over all E),
-// divided by their sum when norm
-void launch_moe_route(const float* logits, int ldl, int T, int E, int k, int norm, int32_t* topi, float* topw,
-                      hipStream_t s);
+// float logits [T][ldl] (the sum of nparts partials ``stride`` apart), and their
+// softmax probabilities (over all E), divided by their sum when norm
+void launch_moe_route(const float* logits, int nparts, int64_t stride, int ldl, int T, int E, int k, int norm,
+                      int32_t* topi, float* topw, hipStream_t s);
 // grouped-GEMM plan of the T*k choices: cnt [E], off / toff [E+1] (rows and
 // 256-row tiles before each expert), xrow [T*k] (token of each grouped row),
 // inv [T*k] (grouped row of choice t*k + j)
