@@ -41,7 +41,7 @@ struct RopeTok {
   int slot, pos;
 };
 AXON_DEV RopeTok rope_token(const EpiArgs& ep, int t) {
-  if (ep.len) return {t, ep.len[t]};
+  if (ep.len) return {ep.slot ? ep.slot[t] : t, ep.len[t]};
   const int e = seq_of_token(ep.cu, ep.nseq, t);
   return {ep.ent_slot ? ep.ent_slot[e] : e, (ep.ent_base ? ep.ent_base[e] : 0) + t - ep.cu[e]};
 }
@@ -210,6 +210,46 @@ AXON_DEV void store_lse(const EpiArgs& ep, int nb, int t, const f32x16& v0, cons
   if (lane < 32) ep.lse_part[(int64_t)t * ((N + LSE_COLS - 1) / LSE_COLS) + nb / LSE_COLS] = float2{m, s};
 }
 
+// EPI_HEAD: the largest logit of a wavefront's AN blocks of token t (rows nb ..)
+// and its lowest index, one partial per token; the logits themselves if wanted.
+template <int AN>
+AXON_DEV void store_head(const EpiArgs& ep, int nb, int t, const f32x16 (&v)[AN], int lane, int N) {
+  const int half = (lane >> 5) * 4;
+  float best = -INFINITY;
+  int bi = 0x7fffffff;
+#pragma unroll
+  for (int a = 0; a < AN; ++a)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const int n = nb + a * 32 + g * 8 + half;
+      const f32x4 o = {v[a][g * 4], v[a][g * 4 + 1], v[a][g * 4 + 2], v[a][g * 4 + 3]};
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (n + j < N && o[j] > best) {
+          best = o[j];
+          bi = n + j;
+        }
+      if (ep.out_f32 && n < N) {
+        float* p = ep.out_f32 + (int64_t)t * ep.ldo + n;
+        // rows of an odd vocabulary are not 16-byte aligned
+        if (ep.ldo % 4 == 0 && n + 4 <= N) *(f32x4*)p = o;
+        else
+          for (int j = 0; j < min(4, N - n); ++j) p[j] = o[j];
+      }
+    }
+  const float ov = lane_xor32(best);
+  const int oi = __float_as_int(lane_xor32(__int_as_float(bi)));
+  if (ov > best || (ov == best && oi < bi)) {
+    best = ov;
+    bi = oi;
+  }
+  if (lane < 32) {
+    const int64_t at = (int64_t)t * ((N + 32 * AN - 1) / (32 * AN)) + nb / (32 * AN);
+    ep.am_val[at] = best;
+    ep.am_idx[at] = bi;
+  }
+}
+
 // Workgroup -> tile: each XCD (workgroup id mod 8) receives a contiguous range
 // of tiles, walked in groups of 8 token tiles so that neighbouring tiles
 // share operand panels in that XCD's L2.
@@ -309,6 +349,28 @@ __global__ void __launch_bounds__(64 * WN * WM) gemm_ring_kernel(const bf16* __r
 #pragma unroll
     for (int b = 0; b < AM; ++b) tok[b] = rope_token(ep, min(m0 + (wm * AM + b) * 32 + (lane & 31), M - 1));
   }
+  // the token's normalization factor (few-token form), behind the same loads
+  constexpr bool NORM = !XP && (EPI == EPI_SILU || EPI == EPI_ROPE || EPI == EPI_HEAD);
+  float inv[AM];
+  if constexpr (NORM) {
+#pragma unroll
+    for (int b = 0; b < AM; ++b) {
+      inv[b] = 1.f;
+      if (ep.ss_in) {
+        const int t = min(m0 + (wm * AM + b) * 32 + (lane & 31), M - 1);
+        float ss = 0.f;
+        for (int j0 = 0; j0 < ep.ss_n; j0 += 8) {  // in order, 8 loads in flight
+          float r[8];
+#pragma unroll
+          for (int q = 0; q < 8; ++q) r[q] = ep.ss_in[(int64_t)min(j0 + q, ep.ss_n - 1) * M + t];
+#pragma unroll
+          for (int q = 0; q < 8; ++q)
+            if (j0 + q < ep.ss_n) ss += r[q];
+        }
+        inv[b] = rsqrtf(ss / (float)K + ep.eps);
+      }
+    }
+  }
 
   struct Frags {
     bf16x8 a[KU * 2][AN], b[KU * 2][AM];
@@ -375,6 +437,19 @@ __global__ void __launch_bounds__(64 * WN * WM) gemm_ring_kernel(const bf16* __r
 #pragma unroll
   for (int b = 0; b < AM; ++b) {
     const int t = m0 + (wm * AM + b) * 32 + (lane & 31);
+    if constexpr (NORM) {
+      if (ep.ss_in)
+#pragma unroll
+        for (int a = 0; a < AN; ++a) acc[a][b] *= inv[b];
+    }
+    if constexpr (EPI == EPI_HEAD) {
+      f32x16 v[AN];
+#pragma unroll
+      for (int a = 0; a < AN; ++a) v[a] = acc[a][b];
+      const int nb = n0 + wn * AN * 32;
+      if (t < M && nb < N) store_head<AN>(ep, nb, t, v, lane, N);
+      continue;
+    }
     if (t >= M) continue;
     if constexpr (EPI == EPI_LSE) {
 #pragma unroll
@@ -929,13 +1004,13 @@ struct TileCost {
 static constexpr TileCost TILE_COST[TILES] = {{256, 256, 1, 660}, {256, 128, 1, 420}, {128, 128, 1, 265},
                                               {128, 64, 1, 190},  {64, 64, 2, 120},   {32, 64, 2, 80},
                                               {32, 32, 2, 71}};
-static Tile pick_tile(int N, int M, int K, int ksplit, int64_t* ns = nullptr, bool two_blocks = false) {
+static Tile pick_tile(int N, int M, int K, int ksplit, int64_t* ns = nullptr, int first = T256x256,
+                      int end = TILES) {
   const int units = K / 32 / ksplit;
-  Tile best = T256x256;
+  Tile best = (Tile)first;
   int64_t least = INT64_MAX;
-  for (int i = 0; i < TILES; ++i) {
+  for (int i = first; i < end; ++i) {
     const TileCost& t = TILE_COST[i];
-    if (two_blocks && i >= T64x64) break;  // EPI_LSE: a wavefront owns pairs of 32-row blocks
     if (units % t.ku) continue;  // a stage is ku whole k-units
     const int64_t tiles = (int64_t)((N + t.bn - 1) / t.bn) * ((M + t.bm - 1) / t.bm) * ksplit;
     const int64_t cost = (tiles + 255) / 256 * t.ns;
@@ -952,7 +1027,8 @@ template <int EPI, bool XP>
 static void launch_tiles(const bf16* W, const bf16* X, int N, int M, int K, int ksplit, const EpiArgs& ep,
                          hipStream_t s) {
   if constexpr (EPI == EPI_LSE) {
-    switch (pick_tile(N, M, K, ksplit, nullptr, true)) {
+    // a wavefront owns pairs of 32-row blocks
+    switch (pick_tile(N, M, K, ksplit, nullptr, T256x256, T64x64)) {
       case T256x128: launch_ring_shape<EPI, XP, 4, 2, 2, 2, 1, 4>(W, X, N, M, K, ksplit, ep, s); return;
       case T128x128: launch_ring_shape<EPI, XP, 2, 2, 2, 2, 1, 4>(W, X, N, M, K, ksplit, ep, s); return;
       case T128x64: launch_ring_shape<EPI, XP, 2, 2, 2, 1, 1, 6>(W, X, N, M, K, ksplit, ep, s); return;
@@ -970,6 +1046,34 @@ static void launch_tiles(const bf16* W, const bf16* X, int N, int M, int K, int 
   }
   const int tiles = ((N + pf2::BN - 1) / pf2::BN) * ((M + pf2::BM - 1) / pf2::BM);
   klaunch(kern_256<EPI, false, XP>(), dim3(tiles, ksplit), dim3(512), pf2::LDS_BYTES, s, W, X, N, M, K, ep);
+}
+
+// The few-token form keeps to tiles of at most 64 tokens.  Against the
+// row-splitting projection kernel with its tokens staged through registers and,
+// on narrow outputs, a K split with an epilogue kernel (us, weights from HBM, 32
+// tokens): QKV 6144 x 2048 16.9 -> 9.9, shared gate/up 5632 x 2048 14.8 -> 9.3,
+// head 102400 x 2048 98 -> 84; 40 tokens: gate/up 37888 x 3584 66 -> 56.
+template <int EPI>
+static void launch_few(const bf16* W, const bf16* X, int N, int M, int K, const EpiArgs& ep, hipStream_t s) {
+  switch (pick_tile(N, M, K, 1, nullptr, T128x64)) {
+    case T64x64: launch_ring_shape<EPI, false, 2, 2, 1, 1, 2, 5>(W, X, N, M, K, 1, ep, s); return;
+    case T32x64: launch_ring_shape<EPI, false, 1, 2, 1, 1, 2, 5>(W, X, N, M, K, 1, ep, s); return;
+    case T32x32: launch_ring_shape<EPI, false, 1, 1, 1, 1, 2, 8>(W, X, N, M, K, 1, ep, s); return;
+    default: launch_ring_shape<EPI, false, 2, 2, 2, 1, 1, 6>(W, X, N, M, K, 1, ep, s); return;
+  }
+}
+
+int few_head_rows(int N, int M, int K) { return pick_tile(N, M, K, 1, nullptr, T128x64) == T128x64 ? 64 : 32; }
+
+void launch_gemm_few(const bf16* W, const bf16* X, int N, int M, int K, int epi, const EpiArgs& ep, hipStream_t s) {
+  if (M <= 0) return;
+  switch (epi) {
+    case EPI_ROPE: launch_few<EPI_ROPE>(W, X, N, M, K, ep, s); return;
+    case EPI_SILU: launch_few<EPI_SILU>(W, X, N, M, K, ep, s); return;
+    case EPI_GELU: launch_few<EPI_GELU>(W, X, N, M, K, ep, s); return;
+    case EPI_HEAD: launch_few<EPI_HEAD>(W, X, N, M, K, ep, s); return;
+    default: return;
+  }
 }
 
 void launch_gemm_bf16_split(const bf16* W, const bf16* X, int N, int M, int K, int ksplit, float* part,

@@ -416,21 +416,22 @@ __global__ void __launch_bounds__(KS * 64) gemv_fused_kernel(GemvArgs a) {
   }
 }
 
-// Projections of 17..64 tokens: the 4 wavefronts of a workgroup split the
+// Residual projections of 17..64 tokens, the router and the grouped experts: the
+// 4 wavefronts of a workgroup split the
 // output rows (16 * RB each) over the workgroup's whole K range and share the
 // token operand, which is staged through LDS in B-fragment lane order (a
 // wavefront reads 1 KB per fragment with consecutive 16-byte lanes, no bank
 // conflicts), double-buffered with one barrier per stage of U k-steps.  There
 // is no cross-wavefront reduction, so registers and LDS stay small enough for
 // several workgroups per CU (the weight stream needs many bytes in flight).
-// Same operands, K splitting (EPI == GV_PART) and epilogues as
-// gemv_fused_kernel.
+// Same K splitting (EPI == GV_PART) as gemv_fused_kernel; GV_F32 and, grouped,
+// GV_SILU epilogues.
 // GROUPED (mixture-of-experts decode, GemvArgs::g_*): expert e = blockIdx.y
 // owns rows g_off[e] .. g_off[e+1]-1 (a workgroup with none leaves at once)
 // and multiplies W + e * g_wstride; its token column c reads X row
 // g_xrow[g_off[e] + c] (row g_off[e] + c without g_xrow) and writes output
 // row g_off[e] + c.
-template <int RB, int NB, bool NORM, int EPI, int U, bool GROUPED = false>
+template <int RB, int NB, int EPI, int U, bool GROUPED = false>
 __global__ void __launch_bounds__(256) gemv_wide_kernel(GemvArgs a) {
   constexpr int NT = 256, ROWS = 64 * RB, COLS = NB * 16;
   constexpr int XCH = U * NB * 64;  // 16-byte token chunks per stage
@@ -439,8 +440,6 @@ __global__ void __launch_bounds__(256) gemv_wide_kernel(GemvArgs a) {
   constexpr int XS_FLOATS = 2 * XCH * 4, TOT_FLOATS = ROWS * (COLS + 1);
   // token stages while streaming, then the finished tile for the epilogue
   __shared__ float smem[XS_FLOATS > TOT_FLOATS ? XS_FLOATS : TOT_FLOATS];
-  __shared__ float s_ss[NT];
-  __shared__ float s_inv[64];
   bf16x8* xs = (bf16x8*)smem;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -480,23 +479,6 @@ __global__ void __launch_bounds__(256) gemv_wide_kernel(GemvArgs a) {
     xsrc[i] = a.X + xr * K + (l >> 4) * 8;
   }
   auto kstep = [&](int j) { return kb + min(j, nsteps - 1) * 32; };  // clamped: every load is unconditional
-
-  constexpr int SSR = 16;
-  float ss_reg[SSR];
-  const int ss_slices = NORM ? min(NT / M, max(1, (a.ss_n + SSR - 1) / SSR)) : 1;
-  const int ss_t = tid % M, ss_sl = tid / M;
-  if constexpr (NORM) {
-    if (wave * 64 < ss_slices * M) {
-#pragma unroll
-      for (int i = 0; i < SSR; ++i) {
-        const int j = min(ss_sl + i * ss_slices, a.ss_n - 1);
-        ss_reg[i] = a.ss_in[(int64_t)j * M + ss_t];
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < SSR; ++i) ss_reg[i] = 0.f;
-    }
-  }
 
   f32x4 acc[RB][NB];
 #pragma unroll
@@ -562,11 +544,6 @@ __global__ void __launch_bounds__(256) gemv_wide_kernel(GemvArgs a) {
     }
   }
 
-  // the prefetched sums of squares are used from here on (see GvPre)
-  if constexpr (NORM) {
-#pragma unroll
-    for (int i = 0; i < SSR; ++i) pin(ss_reg[i]);
-  }
   // finished tile -> LDS (over the token stages): tot[row][col]
   __syncthreads();
   float* tot = smem;
@@ -577,41 +554,12 @@ __global__ void __launch_bounds__(256) gemv_wide_kernel(GemvArgs a) {
 #pragma unroll
       for (int i = 0; i < 4; ++i)
         tot[((wave * RB + r) * 16 + (lane >> 4) * 4 + i) * (COLS + 1) + c * 16 + r16] = acc[r][c][i];
-  if constexpr (NORM) {
-    float ss_part = 0.f;
-    // selects, not branches: a lane-divergent branch per term costs more
-    // than the adds
-    const bool ss_own = ss_sl < ss_slices;
-#pragma unroll
-    for (int i = 0; i < SSR; ++i) ss_part += ss_own && ss_sl + i * ss_slices < a.ss_n ? ss_reg[i] : 0.f;
-    if (ss_sl < ss_slices) {
-      for (int j0 = ss_sl + SSR * ss_slices; j0 < a.ss_n; j0 += SSR * ss_slices) {
-        float v[SSR];
-#pragma unroll
-        for (int i = 0; i < SSR; ++i) v[i] = a.ss_in[(int64_t)min(j0 + i * ss_slices, a.ss_n - 1) * M + ss_t];
-#pragma unroll
-        for (int i = 0; i < SSR; ++i)
-          if (j0 + i * ss_slices < a.ss_n) ss_part += v[i];
-      }
-    }
-    s_ss[tid] = ss_part;
-  }
   __syncthreads();
-  if constexpr (NORM) {
-    if (tid < M) {
-      const float tot = ordered_sum(ss_slices, [&](int sl) { return s_ss[sl * M + tid]; });
-      s_inv[tid] = rsqrtf(tot / (float)K + a.eps);
-    }
-    __syncthreads();
-  }
   auto total = [&](int row, int col) {
-    float s = tot[row * (COLS + 1) + col];
-    if constexpr (NORM) s *= s_inv[col];
-    return s;
+    return tot[row * (COLS + 1) + col];
   };
   if constexpr (EPI == GV_PART) {
-    // partial sums of this K split (already scaled by the token's RMSNorm
-    // factor when NORM): part[split][col][n0 + row]
+    // partial sums of this K split: part[split][col][n0 + row]
     for (int it = tid; it < ROWS * M; it += NT) {
       const int row = it % ROWS, col = it / ROWS, n = n0 + row;
       if (n < a.N) a.part[((int64_t)blockIdx.y * M + col) * a.N + n] = total(row, col);
@@ -631,52 +579,6 @@ __global__ void __launch_bounds__(256) gemv_wide_kernel(GemvArgs a) {
     }
     gv_epilogue<ROWS, COLS, NT, EPI>(a, n0, tid, tot, blockIdx.x, gridDim.x, total);
   }
-}
-
-// Epilogue of a split-K projection: total = the K splits' partial sums in
-// split order (deterministic; a normalized projection's partials already
-// carry the token's RMSNorm factor), then the projection's epilogue on tiles
-// of EROWS features.
-template <int EROWS, int NB, int EPI>
-__global__ void __launch_bounds__(256) gemv_split_epilogue_kernel(GemvArgs a, int nsplit) {
-  constexpr int COLS = NB * 16, NT = 256;
-  static_assert(EROWS >= 16, "the tile doubles as the epilogue scratch");
-  // the tile's totals; the residual and head epilogues overwrite element
-  // (row, col) only after the same thread has read it, so it is also their
-  // scratch
-  __shared__ float s_tot[EROWS * (COLS + 1)];
-  const int tid = threadIdx.x, M = a.M;
-  const int n0 = blockIdx.x * EROWS;
-  // staged rows-fastest (the partials are [split][token][n]: coalesced), the
-  // splits in order; 4 splits' loads in flight per round
-  constexpr int IT = (EROWS * COLS + NT - 1) / NT;
-  const int items = EROWS * M;
-  float sum[IT];
-#pragma unroll
-  for (int j = 0; j < IT; ++j) sum[j] = 0.f;
-  for (int sp0 = 0; sp0 < nsplit; sp0 += 4) {
-    float v[IT][4];
-#pragma unroll
-    for (int j = 0; j < IT; ++j) {
-      const int it = min(tid + j * NT, items - 1);
-      const int n = min(n0 + it % EROWS, a.N - 1), c = it / EROWS;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) v[j][q] = a.part[((int64_t)min(sp0 + q, nsplit - 1) * M + c) * a.N + n];
-    }
-#pragma unroll
-    for (int j = 0; j < IT; ++j)
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        if (sp0 + q < nsplit) sum[j] += v[j][q];
-  }
-#pragma unroll
-  for (int j = 0; j < IT; ++j) {
-    const int it = tid + j * NT;
-    if (it < items) s_tot[(it % EROWS) * (COLS + 1) + it / EROWS] = sum[j];
-  }
-  __syncthreads();
-  auto total = [&](int row, int col) { return s_tot[row * (COLS + 1) + col]; };
-  gv_epilogue<EROWS, COLS, NT, EPI>(a, n0, tid, s_tot, blockIdx.x, gridDim.x, total);
 }
 
 // Residual epilogue of a split-K projection by token rows: workgroup
@@ -822,58 +724,42 @@ GvShape gemv_shape(int N, int K, int M, int epi) {
     // workgroups per 64-row block, since one CU alone streams slowly
     const int blocks = (N + 63) / 64;
     const int ksplit = std::max(1, std::min(K / 64, (32 + blocks - 1) / blocks));
-    return {64, 4, nb == 2 ? 2 : 4, ksplit, 16, 1};
-  }
-  if ((epi == GV_SILU || epi == GV_GELU) && nb >= 2 && (N + 63) / 64 < 256) {
-    // narrow gate/up (shared experts) or GELU up projection: K split towards
-    // ~512 workgroups; 32-row SiLU epilogue tiles hold 16 gate rows and their
-    // 16 up rows
-    const int blocks = (N + 63) / 64;
-    const int ksplit = std::max(2, std::min(12, (512 + blocks / 2) / blocks));
-    return {64, 4, nb == 2 ? 2 : 4, ksplit, epi == GV_SILU ? 32 : 16, 1};
+    return {64, 4, nb == 2 ? 2 : 4, ksplit, 1};
   }
   if (nb == 1) {
     // from timing every (rows, wavefronts, k-steps) candidate on weights
     // streamed from HBM, 1B- and 7B-shaped layers at 8 and 16 tokens (token
     // operands in tile order)
-    if (epi == GV_SILU) return {32, 8, 4, 1, 0};
-    if (epi == GV_GELU) return {32, 4, 4, 1, 0};
-    if (epi == GV_HEAD) return {32, 8, 4, 1, 0};
+    if (epi == GV_SILU) return {32, 8, 4, 1};
+    if (epi == GV_GELU) return {32, 4, 4, 1};
+    if (epi == GV_HEAD) return {32, 8, 4, 1};
     // QKV + RoPE: with a long K, 32-row tiles halve the token-operand reads
     // per weight byte (10.7 against 14.4 us on the 7B shape)
-    if (epi == GV_ROPE) return K >= 3072 ? GvShape{32, 8, 4, 1, 0} : GvShape{16, 16, 4, 1, 0};
-    if (N / 16 < 192) return K >= 2048 ? GvShape{8, 8, 8, 1, 0} : GvShape{8, 16, 2, 1, 0};
-    return {16, 8, 4, 1, 0};
+    if (epi == GV_ROPE) return K >= 3072 ? GvShape{32, 8, 4, 1} : GvShape{16, 16, 4, 1};
+    if (N / 16 < 192) return K >= 2048 ? GvShape{8, 8, 8, 1} : GvShape{8, 16, 2, 1};
+    return {16, 8, 4, 1};
   }
-  // 17..64 tokens: the row-splitting kernel (gemv_wide_kernel), whose token
-  // fragments are reused by 4 or 8 row blocks per workgroup.  3 token blocks
-  // need 4 k-steps per stage (the stage is split evenly over 256 threads).
-  // Shapes and split counts from timing the candidates on weights streamed
-  // from HBM (7B- and 32B-shaped layers at 32 and 64 tokens).
-  if (epi == GV_RESID || epi == GV_ROPE) {
-    // narrow projections: K split over workgroups, then a second kernel sums
-    // the splits and runs the epilogue (the residual one by token rows of
-    // 1024 features, the others on 16-row tiles).  Long K: 128-row tiles
-    // towards ~252 workgroups; short K: 64-row tiles towards ~504 (33..64
-    // tokens) or ~1008 (17..32 tokens) workgroups, which keeps enough weight
-    // bytes in flight per CU
-    const int erows = epi == GV_RESID && N % 4 == 0 ? GV_RESID_ROWS : 16;
-    const int rb = K >= 8192 ? 2 : 1;
-    const int blocks = (N + 64 * rb - 1) / (64 * rb);
-    const int target = rb == 2 ? 252 : nb >= 3 ? 504 : 1008;
-    const int ksplit = std::max(2, std::min(12, (target + blocks / 2) / blocks));
-    return {64 * rb, 4, rb == 2 || nb >= 3 ? 4 : 2, ksplit, erows, 1};
-  }
-  if (epi == GV_SILU || epi == GV_GELU) {
-    if (nb == 2) return {128, 4, 2, 1, 0, 1};
-    return {64, 4, nb == 3 ? 4 : 2, 1, 0, 1};
-  }
-  return {128, 4, nb == 4 ? 2 : 4, 1, 0, 1};  // head
+  // 17..64 tokens: the ring GEMM's few-token tiles, except the residual
+  // projections
+  if (epi != GV_RESID) return {epi == GV_HEAD ? few_head_rows(N, M, K) : 32, 0, 0, 1, 2};
+  // These split K over workgroups of the row-splitting kernel (gemv_wide_kernel),
+  // whose token fragments are reused by 4 or 8 row blocks per workgroup (3 token
+  // blocks need 4 k-steps per stage: the stage is split evenly over 256 threads);
+  // a second kernel sums the splits by token rows of 1024 features.  Shapes and
+  // split counts from timing the candidates on weights streamed from HBM (7B- and
+  // 32B-shaped layers at 32 and 64 tokens): long K 128-row tiles towards ~252
+  // workgroups; short K 64-row tiles towards ~504 (33..64 tokens) or ~1008
+  // (17..32 tokens) workgroups, which keeps enough weight bytes in flight per CU.
+  const int rb = K >= 8192 ? 2 : 1;
+  const int blocks = (N + 64 * rb - 1) / (64 * rb);
+  const int target = rb == 2 ? 252 : nb >= 3 ? 504 : 1008;
+  const int ksplit = std::max(2, std::min(12, (target + blocks / 2) / blocks));
+  return {64 * rb, 4, rb == 2 || nb >= 3 ? 4 : 2, ksplit, 1};
 }
 
 int gemv_rows(int N, int K, int M, int epi) {
   const GvShape sh = gemv_shape(N, K, M, epi);
-  return sh.ksplit > 1 ? sh.erows : sh.rows;
+  return sh.ksplit > 1 ? GV_RESID_ROWS : sh.rows;
 }
 
 int64_t gemv_workspace_floats(int N, int K, int M, int epi) {
@@ -894,73 +780,76 @@ static bool gv(const GemvArgs& a, hipStream_t s) {
   return true;
 }
 
-template <int RB, int U, int NB, bool NORM, int EPI>
-static bool gvw(const GemvArgs& a, hipStream_t s) {
-  klaunch(gemv_wide_kernel<RB, NB, NORM, EPI, U>, dim3((a.N + 64 * RB - 1) / (64 * RB)), dim3(256), 0, s, a);
-  return true;
-}
-
-// every unsplit shape gemv_shape can return, per (epilogue, normalization,
-// token blocks)
+// every one-block shape gemv_shape can return, per (epilogue, normalization)
 template <int EPI, bool NORM>
-static bool gv_dispatch(const GemvArgs& a, const GvShape& sh, int nb, hipStream_t s) {
-#define AXON_GV(R, KS_, U_, NB_) \
-  if (!sh.wide && sh.rows == R && sh.ks == KS_ && sh.u == U_ && nb == NB_) return gv<R, KS_, U_, NB_, NORM, EPI>(a, s);
-#define AXON_GVW(R, U_, NB_) \
-  if (sh.wide && sh.rows == R && sh.u == U_ && nb == NB_) return gvw<R / 64, U_, NB_, NORM, EPI>(a, s);
+static bool gv_dispatch(const GemvArgs& a, const GvShape& sh, hipStream_t s) {
+#define AXON_GV(R, KS_, U_) \
+  if (!sh.wide && sh.rows == R && sh.ks == KS_ && sh.u == U_) return gv<R, KS_, U_, 1, NORM, EPI>(a, s);
   if constexpr (EPI == GV_SILU || EPI == GV_GELU) {
-    AXON_GV(32, 4, 4, 1) AXON_GV(32, 8, 4, 1) AXON_GVW(128, 2, 2) AXON_GVW(64, 4, 3) AXON_GVW(64, 2, 4)
+    AXON_GV(32, 4, 4) AXON_GV(32, 8, 4)
   } else if constexpr (EPI == GV_HEAD) {
-    AXON_GV(32, 8, 4, 1) AXON_GVW(128, 4, 2) AXON_GVW(128, 4, 3) AXON_GVW(128, 2, 4)
+    AXON_GV(32, 8, 4)
   } else {
-    AXON_GV(8, 16, 2, 1) AXON_GV(8, 8, 8, 1) AXON_GV(16, 8, 4, 1) AXON_GV(16, 16, 4, 1) AXON_GV(32, 8, 4, 1)
+    AXON_GV(8, 16, 2) AXON_GV(8, 8, 8) AXON_GV(16, 8, 4) AXON_GV(16, 16, 4) AXON_GV(32, 8, 4)
   }
-#undef AXON_GVW
 #undef AXON_GV
   return false;
 }
 
-// split K: partial sums (grid N/rows x ksplit, normalized when NORM) then the
-// epilogue kernel; a timed launch starts its events with the first kernel
-// and stops with the second
-template <int RB, int U, int NB, bool NORM, int EPI>
+// split K: partial sums (grid N/rows x ksplit), then for the residual projections
+// their sum; a timed launch starts its events with the first kernel and stops
+// with the second
+template <int RB, int U, int NB>
 static bool gv_split(const GemvArgs& a, const GvShape& sh, hipStream_t s) {
-  auto k1 = gemv_wide_kernel<RB, NB, NORM, GV_PART, U>;
-  const bool rows = EPI == GV_RESID && sh.erows == GV_RESID_ROWS;
-  constexpr int ER = EPI == GV_SILU ? 32 : 16;  // the SiLU epilogue pairs 16 gate and 16 up rows
-  if (!rows && sh.erows != ER) return false;
-  auto k2 = rows ? gemv_split_resid_kernel : gemv_split_epilogue_kernel<ER, NB, EPI>;
+  auto k1 = gemv_wide_kernel<RB, NB, GV_PART, U>;
   const dim3 g1((a.N + 64 * RB - 1) / (64 * RB), sh.ksplit);
-  const dim3 g2 = rows ? dim3((a.N + GV_RESID_ROWS - 1) / GV_RESID_ROWS, a.M) : dim3((a.N + ER - 1) / ER);
+  const dim3 g2((a.N + GV_RESID_ROWS - 1) / GV_RESID_ROWS, a.M);
   const TimingSlot t = g_timing_slot;
   g_timing_slot = TimingSlot{};
   if (t.start) {
     hipExtLaunchKernelGGL(k1, g1, dim3(256), 0, s, t.start, a.parts_only ? t.stop : nullptr, 0, a);
     if (a.parts_only) return true;
-    hipExtLaunchKernelGGL(k2, g2, dim3(256), 0, s, nullptr, t.stop, 0, a, sh.ksplit);
+    hipExtLaunchKernelGGL(gemv_split_resid_kernel, g2, dim3(256), 0, s, nullptr, t.stop, 0, a, sh.ksplit);
   } else {
     k1<<<g1, 256, 0, s>>>(a);
     if (a.parts_only) return true;
-    k2<<<g2, 256, 0, s>>>(a, sh.ksplit);
+    gemv_split_resid_kernel<<<g2, 256, 0, s>>>(a, sh.ksplit);
   }
   return true;
 }
 
-template <int EPI, bool NORM>
 static bool gv_split_nb(const GemvArgs& a, const GvShape& sh, int nb, hipStream_t s) {
   if (!sh.wide || !a.part) return false;
 #define AXON_GVS(R, U_, NB_) \
-  if (sh.rows == R && sh.u == U_ && nb == NB_) return gv_split<R / 64, U_, NB_, NORM, EPI>(a, sh, s);
-  if constexpr (EPI == GV_F32) {
-    AXON_GVS(64, 4, 1) AXON_GVS(64, 2, 2) AXON_GVS(64, 4, 3) AXON_GVS(64, 4, 4)
-  } else if constexpr (EPI == GV_SILU || EPI == GV_GELU) {
-    AXON_GVS(64, 2, 2) AXON_GVS(64, 4, 3) AXON_GVS(64, 4, 4)
-  } else {
-    AXON_GVS(64, 2, 2) AXON_GVS(64, 4, 3) AXON_GVS(64, 4, 4)
-    AXON_GVS(128, 4, 2) AXON_GVS(128, 4, 3) AXON_GVS(128, 4, 4)
-  }
+  if (sh.rows == R && sh.u == U_ && nb == NB_) return gv_split<R / 64, U_, NB_>(a, sh, s);
+  AXON_GVS(64, 4, 1) AXON_GVS(64, 2, 2) AXON_GVS(64, 4, 3) AXON_GVS(64, 4, 4)
+  AXON_GVS(128, 4, 2) AXON_GVS(128, 4, 3) AXON_GVS(128, 4, 4)
 #undef AXON_GVS
   return false;
+}
+
+// 17..64 tokens through the ring GEMM
+static bool launch_ring_epi(const GemvArgs& a, int epi, hipStream_t s) {
+  EpiArgs e{};
+  e.ss_in = a.ss_in;
+  e.ss_n = a.ss_n;
+  e.eps = a.eps;
+  e.out_f32 = a.out_f32;
+  e.out_t = a.out_t;
+  e.ldo = a.ldo;
+  e.bias = a.bias;
+  e.cos_t = a.cos_t;
+  e.sin_t = a.sin_t;
+  e.q_out = a.q_out;
+  e.kv = a.kv;
+  e.len = a.len;
+  e.slot = a.slot;
+  e.H = a.H;
+  e.am_val = a.am_val;
+  e.am_idx = a.am_idx;
+  const int ring = epi == GV_ROPE ? EPI_ROPE : epi == GV_SILU ? EPI_SILU : epi == GV_GELU ? EPI_GELU : EPI_HEAD;
+  launch_gemm_few(a.W, a.X, a.N, a.M, a.K, ring, e, s);
+  return true;
 }
 
 bool launch_gemv_fused(const GemvArgs& a, int epi, hipStream_t s) {
@@ -973,26 +862,27 @@ bool launch_gemv_fused(const GemvArgs& a, int epi, hipStream_t s) {
   if ((a.x_tiled || a.out_tiled) && (a.M > XT_ROWS || sh.wide || sh.ksplit > 1 || epi == GV_F32)) return false;
   if (a.out_tiled && epi != GV_RESID && epi != GV_SILU) return false;
   if (a.parts_only && (epi != GV_F32 || sh.ksplit <= 1)) return false;
-  if (sh.ksplit > 1) {
-    if (epi == GV_RESID) return !norm && gv_split_nb<GV_RESID, false>(a, sh, nb, s);
-    if (epi == GV_ROPE) return norm ? gv_split_nb<GV_ROPE, true>(a, sh, nb, s) : gv_split_nb<GV_ROPE, false>(a, sh, nb, s);
-    if (epi == GV_SILU) return norm && gv_split_nb<GV_SILU, true>(a, sh, nb, s);
-    if (epi == GV_GELU) return !norm && a.bias && gv_split_nb<GV_GELU, false>(a, sh, nb, s);
-    if (epi == GV_F32) return !norm && gv_split_nb<GV_F32, false>(a, sh, nb, s);
-    return false;
+  if (sh.ksplit > 1) return !norm && gv_split_nb(a, sh, nb, s);
+  if (sh.wide == 2) {
+    // GV_SILU normalizes, GV_GELU takes a bias instead, as in the one-block forms
+    if ((epi == GV_SILU && !norm) || (epi == GV_GELU && (norm || !a.bias))) return false;
+    return launch_ring_epi(a, epi, s);
   }
   switch (epi) {
-    case GV_SILU: return norm && gv_dispatch<GV_SILU, true>(a, sh, nb, s);
-    case GV_ROPE: return norm ? gv_dispatch<GV_ROPE, true>(a, sh, nb, s) : gv_dispatch<GV_ROPE, false>(a, sh, nb, s);
-    case GV_GELU: return !norm && a.bias && gv_dispatch<GV_GELU, false>(a, sh, nb, s);
-    case GV_RESID: return !norm && gv_dispatch<GV_RESID, false>(a, sh, nb, s);
-    case GV_HEAD: return norm ? gv_dispatch<GV_HEAD, true>(a, sh, nb, s) : gv_dispatch<GV_HEAD, false>(a, sh, nb, s);
-    case GV_F32:  // float rows out (router logits): 64-row workgroups
+    case GV_SILU: return norm && gv_dispatch<GV_SILU, true>(a, sh, s);
+    case GV_ROPE: return norm ? gv_dispatch<GV_ROPE, true>(a, sh, s) : gv_dispatch<GV_ROPE, false>(a, sh, s);
+    case GV_GELU: return !norm && a.bias && gv_dispatch<GV_GELU, false>(a, sh, s);
+    case GV_RESID: return !norm && gv_dispatch<GV_RESID, false>(a, sh, s);
+    case GV_HEAD: return norm ? gv_dispatch<GV_HEAD, true>(a, sh, s) : gv_dispatch<GV_HEAD, false>(a, sh, s);
+    case GV_F32: {  // float rows out (router logits): 64-row workgroups
       if (norm) return false;
-      if (nb == 1) return gvw<1, 4, 1, false, GV_F32>(a, s);
-      if (nb == 2) return gvw<1, 2, 2, false, GV_F32>(a, s);
-      if (nb == 3) return gvw<1, 4, 3, false, GV_F32>(a, s);
-      return gvw<1, 2, 4, false, GV_F32>(a, s);
+      const dim3 grid((a.N + 63) / 64);
+      if (nb == 1) klaunch(gemv_wide_kernel<1, 1, GV_F32, 4>, grid, dim3(256), 0, s, a);
+      else if (nb == 2) klaunch(gemv_wide_kernel<1, 2, GV_F32, 2>, grid, dim3(256), 0, s, a);
+      else if (nb == 3) klaunch(gemv_wide_kernel<1, 3, GV_F32, 4>, grid, dim3(256), 0, s, a);
+      else klaunch(gemv_wide_kernel<1, 4, GV_F32, 2>, grid, dim3(256), 0, s, a);
+      return true;
+    }
     default: return false;
   }
 }
@@ -1002,7 +892,7 @@ static void grouped_launch(const GemvArgs& a, int n_experts, hipStream_t s) {
   // 64-row workgroups, 4 k-steps per stage (measured on the DeepSeek-MoE-16B
   // shape at 32 tokens: 5.48 TB/s; 2 k-steps 5.38, 128-row workgroups 5.32)
   constexpr int U = 4;
-  klaunch(gemv_wide_kernel<1, NB, false, EPI, U, true>, dim3((a.N + 63) / 64, n_experts), dim3(256), 0, s, a);
+  klaunch(gemv_wide_kernel<1, NB, EPI, U, true>, dim3((a.N + 63) / 64, n_experts), dim3(256), 0, s, a);
 }
 
 bool launch_gemv_grouped(const GemvArgs& a, int epi, int n_experts, hipStream_t s) {

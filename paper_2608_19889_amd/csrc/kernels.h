@@ -45,6 +45,8 @@ enum Epi : int {
   EPI_DGU = 7,    // acc = gradient of gated feature n; its gate/up pre-activations
                   // gu [T][2 ldo] give the gradients of both, bf16, interleaved
                   // like gu: out_t [T][2 ldo]
+  EPI_HEAD = 8,   // logits out_f32 (may be null) and, per token and 32 (or 64) columns,
+                  // the largest and its lowest index (am_val / am_idx)
   EPI_GELU = 5    // out_t[t * ldo + n] = gelu_tanh(acc + bias[n])  (GPT-2 MLP, bf16)
 };
 // EPI_F32 / EPI_RESID add EpiArgs::bias[n] to acc when it is set.
@@ -84,6 +86,15 @@ struct EpiArgs {
   // out_t of EPI_SILU / EPI_GU / EPI_DGU; 0: row-major
   int xpair;
   int opair;
+  // few-token GEMM (launch_gemm_few), EPI_SILU / EPI_ROPE / EPI_HEAD: the operand
+  // is bf16(x * g) and the result is scaled by rsqrt(sum of squares / K + eps), the
+  // sums in ss_n partials [ss_n][M]; null: no scaling
+  const float* ss_in;
+  int ss_n;
+  float eps;
+  const int32_t* slot;  // EPI_ROPE with len: the cache slot of token t (t when null)
+  float* am_val;        // EPI_HEAD: [T][ceil(N / few_head_rows)]
+  int32_t* am_idx;
   // EPI_LSE: [T][ceil(N / 64)] (largest, sum) of columns 64 i .. 64 i + 63
   float2* lse_part;
 };
@@ -167,6 +178,10 @@ void launch_set_step_lengths(const int32_t* cu, const int32_t* ent_slot, const i
 // layout (xp_off); ep.opair: the SiLU epilogue's output in that layout.
 void launch_gemm_bf16(const bf16* W, const bf16* X, int N, int M, int K, int epi, const EpiArgs& ep,
                       hipStream_t s);
+// The same GEMM for 17 .. 64 decode tokens (tiles of at most 64 tokens, row-major
+// X, K % 64 == 0): EPI_ROPE, EPI_SILU, EPI_GELU, EPI_HEAD.
+void launch_gemm_few(const bf16* W, const bf16* X, int N, int M, int K, int epi, const EpiArgs& ep, hipStream_t s);
+int few_head_rows(int N, int M, int K);  // columns per EPI_HEAD partial
 // Grouped GEMM of the experts (ep.g_*): rows of all experts together at most
 // max_rows; launches enough 256 x 256 tiles for any split of them over the
 // experts (surplus workgroups exit at once).  EPI_F32 or EPI_SILU.
@@ -252,9 +267,8 @@ constexpr int GEMV_MAX_M = 64;      // token columns one fused projection handle
 constexpr int GV_RESID_ROWS = 1024;  // features per workgroup of the split-K residual epilogue
 struct GvShape {
   int rows, ks, u;  // output rows per workgroup, wavefronts splitting K, k-steps of 32 per stage
-  int ksplit;       // workgroups splitting K (1: fused epilogue; else partials + an epilogue kernel)
-  int erows;        // rows per workgroup of the epilogue kernel (ksplit > 1)
-  int wide = 0;     // 1: gemv_wide_kernel (4 wavefronts splitting the rows, ks unused)
+  int ksplit;       // workgroups splitting K (1: fused epilogue; else partials, summed by their consumer)
+  int wide = 0;     // 1: gemv_wide_kernel (4 wavefronts splitting the rows, ks unused); 2: launch_gemm_few
 };
 // floats of GemvArgs::part a launch of this shape needs (0 when unsplit)
 int64_t gemv_workspace_floats(int N, int K, int M, int epi);
