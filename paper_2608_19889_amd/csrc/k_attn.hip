@@ -964,10 +964,14 @@ void launch_attn_decode(const T* q, KVView kv, T* o, float* part, int32_t* cnt, 
     if (kv.window) max_ctx = std::min(max_ctx, kv.window + 31);  // keys from the window's 32-key chunk
     const int nsplit = plan_decode_splits(B, kv.kv_heads, max_ctx);
     const int split_len = ((max_ctx + nsplit - 1) / nsplit + 63) / 64 * 64;
-    if (kv.hd == 64)
-      decode_launch<64, DECODE_WAVES>(q, kv, o, part, cnt, B, H, len, nsplit, split_len, s, rows, slots, o_tiled);
-    else
-      decode_launch<128, DECODE_WAVES>(q, kv, o, part, cnt, B, H, len, nsplit, split_len, s, rows, slots, o_tiled);
+    // more workgroups than CUs: 4 wavefronts each, two workgroups to a CU, so that
+    // one's loads run under the other's merge (us with 8 / 4 wavefronts: 160
+    // sequences x 8 kv heads of ~100 keys 12.8 / 11.0, 80 x 4 of ~650 28.9 / 27.1,
+    // 64 x 8 of 1500 39.8 / 39.2); up to one per CU 8 are faster (above)
+    const bool many = (int64_t)nsplit * B * kv.kv_heads > 256;
+    auto go = [&](auto launch) { launch(q, kv, o, part, cnt, B, H, len, nsplit, split_len, s, rows, slots, o_tiled); };
+    if (kv.hd == 64) many ? go(decode_launch<64, DECODE_WAVES / 2>) : go(decode_launch<64, DECODE_WAVES>);
+    else many ? go(decode_launch<128, DECODE_WAVES / 2>) : go(decode_launch<128, DECODE_WAVES>);
   }
 }
 

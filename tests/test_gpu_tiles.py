@@ -55,16 +55,18 @@ def test_every_tile_shape_gives_the_same_bits_and_the_oracles_logits(case):
 # decode batches above 64: the residual projections' K splits (the partials are
 # summed by the next normalization) and the argmax over several column chunks;
 # widths, K of even and odd unit counts, an odd vocabulary past two chunks
+# (and, head dimension 128, decode attention of more workgroups than CUs)
 WIDE = {
-    "split_deep": (66, dict(layers=2, vocab=9001, hidden=512, intermediate=8192)),
-    "odd_units": (129, dict(layers=2, vocab=4097, hidden=576, intermediate=1088)),
+    "split_deep": (66, "1b", dict(layers=2, vocab=9001, hidden=512, intermediate=8192)),
+    "odd_units": (129, "1b", dict(layers=2, vocab=4097, hidden=576, intermediate=1088)),
+    "hd128_bias": (70, "7b", dict(layers=2, vocab=1000, hidden=512, intermediate=1024)),
 }
 
 
 @pytest.mark.parametrize("case", list(WIDE))
 def test_decode_above_64_sequences(case):
-    B, ov = WIDE[case]
-    shape = small_shape("1b", **ov)
+    B, base, ov = WIDE[case]
+    shape = small_shape(base, **ov)
     w = model_weights(shape, seed=43)
     V = shape["vocab_size"]
     ids = prompts(B, 6, V, seed=44).numpy()
@@ -78,3 +80,24 @@ def test_decode_above_64_sequences(case):
     m.close()
     check_bf16(got, exact, b16, f"decode above 64 {case}", absolute=False)
     np.testing.assert_array_equal(toks.T, got.argmax(-1))
+
+
+def test_split_decode_attention_of_many_workgroups():
+    """33 sequences x 8 kv heads x 2 key splits: more workgroups than CUs (the
+    4-wavefront form), contexts that end inside either split; the first and the
+    last sequence against the oracle."""
+    lens = [1700 if b in (0, 32) else 3 + b for b in range(33)]
+    shape = small_shape("1b", layers=2, vocab=1000, hidden=512, intermediate=1024)
+    w = model_weights(shape, seed=45)
+    ids = prompts(33, 1702, shape["vocab_size"], seed=46).numpy()
+    seqs, forced = [ids[b, :n] for b, n in enumerate(lens)], ids[:, 1700:1702]
+    m = gpu_model(shape, w, max_batch=33, max_seq=3100)
+    got, _ = run_teacher_forced(m, seqs, forced)
+    m.close()
+    pick = [0, 32]
+    w64 = oracle.weights_f64(w)
+    part = [seqs[b] for b in pick]
+    exact = oracle.teacher_forced(oracle.OracleDecoder(shape, w64), part, forced[pick])
+    b16 = oracle.teacher_forced(oracle.OracleDecoder(shape, w64, io_round="bf16"), part, forced[pick])
+    check_bf16(got[:, pick], exact, b16, "split decode attention", absolute=False)
+    assert np.all(np.isfinite(got))
