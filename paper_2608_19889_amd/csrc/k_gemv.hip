@@ -734,8 +734,12 @@ GvShape gemv_shape(int N, int K, int M, int epi) {
     if (epi == GV_GELU) return {32, 4, 4, 1};
     if (epi == GV_HEAD) return {32, 8, 4, 1};
     // QKV + RoPE: with a long K, 32-row tiles halve the token-operand reads
-    // per weight byte (10.7 against 14.4 us on the 7B shape)
-    if (epi == GV_ROPE) return K >= 3072 ? GvShape{32, 8, 4, 1} : GvShape{16, 16, 4, 1};
+    // per weight byte (10.7 against 14.4 us on the 7B shape).  16 wavefronts fill
+    // a CU's registers: past 256 row blocks a second round of workgroups would
+    // start, where 8 wavefronts leave room for two workgroups (4800 x 1600, 8
+    // tokens: 8.6 against 7.9 us)
+    if (epi == GV_ROPE)
+      return K >= 3072 ? GvShape{32, 8, 4, 1} : N > 16 * 256 ? GvShape{16, 8, 4, 1} : GvShape{16, 16, 4, 1};
     if (N / 16 < 192) return K >= 2048 ? GvShape{8, 8, 8, 1} : GvShape{8, 16, 2, 1};
     return {16, 8, 4, 1};
   }
