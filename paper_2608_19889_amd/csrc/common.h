@@ -83,11 +83,14 @@ AXON_DEV void wait_loads(int n) {
   }
 }
 
-// a workgroup barrier the compiler schedules nothing across
+// a workgroup barrier the compiler moves no memory access or instruction across
+// (the caller has waited for what must be visible)
 AXON_DEV void phase_barrier() {
+  asm volatile("" ::: "memory");
   __builtin_amdgcn_sched_barrier(0);
   __builtin_amdgcn_s_barrier();
   __builtin_amdgcn_sched_barrier(0);
+  asm volatile("" ::: "memory");
 }
 
 // Direct global -> LDS copy: lane L's 16 (4) bytes land at dst + 16 L (4 L)
