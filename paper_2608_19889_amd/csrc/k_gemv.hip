@@ -205,13 +205,9 @@ __global__ void __launch_bounds__(KS * 64) gemv_fused_kernel(GemvArgs a) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n0 = blockIdx.x * ROWS;
   const int K = a.K, M = a.M;
-  // K range of the workgroup (split K: split blockIdx.y of gridDim.y, each a
-  // multiple of 32), divided among the KS wavefronts in whole stages
-  const int klen = EPI == GV_PART ? ((K + gridDim.y - 1) / gridDim.y + 31) / 32 * 32 : K;
-  const int kbase = EPI == GV_PART ? min(K, (int)blockIdx.y * klen) : 0;
-  const int kloc = min(K - kbase, klen);
-  const int kc = ((kloc + KS - 1) / KS + 32 * U - 1) / (32 * U) * (32 * U);
-  const int k0 = kbase + min(kloc, wave * kc), k1 = kbase + min(kloc, wave * kc + kc);
+  // K divided among the KS wavefronts in whole stages
+  const int kc = ((K + KS - 1) / KS + 32 * U - 1) / (32 * U) * (32 * U);
+  const int k0 = min(K, wave * kc), k1 = min(K, wave * kc + kc);
   const int r16 = lane & 15;
 
   // Every load below is unconditional (a load under a lane condition makes
@@ -402,18 +398,10 @@ __global__ void __launch_bounds__(KS * 64) gemv_fused_kernel(GemvArgs a) {
     return s;
   };
 
-  if constexpr (EPI == GV_PART) {
-    // raw tile sums of this K split: part[split][col][n0 + row]
-    for (int it = tid; it < ROWS * COLS; it += NT) {
-      const int row = it % ROWS, col = it / ROWS, n = n0 + row;
-      if (col < M && n < a.N) a.part[((int64_t)blockIdx.y * M + col) * a.N + n] = total(row, col);
-    }
-  } else {
-    // the residual and head epilogues overwrite element (row, col) of their
-    // scratch only after the same thread has read total(row, col): the first
-    // wavefront's tile serves as that scratch
-    gv_epilogue<ROWS, COLS, NT, EPI, PRE>(a, n0, tid, &red[0][0][0], blockIdx.x, gridDim.x, total, pre);
-  }
+  // the residual and head epilogues overwrite element (row, col) of their
+  // scratch only after the same thread has read total(row, col): the first
+  // wavefront's tile serves as that scratch
+  gv_epilogue<ROWS, COLS, NT, EPI, PRE>(a, n0, tid, &red[0][0][0], blockIdx.x, gridDim.x, total, pre);
 }
 
 // Residual projections of 17..64 tokens, the router and the grouped experts: the
@@ -424,8 +412,8 @@ __global__ void __launch_bounds__(KS * 64) gemv_fused_kernel(GemvArgs a) {
 // conflicts), double-buffered with one barrier per stage of U k-steps.  There
 // is no cross-wavefront reduction, so registers and LDS stay small enough for
 // several workgroups per CU (the weight stream needs many bytes in flight).
-// Same K splitting (EPI == GV_PART) as gemv_fused_kernel; GV_F32 and, grouped,
-// GV_SILU epilogues.
+// Epilogues: GV_PART (K split blockIdx.y of gridDim.y, each a multiple of 32, its
+// raw sums to part[split]), GV_F32 and, grouped, GV_SILU.
 // GROUPED (mixture-of-experts decode, GemvArgs::g_*): expert e = blockIdx.y
 // owns rows g_off[e] .. g_off[e+1]-1 (a workgroup with none leaves at once)
 // and multiplies W + e * g_wstride; its token column c reads X row
