@@ -12,6 +12,7 @@
 #include <functional>
 #include <map>
 #include <mutex>
+#include <set>
 #include <string>
 #include <tuple>
 #include <unordered_map>
@@ -62,6 +63,22 @@ void scratch_of_current_device(void** ptr, std::string* err) {
   }
   *ptr = it->second.first;
   *err = it->second.second;
+}
+
+// The projection kernels' LDS limits, raised once per device by the first
+// axon_init_model there.
+std::mutex g_limits_mu;
+std::set<int> g_limits_devices;
+
+hipError_t init_current_device() {
+  int dev = -1;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  std::lock_guard<std::mutex> lk(g_limits_mu);
+  if (g_limits_devices.count(dev)) return hipSuccess;
+  e = gemm_init_device();
+  if (e == hipSuccess) g_limits_devices.insert(dev);
+  return e;
 }
 
 int fail(int code, const std::string& msg) {
@@ -1215,6 +1232,7 @@ extern "C" int axon_init_model(const axon_config* cfg, const axon_weight* weight
     }
   } stage;
   if (m->bf) {
+    HTRY(init_current_device());
     const int64_t Ie = c.moe_intermediate, Is = (int64_t)c.n_shared_experts * Ie;
     const int64_t most = std::max({V * D, nq * D, D * H * hd, 2 * I * D, 2 * Ie * D, 2 * Is * D,
                                    (int64_t)m->moe_ep() * D});

@@ -6,10 +6,41 @@
 // the MFMA A operand (rows = output features) and X as the B operand (columns
 // = tokens): every lane's operand fragment is 8 consecutive k values, one
 // 16-byte load, from either operand.
+#include <vector>
+
 #include "common.h"
 #include "kernels.h"
 
 namespace axon {
+
+// Kernels that take more dynamic LDS than the runtime grants by itself (64 KB)
+// need their limit raised on every device that runs them.  Each instance a
+// launcher refers to enters itself here when the library is loaded, and
+// gemm_init_device raises all limits on the current device, so that no launch --
+// under capture, in a step that must not allocate, from several threads, on a
+// second device -- depends on an earlier one.
+struct LdsKernel {
+  const void* kern;
+  int bytes;
+};
+static std::vector<LdsKernel>& lds_kernels() {
+  static std::vector<LdsKernel> v;
+  return v;
+}
+template <auto KERN, int BYTES>
+struct LdsLimit {
+  static const bool entered;
+};
+template <auto KERN, int BYTES>
+const bool LdsLimit<KERN, BYTES>::entered = (lds_kernels().push_back({(const void*)KERN, BYTES}), true);
+
+hipError_t gemm_init_device() {
+  for (const LdsKernel& k : lds_kernels()) {
+    const hipError_t e = hipFuncSetAttribute(k.kern, hipFuncAttributeMaxDynamicSharedMemorySize, k.bytes);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
 
 AXON_DEV float silu_f(float z) { return z / (1.f + __expf(-z)); }
 
@@ -913,12 +944,8 @@ __global__ void __launch_bounds__(256) wgrad_sum_kernel(TnArgs g, const float* _
 
 template <int MODE, bool XP>
 static void launch_tn(TnArgs g, float* part, int64_t part_floats, hipStream_t s) {
-  static bool attr = false;
   auto kern = gemm_tn_256_kernel<MODE, XP>;
-  if (!attr) {
-    (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, pf2::LDS_BYTES);
-    attr = true;
-  }
+  (void)LdsLimit<gemm_tn_256_kernel<MODE, XP>, pf2::LDS_BYTES>::entered;
   const int tiles = ((g.R + 255) / 256) * ((g.C + 255) / 256), nkt = (g.T + 31) / 32;
   // few tiles: split the tokens towards 256 workgroups, at least 16 k-tiles each
   int ks = 1;
@@ -951,16 +978,11 @@ void launch_wgrad(int mode, const bf16* Y, int ldy, int R, const bf16* X, int C,
 #undef AXON_TN
 }
 
-// the 256 x 256 kernel instance, its LDS size raised at first use
+// the 256 x 256 kernel instance
 template <int EPI, bool GROUPED, bool XP>
 static auto kern_256() {
-  static bool attr = false;
-  auto kern = gemm_bf16_256_kernel<EPI, GROUPED, XP>;
-  if (!attr) {
-    (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, pf2::LDS_BYTES);
-    attr = true;
-  }
-  return kern;
+  (void)LdsLimit<gemm_bf16_256_kernel<EPI, GROUPED, XP>, pf2::LDS_BYTES>::entered;
+  return gemm_bf16_256_kernel<EPI, GROUPED, XP>;
 }
 
 template <int EPI>
@@ -972,17 +994,13 @@ static void launch_grouped(const bf16* W, const bf16* X, int N, int K, int max_r
   klaunch(kern_256<EPI, true, false>(), dim3((unsigned)tiles), dim3(512), pf2::LDS_BYTES, s, W, X, N, 0, K, ep);
 }
 
-// one ring kernel instance, its LDS size raised at first use
+// one ring kernel instance
 template <int EPI, bool XP, int WN, int WM, int AN, int AM, int KU, int S>
 static void launch_ring_shape(const bf16* W, const bf16* X, int N, int M, int K, int ksplit, const EpiArgs& ep,
                               hipStream_t s) {
   using R = RingShape<WN, WM, AN, AM, KU, S>;
-  static bool attr = false;
   auto kern = gemm_ring_kernel<EPI, XP, WN, WM, AN, AM, KU, S>;
-  if (!attr) {
-    (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, R::LDS_BYTES);
-    attr = true;
-  }
+  (void)LdsLimit<gemm_ring_kernel<EPI, XP, WN, WM, AN, AM, KU, S>, R::LDS_BYTES>::entered;
   const int tiles = ((N + R::BN - 1) / R::BN) * ((M + R::BM - 1) / R::BM);
   klaunch(kern, dim3(tiles, ksplit), dim3(64 * R::NW), R::LDS_BYTES, s, W, X, N, M, K, ep);
 }

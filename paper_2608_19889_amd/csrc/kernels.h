@@ -173,6 +173,9 @@ void launch_set_step_lengths(const int32_t* cu, const int32_t* ent_slot, const i
                              int n, hipStream_t s);
 
 // ---- projections (k_gemm.hip)
+// Raises the dynamic LDS limits of the kernels below on the current device; once
+// per device, before any of them is launched there.
+hipError_t gemm_init_device();
 // Many-token GEMM (prefill): bf16 MFMA tiles.  Requires K % 64 == 0, N % 32 == 0
 // (EPI_ROPE: the head dimension a multiple of 32).  ep.xpair: X in the row-pair
 // layout (xp_off); ep.opair: the SiLU epilogue's output in that layout.

@@ -1,0 +1,302 @@
+// A recording stand-in for the HIP runtime, for tests of what the library's
+// host code does without a GPU: memory is address space only, copies do
+// nothing, and every launch is written to stdout, one event a line:
+//   launch <device> <capture 0/1> <lds bytes> <start event> <stop event> <gx> <gy> <kernel>
+//   limit <device> <capture 0/1> <lds bytes> <kernel>     (dynamic LDS limit raised)
+//   alloc <base> <bytes> / fill <base> <bytes>            (hipMalloc / hipMemset)
+//   mark <text>                                            (a step of the scenario)
+// The executable's definitions come before libamdhip64's for libaxon.so too.
+// Usage: recorded_hip <scenario>.
+#include <cxxabi.h>
+#include <stdio.h>
+#include <stdlib.h>
+#include <string.h>
+
+#include <algorithm>
+#include <map>
+#include <string>
+#include <vector>
+
+#include "axon.h"
+#include "kernels.h"
+
+namespace {
+
+int g_device = 0, g_capture = 0;
+uint64_t g_next = 1ull << 40, g_event = 1;
+
+std::map<const void*, std::string>& names() {
+  static std::map<const void*, std::string> n;
+  return n;
+}
+
+const char* name_of(const void* f) {
+  auto it = names().find(f);
+  return it == names().end() ? "?" : it->second.c_str();
+}
+
+void* reserve(size_t bytes) {
+  void* p = (void*)g_next;
+  g_next += (bytes + 4095) / 4096 * 4096;
+  printf("alloc %llu %zu\n", (unsigned long long)p, bytes);
+  return p;
+}
+
+void launched(const void* f, dim3 grid, size_t lds, hipEvent_t a, hipEvent_t b) {
+  printf("launch %d %d %zu %llu %llu %u %u %s\n", g_device, g_capture, lds, (unsigned long long)a,
+         (unsigned long long)b, grid.x, grid.y, name_of(f));
+}
+
+struct Call {
+  dim3 grid, block;
+  size_t lds;
+  hipStream_t s;
+} g_call;
+
+}  // namespace
+
+extern "C" {
+void** __hipRegisterFatBinary(const void*) {
+  static void* handle;
+  return &handle;
+}
+void __hipUnregisterFatBinary(void**) {}
+void __hipRegisterFunction(void**, const void* host, char*, const char* dev, unsigned, void*, void*, void*, void*,
+                           int*) {
+  int st = 0;
+  char* d = abi::__cxa_demangle(dev, nullptr, nullptr, &st);
+  std::string n = st == 0 ? d : dev;
+  free(d);
+  names()[host] = n;
+}
+void __hipRegisterVar(void**, void*, char*, char*, int, size_t, int, int) {}
+hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t lds, hipStream_t s) {
+  g_call = {g, b, lds, s};
+  return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* lds, hipStream_t* s) {
+  *g = g_call.grid;
+  *b = g_call.block;
+  *lds = g_call.lds;
+  *s = g_call.s;
+  return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void* f, dim3 g, dim3, void**, size_t lds, hipStream_t) {
+  launched(f, g, lds, nullptr, nullptr);
+  return hipSuccess;
+}
+hipError_t hipExtLaunchKernel(const void* f, dim3 g, dim3, void**, size_t lds, hipStream_t, hipEvent_t a, hipEvent_t b,
+                              int) {
+  launched(f, g, lds, a, b);
+  return hipSuccess;
+}
+hipError_t hipFuncSetAttribute(const void* f, hipFuncAttribute, int bytes) {
+  printf("limit %d %d %d %s\n", g_device, g_capture, bytes, name_of(f));
+  return hipSuccess;
+}
+hipError_t hipMalloc(void** p, size_t n) {
+  *p = reserve(n);
+  return hipSuccess;
+}
+hipError_t hipFree(void*) { return hipSuccess; }
+hipError_t hipHostMalloc(void** p, size_t n, unsigned) {
+  *p = calloc(1, n);
+  return hipSuccess;
+}
+hipError_t hipHostFree(void* p) {
+  free(p);
+  return hipSuccess;
+}
+hipError_t hipMemcpy(void*, const void*, size_t, hipMemcpyKind) { return hipSuccess; }
+hipError_t hipMemcpyAsync(void*, const void*, size_t, hipMemcpyKind, hipStream_t) { return hipSuccess; }
+hipError_t hipMemcpy2DAsync(void*, size_t, const void*, size_t, size_t, size_t, hipMemcpyKind, hipStream_t) {
+  return hipSuccess;
+}
+hipError_t hipMemsetAsync(void* p, int, size_t n, hipStream_t) {
+  printf("fill %llu %zu\n", (unsigned long long)p, n);
+  return hipSuccess;
+}
+hipError_t hipGetDevice(int* d) {
+  *d = g_device;
+  return hipSuccess;
+}
+hipError_t hipGetLastError(void) { return hipSuccess; }
+const char* hipGetErrorString(hipError_t) { return "recorded"; }
+hipError_t hipGetSymbolAddress(void** p, const void*) {
+  *p = reserve(AXON_NOALLOC_SCRATCH_BYTES);
+  return hipSuccess;
+}
+hipError_t hipEventCreate(hipEvent_t* e) {
+  *e = (hipEvent_t)g_event++;
+  return hipSuccess;
+}
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return hipEventCreate(e); }
+hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) {
+  *ms = 0.f;
+  return hipSuccess;
+}
+hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) {
+  *s = (hipStream_t)1;
+  return hipSuccess;
+}
+hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) {
+  g_capture = 1;
+  return hipSuccess;
+}
+hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t* g) {
+  g_capture = 0;
+  *g = (hipGraph_t)1;
+  return hipSuccess;
+}
+hipError_t hipGraphInstantiate(hipGraphExec_t* e, hipGraph_t, hipGraphNode_t*, char*, size_t) {
+  *e = (hipGraphExec_t)1;
+  return hipSuccess;
+}
+hipError_t hipGraphDestroy(hipGraph_t) { return hipSuccess; }
+hipError_t hipGraphExecDestroy(hipGraphExec_t) { return hipSuccess; }
+hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t) { return hipSuccess; }
+}
+
+namespace {
+
+void mark(const std::string& what) { printf("mark %s\n", what.c_str()); }
+
+void check(int rc, const char* what) {
+  if (rc < 0) {
+    printf("error %s: %s\n", what, axon_last_error());
+    exit(1);
+  }
+}
+
+axon_config llama(int D, int H, int KV, int hd, int I, int V) {
+  axon_config c;
+  memset(&c, 0, sizeof(c));
+  c.hidden = D;
+  c.n_layers = 1;
+  c.n_heads = H;
+  c.n_kv_heads = KV;
+  c.head_dim = hd;
+  c.intermediate = I;
+  c.vocab = V;
+  c.rms_eps = 1e-5f;
+  c.rope_theta = 1e4;
+  c.tie_embeddings = 1;
+  c.dtype = AXON_BF16;
+  return c;
+}
+
+// the weight map of a one-layer model (tied head), as device pointers
+struct Map {
+  std::vector<std::string> names;
+  std::vector<axon_weight> w;
+  Map(const axon_config& c, int dtype) {
+    const int64_t D = c.hidden, H = c.n_heads, KV = c.n_kv_heads, hd = c.head_dim, I = c.intermediate;
+    const std::string p = "model.layers.0.";
+    std::vector<std::pair<std::string, std::pair<int64_t, int64_t>>> l = {
+        {"model.embed_tokens.weight", {c.vocab, D}},
+        {"model.norm.weight", {D, 0}},
+        {p + "input_layernorm.weight", {D, 0}},
+        {p + "post_attention_layernorm.weight", {D, 0}},
+        {p + "self_attn.q_proj.weight", {H * hd, D}},
+        {p + "self_attn.k_proj.weight", {KV * hd, D}},
+        {p + "self_attn.v_proj.weight", {KV * hd, D}},
+        {p + "self_attn.o_proj.weight", {D, H * hd}}};
+    if (c.qkv_bias)
+      for (auto& b : {std::make_pair("q", H), std::make_pair("k", KV), std::make_pair("v", KV)})
+        l.push_back({p + "self_attn." + b.first + "_proj.bias", {b.second * hd, 0}});
+    auto mlp = [&](const std::string& q, int64_t ii) {
+      l.push_back({q + "gate_proj.weight", {ii, D}});
+      l.push_back({q + "up_proj.weight", {ii, D}});
+      l.push_back({q + "down_proj.weight", {D, ii}});
+    };
+    if (c.n_experts > 0) {
+      l.push_back({p + "mlp.gate.weight", {c.n_experts, D}});
+      for (int e = 0; e < c.n_experts; ++e) mlp(p + "mlp.experts." + std::to_string(e) + ".", c.moe_intermediate);
+    } else {
+      mlp(p + "mlp.", I);
+    }
+    for (auto& x : l) names.push_back(x.first);
+    for (size_t i = 0; i < l.size(); ++i) {
+      axon_weight a;
+      memset(&a, 0, sizeof(a));
+      a.name = names[i].c_str();
+      a.data = (void*)(uintptr_t)0x10000;
+      a.dtype = dtype;
+      a.ndim = l[i].second.second ? 2 : 1;
+      a.shape[0] = l[i].second.first;
+      a.shape[1] = l[i].second.second;
+      a.on_device = 1;
+      w.push_back(a);
+    }
+  }
+};
+
+axon_model* make(const axon_config& c) {
+  Map m(c, c.dtype);
+  axon_model* out = nullptr;
+  check(axon_init_model(&c, m.w.data(), (int)m.w.size(), nullptr, &out), "axon_init_model");
+  return out;
+}
+
+int32_t* const TOK = (int32_t*)(uintptr_t)0x20000;
+float* const LOGITS = (float*)(uintptr_t)0x30000;
+
+void prefill(axon_model* m, int batch, int len, int all = 0) {
+  std::vector<int32_t> cu;
+  for (int b = 0; b <= batch; ++b) cu.push_back(b * len);
+  check(axon_prefill(m, batch, TOK, TOK, cu.data(), nullptr, 0, all, LOGITS, TOK, nullptr), "axon_prefill");
+}
+
+void train(axon_model* m, const axon_config& c, int batch, int len) {
+  Map g(c, AXON_F32);
+  std::vector<int32_t> cu;
+  for (int b = 0; b <= batch; ++b) cu.push_back(b * len);
+  check(axon_loss_and_grads(m, batch, TOK, TOK, cu.data(), TOK, LOGITS, g.w.data(), (int)g.w.size(), nullptr),
+        "axon_loss_and_grads");
+}
+
+// calls of many sizes on two devices, one after the other in this process
+void two_devices() {
+  for (int d = 0; d < 2; ++d) {
+    g_device = d;
+    mark("device " + std::to_string(d));
+    axon_config c = llama(1024, 16, 4, 64, 4096, 20000);
+    c.max_batch = 160;
+    c.max_seq = 2048;
+    c.max_tokens = 8192;
+    axon_model* m = make(c);
+    mark("ready");
+    for (int len : {1, 20, 70, 200, 700, 2000}) prefill(m, 4, len);
+    prefill(m, 2, 300, 1);
+    for (int b : {8, 24, 40, 64, 160}) {
+      prefill(m, b, 16);
+      mark("decode " + std::to_string(b));
+      check(axon_decode_step(m, b, TOK, LOGITS, TOK, nullptr), "axon_decode_step");
+      if (b <= 64) {
+        mark("noalloc " + std::to_string(b));
+        check(axon_decode_step_noalloc(m, b, TOK, LOGITS, TOK, nullptr), "axon_decode_step_noalloc");
+      }
+    }
+    for (int len : {40, 500, 2000}) {
+      mark("train " + std::to_string(len));
+      train(m, c, 4, len);
+    }
+    axon_free(m);
+  }
+}
+
+}  // namespace
+
+int main(int argc, char** argv) {
+  setvbuf(stdout, nullptr, _IOFBF, 1 << 20);
+  const std::string s = argc > 1 ? argv[1] : "";
+  if (s == "two_devices") two_devices();
+  else return 2;
+  printf("done\n");
+  return 0;
+}

@@ -1,0 +1,70 @@
+"""What the library's host code launches, without a GPU: tests/recorded_hip.cpp
+stands in for the HIP runtime, drives the C ABI through one scenario per run
+and writes every launch, allocation and attribute call down."""
+import os
+import subprocess
+from collections import namedtuple
+
+import pytest
+
+from paper_2608_19889_amd import axon, build
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+Launch = namedtuple("Launch", "device capture lds start stop gx gy kernel")
+Limit = namedtuple("Limit", "device capture lds kernel")
+
+
+@pytest.fixture(scope="session")
+def recorder(tmp_path_factory):
+    """scenario name -> its events: Launch and Limit tuples, and (kind, ...) tuples."""
+    axon.lib()
+    exe = str(tmp_path_factory.mktemp("recorded") / "recorded_hip")
+    pkg = os.path.dirname(axon.LIB_PATH)
+    subprocess.run([build.HIPCC, *[f for f in build.FLAGS if f not in ("-O3", "-fPIC")], "--offload-host-only", "-x",
+                    "hip", os.path.join(HERE, "recorded_hip.cpp"), "-rdynamic", "-o", exe, "-L" + pkg,
+                    "-l:" + os.path.basename(axon.LIB_PATH), "-Wl,-rpath," + pkg],
+                   check=True, capture_output=True, text=True)
+    done = {}
+
+    def run(scenario):
+        if scenario not in done:
+            r = subprocess.run([exe, scenario], capture_output=True, text=True, timeout=60)
+            assert r.returncode == 0 and r.stdout.endswith("done\n"), r.stdout[-500:] + r.stderr[-500:]
+            done[scenario] = [_event(line) for line in r.stdout.splitlines()[:-1]]
+        return done[scenario]
+    return run
+
+
+def _event(line):
+    f = line.split(" ")
+    if f[0] == "launch":
+        return Launch(*map(int, f[1:8]), " ".join(f[8:]))
+    if f[0] == "limit":
+        return Limit(*map(int, f[1:4]), " ".join(f[4:]))
+    if f[0] == "mark":
+        return ("mark", line[5:])
+    return (f[0], *map(int, f[1:]))
+
+
+DEFAULT_LDS = 64 << 10  # dynamic LDS that a kernel may take without a raised limit
+
+
+def test_lds_limits_are_raised_on_every_device_before_any_launch(recorder):
+    """Two devices in one process: a kernel of more than 64 KB of dynamic LDS is
+    launched only where its limit was raised on that device, and no call after
+    axon_init_model (a graph's capture, the no-allocation step) raises one."""
+    limits, large, step = {}, set(), ""
+    for e in recorder("two_devices"):
+        if isinstance(e, Limit):
+            assert not e.capture and step.startswith("device"), (step, e)
+            limits[e.device, e.kernel] = e.lds
+        elif isinstance(e, Launch) and e.lds > DEFAULT_LDS:
+            assert e.lds <= limits.get((e.device, e.kernel), DEFAULT_LDS), (step, e)
+            large.add((e.device, e.kernel))
+        elif e[0] == "mark":
+            step = e[1]
+    assert {d for d, _ in large} == {0, 1}
+    assert {k for d, k in large if d == 0} == {k for d, k in large if d == 1}
+    # the scenario reaches the 256-tile, ring, few-token and weight-gradient forms
+    for part in ("gemm_bf16_256_kernel<", "gemm_ring_kernel<8", "gemm_ring_kernel<2", "gemm_tn_256_kernel<"):
+        assert any(part in k for _, k in large), part
