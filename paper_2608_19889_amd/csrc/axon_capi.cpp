@@ -589,14 +589,10 @@ void moe_routed(axon_model* m, const LayerW& w, const bf16* h, int T, hipStream_
   if (T <= GEMV_MAX_M) {
     GemvArgs ra{};
     ra.W = (const bf16*)w.wrouter; ra.N = Ep; ra.K = D; ra.M = T; ra.X = h;
-    ra.out_f32 = m->moe_logits; ra.ldo = Ep; ra.part = m->gemv_part;
-    const int ks = gemv_shape(Ep, D, T, GV_F32).ksplit;
-    if (ks > 1) {  // the routing kernel sums the K splits' partials
-      ra.parts_only = 1;
-      logits = m->gemv_part;
-      nparts = ks;
-    }
-    gemv_step(m, ra, GV_F32, s);
+    ra.part = m->gemv_part;
+    gemv_step(m, ra, GV_PART, s);
+    logits = m->gemv_part;  // the routing kernel sums the K splits' partials
+    nparts = gemv_shape(Ep, D, T, GV_PART).ksplit;
   } else {
     gemm_many<bf16>(m, w.wrouter, h, Ep, T, D, EPI_F32, m->moe_logits, nullptr, Ep, s);
   }
@@ -1498,7 +1494,7 @@ extern "C" int axon_init_model(const axon_config* cfg, const axon_weight* weight
                         gemv_workspace_floats(2 * (int)I, (int)D, b, GV_SILU),
                         gemv_workspace_floats((int)I, (int)D, b, GV_GELU),
                         gemv_workspace_floats((int)D, (int)I, b, GV_RESID)});
-        if (m->moe_model()) wsf = std::max(wsf, gemv_workspace_floats(m->moe_ep(), (int)D, b, GV_F32));
+        if (m->moe_model()) wsf = std::max(wsf, gemv_workspace_floats(m->moe_ep(), (int)D, b, GV_PART));
         if (Is > 0)
           wsf = std::max({wsf, gemv_workspace_floats(2 * Is, (int)D, b, GV_SILU),
                           gemv_workspace_floats((int)D, Is, b, GV_RESID)});

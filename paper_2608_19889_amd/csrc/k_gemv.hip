@@ -152,11 +152,6 @@ AXON_DEV void gv_epilogue(const GemvArgs& a, int n0, int tid, float* aux, int wg
         vc[v_el(a.kv, sl, kvh, pos, i + half)] = (bf16)x2;
       }
     }
-  } else if constexpr (EPI == GV_F32) {
-    for (int it = tid; it < ROWS * M; it += NT) {
-      const int row = it % ROWS, col = it / ROWS, n = n0 + row;
-      if (n < a.N) a.out_f32[(int64_t)col * a.ldo + n] = total(row, col);
-    }
   } else {  // GV_HEAD
     for (int it = tid; it < ROWS * M; it += NT) {
       const int row = it % ROWS, col = it / ROWS, n = n0 + row;
@@ -405,15 +400,15 @@ __global__ void __launch_bounds__(KS * 64) gemv_fused_kernel(GemvArgs a) {
 }
 
 // Residual projections of 17..64 tokens, the router and the grouped experts: the
-// 4 wavefronts of a workgroup split the
-// output rows (16 * RB each) over the workgroup's whole K range and share the
-// token operand, which is staged through LDS in B-fragment lane order (a
-// wavefront reads 1 KB per fragment with consecutive 16-byte lanes, no bank
-// conflicts), double-buffered with one barrier per stage of U k-steps.  There
-// is no cross-wavefront reduction, so registers and LDS stay small enough for
-// several workgroups per CU (the weight stream needs many bytes in flight).
-// Epilogues: GV_PART (K split blockIdx.y of gridDim.y, each a multiple of 32, its
-// raw sums to part[split]), GV_F32 and, grouped, GV_SILU.
+// 4 wavefronts of a workgroup split the output rows (16 * RB each) over the
+// workgroup's whole K range and share the token operand, which is staged through
+// LDS in B-fragment lane order (a wavefront reads 1 KB per fragment with
+// consecutive 16-byte lanes, no bank conflicts), double-buffered with one barrier
+// per stage of U k-steps.  There is no cross-wavefront reduction, so registers and
+// LDS stay small enough for several workgroups per CU (the weight stream needs
+// many bytes in flight).  Epilogues: ungrouped, GV_PART (K split blockIdx.y of
+// gridDim.y, each a multiple of 32, its raw sums to part[split]); grouped, GV_F32
+// and GV_SILU.
 // GROUPED (mixture-of-experts decode, GemvArgs::g_*): expert e = blockIdx.y
 // owns rows g_off[e] .. g_off[e+1]-1 (a workgroup with none leaves at once)
 // and multiplies W + e * g_wstride; its token column c reads X row
@@ -422,6 +417,7 @@ __global__ void __launch_bounds__(KS * 64) gemv_fused_kernel(GemvArgs a) {
 template <int RB, int NB, int EPI, int U, bool GROUPED = false>
 __global__ void __launch_bounds__(256) gemv_wide_kernel(GemvArgs a) {
   constexpr int NT = 256, ROWS = 64 * RB, COLS = NB * 16;
+  static_assert(GROUPED ? EPI == GV_F32 || EPI == GV_SILU : EPI == GV_PART, "the epilogues below");
   constexpr int XCH = U * NB * 64;  // 16-byte token chunks per stage
   static_assert(XCH % NT == 0, "stage must split evenly over the threads");
   constexpr int XPT = XCH / NT;
@@ -558,13 +554,8 @@ __global__ void __launch_bounds__(256) gemv_wide_kernel(GemvArgs a) {
       if (n < a.N) a.out_f32[(int64_t)(r0 + col) * a.ldo + n] = total(row, col);
     }
   } else {
-    // the residual and head epilogues overwrite element (row, col) of their
-    // scratch only after the same thread has read total(row, col): the tile
-    // itself serves as that scratch
-    if constexpr (GROUPED) {
-      a.M = M;
-      a.out_t += (int64_t)r0 * a.ldo;
-    }
+    a.M = M;
+    a.out_t += (int64_t)r0 * a.ldo;
     gv_epilogue<ROWS, COLS, NT, EPI>(a, n0, tid, tot, blockIdx.x, gridDim.x, total);
   }
 }
@@ -707,9 +698,9 @@ __global__ void __launch_bounds__(256) embed_ss_kernel(const int32_t* __restrict
 GvShape gemv_shape(int N, int K, int M, int epi) {
   N = std::max(N, 1);
   const int nb = (M + 15) / 16;
-  if (epi == GV_F32) {
-    // float rows (a router's tens of logits): K split over up to 32
-    // workgroups per 64-row block, since one CU alone streams slowly
+  if (epi == GV_PART) {
+    // a router's tens of logits: K split over up to 32 workgroups per 64-row
+    // block, since one CU alone streams slowly
     const int blocks = (N + 63) / 64;
     const int ksplit = std::max(1, std::min(K / 64, (32 + blocks - 1) / blocks));
     return {64, 4, nb == 2 ? 2 : 4, ksplit, 1};
@@ -756,7 +747,7 @@ int gemv_rows(int N, int K, int M, int epi) {
 
 int64_t gemv_workspace_floats(int N, int K, int M, int epi) {
   const GvShape sh = gemv_shape(N, K, M, epi);
-  return sh.ksplit > 1 ? (int64_t)sh.ksplit * M * N : 0;
+  return sh.ksplit > 1 || epi == GV_PART ? (int64_t)sh.ksplit * M * N : 0;
 }
 
 template <int ROWS, int KS, int U, int NB, bool NORM, int EPI>
@@ -788,32 +779,32 @@ static bool gv_dispatch(const GemvArgs& a, const GvShape& sh, hipStream_t s) {
   return false;
 }
 
-// split K: partial sums (grid N/rows x ksplit), then for the residual projections
-// their sum; a timed launch starts its events with the first kernel and stops
-// with the second
+// split K: partial sums (grid N/rows x ksplit), then, with resid, their sum into
+// the residual rows; a timed launch starts its events with the first kernel and
+// stops with the last
 template <int RB, int U, int NB>
-static bool gv_split(const GemvArgs& a, const GvShape& sh, hipStream_t s) {
+static bool gv_split(const GemvArgs& a, const GvShape& sh, bool resid, hipStream_t s) {
   auto k1 = gemv_wide_kernel<RB, NB, GV_PART, U>;
   const dim3 g1((a.N + 64 * RB - 1) / (64 * RB), sh.ksplit);
   const dim3 g2((a.N + GV_RESID_ROWS - 1) / GV_RESID_ROWS, a.M);
   const TimingSlot t = g_timing_slot;
   g_timing_slot = TimingSlot{};
   if (t.start) {
-    hipExtLaunchKernelGGL(k1, g1, dim3(256), 0, s, t.start, a.parts_only ? t.stop : nullptr, 0, a);
-    if (a.parts_only) return true;
+    hipExtLaunchKernelGGL(k1, g1, dim3(256), 0, s, t.start, resid ? nullptr : t.stop, 0, a);
+    if (!resid) return true;
     hipExtLaunchKernelGGL(gemv_split_resid_kernel, g2, dim3(256), 0, s, nullptr, t.stop, 0, a, sh.ksplit);
   } else {
     k1<<<g1, 256, 0, s>>>(a);
-    if (a.parts_only) return true;
+    if (!resid) return true;
     gemv_split_resid_kernel<<<g2, 256, 0, s>>>(a, sh.ksplit);
   }
   return true;
 }
 
-static bool gv_split_nb(const GemvArgs& a, const GvShape& sh, int nb, hipStream_t s) {
-  if (!sh.wide || !a.part) return false;
+static bool gv_split_nb(const GemvArgs& a, const GvShape& sh, int nb, bool resid, hipStream_t s) {
+  if (sh.wide != 1 || !a.part) return false;
 #define AXON_GVS(R, U_, NB_) \
-  if (sh.rows == R && sh.u == U_ && nb == NB_) return gv_split<R / 64, U_, NB_>(a, sh, s);
+  if (sh.rows == R && sh.u == U_ && nb == NB_) return gv_split<R / 64, U_, NB_>(a, sh, resid, s);
   AXON_GVS(64, 4, 1) AXON_GVS(64, 2, 2) AXON_GVS(64, 4, 3) AXON_GVS(64, 4, 4)
   AXON_GVS(128, 4, 2) AXON_GVS(128, 4, 3) AXON_GVS(128, 4, 4)
 #undef AXON_GVS
@@ -851,10 +842,11 @@ bool launch_gemv_fused(const GemvArgs& a, int epi, hipStream_t s) {
   const int nb = (a.M + 15) / 16;
   const bool norm = a.ss_in != nullptr;
   // the tile order serves the unsplit one-block kernel only
-  if ((a.x_tiled || a.out_tiled) && (a.M > XT_ROWS || sh.wide || sh.ksplit > 1 || epi == GV_F32)) return false;
+  if ((a.x_tiled || a.out_tiled) && (a.M > XT_ROWS || sh.wide || sh.ksplit > 1)) return false;
   if (a.out_tiled && epi != GV_RESID && epi != GV_SILU) return false;
-  if (a.parts_only && (epi != GV_F32 || sh.ksplit <= 1)) return false;
-  if (sh.ksplit > 1) return !norm && gv_split_nb(a, sh, nb, s);
+  if (epi == GV_F32) return false;  // stored rows: the grouped launcher's
+  if (epi == GV_PART) return !norm && gv_split_nb(a, sh, nb, false, s);
+  if (sh.ksplit > 1) return epi == GV_RESID && !norm && gv_split_nb(a, sh, nb, true, s);
   if (sh.wide == 2) {
     // GV_SILU normalizes, GV_GELU takes a bias instead, as in the one-block forms
     if ((epi == GV_SILU && !norm) || (epi == GV_GELU && (norm || !a.bias))) return false;
@@ -866,15 +858,6 @@ bool launch_gemv_fused(const GemvArgs& a, int epi, hipStream_t s) {
     case GV_GELU: return !norm && a.bias && gv_dispatch<GV_GELU, false>(a, sh, s);
     case GV_RESID: return !norm && gv_dispatch<GV_RESID, false>(a, sh, s);
     case GV_HEAD: return norm ? gv_dispatch<GV_HEAD, true>(a, sh, s) : gv_dispatch<GV_HEAD, false>(a, sh, s);
-    case GV_F32: {  // float rows out (router logits): 64-row workgroups
-      if (norm) return false;
-      const dim3 grid((a.N + 63) / 64);
-      if (nb == 1) klaunch(gemv_wide_kernel<1, 1, GV_F32, 4>, grid, dim3(256), 0, s, a);
-      else if (nb == 2) klaunch(gemv_wide_kernel<1, 2, GV_F32, 2>, grid, dim3(256), 0, s, a);
-      else if (nb == 3) klaunch(gemv_wide_kernel<1, 3, GV_F32, 4>, grid, dim3(256), 0, s, a);
-      else klaunch(gemv_wide_kernel<1, 4, GV_F32, 2>, grid, dim3(256), 0, s, a);
-      return true;
-    }
     default: return false;
   }
 }

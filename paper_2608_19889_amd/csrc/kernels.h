@@ -215,8 +215,10 @@ void launch_gemm_f32(const float* W, const float* X, int N, int M, int K, int ep
 // a[t][f] = silu(gate) * up of the interleaved gate/up projection [M][2I]
 void launch_silu_f32(const float* gu, float* a, int M, int I, hipStream_t s);
 // ---- fused decode projections (k_gemv.hip)
-enum GvEpi : int { GV_HEAD = 0, GV_RESID = 1, GV_SILU = 2, GV_ROPE = 3, GV_PART = 4 /* internal: split-K partials */,
-                   GV_F32 = 5 /* grouped experts: float rows out_f32[row][n] */,
+enum GvEpi : int { GV_HEAD = 0, GV_RESID = 1, GV_SILU = 2, GV_ROPE = 3,
+                   GV_PART = 4 /* the partials part[split][M][N] of gemv_shape(..).ksplit >= 1 K splits, for their
+                                  consumer to sum in order (router) */,
+                   GV_F32 = 5 /* grouped experts only: float rows out_f32[row][n] */,
                    GV_GELU = 6 /* out_t[t][n] = bf16(gelu_tanh(acc + bias[n])) */ };
 
 struct GemvArgs {
@@ -247,8 +249,8 @@ struct GemvArgs {
   const int32_t* len;   // token t is at position len[t] ...
   const int32_t* slot;  // ... of cache slot slot[t] (t when null)
   int H;
-  // split K (projections of 17..64 tokens): workspace of ksplit * M * N floats
-  // (gemv_workspace_floats), owned by the caller
+  // split K (residual projections of 17..64 tokens, GV_PART): workspace of ksplit
+  // * M * N floats (gemv_workspace_floats), owned by the caller
   float* part;
   // grouped experts (launch_gemv_grouped): expert e multiplies W + e *
   // g_wstride with its rows g_off[e] .. g_off[e+1]-1; row r reads X row
@@ -257,9 +259,6 @@ struct GemvArgs {
   const int32_t* g_off;
   const int32_t* g_xrow;
   int64_t g_wstride;
-  // GV_F32: leave the partials of a split K in ``part`` ([split][M][N]; their
-  // consumer sums them) instead of running the epilogue
-  int parts_only;
   // tile order (xt_off) of the token operands, up to 16 tokens, unsplit
   // fused projections only: x_tiled -- X is stored in it; out_tiled -- the
   // epilogue writes xg_out (GV_RESID) or out_t (GV_SILU) in it
@@ -273,12 +272,13 @@ struct GvShape {
   int ksplit;       // workgroups splitting K (1: fused epilogue; else partials, summed by their consumer)
   int wide = 0;     // 1: gemv_wide_kernel (4 wavefronts splitting the rows, ks unused); 2: launch_gemm_few
 };
-// floats of GemvArgs::part a launch of this shape needs (0 when unsplit)
+// floats of GemvArgs::part a launch of this shape needs (0: none)
 int64_t gemv_workspace_floats(int N, int K, int M, int epi);
 GvShape gemv_shape(int N, int K, int M, int epi);
 int gemv_rows(int N, int K, int M, int epi);  // output rows per workgroup (ss partial count = N / rows)
-// false (nothing launched) when M > GEMV_MAX_M or the normalization does not
-// match the epilogue (GV_SILU and GV_ROPE need ss_in, GV_RESID must not have it)
+// false (nothing launched) when M > GEMV_MAX_M, for GV_F32, or when the
+// normalization does not match the epilogue (GV_SILU needs ss_in, GV_RESID,
+// GV_GELU and GV_PART must not have it)
 bool launch_gemv_fused(const GemvArgs& a, int epi, hipStream_t s);
 void launch_argmax_final(const float* val, const int32_t* idx, int nparts, int M, int32_t* next, int32_t* len,
                          hipStream_t s);

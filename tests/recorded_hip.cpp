@@ -20,6 +20,8 @@
 #include "axon.h"
 #include "kernels.h"
 
+using namespace axon;
+
 namespace {
 
 int g_device = 0, g_capture = 0;
@@ -290,12 +292,35 @@ void two_devices() {
   }
 }
 
+// float rows of an ungrouped few-token projection: raw partials only
+void raw_rows() {
+  for (int K : {64, 1024})
+    for (int M : {1, 16, 17, 64}) {
+      GemvArgs a{};
+      a.W = a.X = (const bf16*)TOK;
+      a.N = 64;
+      a.K = K;
+      a.M = M;
+      a.ldo = a.N;
+      a.out_f32 = LOGITS;
+      a.part = LOGITS;
+      for (int epi : {GV_F32, GV_PART}) {
+        mark("raw " + std::to_string(epi) + " " + std::to_string(K) + " " + std::to_string(M));
+        const bool ok = launch_gemv_fused(a, epi, nullptr);
+        mark(ok ? "launched" : "refused");
+        if (epi == GV_PART && (int64_t)gemv_shape(a.N, K, M, epi).ksplit * M * a.N > gemv_workspace_floats(a.N, K, M, epi))
+          mark("workspace too small");
+      }
+    }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
   setvbuf(stdout, nullptr, _IOFBF, 1 << 20);
   const std::string s = argc > 1 ? argv[1] : "";
   if (s == "two_devices") two_devices();
+  else if (s == "raw_rows") raw_rows();
   else return 2;
   printf("done\n");
   return 0;

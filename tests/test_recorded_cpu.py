@@ -68,3 +68,20 @@ def test_lds_limits_are_raised_on_every_device_before_any_launch(recorder):
     # the scenario reaches the 256-tile, ring, few-token and weight-gradient forms
     for part in ("gemm_bf16_256_kernel<", "gemm_ring_kernel<8", "gemm_ring_kernel<2", "gemm_tn_256_kernel<"):
         assert any(part in k for _, k in large), part
+
+
+def test_float_rows_of_a_split_projection_are_never_accumulated(recorder):
+    """A few-token projection to float rows leaves the raw partials of its K
+    splits (GV_PART, one launch, enough workspace reported); storing rows (GV_F32)
+    is the grouped experts' form and refused elsewhere, not run through the
+    residual sum, which would add to what the rows held."""
+    ev = [e for e in recorder("raw_rows") if isinstance(e, Launch) or e[0] == "mark"]
+    seen = 0
+    for i, e in enumerate(ev):
+        if e[0] == "mark" and e[1].startswith("raw 5 "):
+            assert ev[i + 1] == ("mark", "refused"), ev[i:i + 4]
+        elif e[0] == "mark" and e[1].startswith("raw 4 "):
+            assert "gemv_wide_kernel<" in ev[i + 1].kernel and ev[i + 1].gy == (1 if " 64 " in e[1] else 16), ev[i + 1]
+            assert ev[i + 2] == ("mark", "launched")
+            seen += 1
+    assert seen == 8 and ("mark", "workspace too small") not in ev
