@@ -956,9 +956,18 @@ static void launch_tn(TnArgs g, float* part, int64_t part_floats, hipStream_t s)
   }
   TnArgs p = g;
   p.out = part;
-  klaunch(kern, dim3(tiles, ks), dim3(512), pf2::LDS_BYTES, s, p);
   const int64_t n4 = (int64_t)g.R * g.C / 4;
-  wgrad_sum_kernel<MODE><<<(unsigned)((n4 + 255) / 256), 256, 0, s>>>(g, part, ks);
+  const dim3 grid(tiles, ks), sums((unsigned)((n4 + 255) / 256));
+  // a timed launch starts its events with the GEMM and stops with the sum
+  const TimingSlot t = g_timing_slot;
+  g_timing_slot = TimingSlot{};
+  if (t.start) {
+    hipExtLaunchKernelGGL(kern, grid, dim3(512), pf2::LDS_BYTES, s, t.start, nullptr, 0, p);
+    hipExtLaunchKernelGGL(wgrad_sum_kernel<MODE>, sums, dim3(256), 0, s, nullptr, t.stop, 0, g, part, ks);
+  } else {
+    kern<<<grid, 512, pf2::LDS_BYTES, s>>>(p);
+    wgrad_sum_kernel<MODE><<<sums, 256, 0, s>>>(g, part, ks);
+  }
 }
 
 void launch_wgrad(int mode, const bf16* Y, int ldy, int R, const bf16* X, int C, int T, bool xpair, float* out,

@@ -314,6 +314,17 @@ void raw_rows() {
     }
 }
 
+// a timed training step whose weight gradients split over the tokens
+void timed_train() {
+  axon_config c = llama(512, 8, 2, 64, 1024, 3000);
+  c.max_batch = 2;
+  c.max_seq = 1024;
+  axon_model* m = make(c);
+  check(axon_timing_enable(m, 1), "axon_timing_enable");
+  mark("train");
+  train(m, c, 2, 1000);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -321,6 +332,7 @@ int main(int argc, char** argv) {
   const std::string s = argc > 1 ? argv[1] : "";
   if (s == "two_devices") two_devices();
   else if (s == "raw_rows") raw_rows();
+  else if (s == "timed_train") timed_train();
   else return 2;
   printf("done\n");
   return 0;

@@ -85,3 +85,15 @@ def test_float_rows_of_a_split_projection_are_never_accumulated(recorder):
             assert ev[i + 2] == ("mark", "launched")
             seen += 1
     assert seen == 8 and ("mark", "workspace too small") not in ev
+
+
+def test_timed_weight_gradient_includes_the_sum_of_its_splits(recorder):
+    """With kernel timing on, a weight gradient split over the tokens starts its
+    event pair with the GEMM and stops it with the kernel that sums the splits."""
+    launches = [e for e in recorder("timed_train") if isinstance(e, Launch)]
+    split = [i for i, e in enumerate(launches) if "gemm_tn_256_kernel<" in e.kernel and e.gy > 1]
+    assert {launches[i].kernel.split("<")[1][0] for i in split} == {"0", "1", "2"}  # every row order
+    for i in split:
+        gemm, total = launches[i], launches[i + 1]
+        assert "wgrad_sum_kernel<" in total.kernel
+        assert gemm.start and not gemm.stop and not total.start and total.stop == gemm.start + 1, (gemm, total)
