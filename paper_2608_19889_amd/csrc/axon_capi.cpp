@@ -329,6 +329,7 @@ struct axon_model {
   float* gemv_part = nullptr;  // split-K partial sums of the decode projections
   float* gemm_part = nullptr;  // split-K partial sums of the narrow prefill / training GEMMs
   int64_t gemm_part_floats = 0;
+  int64_t decode_part_floats = 0;  // what gemm_part held at init (decode_split)
   float* ss = nullptr;       // per-workgroup sums of squares of x rows
   void* xg = nullptr;        // bf16(x * g) for the next normalized projection
   int ss_n = 0;              // number of partials currently in ss
@@ -527,9 +528,11 @@ int prefill_split(axon_model* m, int N, int M, int K) {
 }
 
 // Split of a decode step's residual projection over more tokens than the
-// fused kernels take.
+// fused kernels take, within the partials' buffer as the model was made: the
+// first training step enlarges it, and a decode step gives the same bits before
+// and after one.
 int decode_split(axon_model* m, int N, int M, int K) {
-  const int64_t fit = m->gemm_part_floats / ((int64_t)M * N);
+  const int64_t fit = m->decode_part_floats / ((int64_t)M * N);
   return gemm_ksplit_cost(N, M, K, (int)std::min<int64_t>(fit, 8));
 }
 
@@ -1505,6 +1508,7 @@ extern "C" int axon_init_model(const axon_config* cfg, const axon_weight* weight
       if (!m->gpt2() && D <= 2048) m->gemm_part_floats = 2 * tmax * D;
       if (!m->gpt2() && c.max_batch > GEMV_MAX_M)
         m->gemm_part_floats = std::max(m->gemm_part_floats, std::min<int64_t>(8 * c.max_batch * D, 16 << 20));
+      m->decode_part_floats = m->gemm_part_floats;
       if (m->gemm_part_floats > 0) TRY(dev_alloc(m, (void**)&m->gemm_part, (size_t)m->gemm_part_floats * 4));
     }
     TRY(dev_alloc(m, (void**)&m->ss, (int64_t)std::max<int64_t>(D / 8, 1) * c.max_batch * 4));

@@ -325,6 +325,21 @@ void timed_train() {
   train(m, c, 2, 1000);
 }
 
+// the same decode step of a wide batch before and after a training step
+void decode_after_training() {
+  axon_config c = llama(4160, 16, 16, 64, 16384, 1000);
+  c.max_batch = 1024;
+  c.max_seq = 4;
+  axon_model* m = make(c);
+  for (int pass = 0; pass < 2; ++pass) {
+    prefill(m, 1024, 1);
+    mark("decode");
+    check(axon_decode_step(m, 1024, TOK, LOGITS + 4 * pass, TOK, nullptr), "axon_decode_step");
+    mark("end");
+    train(m, c, 1024, 2);
+  }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -333,6 +348,7 @@ int main(int argc, char** argv) {
   if (s == "two_devices") two_devices();
   else if (s == "raw_rows") raw_rows();
   else if (s == "timed_train") timed_train();
+  else if (s == "decode_after_training") decode_after_training();
   else return 2;
   printf("done\n");
   return 0;

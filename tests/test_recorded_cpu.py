@@ -97,3 +97,20 @@ def test_timed_weight_gradient_includes_the_sum_of_its_splits(recorder):
         gemm, total = launches[i], launches[i + 1]
         assert "wgrad_sum_kernel<" in total.kernel
         assert gemm.start and not gemm.stop and not total.start and total.stop == gemm.start + 1, (gemm, total)
+
+
+def test_decode_splits_do_not_depend_on_an_earlier_training_step(recorder):
+    """A decode step above 64 sequences takes the same launches (so the same order
+    of sums, the same bits) whether or not the model has run a training step, which
+    enlarges the shared buffer of partials: here the buffer a model starts with
+    bounds the split of the down projection."""
+    steps, inside = [], False
+    for e in recorder("decode_after_training"):
+        if e[0] == "mark":
+            inside = e[1] == "decode"
+            if inside:
+                steps.append([])
+        elif inside and isinstance(e, Launch):
+            steps[-1].append((e.kernel, e.gx, e.gy))
+    assert len(steps) == 2 and steps[0] == steps[1]
+    assert any("gemm_" in k and gy > 1 for k, _, gy in steps[0])
