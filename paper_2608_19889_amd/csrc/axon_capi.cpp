@@ -1476,6 +1476,10 @@ extern "C" int axon_init_model(const axon_config* cfg, const axon_weight* weight
       m->moe_toff = m->moe_off + E + 1;
       TRY(dev_alloc(m, (void**)&m->moe_xrow, tmax * k * 4));
       TRY(dev_alloc(m, (void**)&m->moe_inv, tmax * k * 4));
+      // a choice without an expert (NaN router logits) gets no row in the plan: its
+      // readers find zeros or an earlier call's rows, in range either way
+      HTRY(hipMemsetAsync(m->moe_xrow, 0, tmax * k * 4, s));
+      HTRY(hipMemsetAsync(m->moe_inv, 0, tmax * k * 4, s));
       TRY(dev_alloc(m, &m->moe_a, tmax * k * c.moe_intermediate * esz));
       TRY(dev_alloc(m, (void**)&m->moe_y, tmax * k * D * 4));
     }

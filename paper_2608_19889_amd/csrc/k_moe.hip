@@ -83,7 +83,7 @@ __global__ void __launch_bounds__(256) moe_route_kernel(const float* __restrict_
     }
     if (bi < 0) bi = 0x7fffffff;  // NaN logits: no expert compares equal
     if (lane == c) {
-      wsel = bv;
+      wsel = bi < E ? bv : NAN;  // no expert: the token's output is NaN
       isel = bi;
     }
     wsum += bv;

@@ -340,6 +340,17 @@ void decode_after_training() {
   }
 }
 
+// a mixture-of-experts model's buffers: 7 tokens x 3 choices, 4 experts
+void moe_init() {
+  axon_config c = llama(128, 2, 2, 64, 64, 100);
+  c.n_experts = 4;
+  c.top_k = 3;
+  c.moe_intermediate = 64;
+  c.max_batch = 1;
+  c.max_seq = 7;
+  make(c);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -348,6 +359,7 @@ int main(int argc, char** argv) {
   if (s == "two_devices") two_devices();
   else if (s == "raw_rows") raw_rows();
   else if (s == "timed_train") timed_train();
+  else if (s == "moe_init") moe_init();
   else if (s == "decode_after_training") decode_after_training();
   else return 2;
   printf("done\n");

@@ -40,3 +40,36 @@ def test_routing_plan_edges_against_oracle(E, k, B):
     clear = gaps >= NEAR_TIE
     assert clear.any()
     check_bf16(got[clear], exact[clear], b16[clear], f"plan E {E} k {k} B {B}", absolute=False)
+
+
+@pytest.mark.parametrize("E,k", [(64, 6), (256, 8)])
+def test_nan_router_logits_stay_with_their_token(E, k):
+    """A token whose router logits are NaN (its embedding row is) has no expert: its
+    own logits are NaN and every other sequence's are bit for bit those of a
+    model whose embedding is finite, through the small plan and the large one."""
+    shape = dict(small_shape("moe16b", layers=2, vocab=512, hidden=512, intermediate=512), n_routed_experts=E,
+                 num_experts_per_tok=k, moe_intermediate_size=64, n_shared_experts=0)
+    w = model_weights(shape, seed=53)
+    bad = 511
+    ids = prompts(3, 60, bad, seed=54).numpy()
+    ids[1, 3] = bad
+    out = []
+    for nan in (True, False):
+        if nan:
+            w = dict(w)
+            good = w["model.embed_tokens.weight"]
+            w["model.embed_tokens.weight"] = good.clone()
+            w["model.embed_tokens.weight"][bad] = float("nan")
+        else:
+            w["model.embed_tokens.weight"] = good
+        m = gpu_model(shape, w, max_batch=3, max_seq=64)
+        print(f"E {E} k {k} nan {nan}", flush=True)
+        for n in (2, 4, 60):  # 6 and 12 tokens: the small plan; 180: the large one
+            got, _ = run_teacher_forced(m, [ids[b, :n] for b in range(3)], ids[:, n - 1:n])
+            out.append(got)
+        m.close()
+    for a, b in zip(out[:3], out[3:]):
+        assert np.all(np.isfinite(b))
+        np.testing.assert_array_equal(a[:, [0, 2]], b[:, [0, 2]])
+    np.testing.assert_array_equal(out[0], out[3])  # the token is not among the first two
+    assert np.all(np.isnan(out[1][:, 1])) and np.all(np.isnan(out[2][:, 1]))

@@ -114,3 +114,15 @@ def test_decode_splits_do_not_depend_on_an_earlier_training_step(recorder):
             steps[-1].append((e.kernel, e.gx, e.gy))
     assert len(steps) == 2 and steps[0] == steps[1]
     assert any("gemm_" in k and gy > 1 for k, _, gy in steps[0])
+
+
+def test_routing_rows_are_in_range_before_the_first_call(recorder):
+    """Choices without an expert (NaN router logits) get no row in the plan, and
+    what reads the plan then finds what its buffers held: token and row numbers of
+    an earlier call, or zeros, never uninitialized memory."""
+    ev = recorder("moe_init")
+    size = 7 * 3 * 4  # max_tokens x top_k int32: choices, their weights, token and row of each choice
+    at = [e[1] for e in ev if e[0] == "alloc" and e[2] == size]
+    assert len(at) == 4
+    filled = {e[1] for e in ev if e[0] == "fill" and e[2] == size}
+    assert set(at[2:]) <= filled
