@@ -1501,11 +1501,15 @@ extern "C" int axon_init_model(const axon_config* cfg, const axon_weight* weight
                         gemv_workspace_floats(2 * (int)I, (int)D, b, GV_SILU),
                         gemv_workspace_floats((int)I, (int)D, b, GV_GELU),
                         gemv_workspace_floats((int)D, (int)I, b, GV_RESID)});
-        if (m->moe_model()) wsf = std::max(wsf, gemv_workspace_floats(m->moe_ep(), (int)D, b, GV_PART));
         if (Is > 0)
           wsf = std::max({wsf, gemv_workspace_floats(2 * Is, (int)D, b, GV_SILU),
                           gemv_workspace_floats((int)D, Is, b, GV_RESID)});
       }
+      // the router also takes the few-token form in a prompt of up to 64 tokens,
+      // however few sequence slots there are
+      if (m->moe_model())
+        for (int t = 1; t <= std::min<int64_t>(tmax, GEMV_MAX_M); ++t)
+          wsf = std::max(wsf, gemv_workspace_floats(m->moe_ep(), (int)D, t, GV_PART));
       if (wsf > 0) TRY(dev_alloc(m, (void**)&m->gemv_part, (size_t)wsf * 4));
       // two K halves of the narrow prefill residual projections (hidden <=
       // 2048); up to 8 splits of a decode step above 64 sequences, 64 MB at most

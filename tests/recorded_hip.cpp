@@ -4,9 +4,10 @@
 //   launch <device> <capture 0/1> <lds bytes> <start event> <stop event> <gx> <gy> <kernel>
 //   limit <device> <capture 0/1> <lds bytes> <kernel>     (dynamic LDS limit raised)
 //   alloc <base> <bytes> / fill <base> <bytes>            (hipMalloc / hipMemset)
+//   parts <base> <bytes>                                   (split-K partials a projection writes)
 //   mark <text>                                            (a step of the scenario)
 // The executable's definitions come before libamdhip64's for libaxon.so too.
-// Usage: recorded_hip <scenario>.
+// Usage: recorded_hip <scenario> [number ...].
 #include <cxxabi.h>
 #include <stdio.h>
 #include <stdlib.h>
@@ -44,7 +45,24 @@ void* reserve(size_t bytes) {
   return p;
 }
 
-void launched(const void* f, dim3 grid, size_t lds, hipEvent_t a, hipEvent_t b) {
+// the partials written by the launch of a split projection, from its arguments
+void partials(const std::string& k, dim3 grid, void** args) {
+  auto say = [](const float* p, int64_t floats) {
+    printf("parts %llu %lld\n", (unsigned long long)p, (long long)floats * 4);
+  };
+  if (k.find("gemv_wide_kernel<") != std::string::npos) {
+    const GemvArgs& a = *(const GemvArgs*)args[0];
+    if (!a.g_off) say(a.part, (int64_t)grid.y * a.M * a.N);
+  } else if (grid.y > 1 && (k.find("gemm_ring_kernel<") != std::string::npos ||
+                            k.find("gemm_bf16_256_kernel<") != std::string::npos)) {
+    const int64_t N = *(const int*)args[2], M = *(const int*)args[3];
+    const EpiArgs& e = *(const EpiArgs*)args[5];
+    say(e.out_f32, (grid.y - 1) * e.part_stride + M * N);
+  }
+}
+
+void launched(const void* f, dim3 grid, size_t lds, hipEvent_t a, hipEvent_t b, void** args) {
+  partials(name_of(f), grid, args);
   printf("launch %d %d %zu %llu %llu %u %u %s\n", g_device, g_capture, lds, (unsigned long long)a,
          (unsigned long long)b, grid.x, grid.y, name_of(f));
 }
@@ -83,13 +101,13 @@ hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* lds, hipStream_t*
   *s = g_call.s;
   return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void* f, dim3 g, dim3, void**, size_t lds, hipStream_t) {
-  launched(f, g, lds, nullptr, nullptr);
+hipError_t hipLaunchKernel(const void* f, dim3 g, dim3, void** args, size_t lds, hipStream_t) {
+  launched(f, g, lds, nullptr, nullptr, args);
   return hipSuccess;
 }
-hipError_t hipExtLaunchKernel(const void* f, dim3 g, dim3, void**, size_t lds, hipStream_t, hipEvent_t a, hipEvent_t b,
-                              int) {
-  launched(f, g, lds, a, b);
+hipError_t hipExtLaunchKernel(const void* f, dim3 g, dim3, void** args, size_t lds, hipStream_t, hipEvent_t a,
+                              hipEvent_t b, int) {
+  launched(f, g, lds, a, b, args);
   return hipSuccess;
 }
 hipError_t hipFuncSetAttribute(const void* f, hipFuncAttribute, int bytes) {
@@ -192,7 +210,7 @@ axon_config llama(int D, int H, int KV, int hd, int I, int V) {
   return c;
 }
 
-// the weight map of a one-layer model (tied head), as device pointers
+// the weight map of a one-layer model, as device pointers
 struct Map {
   std::vector<std::string> names;
   std::vector<axon_weight> w;
@@ -208,6 +226,7 @@ struct Map {
         {p + "self_attn.k_proj.weight", {KV * hd, D}},
         {p + "self_attn.v_proj.weight", {KV * hd, D}},
         {p + "self_attn.o_proj.weight", {D, H * hd}}};
+    if (!c.tie_embeddings) l.push_back({"lm_head.weight", {c.vocab, D}});
     if (c.qkv_bias)
       for (auto& b : {std::make_pair("q", H), std::make_pair("k", KV), std::make_pair("v", KV)})
         l.push_back({p + "self_attn." + b.first + "_proj.bias", {b.second * hd, 0}});
@@ -254,12 +273,16 @@ void prefill(axon_model* m, int batch, int len, int all = 0) {
   check(axon_prefill(m, batch, TOK, TOK, cu.data(), nullptr, 0, all, LOGITS, TOK, nullptr), "axon_prefill");
 }
 
-void train(axon_model* m, const axon_config& c, int batch, int len) {
+void train(axon_model* m, const axon_config& c, const std::vector<int32_t>& cu) {
   Map g(c, AXON_F32);
+  check(axon_loss_and_grads(m, (int)cu.size() - 1, TOK, TOK, cu.data(), TOK, LOGITS, g.w.data(), (int)g.w.size(), nullptr),
+        "axon_loss_and_grads");
+}
+
+void train(axon_model* m, const axon_config& c, int batch, int len) {
   std::vector<int32_t> cu;
   for (int b = 0; b <= batch; ++b) cu.push_back(b * len);
-  check(axon_loss_and_grads(m, batch, TOK, TOK, cu.data(), TOK, LOGITS, g.w.data(), (int)g.w.size(), nullptr),
-        "axon_loss_and_grads");
+  train(m, c, cu);
 }
 
 // calls of many sizes on two devices, one after the other in this process
@@ -351,14 +374,65 @@ void moe_init() {
   make(c);
 }
 
+// prompts and decode steps of models with few and many sequence slots: a dense
+// one, one of each head dimension and width, and a mixture of experts
+void partials_of_many_sizes() {
+  for (int max_batch : {1, 3, 40, 64, 65, 300})
+    for (int kind = 0; kind < 4; ++kind) {
+      axon_config c = kind == 1 ? llama(3584, 28, 4, 128, 18944, 1000) : llama(512, 8, 2, 64, 1536, 1000);
+      if (kind == 2) c.dtype = AXON_F32;
+      if (kind == 3) {
+        c.n_experts = 256;
+        c.top_k = 8;
+        c.moe_intermediate = 64;
+      }
+      c.max_batch = max_batch;
+      c.max_seq = 82;
+      axon_model* m = make(c);
+      for (int len : {1, 2, 4, 12, 16, 21, 33, 64, 79}) {
+        for (int b : {1, 3, 40, 64, 65, 300})
+          if (b <= max_batch) {
+            mark("max_batch " + std::to_string(max_batch) + " kind " + std::to_string(kind) + " " + std::to_string(b) +
+                 " x " + std::to_string(len));
+            prefill(m, b, len);
+            check(axon_decode_step(m, b, TOK, LOGITS, TOK, nullptr), "axon_decode_step");
+            if (b <= 64 && kind < 2)
+              check(axon_decode_step_noalloc(m, b, TOK, LOGITS, TOK, nullptr), "axon_decode_step_noalloc");
+          }
+      }
+      axon_free(m);
+    }
+}
+
+// one training step: hidden, heads, kv heads, head dimension, intermediate,
+// vocabulary, biases, tied head, sequence lengths
+void train_step(const std::vector<int>& v) {
+  axon_config c = llama(v[0], v[1], v[2], v[3], v[4], v[5]);
+  c.qkv_bias = v[6];
+  c.tie_embeddings = v[7];
+  std::vector<int32_t> cu{0};
+  for (size_t i = 8; i < v.size(); ++i) {
+    cu.push_back(cu.back() + v[i]);
+    c.max_seq = std::max(c.max_seq, (int32_t)v[i]);
+  }
+  c.max_batch = (int)cu.size() - 1;
+  axon_model* m = make(c);
+  mark("train");
+  train(m, c, cu);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
   setvbuf(stdout, nullptr, _IOFBF, 1 << 20);
   const std::string s = argc > 1 ? argv[1] : "";
+  std::vector<int> v;
+  for (int i = 2; i < argc; ++i) v.push_back(atoi(argv[i]));
   if (s == "two_devices") two_devices();
   else if (s == "raw_rows") raw_rows();
+  else if (s == "train_step" && v.size() > 8) train_step(v);
   else if (s == "timed_train") timed_train();
+  else if (s == "partials") partials_of_many_sizes();
   else if (s == "moe_init") moe_init();
   else if (s == "decode_after_training") decode_after_training();
   else return 2;

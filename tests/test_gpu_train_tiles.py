@@ -9,6 +9,12 @@ multiple of 64); RMSNorm's backward holds a row in registers in four widths
 (hidden up to 1024, 2048, 4096, 8192) and reads wider rows twice.  The shapes
 stand on both sides of each of these.
 
+The sizes of a real step take other forms of the GEMMs: 256 x 256 tiles for the
+fused QKV, gate/up, logits and gated-activation-gradient epilogues, and weight
+gradients split over the tokens, their partials summed in each of the three row
+orders.  REACHES names these for the cases that stand for them (a CPU test holds
+the launch rules to it).
+
 The gradients' bars are those of the gradient test over ordinary shapes,
 derived there, except the element-wise one of hidden 8256: its logits are the
 largest (see the loss) and its tensors have up to 1.06M elements.  An element's
@@ -41,6 +47,20 @@ CASES = {
     "hidden_2112": ("7b", 2, 1, 2112, 128, 191, [33, 30]),
     "hidden_4160": ("1b", 2, 1, 4160, 64, 129, [31, 1]),
     "hidden_8256": ("1b", 2, 2, 8256, 64, 65, [21, 12]),
+    # odd token counts, no multiple of 32: the last of the token splits is masked
+    "tiles_256_tied": ("1b", 8, 2, 512, 8192, 12001, [400, 301, 400]),
+    "tiles_256_bias": ("7b", 40, 8, 512, 6144, 12001, [300, 257, 391, 301]),
+    "token_splits_8": ("1b", 2, 1, 128, 128, 130, [258] * 15 + [257]),
+}
+# (part of a kernel's name, its K or token splits): GEMM epilogues 3 logits with
+# softmax partials, 4 QKV with rotation, 6 gate/up, 7 gated-activation gradient;
+# weight-gradient row orders 0 plain, 1 QKV, 2 gate/up
+REACHES = {
+    "tiles_256_tied": [("gemm_bf16_256_kernel<3, false, true>", 1), ("gemm_bf16_256_kernel<7, false, true>", 1)]
+                      + [(f"gemm_tn_256_kernel<{r}", 2) for r in range(3)],
+    "tiles_256_bias": [(f"gemm_bf16_256_kernel<{e}, false, true>", 1) for e in (3, 4, 6)]
+                      + [(f"gemm_tn_256_kernel<{r}", 2) for r in range(3)],
+    "token_splits_8": [(f"gemm_tn_256_kernel<{r}", 8) for r in range(3)],
 }
 
 

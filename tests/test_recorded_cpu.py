@@ -8,6 +8,8 @@ from collections import namedtuple
 import pytest
 
 from paper_2608_19889_amd import axon, build
+from synthetic import MODEL_SHAPES
+from test_gpu_train_tiles import CASES, REACHES
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 Launch = namedtuple("Launch", "device capture lds start stop gx gy kernel")
@@ -26,9 +28,9 @@ def recorder(tmp_path_factory):
                    check=True, capture_output=True, text=True)
     done = {}
 
-    def run(scenario):
+    def run(*scenario):
         if scenario not in done:
-            r = subprocess.run([exe, scenario], capture_output=True, text=True, timeout=60)
+            r = subprocess.run([exe, *map(str, scenario)], capture_output=True, text=True, timeout=60)
             assert r.returncode == 0 and r.stdout.endswith("done\n"), r.stdout[-500:] + r.stderr[-500:]
             done[scenario] = [_event(line) for line in r.stdout.splitlines()[:-1]]
         return done[scenario]
@@ -126,3 +128,36 @@ def test_routing_rows_are_in_range_before_the_first_call(recorder):
     assert len(at) == 4
     filled = {e[1] for e in ev if e[0] == "fill" and e[2] == size}
     assert set(at[2:]) <= filled
+
+
+@pytest.mark.parametrize("case", list(REACHES))
+def test_training_cases_reach_the_kernels_they_stand_for(recorder, case):
+    """The GPU test over the training step's tile edges takes the launches that it
+    names, by the launch rules themselves."""
+    base, heads, kv, hidden, inter, vocab, lens = CASES[case]
+    shape = MODEL_SHAPES[base]
+    launches = [e for e in recorder("train_step", hidden, heads, kv, shape["head_dim"], inter, vocab,
+                                    int(shape["attention_bias"]), int(shape["tie_word_embeddings"]), *lens)
+                if isinstance(e, Launch)]
+    for kernel, splits in REACHES[case]:
+        assert any(kernel in e.kernel and e.gy == splits for e in launches), (kernel, splits)
+
+
+def test_split_partials_stay_inside_their_buffer(recorder):
+    """Every launch of a projection that leaves K-split partials writes them inside
+    one allocation of the model (or the fixed work array), for prompts of few and
+    many tokens under few and many sequence slots: a prompt may have more tokens
+    than the model has slots."""
+    ends, step, seen = {}, "", 0
+    for e in recorder("partials"):
+        if isinstance(e, (Launch, Limit)):
+            continue
+        if e[0] == "alloc":
+            ends[e[1]] = e[1] + e[2]
+        elif e[0] == "mark":
+            step = e[1]
+        elif e[0] == "parts":
+            base = max((b for b in ends if b <= e[1]), default=None)
+            assert base is not None and e[1] + e[2] <= ends[base], (step, e, base and ends[base] - e[1])
+            seen += 1
+    assert seen > 100

@@ -80,6 +80,35 @@ def test_noalloc_decode_equals_decode(kind):
     new.close()
 
 
+@pytest.mark.parametrize("base,batch", [("1b", 17), ("7b", 64)])
+def test_noalloc_decode_of_many_sequences_equals_decode(base, batch):
+    """17 and 64 sequences, the ends of the range whose projections run as
+    few-token GEMM tiles: the no-allocation step comes first in its process to
+    use them where the test runs alone, and gives the ordinary step's bits."""
+    shape = small_shape(base, layers=2, vocab=5003)
+    print(f"[noalloc] {base} {batch}", flush=True)
+    w = model_weights(shape, seed=23, device="cuda")
+    V = shape["vocab_size"]
+    ids = prompts(batch, 40, V, seed=24).numpy()
+    flat, cu = pack([ids[b, :1 + b % 40] for b in range(batch)])
+    ref = Model(shape, w, max_batch=batch, max_seq=48)
+    new = Model(shape, w, max_batch=batch, max_seq=48)
+    _, tok = ref.prefill(flat, cu)
+    new.prefill(flat, cu)
+    lg_new = torch.full((batch, V), float("nan"), dtype=torch.float32, device="cuda")
+    nx_new = torch.full((batch,), -1, dtype=torch.int32, device="cuda")
+    new.decode_step_noalloc(tok, logits=lg_new, next_tokens=nx_new)
+    lg_ref = torch.empty((batch, V), dtype=torch.float32, device="cuda")
+    nx_ref = torch.empty(batch, dtype=torch.int32, device="cuda")
+    ref.decode_step(tok, logits=lg_ref, next_tokens=nx_ref)
+    torch.cuda.synchronize()
+    assert torch.isfinite(lg_ref).all()
+    assert torch.equal(lg_ref, lg_new), (lg_ref - lg_new).abs().max().item()
+    assert torch.equal(nx_ref, nx_new)
+    ref.close()
+    new.close()
+
+
 def test_noalloc_refuses_other_models():
     """float32 models are refused before any work is enqueued (and lengths do
     not move)."""
