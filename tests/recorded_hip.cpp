@@ -4,7 +4,8 @@
 //   launch <device> <capture 0/1> <lds bytes> <start event> <stop event> <gx> <gy> <kernel>
 //   limit <device> <capture 0/1> <lds bytes> <kernel>     (dynamic LDS limit raised)
 //   alloc <base> <bytes> / fill <base> <bytes>            (hipMalloc / hipMemset)
-//   parts <base> <bytes>                                   (split-K partials a projection writes)
+//   parts <base> <bytes>   (partials that a launch writes for the next kernel: K or key splits,
+//                           sums of squares, argmax)
 //   mark <text>                                            (a step of the scenario)
 // The executable's definitions come before libamdhip64's for libaxon.so too.
 // Usage: recorded_hip <scenario> [number ...].
@@ -45,19 +46,38 @@ void* reserve(size_t bytes) {
   return p;
 }
 
-// the partials written by the launch of a split projection, from its arguments
+// the partials written by a launch, from its arguments
 void partials(const std::string& k, dim3 grid, void** args) {
-  auto say = [](const float* p, int64_t floats) {
-    printf("parts %llu %lld\n", (unsigned long long)p, (long long)floats * 4);
+  auto say = [](const void* p, int64_t words) {
+    if (p) printf("parts %llu %lld\n", (unsigned long long)p, (long long)words * 4);
   };
-  if (k.find("gemv_wide_kernel<") != std::string::npos) {
+  auto is = [&](const char* part) { return k.find(part) != std::string::npos; };
+  const int64_t wgs = grid.x;
+  if (is("gemv_wide_kernel<")) {
     const GemvArgs& a = *(const GemvArgs*)args[0];
     if (!a.g_off) say(a.part, (int64_t)grid.y * a.M * a.N);
-  } else if (grid.y > 1 && (k.find("gemm_ring_kernel<") != std::string::npos ||
-                            k.find("gemm_bf16_256_kernel<") != std::string::npos)) {
+  } else if (is("gemv_fused_kernel<") || is("gemv_split_resid_kernel")) {
+    const GemvArgs& a = *(const GemvArgs*)args[0];
+    say(a.ss_out, wgs * a.M);
+    say(a.am_val, wgs * a.M);
+    say(a.am_idx, wgs * a.M);
+  } else if (is("gemm_ring_kernel<") || is("gemm_bf16_256_kernel<")) {
     const int64_t N = *(const int*)args[2], M = *(const int*)args[3];
     const EpiArgs& e = *(const EpiArgs*)args[5];
-    say(e.out_f32, (grid.y - 1) * e.part_stride + M * N);
+    if (grid.y > 1) say(e.out_f32, (grid.y - 1) * e.part_stride + M * N);
+    if (is("gemm_ring_kernel<8")) {
+      const int rows = few_head_rows((int)N, (int)M, *(const int*)args[4]);
+      say(e.am_val, M * ((N + rows - 1) / rows));
+      say(e.am_idx, M * ((N + rows - 1) / rows));
+    }
+  } else if (is("argmax_part_kernel")) {
+    say(*(void**)args[2], wgs * grid.y);
+    say(*(void**)args[3], wgs * grid.y);
+  } else if (is("attn_decode_bf16_kernel")) {
+    const KVView& kv = *(const KVView*)args[1];
+    const int64_t H = *(const int*)args[5];
+    say(*(void**)args[3], wgs * grid.z * H * (kv.hd + 2));
+    say(*(void**)args[4], (int64_t)grid.z * grid.y);
   }
 }
 
@@ -387,7 +407,8 @@ void partials_of_many_sizes() {
         c.moe_intermediate = 64;
       }
       c.max_batch = max_batch;
-      c.max_seq = 82;
+      c.max_seq = max_batch <= 40 ? 3000 : 82;  // (long: the decode attention splits the keys)
+      c.max_tokens = 300 * 82;
       axon_model* m = make(c);
       for (int len : {1, 2, 4, 12, 16, 21, 33, 64, 79}) {
         for (int b : {1, 3, 40, 64, 65, 300})

@@ -143,11 +143,11 @@ def test_training_cases_reach_the_kernels_they_stand_for(recorder, case):
         assert any(kernel in e.kernel and e.gy == splits for e in launches), (kernel, splits)
 
 
-def test_split_partials_stay_inside_their_buffer(recorder):
-    """Every launch of a projection that leaves K-split partials writes them inside
-    one allocation of the model (or the fixed work array), for prompts of few and
-    many tokens under few and many sequence slots: a prompt may have more tokens
-    than the model has slots."""
+def test_partials_stay_inside_their_buffer(recorder):
+    """Every launch that leaves partials for the next kernel (K splits, key splits,
+    sums of squares, argmax) writes them inside one allocation of the model (or the
+    fixed work array), for prompts of few and many tokens under few and many
+    sequence slots: a prompt may have more tokens than the model has slots."""
     ends, step, seen = {}, "", 0
     for e in recorder("partials"):
         if isinstance(e, (Launch, Limit)):
