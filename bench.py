@@ -699,7 +699,7 @@ def summarize_counters(fetch_csv, write_csv, workload):
             if "gemv_fused_kernel" not in name:
                 continue
             targs = name[name.index("gemv_fused_kernel<") + 18:name.index(">")].split(",")
-            norm, epi = targs[3].strip() == "true", int(targs[4])
+            norm, epi = targs[2].strip() == "true", int(targs[3])
             if epi == 3:
                 role = after = "qkv"
             elif epi == 2:

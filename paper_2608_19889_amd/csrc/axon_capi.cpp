@@ -2059,7 +2059,7 @@ void enqueue_train(axon_model* m, int B, int T, const int32_t* d_tokens, const i
   auto dW = [&](const bf16* dY, int ldy, int N, const bf16* X, int K, int mode, float* o0, float* o1 = nullptr,
                 float* o2 = nullptr) {
     m->timed(1, K, N, T, s, [&] {
-      launch_wgrad(mode, dY, ldy, N, X, K, T, true, o0, o1, o2, hd, H, KV, m->gemm_part, m->gemm_part_floats, s);
+      launch_wgrad(mode, dY, ldy, N, X, K, T, o0, o1, o2, hd, H, KV, m->gemm_part, m->gemm_part_floats, s);
     });
   };
   // dX = dY W ([T][K] from dY [T][N] and the tiled W^T [K][N]) through a

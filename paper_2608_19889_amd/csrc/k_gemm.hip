@@ -153,7 +153,7 @@ AXON_DEV void store_block(const EpiArgs& ep, int nb, int t, RopeTok tok, const f
         *(f32x4*)(ep.out_f32 + (int64_t)t * ep.ldo + nb + g * 8 + (lane >> 5) * 4) =
             f32x4{v[g * 4], v[g * 4 + 1], v[g * 4 + 2], v[g * 4 + 3]};
     }
-    bf16* out = (bf16*)ep.out_t + (ep.opair ? xp_off(t, f0, lda) : (int64_t)t * lda + f0);
+    bf16* out = (bf16*)ep.out_t + (EPI == EPI_GU || ep.opair ? xp_off(t, f0, lda) : (int64_t)t * lda + f0);
 #pragma unroll
     for (int g = 0; g < 2; ++g) {
       const int f = g * 8 + (lane >> 5) * 4;
@@ -177,7 +177,7 @@ AXON_DEV void store_block(const EpiArgs& ep, int nb, int t, RopeTok tok, const f
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int64_t c0 = 2 * (int64_t)nb + (q >> 1) * 32;
-      bf16* out = (bf16*)ep.out_t + (ep.opair ? xp_off(t, c0, 2 * ep.ldo) : (int64_t)t * 2 * ep.ldo + c0) + (q & 1) * 8 + half;
+      bf16* out = (bf16*)ep.out_t + xp_off(t, c0, 2 * ep.ldo) + (q & 1) * 8 + half;
       bf16x4 dg, du;
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
@@ -755,7 +755,7 @@ __global__ void __launch_bounds__(512, 1) gemm_bf16_256_kernel(const bf16* __res
 // row T - 1; their Y values are zeroed in the last k-tile.
 // The transposed copies it replaces (both operands through LDS tiles, X also
 // fragment-tiled) took 2.4 ms of the 21.1 ms 1B-shaped 4-layer training step.
-// XP: Y and X in the row-pair layout (xp_off).
+// Y and X lie in the row-pair layout (xp_off).
 // ============================================================================
 struct TnArgs {
   const bf16* Y;  // [T][ldy], output row r = column r
@@ -785,7 +785,7 @@ AXON_DEV float* wgrad_row(const TnArgs& a, int r) {
   }
 }
 
-template <int MODE, bool XP>
+template <int MODE>
 __global__ void __launch_bounds__(512, 1) gemm_tn_256_kernel(TnArgs g) {
   using namespace pf2;
   extern __shared__ bf16x8 lds2[];
@@ -803,12 +803,9 @@ __global__ void __launch_bounds__(512, 1) gemm_tn_256_kernel(TnArgs g) {
   // load i of a wavefront: token rows 4 wave + 2 i, + 1 of the k-tile, 32 chunks
   // of 8 columns each; columns past the operand read its last 8 (never stored)
   const int lrow = wave * 4 + (lane >> 5), pch = lane & 31;
-  auto at = [&](int ld, int t, int c) -> int64_t {
-    c = min(c, ld - 8);
-    return XP ? xp_off(t, c, ld) : (int64_t)t * ld + c;
-  };
-  // a k-tile's 32 token rows are 32 ld elements in either layout: addresses are
-  // a fixed offset plus that, except in a k-tile that passes T
+  auto at = [&](int ld, int t, int c) -> int64_t { return xp_off(t, min(c, ld - 8), ld); };
+  // a k-tile's 32 token rows are 32 ld elements: addresses are a fixed offset plus
+  // that, except in a k-tile that passes T
   const int c0 = (pch ^ ((lrow & 3) << 2)) * 8, c1 = (pch ^ (((lrow + 2) & 3) << 2)) * 8;
   const bf16* xs[2] = {g.X + at(g.ldx, lrow, n0 + c0), g.X + at(g.ldx, lrow + 2, n0 + c1)};
   const bf16* ys[2] = {g.Y + at(g.ldy, lrow, m0 + c0), g.Y + at(g.ldy, lrow + 2, m0 + c1)};
@@ -942,10 +939,10 @@ __global__ void __launch_bounds__(256) wgrad_sum_kernel(TnArgs g, const float* _
   *(f32x4*)(wgrad_row<MODE>(g, r) + c) = v;
 }
 
-template <int MODE, bool XP>
+template <int MODE>
 static void launch_tn(TnArgs g, float* part, int64_t part_floats, hipStream_t s) {
-  auto kern = gemm_tn_256_kernel<MODE, XP>;
-  (void)LdsLimit<gemm_tn_256_kernel<MODE, XP>, pf2::LDS_BYTES>::entered;
+  auto kern = gemm_tn_256_kernel<MODE>;
+  (void)LdsLimit<gemm_tn_256_kernel<MODE>, pf2::LDS_BYTES>::entered;
   const int tiles = ((g.R + 255) / 256) * ((g.C + 255) / 256), nkt = (g.T + 31) / 32;
   // few tiles: split the tokens towards 256 workgroups, at least 16 k-tiles each
   int ks = 1;
@@ -970,21 +967,15 @@ static void launch_tn(TnArgs g, float* part, int64_t part_floats, hipStream_t s)
   }
 }
 
-void launch_wgrad(int mode, const bf16* Y, int ldy, int R, const bf16* X, int C, int T, bool xpair, float* out,
-                  float* out1, float* out2, int hd, int H, int KVh, float* part, int64_t part_floats, hipStream_t s) {
+void launch_wgrad(int mode, const bf16* Y, int ldy, int R, const bf16* X, int C, int T, float* out, float* out1,
+                  float* out2, int hd, int H, int KVh, float* part, int64_t part_floats, hipStream_t s) {
   if (T <= 0 || R <= 0 || C <= 0) return;
   const TnArgs g{Y, X, R, C, T, ldy, C, out, out1, out2, hd, H, KVh};
-#define AXON_TN(M)                                            \
-  case M:                                                     \
-    if (xpair) launch_tn<M, true>(g, part, part_floats, s);   \
-    else launch_tn<M, false>(g, part, part_floats, s);        \
-    return;
   switch (mode) {
-    AXON_TN(WGRAD_ROWS)
-    AXON_TN(WGRAD_QKV)
-    AXON_TN(WGRAD_GU)
+    case WGRAD_ROWS: launch_tn<WGRAD_ROWS>(g, part, part_floats, s); return;
+    case WGRAD_QKV: launch_tn<WGRAD_QKV>(g, part, part_floats, s); return;
+    case WGRAD_GU: launch_tn<WGRAD_GU>(g, part, part_floats, s); return;
   }
-#undef AXON_TN
 }
 
 // the 256 x 256 kernel instance
@@ -1163,9 +1154,10 @@ void launch_gemm_bf16(const bf16* W, const bf16* X, int N, int M, int K, int epi
     AXON_TILES(EPI_RESID)
     AXON_TILES(EPI_SILU)
     AXON_TILES(EPI_ROPE)
-    AXON_TILES(EPI_LSE)
-    AXON_TILES(EPI_GU)
-    AXON_TILES(EPI_DGU)
+    // the training step's: row-pair operands only
+    case EPI_LSE: launch_tiles<EPI_LSE, true>(W, X, N, M, K, 1, ep, s); return;
+    case EPI_GU: launch_tiles<EPI_GU, true>(W, X, N, M, K, 1, ep, s); return;
+    case EPI_DGU: launch_tiles<EPI_DGU, true>(W, X, N, M, K, 1, ep, s); return;
     case EPI_GELU: launch_tiles<EPI_GELU, false>(W, X, N, M, K, 1, ep, s); return;  // GPT-2: row-major only
     default: return;
   }

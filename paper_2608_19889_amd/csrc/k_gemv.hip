@@ -1,12 +1,13 @@
 // Few-token projections for the decode step (M <= 64 tokens), fused with
 // their neighbours.  HBM-bound on the weight stream.
 //
-// A workgroup owns 16*RB output features of W [N][K] and the whole K range;
-// its KS wavefronts split K into contiguous chunks, run
-// v_mfma_f32_16x16x32_bf16 with W as the A operand (16 rows per block) and the
-// tokens as the B operand (16 columns per block, NB blocks), and reduce their
-// partial tiles through LDS in a fixed order (deterministic, no split-K
-// partials in HBM).
+// Up to 16 tokens (gemv_fused_kernel) a workgroup owns 8 to 32 output features of
+// W [N][K] and the whole K range; its KS wavefronts split K into contiguous chunks,
+// run v_mfma_f32_16x16x32_bf16 with W as the A operand (16 rows per block) and
+// the tokens as the B operand (16 columns), and reduce their partial tiles
+// through LDS in a fixed order (deterministic, no split-K partials in HBM).
+// 17 to 64 tokens take the few-token tiles of the prefill GEMM, except the
+// residual projections (gemv_wide_kernel and a sum over its K splits).
 //
 // Normalized operand (NORM): RMSNorm(x) g enters as bf16(x[t][k] * g[k]),
 // written by the producer of x together with per-workgroup partial sums of
@@ -33,8 +34,6 @@
 namespace axon {
 
 AXON_DEV float silu_g(float z) { return z / (1.f + __expf(-z)); }
-
-constexpr int GV_U = 4;  // k-steps of 32 per pipeline stage
 
 // v(0) + v(1) + ... + v(n - 1) in that order, 8 independent (LDS) reads per
 // round instead of a chain of dependent ones
@@ -186,16 +185,16 @@ AXON_DEV void gv_epilogue(const GemvArgs& a, int n0, int tid, float* aux, int wg
   }
 }
 
-// XT: the token operand is in tile order (xt_off; one token block)
-template <int ROWS, int KS, int NB, bool NORM, int EPI, int U = GV_U, bool XT = false>
+// Up to 16 tokens (one column block).  XT: the token operand is in tile order
+// (xt_off).
+template <int ROWS, int KS, bool NORM, int EPI, int U, bool XT>
 __global__ void __launch_bounds__(KS * 64) gemv_fused_kernel(GemvArgs a) {
-  static_assert(!XT || NB == 1, "the tile order holds one block of 16 tokens");
   constexpr int RB = ROWS < 16 ? 1 : ROWS / 16;  // 16-row MFMA blocks (an 8-row tile leaves 8 rows idle)
-  constexpr int COLS = NB * 16;
+  constexpr int COLS = 16;
   constexpr int NT = KS * 64;
   __shared__ float red[KS][RB * 16][COLS + 1];
   __shared__ float s_ss[NT];
-  __shared__ float s_inv[64];
+  __shared__ float s_inv[COLS];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n0 = blockIdx.x * ROWS;
@@ -224,11 +223,8 @@ __global__ void __launch_bounds__(KS * 64) gemv_fused_kernel(GemvArgs a) {
   // (tokens past M-1 read token M-1: no bytes beyond the tokens' own), from
   // row r16 (row-major) or, in tile order, from the k-step's 1 KB at 16 k
   // (xt_off)
-  const bf16* xrow[NB];
-#pragma unroll
-  for (int c = 0; c < NB; ++c)
-    xrow[c] = XT ? a.X + ((lane >> 4) * 16 + min(r16, M - 1)) * 8
-                 : a.X + (int64_t)min(c * 16 + r16, M - 1) * K + (lane >> 4) * 8;
+  const bf16* xrow = XT ? a.X + ((lane >> 4) * 16 + min(r16, M - 1)) * 8
+                        : a.X + (int64_t)min(r16, M - 1) * K + (lane >> 4) * 8;
   auto xoff = [](int k) -> int64_t { return XT ? (int64_t)k * 16 : (int64_t)k; };
 
   // sums of squares of the normalized rows: the first SSR partials of this
@@ -254,33 +250,28 @@ __global__ void __launch_bounds__(KS * 64) gemv_fused_kernel(GemvArgs a) {
     }
   }
 
-  f32x4 acc[RB][NB];
+  f32x4 acc[RB];
 #pragma unroll
-  for (int r = 0; r < RB; ++r)
-#pragma unroll
-    for (int c = 0; c < NB; ++c) acc[r][c] = f32x4{};
+  for (int r = 0; r < RB; ++r) acc[r] = f32x4{};
 
   // software-pipelined stream over the full stages of [k0, k1): stage s+1 is
   // loaded while stage s feeds the MFMAs; the rest (k1 - k0 is a multiple of
   // 32) in single k-steps
-  bf16x8 wa[U][RB], xb[U][NB];
+  bf16x8 wa[U][RB], xb[U];
   auto load_stage = [&](int k) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
 #pragma unroll
       for (int r = 0; r < RB; ++r) wa[u][r] = *(const bf16x8*)(wrow[r] + woff(k + u * 32));
-#pragma unroll
-      for (int c = 0; c < NB; ++c) xb[u][c] = *(const bf16x8*)(xrow[c] + xoff(k + u * 32));
+      xb[u] = *(const bf16x8*)(xrow + xoff(k + u * 32));
     }
   };
-  auto mfma_stage = [&](const bf16x8 (&wv)[U][RB], const bf16x8 (&xv)[U][NB]) {
+  auto mfma_stage = [&](const bf16x8 (&wv)[U][RB], const bf16x8 (&xv)[U]) {
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
       for (int r = 0; r < RB; ++r)
-#pragma unroll
-        for (int c = 0; c < NB; ++c)
-          acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv[u][r], xv[u][c], acc[r][c], 0, 0, 0);
+        acc[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv[u][r], xv[u], acc[r], 0, 0, 0);
   };
   // epilogue operands (one item per thread), loaded behind the first stage
   constexpr bool PRE = (EPI == GV_RESID && ROWS * COLS <= NT) || (EPI == GV_ROPE && (ROWS / 2) * COLS <= NT);
@@ -318,13 +309,12 @@ __global__ void __launch_bounds__(KS * 64) gemv_fused_kernel(GemvArgs a) {
   prefetch();
   if (nst > 0) {
     for (int st = 1; st < nst; ++st) {
-      bf16x8 ca[U][RB], cb[U][NB];
+      bf16x8 ca[U][RB], cb[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
 #pragma unroll
         for (int r = 0; r < RB; ++r) ca[u][r] = wa[u][r];
-#pragma unroll
-        for (int c = 0; c < NB; ++c) cb[u][c] = xb[u][c];
+        cb[u] = xb[u];
       }
       load_stage(k0 + st * 32 * U);
       mfma_stage(ca, cb);
@@ -332,15 +322,12 @@ __global__ void __launch_bounds__(KS * 64) gemv_fused_kernel(GemvArgs a) {
     mfma_stage(wa, xb);
   }
   for (int k = k0 + nst * 32 * U; k < k1; k += 32) {
-    bf16x8 w1[RB], x1[NB];
+    bf16x8 w1[RB];
 #pragma unroll
     for (int r = 0; r < RB; ++r) w1[r] = *(const bf16x8*)(wrow[r] + woff(k));
+    const bf16x8 x1 = *(const bf16x8*)(xrow + xoff(k));
 #pragma unroll
-    for (int c = 0; c < NB; ++c) x1[c] = *(const bf16x8*)(xrow[c] + xoff(k));
-#pragma unroll
-    for (int r = 0; r < RB; ++r)
-#pragma unroll
-      for (int c = 0; c < NB; ++c) acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1[r], x1[c], acc[r][c], 0, 0, 0);
+    for (int r = 0; r < RB; ++r) acc[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1[r], x1, acc[r], 0, 0, 0);
   }
 
   // the prefetched values are used from here on (see GvPre)
@@ -349,13 +336,11 @@ __global__ void __launch_bounds__(KS * 64) gemv_fused_kernel(GemvArgs a) {
 #pragma unroll
     for (int i = 0; i < SSR; ++i) pin(ss_reg[i]);
   }
-  // ---- cross-wavefront reduction: acc[r][c][i] = C[n0 + r*16 + (lane/16)*4 + i][c*16 + lane%16]
+  // ---- cross-wavefront reduction: acc[r][i] = C[n0 + r*16 + (lane/16)*4 + i][lane%16]
 #pragma unroll
   for (int r = 0; r < RB; ++r)
 #pragma unroll
-    for (int c = 0; c < NB; ++c)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) red[wave][r * 16 + (lane >> 4) * 4 + i][c * 16 + r16] = acc[r][c][i];
+    for (int i = 0; i < 4; ++i) red[wave][r * 16 + (lane >> 4) * 4 + i][r16] = acc[r][i];
   if constexpr (NORM) {
     float ss_part = 0.f;
     // selects, not branches: a lane-divergent branch per term costs more
@@ -750,16 +735,11 @@ int64_t gemv_workspace_floats(int N, int K, int M, int epi) {
   return sh.ksplit > 1 || epi == GV_PART ? (int64_t)sh.ksplit * M * N : 0;
 }
 
-template <int ROWS, int KS, int U, int NB, bool NORM, int EPI>
+template <int ROWS, int KS, int U, bool NORM, int EPI>
 static bool gv(const GemvArgs& a, hipStream_t s) {
-  if constexpr (NB == 1) {
-    if (a.x_tiled) {
-      klaunch(gemv_fused_kernel<ROWS, KS, NB, NORM, EPI, U, true>, dim3((a.N + ROWS - 1) / ROWS), dim3(KS * 64), 0, s,
-              a);
-      return true;
-    }
-  }
-  klaunch(gemv_fused_kernel<ROWS, KS, NB, NORM, EPI, U>, dim3((a.N + ROWS - 1) / ROWS), dim3(KS * 64), 0, s, a);
+  const dim3 grid((a.N + ROWS - 1) / ROWS);
+  if (a.x_tiled) klaunch(gemv_fused_kernel<ROWS, KS, NORM, EPI, U, true>, grid, dim3(KS * 64), 0, s, a);
+  else klaunch(gemv_fused_kernel<ROWS, KS, NORM, EPI, U, false>, grid, dim3(KS * 64), 0, s, a);
   return true;
 }
 
@@ -767,13 +747,15 @@ static bool gv(const GemvArgs& a, hipStream_t s) {
 template <int EPI, bool NORM>
 static bool gv_dispatch(const GemvArgs& a, const GvShape& sh, hipStream_t s) {
 #define AXON_GV(R, KS_, U_) \
-  if (!sh.wide && sh.rows == R && sh.ks == KS_ && sh.u == U_) return gv<R, KS_, U_, 1, NORM, EPI>(a, s);
-  if constexpr (EPI == GV_SILU || EPI == GV_GELU) {
-    AXON_GV(32, 4, 4) AXON_GV(32, 8, 4)
-  } else if constexpr (EPI == GV_HEAD) {
-    AXON_GV(32, 8, 4)
+  if (!sh.wide && sh.rows == R && sh.ks == KS_ && sh.u == U_) return gv<R, KS_, U_, NORM, EPI>(a, s);
+  if constexpr (EPI == GV_GELU) {
+    AXON_GV(32, 4, 4)
+  } else if constexpr (EPI == GV_RESID) {
+    AXON_GV(8, 16, 2) AXON_GV(8, 8, 8) AXON_GV(16, 8, 4)
+  } else if constexpr (EPI == GV_ROPE) {
+    AXON_GV(16, 8, 4) AXON_GV(16, 16, 4) AXON_GV(32, 8, 4)
   } else {
-    AXON_GV(8, 16, 2) AXON_GV(8, 8, 8) AXON_GV(16, 8, 4) AXON_GV(16, 16, 4) AXON_GV(32, 8, 4)
+    AXON_GV(32, 8, 4)
   }
 #undef AXON_GV
   return false;

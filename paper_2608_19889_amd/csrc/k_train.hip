@@ -341,9 +341,10 @@ __global__ void __launch_bounds__(256) attn_bwd_do_kernel(const float* __restric
 // 32-query tiles of Q and dO rows with their statistics.  Rows, columns and both
 // transposes come from the one tile.  One wavefront per block reading packed,
 // transposed copies from L2 waited for each block's loads in turn (1B shape, 8 x
-// 512 tokens: dQ 130 us, dK / dV 136, the copies 71; now 50 and
-// 79, with launch bounds that keep the accumulators out of the second register
-// file half: 67 and 88 before).
+// 512 tokens: dQ 130 us, dK / dV 136, the copies 71; now 47 and 74).  The launch
+// bounds keep the accumulators out of the second register file half (67 and 88 us
+// without), except dK / dV of head dimension 128: 256 + 159 registers, one
+// wavefront per SIMD.
 
 // the ``rows``-position block blk of the sequences in order: (sequence, first position)
 AXON_DEV void locate_block(const int32_t* __restrict__ cu, int nseq, int blk, int rows, int& e, int& p0) {

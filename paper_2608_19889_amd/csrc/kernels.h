@@ -38,6 +38,7 @@ enum Epi : int {
   EPI_ROPE = 4,   // bf16 fused QKV projection (rows in the rotation-pair order of
                   // the decode projections): bias + rotary embedding, then q ->
                   // q_out, k -> K pages, v -> transposed V pages
+  // EPI_LSE, EPI_GU, EPI_DGU (training): X and bf16 outputs in the row-pair layout
   EPI_LSE = 3,    // EPI_F32 (no bias) and, per token and 64 columns, their largest
                   // value and the sum of exp(value - largest) (lse_part)
   EPI_GU = 6,     // the interleaved gate/up pre-activations kept (out_f32, rows of
@@ -83,7 +84,7 @@ struct EpiArgs {
   int g_E;
   const float* gu;  // EPI_DGU
   // row-pair layout (xp_off) of the token operand X, and of the bf16 output
-  // out_t of EPI_SILU / EPI_GU / EPI_DGU; 0: row-major
+  // out_t of EPI_SILU; 0: row-major
   int xpair;
   int opair;
   // few-token GEMM (launch_gemm_few), EPI_SILU / EPI_ROPE / EPI_HEAD: the operand
@@ -176,13 +177,14 @@ void launch_set_step_lengths(const int32_t* cu, const int32_t* ent_slot, const i
 // Raises the dynamic LDS limits of the kernels below on the current device; once
 // per device, before any of them is launched there.
 hipError_t gemm_init_device();
-// Many-token GEMM (prefill): bf16 MFMA tiles.  Requires K % 64 == 0, N % 32 == 0
-// (EPI_ROPE: the head dimension a multiple of 32).  ep.xpair: X in the row-pair
+// Many-token GEMM (prefill): bf16 MFMA tiles.  Requires K % 32 == 0, and N % 32 ==
+// 0 except for EPI_F32, EPI_RESID and EPI_LSE (EPI_ROPE: the head dimension a
+// multiple of 32).  ep.xpair: X in the row-pair
 // layout (xp_off); ep.opair: the SiLU epilogue's output in that layout.
 void launch_gemm_bf16(const bf16* W, const bf16* X, int N, int M, int K, int epi, const EpiArgs& ep,
                       hipStream_t s);
 // The same GEMM for 17 .. 64 decode tokens (tiles of at most 64 tokens, row-major
-// X, K % 64 == 0): EPI_ROPE, EPI_SILU, EPI_GELU, EPI_HEAD.
+// X, K % 32 == 0): EPI_ROPE, EPI_SILU, EPI_GELU, EPI_HEAD (any N).
 void launch_gemm_few(const bf16* W, const bf16* X, int N, int M, int K, int epi, const EpiArgs& ep, hipStream_t s);
 int few_head_rows(int N, int M, int K);  // columns per EPI_HEAD partial
 // Grouped GEMM of the experts (ep.g_*): rows of all experts together at most
@@ -191,8 +193,8 @@ int few_head_rows(int N, int M, int K);  // columns per EPI_HEAD partial
 void launch_gemm_bf16_grouped(const bf16* W, const bf16* X, int N, int K, int max_rows, int epi, const EpiArgs& ep,
                               hipStream_t s);
 // split K over gridDim.y = ksplit workgroup rows: float32 partials
-// part[s * part_stride + m * N + n] (the 256 x 256 kernel; ksplit divides K /
-// 32).  gemm_ksplit: the split worth taking for an output of few 256-tiles
+// part[s * part_stride + m * N + n] (ksplit divides K / 32; tiles as for the
+// unsplit GEMM).  gemm_ksplit: the split worth taking for an output of few 256-tiles
 // (1: none).
 void launch_gemm_bf16_split(const bf16* W, const bf16* X, int N, int M, int K, int ksplit, float* part,
                             int64_t part_stride, hipStream_t s, bool xpair = false);
@@ -201,14 +203,14 @@ int gemm_ksplit(int N, int M, int K);
 // 64, the backward pass): the least of its time and the partials' traffic
 int gemm_ksplit_cost(int N, int M, int K, int max_split);
 // Weight gradient dW = Y^T X over T token rows: out[r][c] = sum_t Y[t][r] X[t][c],
-// Y [T][ldy] (R <= ldy columns used, ldy % 8 == 0), X [T][C] (C % 32 == 0), both
-// row-major or (xpair) both in the row-pair layout.  The rows go to out [R][C], or
+// Y [T][ldy] (R <= ldy columns used, ldy % 32 == 0), X [T][C] (C % 32 == 0), both
+// in the row-pair layout.  The rows go to out [R][C], or
 // back from the kernel row orders to the weight map's tensors: WGRAD_QKV out / out1
 // / out2 = q / k / v, WGRAD_GU out / out1 = gate / up.  part: part_floats floats of
 // scratch for a split over the tokens.
 enum WgradMode : int { WGRAD_ROWS = 0, WGRAD_QKV = 1, WGRAD_GU = 2 };
-void launch_wgrad(int mode, const bf16* Y, int ldy, int R, const bf16* X, int C, int T, bool xpair, float* out,
-                  float* out1, float* out2, int hd, int H, int KVh, float* part, int64_t part_floats, hipStream_t s);
+void launch_wgrad(int mode, const bf16* Y, int ldy, int R, const bf16* X, int C, int T, float* out, float* out1,
+                  float* out2, int hd, int H, int KVh, float* part, int64_t part_floats, hipStream_t s);
 // float32 check-mode GEMM (any M): EPI_F32 / EPI_RESID.
 void launch_gemm_f32(const float* W, const float* X, int N, int M, int K, int epi, const EpiArgs& ep,
                      hipStream_t s);
