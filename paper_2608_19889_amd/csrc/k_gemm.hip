@@ -1014,7 +1014,9 @@ static void launch_ring_shape(const bf16* W, const bf16* X, int N, int M, int K,
 // shape gives the same bits.  us at 3584 x 3584 (N x K): 93 tokens 128x128
 // tiles 33, 64x64 16, 32x64 14; 700 tokens 128x128 35, 64x64 40, 256x256 79;
 // 1500 tokens 256x128 52, 128x128 60, 256x256 81.  The 128x128 kernel before
-// this one, staged through registers one k-tile ahead, took 74-80 for all.
+// this one, staged through registers one k-tile ahead, took 74-80 for all.  The
+// costs are a plain float32 store's: they leave out what the RoPE epilogue and
+// float32 logits add (1.6 to 2.5 times the cost on a short K).
 enum Tile : int { T256x256, T256x128, T128x128, T128x64, T64x64, T32x64, T32x32, TILES };
 struct TileCost {
   int bn, bm, ku, ns;
@@ -1070,7 +1072,9 @@ static void launch_tiles(const bf16* W, const bf16* X, int N, int M, int K, int 
 // row-splitting projection kernel with its tokens staged through registers and,
 // on narrow outputs, a K split with an epilogue kernel (us, weights from HBM, 32
 // tokens): QKV 6144 x 2048 16.9 -> 9.9, shared gate/up 5632 x 2048 14.8 -> 9.3,
-// head 102400 x 2048 98 -> 84; 40 tokens: gate/up 37888 x 3584 66 -> 56.
+// head 102400 x 2048 98 -> 84; 40 tokens: gate/up 37888 x 3584 66 -> 56.  The
+// costs put 128x64 before 64x64 on that head (84.3 us, 64x64 80.4), and a 256x64
+// tile, not built, timed 57.6 us on 37888 x 3584 at 64 tokens (64x64 62.3).
 template <int EPI>
 static void launch_few(const bf16* W, const bf16* X, int N, int M, int K, const EpiArgs& ep, hipStream_t s) {
   switch (pick_tile(N, M, K, 1, nullptr, T128x64)) {

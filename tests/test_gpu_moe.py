@@ -175,9 +175,9 @@ def test_moe_decode_beyond_64_sequences_against_oracle():
 
 @pytest.mark.parametrize("case", list(CASES))
 def test_moe_wide_decode_batch_against_oracle(case):
-    """17..64 decode tokens: the few-token projections take their row-splitting
-    form (K split for the narrow router and shared-expert gate/up) and every
-    expert sees several tokens."""
+    """17..64 decode tokens: QKV, the shared experts' gate/up and the head run as
+    few-token GEMM tiles, the router and the residual projections in the
+    row-splitting form (K split), and every expert sees several tokens."""
     rng = np.random.default_rng(41)
     _against_oracle(case, [int(n) for n in rng.integers(3, 48, size=37)], steps=3, seed=43)
 
