@@ -2101,8 +2101,7 @@ void enqueue_train(axon_model* m, int B, int T, const int32_t* d_tokens, const i
        G(p + "self_attn.v_proj.weight"));
     dX_norm(t.wqkvT, tb.dqkv, nq, t.xin, w.gin, G(p + "input_layernorm.weight"), 1);
   }
-  if (!tied) (void)hipMemsetAsync(g_embed, 0, (size_t)V * D * 4, s);
-  launch_embed_bwd(d_tokens, tb.dx, T, D, V, g_embed, s);
+  launch_embed_bwd(d_tokens, tb.dx, T, D, V, g_embed, !tied, s);
 }
 
 }  // namespace

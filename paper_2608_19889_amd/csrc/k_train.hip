@@ -667,6 +667,13 @@ __global__ void __launch_bounds__(128) rope_bwd_kernel(const float* __restrict__
   }
 }
 
+// dst[0 .. 4 n4) = 0.  A kernel, since a caller may capture the step and
+// memory-set nodes have given wrong results on a graph's later replays.
+__global__ void __launch_bounds__(256) zero_f32_kernel(float* __restrict__ dst, int64_t n4) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < n4) *(f32x4*)(dst + i * 4) = f32x4{};
+}
+
 // dE[tok[t]] += dx[t] (tokens repeat, hence atomic additions)
 __global__ void __launch_bounds__(256) embed_bwd_kernel(const int32_t* __restrict__ tok, const float* __restrict__ dx,
                                                         int D, int V, float* __restrict__ dE) {
@@ -748,7 +755,9 @@ void launch_rope_bwd(const float* dq, const float* dkh, const float* dvh, const 
   if (dbq) colsum_final(bpart, n, nq, dbq, H * hd, dbk, (H + KVh) * hd, dbv, s);
 }
 
-void launch_embed_bwd(const int32_t* tok, const float* dx, int T, int D, int V, float* dE, hipStream_t s) {
+void launch_embed_bwd(const int32_t* tok, const float* dx, int T, int D, int V, float* dE, bool clear, hipStream_t s) {
+  const int64_t n4 = (int64_t)V * D / 4;
+  if (clear) zero_f32_kernel<<<(unsigned)((n4 + 255) / 256), 256, 0, s>>>(dE, n4);
   if (T > 0) embed_bwd_kernel<<<T, 256, 0, s>>>(tok, dx, D, V, dE);
 }
 

@@ -148,7 +148,8 @@ void launch_attn_bwd(const bf16* q, KVView kv, const bf16* o, const float* dof, 
 void launch_rope_bwd(const float* dq, const float* dkh, const float* dvh, const float* cos_t, const float* sin_t,
                      const int32_t* cu, int nseq, int T, int H, int KVh, int hd, bf16* dqkv, float* bpart, float* dbq,
                      float* dbk, float* dbv, hipStream_t s);
-void launch_embed_bwd(const int32_t* tok, const float* dx, int T, int D, int V, float* dE, hipStream_t s);
+// dE [V][D] += the tokens' rows of dx [T][D]; clear: dE = 0 first (D % 4 == 0)
+void launch_embed_bwd(const int32_t* tok, const float* dx, int T, int D, int V, float* dE, bool clear, hipStream_t s);
 
 // ---- weight layout (k_layout.hip): fragment-tiled copy of row-major bf16
 // W [N][K] (K % 32 == 0) into dst of round_up(N, 16) * K elements

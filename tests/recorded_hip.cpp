@@ -442,6 +442,18 @@ void train_step(const std::vector<int>& v) {
   train(m, c, cu);
 }
 
+// a second training step of a model with an untied head
+void train_twice() {
+  axon_config c = llama(256, 4, 2, 64, 256, 1000);
+  c.tie_embeddings = 0;
+  c.max_batch = 2;
+  c.max_seq = 64;
+  axon_model* m = make(c);
+  train(m, c, 2, 50);
+  mark("second");
+  train(m, c, 2, 60);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -452,6 +464,7 @@ int main(int argc, char** argv) {
   if (s == "two_devices") two_devices();
   else if (s == "raw_rows") raw_rows();
   else if (s == "train_step" && v.size() > 8) train_step(v);
+  else if (s == "train_twice") train_twice();
   else if (s == "timed_train") timed_train();
   else if (s == "partials") partials_of_many_sizes();
   else if (s == "moe_init") moe_init();

@@ -161,3 +161,13 @@ def test_partials_stay_inside_their_buffer(recorder):
             assert base is not None and e[1] + e[2] <= ends[base], (step, e, base and ends[base] - e[1])
             seen += 1
     assert seen > 100
+
+
+def test_training_step_records_no_memset(recorder):
+    """After the first call's set-up a training step (untied head: the embedding's
+    gradient starts at zero) enqueues kernels only, so a caller may capture it: a
+    memory-set node in a captured graph is not reliable on replays."""
+    ev = recorder("train_twice")
+    second = ev[ev.index(("mark", "second")):]
+    assert any(isinstance(e, Launch) and "embed_bwd" in e.kernel for e in second)
+    assert not any(e[0] in ("fill", "alloc") for e in second if not isinstance(e, (Launch, Limit)))
