@@ -153,7 +153,9 @@ AXON_DEV void store_block(const EpiArgs& ep, int nb, int t, RopeTok tok, const f
         *(f32x4*)(ep.out_f32 + (int64_t)t * ep.ldo + nb + g * 8 + (lane >> 5) * 4) =
             f32x4{v[g * 4], v[g * 4 + 1], v[g * 4 + 2], v[g * 4 + 3]};
     }
-    bf16* out = (bf16*)ep.out_t + (EPI == EPI_GU || ep.opair ? xp_off(t, f0, lda) : (int64_t)t * lda + f0);
+    // (EPI_GU's is always the row-pair layout, but known at compile time the 4096 x
+    // 16384 x 2048 GEMM took 319 us, against 311 with the choice left in)
+    bf16* out = (bf16*)ep.out_t + (ep.opair ? xp_off(t, f0, lda) : (int64_t)t * lda + f0);
 #pragma unroll
     for (int g = 0; g < 2; ++g) {
       const int f = g * 8 + (lane >> 5) * 4;

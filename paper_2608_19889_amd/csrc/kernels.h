@@ -84,7 +84,7 @@ struct EpiArgs {
   int g_E;
   const float* gu;  // EPI_DGU
   // row-pair layout (xp_off) of the token operand X, and of the bf16 output
-  // out_t of EPI_SILU; 0: row-major
+  // out_t of EPI_SILU and EPI_GU (there always 1); 0: row-major
   int xpair;
   int opair;
   // few-token GEMM (launch_gemm_few), EPI_SILU / EPI_ROPE / EPI_HEAD: the operand
