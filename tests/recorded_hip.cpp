@@ -236,8 +236,20 @@ struct Map {
   std::vector<axon_weight> w;
   Map(const axon_config& c, int dtype) {
     const int64_t D = c.hidden, H = c.n_heads, KV = c.n_kv_heads, hd = c.head_dim, I = c.intermediate;
-    const std::string p = "model.layers.0.";
-    std::vector<std::pair<std::string, std::pair<int64_t, int64_t>>> l = {
+    const std::string p = c.arch == AXON_ARCH_GPT2 ? "transformer.h.0." : "model.layers.0.";
+    std::vector<std::pair<std::string, std::pair<int64_t, int64_t>>> l;
+    if (c.arch == AXON_ARCH_GPT2) {
+      l = {
+        {"transformer.wte.weight", {c.vocab, D}}, {"transformer.wpe.weight", {c.max_positions, D}},
+        {p + "ln_1.weight", {D, 0}}, {p + "ln_1.bias", {D, 0}},
+        {p + "attn.c_attn.weight", {D, 3 * D}}, {p + "attn.c_attn.bias", {3 * D, 0}},
+        {p + "attn.c_proj.weight", {D, D}}, {p + "attn.c_proj.bias", {D, 0}},
+        {p + "ln_2.weight", {D, 0}}, {p + "ln_2.bias", {D, 0}},
+        {p + "mlp.c_fc.weight", {D, I}}, {p + "mlp.c_fc.bias", {I, 0}},
+        {p + "mlp.c_proj.weight", {I, D}}, {p + "mlp.c_proj.bias", {D, 0}},
+        {"transformer.ln_f.weight", {D, 0}}, {"transformer.ln_f.bias", {D, 0}}};
+    } else {
+      l = {
         {"model.embed_tokens.weight", {c.vocab, D}},
         {"model.norm.weight", {D, 0}},
         {p + "input_layernorm.weight", {D, 0}},
@@ -246,8 +258,10 @@ struct Map {
         {p + "self_attn.k_proj.weight", {KV * hd, D}},
         {p + "self_attn.v_proj.weight", {KV * hd, D}},
         {p + "self_attn.o_proj.weight", {D, H * hd}}};
+    }
     if (!c.tie_embeddings) l.push_back({"lm_head.weight", {c.vocab, D}});
-    if (c.qkv_bias)
+    const bool gpt2 = c.arch == AXON_ARCH_GPT2;
+    if (c.qkv_bias && !gpt2)
       for (auto& b : {std::make_pair("q", H), std::make_pair("k", KV), std::make_pair("v", KV)})
         l.push_back({p + "self_attn." + b.first + "_proj.bias", {b.second * hd, 0}});
     auto mlp = [&](const std::string& q, int64_t ii) {
@@ -258,7 +272,7 @@ struct Map {
     if (c.n_experts > 0) {
       l.push_back({p + "mlp.gate.weight", {c.n_experts, D}});
       for (int e = 0; e < c.n_experts; ++e) mlp(p + "mlp.experts." + std::to_string(e) + ".", c.moe_intermediate);
-    } else {
+    } else if (!gpt2) {
       mlp(p + "mlp.", I);
     }
     for (auto& x : l) names.push_back(x.first);
@@ -394,17 +408,23 @@ void moe_init() {
   make(c);
 }
 
-// prompts and decode steps of models with few and many sequence slots: a dense
-// one, one of each head dimension and width, and a mixture of experts
+// prompts, decode steps and mixed steps of models with few and many sequence
+// slots: a dense one of each head dimension, a float32 one, a mixture of experts and GPT-2
 void partials_of_many_sizes() {
   for (int max_batch : {1, 3, 40, 64, 65, 300})
-    for (int kind = 0; kind < 4; ++kind) {
+    for (int kind = 0; kind < 5; ++kind) {
       axon_config c = kind == 1 ? llama(3584, 28, 4, 128, 18944, 1000) : llama(512, 8, 2, 64, 1536, 1000);
       if (kind == 2) c.dtype = AXON_F32;
       if (kind == 3) {
         c.n_experts = 256;
         c.top_k = 8;
         c.moe_intermediate = 64;
+      }
+      if (kind == 4) {
+        c = llama(1600, 25, 25, 64, 6400, 1001);
+        c.arch = AXON_ARCH_GPT2;
+        c.qkv_bias = 1;
+        c.max_positions = 3000;
       }
       c.max_batch = max_batch;
       c.max_seq = max_batch <= 40 ? 3000 : 82;  // (long: the decode attention splits the keys)
@@ -419,6 +439,16 @@ void partials_of_many_sizes() {
             check(axon_decode_step(m, b, TOK, LOGITS, TOK, nullptr), "axon_decode_step");
             if (b <= 64 && kind < 2)
               check(axon_decode_step_noalloc(m, b, TOK, LOGITS, TOK, nullptr), "axon_decode_step_noalloc");
+            // a step of prompt chunks in the even slots and decode tokens in the odd ones
+            std::vector<int32_t> slots, fresh, cu{0};
+            for (int i = 0; i < b; ++i) {
+              slots.push_back(i);
+              fresh.push_back(i % 2 == 0);
+              cu.push_back(cu.back() + (i % 2 == 0 ? len : 1));
+            }
+            if (len <= 64)
+              check(axon_step(m, b, slots.data(), fresh.data(), TOK, TOK, cu.data(), nullptr, 0, LOGITS, TOK, nullptr),
+                    "axon_step");
           }
       }
       axon_free(m);
