@@ -668,7 +668,8 @@ __global__ void __launch_bounds__(128) rope_bwd_kernel(const float* __restrict__
 }
 
 // dst[0 .. 4 n4) = 0.  A kernel, since a caller may capture the step and
-// memory-set nodes have given wrong results on a graph's later replays.
+// memory-set nodes have given wrong results on a graph's later replays.  HBM
+// bound: 152064 x 3584 floats 309 us (7.05 TB/s), the memory-set 327.
 __global__ void __launch_bounds__(256) zero_f32_kernel(float* __restrict__ dst, int64_t n4) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i < n4) *(f32x4*)(dst + i * 4) = f32x4{};
